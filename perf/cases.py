@@ -408,3 +408,97 @@ def tolerance(case):
         return "exact"
     # bf16 results of fp32 sums
     return dict(rel=1e-2)
+
+
+# ---- the same in 64 bits, plain torch --------------------------------------------------------------
+def _d(t):
+    return t.double()
+
+
+def _mlp64(m):
+    dA, dB, Z, dX = 0.0, 0.0, [], []
+    At, B = _d(m.At), _d(m.B)
+    for X, dZ in zip(map(_d, m.X), map(_d, m.dZ)):
+        P = (X @ At.T).requires_grad_()
+        Y = torch.nn.functional.gelu(P, approximate="tanh" if m.mode == K.NTP_GELU_TANH else "none")
+        (dP,) = torch.autograd.grad(Y, P, dZ @ B.T)
+        P, Y = P.detach(), Y.detach()
+        Z.append(Y @ B)
+        dX.append(dP @ At)
+        dA, dB = dA + dP.T @ X, dB + Y.T @ dZ
+    return dict(P=P, Y=Y, dP=dP, Z=Z, dX=dX, dA=dA, dB=dB)
+
+
+def _core64(n_seq, seq, q, kv, head_of, dim, causal, QKV, dC):
+    """`head_of[j]`: the local KV head that local query head j reads."""
+    m, scale = n_seq * seq, 1.0 / math.sqrt(dim)
+    C, dQKV = QKV.new_zeros(m, q * dim), torch.zeros_like(QKV)
+    LSE = QKV.new_zeros(q, m)
+    future = torch.ones(seq, seq, dtype=torch.bool, device=QKV.device).triu_(1) if causal else None
+    for i in range(n_seq):
+        rows = slice(i * seq, (i + 1) * seq)
+        for j in range(q):
+            cq, ck, cv = (slice(b * dim, (b + 1) * dim) for b in (j, q + head_of[j], q + kv + head_of[j]))
+            Q, Kh, V = QKV[rows, cq], QKV[rows, ck], QKV[rows, cv]
+            S = Q @ Kh.T * scale
+            if causal:
+                S.masked_fill_(future, -math.inf)
+            LSE[j, rows] = lse = torch.logsumexp(S, 1)
+            P = S.sub_(lse[:, None]).exp_()
+            C[rows, cq] = O = P @ V
+            if dC is not None:
+                dO = dC[rows, cq]
+                dQKV[rows, cv] += P.T @ dO
+                dS = P * (dO @ V.T - (dO * O).sum(1, keepdim=True)) * scale
+                dQKV[rows, cq] = dS @ Kh
+                dQKV[rows, ck] += dS.T @ Q
+    return C, LSE, dQKV
+
+
+def _attn64(case, a):
+    p = N.ntp_attn_shard_plan(case["n_q"], case["n_kv"], case["dim"], case["tp"], case.get("rank", 0))
+    group = case["n_q"] // case["n_kv"]
+    head_of = [(p["q_off"] + j) // group - p["kv_off"] for j in range(p["q_cnt"])]
+    X, dZ, Wqkv, Wo = map(_d, (a.X, a.dZ, a.Wqkv, a.Wo))
+    QKV, dC = X @ Wqkv.T, dZ @ Wo.T
+    C, LSE, dQKV = _core64(case.get("n_seq", 1), case["seq"], p["q_cnt"], p["kv_cnt"], head_of, case["dim"], case.get("causal", True), QKV, dC)
+    return dict(QKV=QKV, C=C, LSE=LSE, Z=C @ Wo, dC=dC, dQKV=dQKV, dX=dQKV @ Wqkv, dWqkv=dQKV.T @ X, dWo=C.T @ dZ)
+
+
+def _own(n, tp, r):
+    lo = r * (n // tp) + min(r, n % tp)
+    return lo, lo + n // tp + (r < n % tp)
+
+
+def _full_shards(dW, blocks, unit, n, full):
+    """The parts of the TP = full shards that lie in rank 0's rows: `blocks` blocks of n units a tensor, rank 0's first units of each in dW."""
+    mine, out = dW.view(blocks, -1, dW.shape[1]), []
+    for r in range(full):
+        lo, hi = (v * unit for v in _own(n, full, r))
+        if lo < mine.shape[1]:
+            t = dW.new_zeros(blocks, hi - lo, dW.shape[1])
+            part = mine[:, lo:hi]
+            t[:, : part.shape[1]] = part
+            out.append(t.view(-1, dW.shape[1]))
+    return out
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind in ("reshard", "mapped"):
+        return None  # copies
+    s = prepare(case, seed)
+    if kind == "mlp":
+        return _mlp64(s["mlp"])
+    if kind == "attn":
+        return _attn64(case, s["attn"])
+    if kind == "core":
+        q, kv = case["heads"], case["kv"]
+        C, LSE, dQKV = _core64(case["n_seq"], case["seq"], q, kv, [j // (q // kv) for j in range(q)], case["dim"], case["causal"], _d(s["QKV"]),
+                               None if s["dC"] is None else _d(s["dC"]))
+        return dict(C=C, LSE=LSE, dQKV=dQKV) if case["back"] else dict(C=C, LSE=LSE)
+    a, m = _attn64(case, s["attn"]), _mlp64(s["mlp"])
+    d, full = case["dim"], case["full"]
+    grads = [_full_shards(a["dWqkv"], 3, d, case["n_q"], full), _full_shards(a["dWo"], 1, d, case["n_q"], full),
+             _full_shards(m["dA"], 1, 1, case["ffn"], full), _full_shards(m["dB"], 1, 1, case["ffn"], full)]
+    return dict(Zattn=a["Z"], Zmlp=m["Z"][0], dXmlp=m["dX"][0], dXattn=a["dX"], C=a["C"], dQKV=a["dQKV"], grads=grads)
