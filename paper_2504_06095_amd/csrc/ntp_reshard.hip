@@ -23,7 +23,6 @@ namespace {
 
 constexpr int kMaxSegs = 56;          // per launch; the argument block stays below 4 KiB
 constexpr int kThreads = 256;         // 4 wavefronts
-constexpr int kWaves = kThreads / 64;
 constexpr int64_t kColChunk = 8192;   // bytes of a row handled by one workgroup
 constexpr int64_t kBlockBytes = 65536;  // target bytes per workgroup
 
@@ -352,182 +351,200 @@ __global__ __launch_bounds__(kThreads) void reshard_dense_kernel(const DenseBatc
   }
 }
 
-// ---- layouts given unit by unit (Sec. 3.1, Alg. 1): gather through a run table -------------------
-// The destination shards are dense and are written like the flat kernel writes them: as one flat
-// byte range cut into blocks at 64-byte boundaries, every 16-byte chunk stored whole and aligned.
-// A destination shard is a sequence of runs (units that follow each other in one source shard too);
-// the plan keeps, in device memory, the runs of every destination shard and for every destination
-// unit the number of its run.  A workgroup serves one destination shard: it copies both tables into
-// LDS (runs joined with this call's source pointers) and then takes one block of the shard, or walks
-// over several when the shard is very large.  A chunk that lies inside one run is moved by one
-// 16-byte load and store.  The
-// other chunks (they straddle a run boundary or a row end, or are the short last chunk of the
-// shard) are put on a queue that each wavefront keeps in LDS, and are put together word by word when
-// the queue has filled up, so that this slower code runs with most lanes in use even when few
-// chunks need it.  Needs: 4-byte elements, dense 64-byte aligned destinations,
-// (block + W + 16) * W <= 2^32 for the row width W in bytes, source strides below 2^32 bytes, at
-// most kMaxRanks source ranks, at most 65535 runs per shard.
-constexpr int kMaxRanks = 96;
-constexpr int kUnitDsts = 16;               // destination shards per launch: few write streams at a time measured fastest
-constexpr uint32_t kUnitLdsMax = 60 << 10;  // bytes of LDS a workgroup may ask for
-constexpr uint32_t kQueueCap = 512;         // queued chunks per wavefront
-constexpr uint32_t kUnitBlocksPerCu = 256;  // workgroups per compute unit and launch before they start to walk over several blocks
+// ---- layouts given unit by unit (Sec. 3.1, Alg. 1): gather through a unit table -------------------
+// The destination shards are dense and are written as one flat byte range each, cut into blocks, every
+// 16-byte chunk stored whole and aligned.  The plan keeps in device memory, for every unit of every
+// destination shard (one shard after the other), where it comes from: rank << 24 | unit in that rank's shard.
+// The table is 4 bytes a unit and stays in the L2s; nothing about it has to fit in LDS, so every layout of a plan
+// takes one launch, whether a destination shard is two long runs or every unit comes from another rank.
+// (The earlier form kept a 32-byte record per run in LDS: layouts with more than about 1300 runs a shard, or with
+// rows above 57 KB, were copied sub-shard by sub-shard, 8 units a job: 93.8 ms for the gradients of a hidden-12800
+// layer between TP 7 and TP 5, which the table moves in 2.10 ms.)
+constexpr int kMaxRanks = 96;       // source ranks, and destination shards per launch: the argument block stays below 4 KiB
+constexpr uint32_t kUnitBits = 24;  // of a table entry; the rank has the other 8
+
+// Column-partitioned tensors are copied in bands of rows of about this many bytes, every destination shard's part of a band
+// before the next band: where the units of one source row go to several destination shards in turn, its lines are still in the
+// device's last-level cache when the next shard needs them (54 to 45 ranks and back 1397 to 960 us).  Elsewhere whole shards one after the other are 3-5 % faster
+// (few write streams): ntp_reshard_plan::interleaved.
+constexpr int64_t kBandBytes = int64_t(64) << 20;
 
 struct UnitSrc {
   const char* base;  // first byte of the source shard
   uint64_t stride;   // bytes between its rows
 };
-struct RunDev {      // one run of a destination shard (plan, device memory)
-  uint32_t begin, end;  // byte range in a destination row
-  uint32_t src_off;     // byte offset in a source row of what goes to `begin`
-  uint32_t rank;        // source rank
-};
-struct RunLds {      // the same, joined with the source pointers of this call
-  uint32_t begin, end, stride, pad_;
-  uint64_t adj;      // source base + src_off - begin: column c of row r is at adj + r * stride + c
-  uint64_t pad2_;
-};
-struct UnitDst {
+struct TableDst {
   char* dst;
-  uint32_t idx_first, n_units;   // this shard's slice of the unit -> run numbers
-  uint32_t runs_first, n_runs;   // this shard's slice of the runs
+  uint32_t first_unit, n_units;    // this shard's slice of the table
+  uint32_t first_block, per_band;  // its blocks in a band
 };
-struct UnitBatch {
+struct TableBatch {
   UnitSrc src[kMaxRanks];
-  UnitDst dst[kUnitDsts];
-  const RunDev* runs;
-  const uint16_t* run_of_unit;
-  uint32_t rows, unit_bytes, ndst, block_bytes;
+  TableDst dst[kMaxRanks];
+  const uint32_t* table;
+  uint32_t rows;        // columns partitioned: rows of the tensor
+  uint32_t row_bytes;   // rows partitioned: bytes of a row
+  uint32_t unit;        // columns partitioned: bytes of a unit; rows partitioned: rows of a unit
+  uint32_t block_bytes;
+  uint32_t band_blocks;
+  int32_t ndst, nsrc;
 };
 
-__host__ __device__ inline uint32_t unit_tables_bytes(uint32_t n_runs, uint32_t n_units) {
-  return n_runs * uint32_t(sizeof(RunLds)) + ((n_units * 2u + 15u) & ~15u);
-}
-__host__ __device__ inline uint32_t unit_lds_bytes(uint32_t n_runs, uint32_t n_units) {
-  return unit_tables_bytes(n_runs, n_units) + kWaves * kQueueCap * uint32_t(sizeof(uint2));
+// The destination shard of block `b` of a band (the last one whose first block is <= b): one load per lane instead of a
+// chain of scalar loads.
+__device__ __forceinline__ int table_dst(const TableBatch& batch, uint32_t b) {
+  const int lane = threadIdx.x & 63;
+  int n = 0;
+#pragma unroll
+  for (int i = 0; i < kMaxRanks; i += 64) n += __popcll(__ballot(i + lane < batch.ndst && batch.dst[min(i + lane, kMaxRanks - 1)].first_block <= b));
+  return n - 1;
 }
 
-__global__ __launch_bounds__(kThreads) void reshard_units_kernel(const UnitBatch batch) {
-  extern __shared__ __align__(16) unsigned char unit_lds[];
-  // consecutive workgroups take consecutive blocks of one destination shard
-  const uint32_t nslots = gridDim.x / batch.ndst;
-  const uint32_t di = blockIdx.x / nslots, slot = blockIdx.x - di * nslots;
-  const UnitDst& dd = batch.dst[di];
-  const uint32_t ub = batch.unit_bytes, blk = batch.block_bytes;
+// Column-partitioned, 4-byte elements; ONE: units of one element.  A chunk whose four words follow each other in one source
+// row is moved by one 16-byte load (any 4-byte alignment), the others (units of several ranks side by side, row ends) by four
+// word loads in a second pass, before the first pass's loads are waited for.  Bound by HBM where the runs are long (49152
+// columns of fp32 between 32 and 30 ranks: 5.4 TB/s, 892 us; the run table in LDS took 900), by the word loads where they are
+// single units (54 to 45 ranks and back: 3.1 TB/s).  Six wavefronts per SIMD: at eight the second pass spills or has to wait
+// for the stores (920 us).
+template <bool ONE>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void reshard_table_cols_kernel(const TableBatch batch) {
+  __shared__ UnitSrc src[kMaxRanks];
+  for (int i = threadIdx.x; i < batch.nsrc; i += kThreads) src[i] = batch.src[i];
+  const uint32_t band = blockIdx.x / batch.band_blocks, bb = blockIdx.x - band * batch.band_blocks;
+  const TableDst& dd = batch.dst[table_dst(batch, bb)];
+  const uint32_t ub = ONE ? 4u : batch.unit, blk = batch.block_bytes;
   const uint32_t W = dd.n_units * ub;
   const int64_t T = int64_t(batch.rows) * W;
-  int64_t b0 = int64_t(slot) * blk;
-  if (b0 >= T) return;  // the whole workgroup leaves: nothing left for it in this shard
-  RunLds* const runs = reinterpret_cast<RunLds*>(unit_lds);
-  uint16_t* const run_of = reinterpret_cast<uint16_t*>(unit_lds + dd.n_runs * sizeof(RunLds));
-  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-  uint2* const queue = reinterpret_cast<uint2*>(unit_lds + unit_tables_bytes(dd.n_runs, dd.n_units)) + wave * kQueueCap;
-  for (uint32_t r = threadIdx.x; r < dd.n_runs; r += kThreads) {
-    const RunDev rd = batch.runs[dd.runs_first + r];
-    const UnitSrc sr = batch.src[rd.rank];
-    RunLds o;
-    o.begin = rd.begin;
-    o.end = rd.end;
-    o.stride = uint32_t(sr.stride);
-    o.pad_ = 0;
-    o.adj = uint64_t(reinterpret_cast<uintptr_t>(sr.base)) + rd.src_off - rd.begin;
-    o.pad2_ = 0;
-    runs[r] = o;
-  }
-  for (uint32_t j = threadIdx.x; j < dd.n_units; j += kThreads) run_of[j] = batch.run_of_unit[dd.idx_first + j];
-  __syncthreads();  // the only workgroup-wide wait: from here on the wavefronts run on their own
-
-  // W and the unit size are at least 4: the multiply-high division needs no special case
+  const int64_t b0 = (int64_t(band) * dd.per_band + (bb - dd.first_block)) * blk;
+  if (b0 >= T) return;  // the whole workgroup, before the barrier
+  const uint32_t nb = uint32_t(std::min<int64_t>(blk, T - b0));
+  const uint32_t row0 = uint32_t(b0 / W), c0 = uint32_t(b0 - int64_t(row0) * W);
+  char* __restrict__ d = dd.dst + b0;
+  const uint32_t* __restrict__ tab = batch.table + dd.first_unit;
+  const bool wide = W > blk + 16u;  // at most one row end in a block; else the multiply-high is exact (see table_path_ok)
   const uint32_t magic_w = div_magic(W), magic_u = div_magic(ub);
-  const char* const dummy = reinterpret_cast<const char*>(batch.runs);  // 16 readable bytes for lanes with nothing to load
-  // queued chunks of this wavefront, word by word
-  uint32_t nq = 0;  // chunks on this wavefront's queue (the same value in all lanes)
-  auto flush = [&]() {
-    // what other lanes have queued becomes visible
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (uint32_t i = lane; i < nq; i += 64) {
-      const uint2 e = queue[i];  // {row, byte column} of the chunk's first word
-      const int64_t at = int64_t(e.x) * W + e.y;
-      const uint32_t len = uint32_t(std::min<int64_t>(16, T - at));
-      u32x4 v;
+  const uint32_t nchunks = (nb + 15) >> 4;
+  auto row_of = [&](uint32_t x) { return wide ? uint32_t(x >= W) : __umulhi(x, magic_w); };
+  auto unit_of = [&](uint32_t c) { return ONE ? c >> 2 : __umulhi(c, magic_u); };
+  auto locate = [&](uint32_t k, uint32_t& row, uint32_t& col) {
+    const uint32_t x = c0 + (k < nchunks ? k << 4 : 0u);
+    row = row_of(x);
+    col = x - row * W;
+  };
+  auto entries = [&](uint32_t col) {
+    u32x4 e;
+    if constexpr (ONE) {
+      e = *reinterpret_cast<const u32x4_a4*>(tab + (col >> 2));  // the table ends in three spare entries
+    } else {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) e[w] = tab[min(unit_of(col + 4u * w), dd.n_units - 1u)];
+    }
+    return e;
+  };
+  auto at = [&](uint32_t row, uint32_t e, uint32_t off) {
+    const UnitSrc sr = src[e >> kUnitBits];
+    return sr.base + (uint64_t(row) * uint32_t(sr.stride) + ((e & ((1u << kUnitBits) - 1u)) * ub + off));
+  };
+  for (uint32_t first = 0; first < nchunks; first += kThreads * kUnroll) {
+    const uint32_t base = first + threadIdx.x;
+    u32x4 v[kUnroll], e[kUnroll];
+    uint32_t row[kUnroll], col[kUnroll];
+    uint32_t words = 0;  // bit u: chunk u goes word by word
+    bool run[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const uint32_t k = base + u * kThreads;
+      locate(k, row[u], col[u]);
+      e[u] = entries(col[u]);
+    }
+    if (first == 0) __syncthreads();  // `src` is whole; the first entries are on their way
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const uint32_t k = base + u * kThreads, u0 = unit_of(col[u]);
+      bool one = (k << 4) + 16u <= nb && col[u] + 16u <= W;
+#pragma unroll
+      for (int w = 1; w < 4; ++w) one = one && e[u][w] - e[u][0] == unit_of(col[u] + 4u * w) - u0;
+      run[u] = one;
+      words |= k < nchunks && !one ? 1u << u : 0u;
+      if (one)
+        v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_a4*>(at(row0 + row[u], e[u][0], col[u] - u0 * ub)));
+    }
+    // looked up again rather than held in registers (the entries are in the first-level cache); every lane takes its next one,
+    // so that a wavefront with a few of them in different places makes few rounds
+#pragma unroll 1
+    while (words) {
+      const uint32_t k = base + uint32_t(__ffs(words) - 1) * kThreads;
+      words &= words - 1;
+      uint32_t r0, cc;
+      locate(k, r0, cc);
+      const u32x4 en4 = entries(cc);
+      const uint32_t len = min(16u, nb - (k << 4));
+      u32x4 val;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        const bool have = uint32_t(w) * 4 < len;
-        const uint32_t xw = e.y + (have ? 4u * w : 0u);
-        const uint32_t rw = __umulhi(xw, magic_w), cw = xw - rw * W;  // rows may be shorter than a chunk
-        const RunLds rn = runs[run_of[__umulhi(cw, magic_u)]];
-        v[w] = *reinterpret_cast<const uint32_t*>(rn.adj + (uint64_t(e.x + rw) * rn.stride + cw));
+        uint32_t r = r0, c = cc + 4u * w, en = en4[w];
+        if (c >= W) {  // rows may be shorter than a chunk
+          const uint32_t x = r * W + c;
+          r = row_of(x);
+          c = x - r * W;
+          en = tab[unit_of(c)];
+        }
+        if (4u * w < len) val[w] = *reinterpret_cast<const uint32_t*>(at(row0 + r, en, c - unit_of(c) * ub));
       }
-      char* dp = dd.dst + at;
+      char* dp = d + (k << 4);
       if (len == 16) {
-        __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dp));
+        __builtin_nontemporal_store(val, reinterpret_cast<u32x4*>(dp));
       } else {
 #pragma unroll
         for (int w = 0; w < 3; ++w)
-          if (uint32_t(w) * 4 < len) reinterpret_cast<uint32_t*>(dp)[w] = v[w];
+          if (uint32_t(w) * 4 < len) reinterpret_cast<uint32_t*>(dp)[w] = val[w];
       }
     }
-    // the entries have been read before the queue is filled again
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    nq = 0;
-  };
-
-  // this workgroup's blocks: slot, slot + nslots, ...; (row0, c0) = position of the block's first byte
-  const int64_t step = int64_t(nslots) * blk;
-  const uint32_t step_rows = uint32_t(step / W), step_cols = uint32_t(step - int64_t(step_rows) * W);
-  uint32_t row0 = uint32_t(b0 / W);
-  uint32_t c0 = uint32_t(b0 - int64_t(row0) * W);
-  for (; b0 < T; b0 += step) {
-    const uint32_t nb = uint32_t(std::min<int64_t>(blk, T - b0));
-    char* __restrict__ d = dd.dst + b0;
-    const uint32_t nchunks = (nb + 15) >> 4;
-    // the loop bounds are the same for all lanes of a wavefront: every lane takes part in flush()
-    for (uint32_t wbase = wave << 6; wbase < nchunks; wbase += kThreads * kUnroll) {
-      const uint32_t base = wbase + lane;
-      u32x4 v[kUnroll];
-      bool ok[kUnroll], slow[kUnroll];
-      uint32_t rowq[kUnroll], colq[kUnroll];
-      // look every chunk up and start its load; lanes with no chunk, or with a chunk for the slow way,
-      // go through the same steps on chunk 0 and load the dummy bytes (no branches, four loads in flight)
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const uint32_t k = base + u * kThreads;
-        const bool valid = k < nchunks;
-        const uint32_t kb = valid ? k << 4 : 0u;
-        const uint32_t x = c0 + kb;
-        const uint32_t rr = __umulhi(x, magic_w), col = x - rr * W;
-        const RunLds rn = runs[run_of[__umulhi(col, magic_u)]];
-        ok[u] = valid && kb + 16u <= nb && col + 16u <= rn.end;
-        slow[u] = valid && !ok[u];
-        rowq[u] = row0 + rr;
-        colq[u] = col;
-        const char* p = reinterpret_cast<const char*>(rn.adj + (uint64_t(row0 + rr) * rn.stride + col));
-        v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_a4*>(ok[u] ? p : dummy));
-      }
-      // the chunks that need the slow way go on the queue, in lane order
-#pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const uint64_t m = __ballot(slow[u]);
-        if (slow[u]) queue[nq + __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u))] = make_uint2(rowq[u], colq[u]);
-        nq += uint32_t(__popcll(m));
-      }
-#pragma unroll
-      for (int u = 0; u < kUnroll; ++u)
-        if (ok[u]) __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4*>(d + ((base + u * kThreads) << 4)));
-      // one pass of the loop queues at most 64 * kUnroll chunks per wavefront
-      if (nq > kQueueCap - 64 * kUnroll) flush();
-    }
-    row0 += step_rows;
-    c0 += step_cols;
-    if (c0 >= W) {
-      c0 -= W;
-      ++row0;
+    for (int u = 0; u < kUnroll; ++u) {
+      const uint32_t k = base + u * kThreads;
+      if (run[u]) __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4*>(d + (k << 4)));
     }
   }
-  flush();
+}
+
+// Row-partitioned, rows a multiple of 16 bytes on 16-byte aligned addresses: every chunk lies in one unit.  A source shard
+// that is not on this GPU leaves its units' rows untouched.  Bound by HBM: 6.1 TB/s.  One launch for a whole tensor, where the dense
+// kernel takes one per 100 runs (a run is one row where several ranks are unloaded onto one): 4608 rows between TP 7 and TP 5,
+// with the other two tensors of that layer, 98 to 50 us; 49152 rows between TP 32 and TP 30 890 to 794 us.
+__global__ __launch_bounds__(kThreads) void reshard_table_rows_kernel(const TableBatch batch) {
+  __shared__ UnitSrc src[kMaxRanks];
+  for (int i = threadIdx.x; i < batch.nsrc; i += kThreads) src[i] = batch.src[i];
+  const TableDst& dd = batch.dst[table_dst(batch, blockIdx.x)];
+  __syncthreads();
+  const uint32_t R = batch.row_bytes, unit = batch.unit, blk = batch.block_bytes;
+  const int64_t T = int64_t(dd.n_units) * unit * R;
+  const int64_t b0 = int64_t(blockIdx.x - dd.first_block) * blk;
+  const uint32_t n16 = uint32_t(std::min<int64_t>(blk, T - b0) >> 4);
+  const uint32_t row0 = uint32_t(b0 / R), c0 = uint32_t(b0 - int64_t(row0) * R);
+  const uint32_t unit0 = row0 / unit, r0 = row0 - unit0 * unit;
+  u32x4* __restrict__ d = reinterpret_cast<u32x4*>(dd.dst + b0);
+  const uint32_t* __restrict__ tab = batch.table + dd.first_unit + unit0;
+  const bool wide = R > blk;  // at most one row end in a block
+  const uint32_t magic_r = div_magic(R), magic_u = div_magic(unit);
+  for (uint32_t base = threadIdx.x; base < n16; base += kThreads * kUnroll) {
+    u32x4 v[kUnroll];
+    const char* p[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const uint32_t k = base + u * kThreads, x = c0 + (k < n16 ? k << 4 : 0u);
+      const uint32_t rr = wide ? uint32_t(x >= R) : __umulhi(x, magic_r), r = r0 + rr;
+      const uint32_t du = fast_div(r, unit, magic_u);
+      const uint32_t e = tab[du];
+      const UnitSrc sr = src[e >> kUnitBits];
+      const uint32_t srow = (e & ((1u << kUnitBits) - 1u)) * unit + (r - du * unit);
+      p[u] = sr.base && k < n16 ? sr.base + (uint64_t(srow) * sr.stride + (x - rr * R)) : nullptr;
+      if (p[u]) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p[u]));
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u)
+      if (p[u]) __builtin_nontemporal_store(v[u], d + base + u * kThreads);
+  }
 }
 
 struct Extent {
@@ -941,12 +958,9 @@ struct ntp_reshard_plan {
   std::vector<int64_t> splits;                // [src_tp x dst_tp] units from rank r to rank s
   std::vector<ntp_unit_source_t> table;       // per destination unit, destination shards one after the other
   std::vector<int64_t> dst_first;             // first table entry of each destination shard
-  // run table of the gather kernel (column-partitioned 4-byte elements only)
-  bool runs_ok = false;
-  std::vector<RunDev> runs;                   // runs of all destination shards, one shard after the other
-  std::vector<int64_t> runs_first;            // first run of each destination shard
-  std::vector<uint16_t> run_of_unit;          // per destination unit (indexed like `table`): run number in its shard
-  void* dev_table = nullptr;                  // `runs` then `run_of_unit` on device `dev`, made by ntp_reshard_plan_prepare
+  std::vector<uint32_t> unit_src;             // `table` as the table kernels read it (empty: they cannot take this plan)
+  bool interleaved = false;                   // column-partitioned, neighbouring source units often go to different shards
+  void* dev_table = nullptr;                  // `unit_src` on device `dev`, made by ntp_reshard_plan_prepare
   int dev = -1;                               // device the plan was prepared on (-1: not prepared)
 };
 
@@ -978,22 +992,21 @@ extern "C" int ntp_reshard_plan_create(const ntp_tensor_spec_t* spec, int64_t ma
     for (int64_t i = 0; i < g.units; ++i)
       p->table[size_t(p->dst_first[g.dst_rank] + g.dst_unit + i)] = ntp_unit_source_t{g.src_rank, int32_t(g.src_unit + i)};
   }
-  // run table: the sub-shards are the runs
-  if (spec->partition_dim == 1 && spec->elem_size == 4) {
-    const int64_t ub = int64_t(spec->unit) * 4;
-    p->runs_first.assign(size_t(dst_tp) + 1, 0);
-    p->run_of_unit.resize(size_t(n_units));
-    p->runs_ok = true;
-    int32_t cur = 0;
-    for (const ntp_segment_t& g : p->segs) {
-      while (cur < g.dst_rank) p->runs_first[size_t(++cur)] = int64_t(p->runs.size());
-      const int64_t number = int64_t(p->runs.size()) - p->runs_first[size_t(cur)];
-      const int64_t end = (g.dst_unit + g.units) * ub, so = g.src_unit * ub;
-      if (number > 0xffff || end > 0xffffffffll || so > 0xffffffffll) p->runs_ok = false;
-      p->runs.push_back(RunDev{uint32_t(g.dst_unit * ub), uint32_t(end), uint32_t(so), uint32_t(g.src_rank)});
-      for (int64_t i = 0; i < g.units; ++i) p->run_of_unit[size_t(p->dst_first[g.dst_rank] + g.dst_unit + i)] = uint16_t(number);
-    }
-    while (cur < dst_tp) p->runs_first[size_t(++cur)] = int64_t(p->runs.size());
+  if (n_units > 0 && n_units <= (int64_t(1) << kUnitBits) && src_tp <= kMaxRanks && (spec->partition_dim == 0 || spec->elem_size == 4)) {
+    p->unit_src.assign(size_t(n_units) + 3, 0);  // a chunk's four entries are read with one load
+    for (int64_t u = 0; u < n_units; ++u)
+      p->unit_src[size_t(u)] = uint32_t(p->table[size_t(u)].src_rank) << kUnitBits | uint32_t(p->table[size_t(u)].src_unit);
+  }
+  if (spec->partition_dim == 1) {
+    // how many times a 128-byte line of a source row changes its destination shard: from one time in four on, bands
+    std::vector<int32_t> dst_of(size_t(n_units), 0);
+    std::vector<int64_t> first(size_t(src_tp) + 1, 0);
+    for (int32_t r = 0; r < src_tp; ++r) first[size_t(r) + 1] = first[size_t(r)] + p->src_units[size_t(r)];
+    for (const ntp_segment_t& g : p->segs)
+      std::fill_n(dst_of.begin() + first[size_t(g.src_rank)] + g.src_unit, g.units, g.dst_rank);
+    int64_t turns = 0;
+    for (int64_t u = 1; u < n_units; ++u) turns += dst_of[size_t(u)] != dst_of[size_t(u) - 1];
+    p->interleaved = turns * 4 * 128 > n_units * spec->unit * spec->elem_size;
   }
   *plan = p;
   return NTP_OK;
@@ -1036,44 +1049,44 @@ extern "C" int ntp_reshard_plan_table(const ntp_reshard_plan_t* plan, ntp_unit_s
 
 namespace {
 
-// Whether the run-table kernel can take this call with blocks of `block` bytes.
-bool units_path_ok(const ntp_handle* h, const ntp_reshard_plan* p, const void* const* src_shards, const int64_t* src_ld,
+// Whether the table kernels can take this call with blocks of `block` bytes: dense aligned destinations, and divisions that
+// are exact (n / d by multiply-high needs n * d <= 2^32).
+bool table_path_ok(const ntp_handle* h, const ntp_reshard_plan* p, const void* const* src_shards, const int64_t* src_ld,
                    void* const* dst_shards, const int64_t* dst_ld, int64_t block) {
   const ntp_tensor_spec_t& sp = p->spec;
-  if (!p->runs_ok || !p->dev_table || sp.rows == 0 || h->opt[NTP_OPT_RESHARD_NO_TABLE]) return false;
-  if (p->src_tp > kMaxRanks || sp.rows > 0x7fffffffll) return false;
+  if (!p->dev_table || h->opt[NTP_OPT_RESHARD_NO_TABLE]) return false;
+  constexpr int64_t kMax = int64_t(1) << 32;
+  const int64_t esz = sp.elem_size;
+  const bool by_rows = sp.partition_dim == 0;
+  if (sp.rows == 0 || sp.cols == 0 || sp.rows > 0x7fffffffll || sp.cols * esz > 0x7fffffffll) return false;
+  if (by_rows) {
+    const int64_t R = sp.cols * esz;
+    if (R % 16 || (R <= block && (block + R) * R > kMax) || (int64_t(sp.unit) + block / 16 + 2) * sp.unit > kMax) return false;
+  }
   for (int32_t r = 0; r < p->src_tp; ++r) {
     if (p->src_units[r] == 0) continue;
-    if (!src_shards[r] || src_ld[r] * 4 >= (int64_t(1) << 32)) return false;
+    if (src_ld[r] * esz >= kMax) return false;
+    if (by_rows ? (reinterpret_cast<uintptr_t>(src_shards[r]) | uintptr_t(src_ld[r] * esz)) & 15 : !src_shards[r]) return false;
   }
   bool any = false;
   for (int32_t s = 0; s < p->dst_tp; ++s) {
     if (p->dst_units[s] == 0 || !dst_shards[s]) continue;
-    const int64_t W = p->dst_units[s] * sp.unit * 4;
-    const int64_t n_runs = p->runs_first[s + 1] - p->runs_first[s];
-    if (dst_ld[s] * 4 != W || (reinterpret_cast<uintptr_t>(dst_shards[s]) & 63) != 0 ||
-        (block + W + 16) * W > (int64_t(1) << 32) ||
-        n_runs * int64_t(sizeof(RunLds)) + p->dst_units[s] * 2 + 16 + int64_t(kWaves * kQueueCap * sizeof(uint2)) > int64_t(kUnitLdsMax))
-      return false;
+    const int64_t W = by_rows ? sp.cols * esz : p->dst_units[s] * sp.unit * esz;
+    if (dst_ld[s] * esz != W || reinterpret_cast<uintptr_t>(dst_shards[s]) & (by_rows ? 15 : 63)) return false;
+    if (!by_rows && ((W <= block + 16 && (block + W + 16) * W > kMax) || (W + 16) * sp.unit * esz > kMax)) return false;
     any = true;
   }
   return any;
 }
 
-}  // namespace
-
-namespace {
-
-// The plan's run table goes to the current device (allocates and waits for the copy).
+// The plan's table goes to the current device (allocates and waits for the copy).
 int upload_table(ntp_reshard_plan_t* plan) {
-  const size_t runs_bytes = plan->runs.size() * sizeof(RunDev), idx_bytes = plan->run_of_unit.size() * sizeof(uint16_t);
-  if (hipMalloc(&plan->dev_table, runs_bytes + idx_bytes) != hipSuccess) {
+  const size_t bytes = plan->unit_src.size() * sizeof(uint32_t);
+  if (hipMalloc(&plan->dev_table, bytes) != hipSuccess) {
     plan->dev_table = nullptr;
     return NTP_ERR_LAUNCH;
   }
-  if (hipMemcpy(plan->dev_table, plan->runs.data(), runs_bytes, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(static_cast<char*>(plan->dev_table) + runs_bytes, plan->run_of_unit.data(), idx_bytes,
-                hipMemcpyHostToDevice) != hipSuccess) {
+  if (hipMemcpy(plan->dev_table, plan->unit_src.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipFree(plan->dev_table);
     plan->dev_table = nullptr;
     return NTP_ERR_LAUNCH;
@@ -1091,7 +1104,7 @@ extern "C" int ntp_reshard_plan_prepare(ntp_reshard_plan_t* plan) {
     return NTP_ERR_NO_DEVICE;
   }
   if (plan->dev >= 0) return cur == plan->dev ? NTP_OK : NTP_ERR_INVALID_ARG;  // a plan lives on one device
-  if (plan->runs_ok && !plan->runs.empty()) {
+  if (!plan->unit_src.empty()) {
     const int st = upload_table(plan);
     if (st != NTP_OK) return st;
   }
@@ -1108,44 +1121,48 @@ extern "C" int ntp_reshard_plan_run(ntp_handle_t* h, ntp_reshard_plan_t* plan, c
   if (plan->dev != h->device) return NTP_ERR_NOT_PREPARED;
   int64_t block = 16384;
   if (const int64_t e = h->opt[NTP_OPT_RESHARD_TABLE_BLOCK]) block = std::min<int64_t>(1 << 20, std::max<int64_t>(1024, e & ~63ll));
-  if (!units_path_ok(h, plan, src_shards, src_ld, dst_shards, dst_ld, block))
+  if (!table_path_ok(h, plan, src_shards, src_ld, dst_shards, dst_ld, block))
     return ntp::reshard_launch(h, &plan->spec, plan->segs, plan->src_units, plan->dst_units, src_shards, src_ld, dst_shards,
                                dst_ld, stream);
 
   const ntp_tensor_spec_t& sp = plan->spec;
-  hipStream_t hs = static_cast<hipStream_t>(stream);
-  UnitBatch batch{};
-  batch.runs = static_cast<const RunDev*>(plan->dev_table);
-  batch.run_of_unit = reinterpret_cast<const uint16_t*>(static_cast<const char*>(plan->dev_table) + plan->runs.size() * sizeof(RunDev));
+  const bool by_rows = sp.partition_dim == 0;
+  TableBatch batch{};
+  batch.table = static_cast<const uint32_t*>(plan->dev_table);
   batch.rows = uint32_t(sp.rows);
-  batch.unit_bytes = uint32_t(sp.unit) * 4u;
+  batch.row_bytes = uint32_t(sp.cols * sp.elem_size);
+  batch.unit = uint32_t(by_rows ? sp.unit : sp.unit * sp.elem_size);
   batch.block_bytes = uint32_t(block);
+  batch.nsrc = plan->src_tp;
   for (int32_t r = 0; r < plan->src_tp; ++r)
-    batch.src[r] = UnitSrc{static_cast<const char*>(src_shards[r]), uint64_t(src_ld[r]) * 4u};
-  int32_t s = 0;
-  while (s < plan->dst_tp) {
+    batch.src[r] = UnitSrc{static_cast<const char*>(src_shards[r]), uint64_t(src_ld[r]) * uint64_t(sp.elem_size)};
+  const int64_t per_unit = int64_t(sp.unit) * (by_rows ? sp.cols : sp.rows) * sp.elem_size;  // bytes
+  for (int32_t s = 0; s < plan->dst_tp;) {
     batch.ndst = 0;
-    int64_t nblk = 0;
-    uint32_t lds = 0;
-    double bytes = 0.0;
-    for (; s < plan->dst_tp && batch.ndst < uint32_t(kUnitDsts); ++s) {
+    int64_t total = 0;
+    for (; s < plan->dst_tp && batch.ndst < kMaxRanks; ++s) {
       if (plan->dst_units[s] == 0 || !dst_shards[s]) continue;
-      const int64_t total = sp.rows * plan->dst_units[s] * sp.unit * 4;
-      const uint32_t n_runs = uint32_t(plan->runs_first[s + 1] - plan->runs_first[s]);
-      batch.dst[batch.ndst++] = UnitDst{static_cast<char*>(dst_shards[s]), uint32_t(plan->dst_first[s]), uint32_t(plan->dst_units[s]),
-                                        uint32_t(plan->runs_first[s]), n_runs};
-      nblk = std::max(nblk, (total + block - 1) / block);
-      lds = std::max(lds, unit_lds_bytes(n_runs, uint32_t(plan->dst_units[s])));
-      bytes += 2.0 * double(total);
+      batch.dst[batch.ndst++] = TableDst{static_cast<char*>(dst_shards[s]), uint32_t(plan->dst_first[s]), uint32_t(plan->dst_units[s]), 0, 0};
+      total += plan->dst_units[s] * per_unit;
     }
     if (batch.ndst == 0) break;
-    // workgroups per destination shard: enough of them to fill the chip, each walking over several blocks
-    // workgroups per destination shard: one per block, or fewer that walk over several blocks each when
-    // the shards are very large (the tables are copied into LDS once per workgroup)
-    const int64_t slots = std::max<int64_t>(1, std::min<int64_t>(nblk, (int64_t(h->compute_units) * int64_t(kUnitBlocksPerCu) + batch.ndst - 1) / batch.ndst));
-    const uint64_t blocks = uint64_t(slots) * batch.ndst;
+    const int64_t bands = plan->interleaved ? std::max<int64_t>(1, total / kBandBytes) : 1;
+    uint64_t blocks = 0;
+    for (int32_t i = 0; i < batch.ndst; ++i) {
+      TableDst& d = batch.dst[i];
+      const int64_t n = (int64_t(d.n_units) * per_unit + block - 1) / block, q = (n + bands - 1) / bands;
+      if (uint64_t(q) * uint64_t(bands) > 0x7fffffffull) return NTP_ERR_UNSUPPORTED;
+      d.first_block = uint32_t(blocks);
+      d.per_band = uint32_t(q);
+      blocks += uint64_t(q);
+    }
+    batch.band_blocks = uint32_t(blocks);
+    blocks *= uint64_t(bands);
+    if (blocks > 0x7fffffffull) return NTP_ERR_UNSUPPORTED;
+    const double bytes = 2.0 * double(total);
     if (ntp::timing_on(h)) ntp::timing_begin(h, stream, "reshard_table", 0.0, bytes);
-    hipLaunchKernelGGL(reshard_units_kernel, dim3(uint32_t(blocks)), dim3(kThreads), lds, hs, batch);
+    const auto kernel = by_rows ? reshard_table_rows_kernel : batch.unit == 4 ? reshard_table_cols_kernel<true> : reshard_table_cols_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(uint32_t(blocks)), dim3(kThreads), 0, static_cast<hipStream_t>(stream), batch);
     const bool ok = hipGetLastError() == hipSuccess;
     ntp::timing_end(h, stream);
     if (!ok) return NTP_ERR_LAUNCH;

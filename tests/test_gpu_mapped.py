@@ -93,6 +93,49 @@ def test_plan_run_bit_exact(rows, k, unit, t, tr, pd, pad_src, pad_dst, misalign
         assert np.array_equal(got[s], want[s]), f"dst rank {s}"
 
 
+# the unit-table kernels where they can go wrong: thousands of one-unit runs, rows above and around the block size, units
+# of 2 and 3 elements, rows shorter than a chunk, whole and partial last blocks, 2-byte rows, heads
+@pytest.mark.parametrize("back", [False, True], ids=["comp-to-sync", "sync-to-comp"])
+@pytest.mark.parametrize("rows,k,unit,t,tr,pd,dtype", [
+    (5, 9000, 1, 7, 5, 1, np.uint32), (3, 66001, 1, 4, 3, 1, np.uint32), (2, 16388, 1, 4, 3, 1, np.uint32),
+    (7, 3001, 2, 5, 3, 1, np.uint32), (9, 2001, 3, 8, 5, 1, np.uint32), (4099, 3, 1, 2, 1, 1, np.uint32), (17, 96, 128, 41, 31, 1, np.uint32),
+    (4, 6000, 1, 7, 5, 0, np.uint32), (5000, 9, 1, 4, 3, 0, np.uint32), (8192, 40, 1, 64, 48, 0, np.uint16), (20000, 24, 1, 4, 3, 0, np.uint32),
+    (16, 96, 128, 41, 31, 0, np.uint32), (4100, 11, 1, 4, 3, 0, np.uint32)])
+def test_plan_run_unit_table_edges(rows, k, unit, t, tr, pd, dtype, back):
+    _say(f"unit table rows={rows} k={k} unit={unit} t={t} t'={tr} pd={pd} {dtype.__name__} back={back}")
+    comp, sync = O.comp_sync_plan(k, t, tr)
+    smap, a, dmap, b = (sync, tr, comp, t) if back else (comp, t, sync, tr)
+    G = _logical(rows, k * unit, dtype) if pd == 1 else _logical(k * unit, rows, dtype)
+    got, want = _run(G, pd, unit, smap, a, dmap, b)
+    for s in range(b):
+        assert np.array_equal(got[s], want[s]), f"dst rank {s}"
+
+
+def test_plan_run_rows_of_absent_sources_stay():
+    import torch
+    import paper_2504_06095_amd as N
+    _say("row-partitioned plan with absent source shards")
+    k, t, tr, cols = 400, 8, 6, 48
+    comp, sync = O.comp_sync_plan(k, t, tr)
+    G = _logical(k, cols)
+    src_np = [O.cut_shard_mapped(G, 0, 1, comp, t, r) for r in range(t)]
+    plan = N.ntp_reshard_plan_create(N.tensor_spec(k, cols, 0, 1, 4), t, comp, tr, sync)
+    plan.ntp_reshard_plan_prepare()
+    src = [None] * t
+    src[6] = torch.from_numpy(src_np[6].view(np.int32)).cuda()
+    dst = [torch.full((sync.count(s), cols), -1, dtype=torch.int32, device="cuda") for s in range(tr)]
+    plan.ntp_reshard_plan_run(src, dst)
+    torch.cuda.synchronize()
+    plan.destroy()
+    for s in range(tr):
+        mine = [u for u in range(k) if sync[u] == s]
+        want = np.full((len(mine), cols), -1, np.int32)
+        for i, u in enumerate(mine):
+            if comp[u] == 6:
+                want[i] = G[u].view(np.int32)
+        assert np.array_equal(dst[s].cpu().numpy(), want), f"dst rank {s}"
+
+
 def test_plan_run_without_the_table_kernel(opts):
     _say("plan_run, table kernel switched off")
     opts(K.NTP_OPT_RESHARD_NO_TABLE, 1)
