@@ -45,6 +45,13 @@ struct CopyBatch {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+
+// An address that was read from LDS, as a pointer to device memory (without the address space the compiler would use flat loads).
+template <typename T>
+__device__ __forceinline__ const T __attribute__((address_space(1))) * global_ptr(uint64_t p) {
+  return reinterpret_cast<const T __attribute__((address_space(1)))*>(p);
+}
 
 constexpr int kUnroll = 4;  // independent 16-byte transfers per lane in flight
 
@@ -150,7 +157,7 @@ __global__ __launch_bounds__(kThreads) void reshard_copy_kernel(const CopyBatch 
 }
 
 
-// ---- column-partitioned tensors of 4-byte elements: destination-major gather ------------------
+// ---- column-partitioned tensors: destination-major gather ------------------
 // A job is a block of destination columns of one destination shard together with the pieces
 // (sub-shards) that fill it, each from another source shard.  A workgroup takes a block of
 // destination rows and copies all pieces of those rows, so destination rows are written whole and
@@ -312,6 +319,103 @@ __global__ __launch_bounds__(kThreads) void reshard_flat_kernel(const GatherBatc
   }
 }
 
+// The same for 2-byte elements: loads of any 2-byte alignment, and a chunk that straddles a row end or a piece boundary is
+// put together half-word by half-word in a second pass (halves have to be waited for before they are packed), whose loads
+// go out before the first pass's are waited for.  The pieces are looked up in LDS.  Bound by HBM: 12288 x 49152 from 8 to 7
+// ranks 612 to 421 us (5.7 TB/s) against the row-by-row copy, whose 16-byte stores are not aligned.  (4-byte elements stay
+// with the kernel above: the same second pass costs them 4 % at odd widths.)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void reshard_flat2_kernel(const GatherBatch batch) {
+  struct PieceLds {
+    uint64_t adj;  // what goes to column c of the block's row r is at adj + r * stride + c
+    uint32_t stride, end;
+  };
+  __shared__ PieceLds piece[kMaxPieces];
+  // consecutive workgroups take consecutive blocks of one job (measured faster than dealing the jobs round)
+  const uint32_t nblk = gridDim.x / uint32_t(batch.njobs);
+  const uint32_t ji = blockIdx.x / nblk, bi = blockIdx.x - ji * nblk;
+  const GatherJob& job = batch.job[ji];
+  const uint32_t np = job.npieces;
+  const uint32_t W = job.piece[np - 1].end;
+  const int64_t T = int64_t(job.rows) * W;
+  const uint32_t blk = batch.rows_per_block;  // bytes per block here
+  const int64_t b0 = int64_t(bi) * blk;
+  if (b0 >= T) return;  // the whole workgroup, before the barrier
+  const uint32_t nb = uint32_t(std::min<int64_t>(blk, T - b0));
+  const int64_t row0 = b0 / W;
+  const uint32_t c0 = uint32_t(b0 - row0 * W);
+  if (threadIdx.x < np) {
+    const Piece& pc = job.piece[threadIdx.x];
+    piece[threadIdx.x] = PieceLds{uint64_t(reinterpret_cast<uintptr_t>(pc.src)) + uint64_t(row0 * pc.src_stride) - pc.begin, uint32_t(pc.src_stride), pc.end};
+  }
+  __syncthreads();
+  const bool wide = W > blk + 16u;  // at most one row end in a block
+  const uint32_t magic = div_magic(W);
+  char* __restrict__ d = job.dst + b0;
+  const uint32_t nchunks = (nb + 15) >> 4;
+  auto locate = [&](uint32_t x, uint32_t& row, uint32_t& col) {
+    row = wide ? uint32_t(x >= W) : fast_div(x, W, magic);
+    col = x - row * W;
+  };
+  auto piece_of = [&](uint32_t col) {
+    uint32_t pi = 0;
+    for (uint32_t p = 1; p < np; ++p) pi += col >= job.piece[p].begin;
+    return piece[pi];
+  };
+  for (uint32_t base = threadIdx.x; base < nchunks; base += kThreads * kUnroll) {
+    u32x4 v[kUnroll];
+    bool run[kUnroll];
+    uint32_t split = 0;  // bit u: chunk u goes half-word by half-word
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const uint32_t k = base + u * kThreads;
+      uint32_t row, col;
+      locate(c0 + (k < nchunks ? k << 4 : 0u), row, col);
+      const PieceLds pc = piece_of(col);
+      run[u] = (k << 4) + 16u <= nb && col + 16u <= pc.end;
+      split |= k < nchunks && !run[u] ? 1u << u : 0u;
+      if (run[u]) v[u] = __builtin_nontemporal_load(global_ptr<u32x4_a2>(pc.adj + (row * pc.stride + col)));
+    }
+#pragma unroll 1
+    while (split) {
+      const uint32_t k = base + uint32_t(__ffs(split) - 1) * kThreads;
+      split &= split - 1;
+      const uint32_t len = min(16u, nb - (k << 4));
+      uint16_t val[8];
+#pragma unroll
+      for (int w = 0; w < 8; ++w) {
+        if (uint32_t(w) * 2 >= len) continue;
+        uint32_t row, col;  // rows may be shorter than a chunk
+        locate(c0 + (k << 4) + uint32_t(w) * 2, row, col);
+        const PieceLds pc = piece_of(col);
+        val[w] = *global_ptr<uint16_t>(pc.adj + (row * pc.stride + col));
+      }
+      char* dp = d + (k << 4);
+      if (len == 16) {
+        u32x4 out;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) out[w] = uint32_t(val[2 * w]) | uint32_t(val[2 * w + 1]) << 16;
+        __builtin_nontemporal_store(out, reinterpret_cast<u32x4*>(dp));
+      } else {
+#pragma unroll
+        for (int w = 0; w < 8; ++w)
+          if (uint32_t(w) * 2 < len) reinterpret_cast<uint16_t*>(dp)[w] = val[w];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u)
+      if (run[u]) __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4*>(d + ((base + u * kThreads) << 4)));
+  }
+}
+
+// Whether a job's destination is a dense aligned shard that its flat kernel can divide into rows exactly.
+bool flat_ok(const GatherJob& j, int64_t block, int64_t esz) {
+  const int64_t W = j.piece[j.npieces - 1].end;
+  int64_t smax = 0;
+  for (uint32_t p = 0; p < j.npieces; ++p) smax = std::max(smax, j.piece[p].src_stride);
+  return j.dst_stride == W && (reinterpret_cast<uintptr_t>(j.dst) & 63) == 0 &&
+         ((esz == 2 && W > block + 16) || (block + W + 16) * W <= (int64_t(1) << 32)) && smax * (block / W + 2) < (int64_t(1) << 32);
+}
+
 // ---- dense ranges (row-partitioned tensors whose shards are dense): plain streaming copy --------
 constexpr int kMaxRanges = 100;  // 100 x 32 B + header < 4 KiB of kernel arguments
 constexpr int64_t kDenseBlock = 16384;  // bytes per workgroup
@@ -329,12 +433,11 @@ struct DenseBatch {
 
 __global__ __launch_bounds__(kThreads) void reshard_dense_kernel(const DenseBatch batch) {
   const uint32_t b = blockIdx.x;
-  int lo = 0, hi = batch.n - 1;  // last range whose first block is <= b
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (batch.r[mid].first_block <= b) lo = mid;
-    else hi = mid - 1;
-  }
+  // last range whose first block is <= b: one load per lane instead of a chain of scalar loads
+  const int lane = threadIdx.x & 63;
+  int lo = -1;
+#pragma unroll
+  for (int i = 0; i < kMaxRanges; i += 64) lo += __popcll(__ballot(i + lane < batch.n && batch.r[min(i + lane, kMaxRanges - 1)].first_block <= b));
   const DenseRange& rg = batch.r[lo];
   const int64_t off = int64_t(b - rg.first_block) * kDenseBlock;
   const uint32_t n16 = uint32_t(std::min<int64_t>(kDenseBlock, rg.bytes - off) >> 4);
@@ -443,7 +546,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
   };
   auto at = [&](uint32_t row, uint32_t e, uint32_t off) {
     const UnitSrc sr = src[e >> kUnitBits];
-    return sr.base + (uint64_t(row) * uint32_t(sr.stride) + ((e & ((1u << kUnitBits) - 1u)) * ub + off));
+    return uint64_t(reinterpret_cast<uintptr_t>(sr.base)) + (uint64_t(row) * uint32_t(sr.stride) + ((e & ((1u << kUnitBits) - 1u)) * ub + off));
   };
   for (uint32_t first = 0; first < nchunks; first += kThreads * kUnroll) {
     const uint32_t base = first + threadIdx.x;
@@ -467,7 +570,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
       run[u] = one;
       words |= k < nchunks && !one ? 1u << u : 0u;
       if (one)
-        v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_a4*>(at(row0 + row[u], e[u][0], col[u] - u0 * ub)));
+        v[u] = __builtin_nontemporal_load(global_ptr<u32x4_a4>(at(row0 + row[u], e[u][0], col[u] - u0 * ub)));
     }
     // looked up again rather than held in registers (the entries are in the first-level cache); every lane takes its next one,
     // so that a wavefront with a few of them in different places makes few rounds
@@ -489,7 +592,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
           c = x - r * W;
           en = tab[unit_of(c)];
         }
-        if (4u * w < len) val[w] = *reinterpret_cast<const uint32_t*>(at(row0 + r, en, c - unit_of(c) * ub));
+        if (4u * w < len) val[w] = *global_ptr<uint32_t>(at(row0 + r, en, c - unit_of(c) * ub));
       }
       char* dp = d + (k << 4);
       if (len == 16) {
@@ -529,7 +632,7 @@ __global__ __launch_bounds__(kThreads) void reshard_table_rows_kernel(const Tabl
   const uint32_t magic_r = div_magic(R), magic_u = div_magic(unit);
   for (uint32_t base = threadIdx.x; base < n16; base += kThreads * kUnroll) {
     u32x4 v[kUnroll];
-    const char* p[kUnroll];
+    uint64_t p[kUnroll];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const uint32_t k = base + u * kThreads, x = c0 + (k < n16 ? k << 4 : 0u);
@@ -538,8 +641,8 @@ __global__ __launch_bounds__(kThreads) void reshard_table_rows_kernel(const Tabl
       const uint32_t e = tab[du];
       const UnitSrc sr = src[e >> kUnitBits];
       const uint32_t srow = (e & ((1u << kUnitBits) - 1u)) * unit + (r - du * unit);
-      p[u] = sr.base && k < n16 ? sr.base + (uint64_t(srow) * sr.stride + (x - rr * R)) : nullptr;
-      if (p[u]) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p[u]));
+      p[u] = sr.base && k < n16 ? uint64_t(reinterpret_cast<uintptr_t>(sr.base)) + (uint64_t(srow) * sr.stride + (x - rr * R)) : 0;
+      if (p[u]) v[u] = __builtin_nontemporal_load(global_ptr<u32x4>(p[u]));
     }
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u)
@@ -746,7 +849,9 @@ int ntp::reshard_launch(ntp_handle* h, const ntp_tensor_spec_t* spec, const std:
 
   hipStream_t hs = static_cast<hipStream_t>(stream);
 
-  if (!by_rows && esz == 4) {
+  std::vector<CopySeg> copies;
+  std::vector<DenseRange> ranges;
+  if (!by_rows) {
     // destination-major gather: consecutive sub-shards of one destination shard form a job
     std::vector<GatherJob> jobs;
     int32_t cur_dst = -1;
@@ -757,7 +862,12 @@ int ntp::reshard_launch(ntp_handle* h, const ntp_tensor_spec_t* spec, const std:
       char* dp = static_cast<char*>(dst_shards[g.dst_rank]);
       const int64_t c0 = g.dst_unit * spec->unit * esz, c1 = c0 + g.units * spec->unit * esz;
       if (!sp || !dp || c1 == c0 || spec->rows == 0) continue;  // not on this GPU, or empty
-      if (spec->rows > 0xffffffffll || c1 - c0 > 0x7fffffffll) return NTP_ERR_UNSUPPORTED;
+      if (spec->rows > 0xffffffffll || c1 - c0 > 0x7fffffffll) {
+        if (esz == 4) return NTP_ERR_UNSUPPORTED;
+        const int64_t sld = src_ld[g.src_rank] * esz, dld = dst_ld[g.dst_rank] * esz;
+        copies.push_back(CopySeg{sp + g.src_unit * spec->unit * esz, dp + c0, sld, dld, c1 - c0, spec->rows, 0, 0, 0, 0});
+        continue;
+      }
       const bool fresh = jobs.empty() || g.dst_rank != cur_dst || c0 != cur_end || jobs.back().npieces == kMaxPieces ||
                          c1 - job_col0 > 0x7fffffffll;
       if (fresh) {
@@ -782,15 +892,7 @@ int ntp::reshard_launch(ntp_handle* h, const ntp_tensor_spec_t* spec, const std:
                                    ? std::min<int64_t>(kFlatBlockMax, std::max<int64_t>(1024, h->opt[NTP_OPT_RESHARD_FLAT_BLOCK] & ~63ll))
                                    : 16384;
     std::vector<GatherJob> flat, rowwise;
-    for (const GatherJob& j : jobs) {
-      const int64_t W = j.piece[j.npieces - 1].end;
-      int64_t smax = 0;
-      for (uint32_t p = 0; p < j.npieces; ++p) smax = std::max(smax, j.piece[p].src_stride);
-      const bool ok = j.dst_stride == W && (reinterpret_cast<uintptr_t>(j.dst) & 63) == 0 &&
-                      (int64_t(kFlatBlock) + W + 16) * W <= (int64_t(1) << 32) &&
-                      smax * (int64_t(kFlatBlock) / W + 2) < (int64_t(1) << 32) && !h->opt[NTP_OPT_RESHARD_NO_FLAT];
-      (ok ? flat : rowwise).push_back(j);
-    }
+    for (const GatherJob& j : jobs) (flat_ok(j, kFlatBlock, esz) && !h->opt[NTP_OPT_RESHARD_NO_FLAT] ? flat : rowwise).push_back(j);
     for (size_t base = 0; base < flat.size(); base += kMaxJobs) {
       GatherBatch batch{};
       batch.njobs = int32_t(std::min<size_t>(kMaxJobs, flat.size() - base));
@@ -808,12 +910,20 @@ int ntp::reshard_launch(ntp_handle* h, const ntp_tensor_spec_t* spec, const std:
       if (blocks > 0x7fffffffull) return NTP_ERR_UNSUPPORTED;
       if (blocks == 0) continue;
       if (ntp::timing_on(h)) ntp::timing_begin(h, stream, "reshard_flat", 0.0, bytes);
-      hipLaunchKernelGGL(reshard_flat_kernel, dim3(uint32_t(blocks)), dim3(kThreads), 0, hs, batch);
+      hipLaunchKernelGGL(esz == 4 ? reshard_flat_kernel : reshard_flat2_kernel, dim3(uint32_t(blocks)), dim3(kThreads), 0, hs, batch);
       const bool ok = hipGetLastError() == hipSuccess;
       ntp::timing_end(h, stream);
       if (!ok) return NTP_ERR_LAUNCH;
     }
     jobs.swap(rowwise);
+    if (esz != 4) {  // the row-wise kernel moves words: what is left of 2-byte elements is copied piece by piece
+      for (const GatherJob& j : jobs)
+        for (uint32_t p = 0; p < j.npieces; ++p) {
+          const Piece& pc = j.piece[p];
+          copies.push_back(CopySeg{pc.src, j.dst + pc.begin, pc.src_stride, j.dst_stride, int64_t(pc.end - pc.begin), int64_t(j.rows), 0, 0, 0, 0});
+        }
+      jobs.clear();
+    }
     for (size_t base = 0; base < jobs.size(); base += kMaxJobs) {
       GatherBatch batch{};
       batch.njobs = int32_t(std::min<size_t>(kMaxJobs, jobs.size() - base));
@@ -842,29 +952,20 @@ int ntp::reshard_launch(ntp_handle* h, const ntp_tensor_spec_t* spec, const std:
       ntp::timing_end(h, stream);
       if (!ok) return NTP_ERR_LAUNCH;
     }
-    return NTP_OK;
   }
 
-  // segments -> dense ranges and 2-D copies
-  std::vector<CopySeg> copies;
-  std::vector<DenseRange> ranges;
+  // row-partitioned: segments -> dense ranges and 2-D copies
   for (const ntp_segment_t& g : segs) {
+    if (!by_rows) break;
     const char* sp = static_cast<const char*>(src_shards[g.src_rank]);
     char* dp = static_cast<char*>(dst_shards[g.dst_rank]);
     if (!sp || !dp) continue;  // not on this GPU
     const int64_t sld = src_ld[g.src_rank] * esz, dld = dst_ld[g.dst_rank] * esz;
     CopySeg c{};
-    if (by_rows) {
-      c.src = sp + g.src_unit * spec->unit * sld;
-      c.dst = dp + g.dst_unit * spec->unit * dld;
-      c.rows = g.units * spec->unit;
-      c.row_bytes = spec->cols * esz;
-    } else {
-      c.src = sp + g.src_unit * spec->unit * esz;
-      c.dst = dp + g.dst_unit * spec->unit * esz;
-      c.rows = spec->rows;
-      c.row_bytes = g.units * spec->unit * esz;
-    }
+    c.src = sp + g.src_unit * spec->unit * sld;
+    c.dst = dp + g.dst_unit * spec->unit * dld;
+    c.rows = g.units * spec->unit;
+    c.row_bytes = spec->cols * esz;
     c.src_stride = sld;
     c.dst_stride = dld;
     if (c.rows == 0 || c.row_bytes == 0) continue;

@@ -95,6 +95,28 @@ def test_reshard_bf16_elements(pd, a, b, misalign):
         assert np.array_equal(got[s], want[s])
 
 
+# the flat kernel of 2-byte elements: one- to three-element rows, rows around and above the block of 16 KiB, several blocks,
+# shards smaller than a chunk, heads, total sizes of every remainder
+@pytest.mark.parametrize("rows,cols,unit,a,b", [
+    (1000, 5, 1, 2, 3), (4099, 3, 1, 2, 3), (3, 7, 1, 2, 3), (3, 33000, 1, 5, 4), (2, 16396, 1, 2, 2), (3, 8190 * 3, 1, 4, 3), (257, 2251, 1, 3, 2),
+    (1111, 515, 1, 8, 7), (40, 16 * 24, 16, 7, 5), (1, 100001, 1, 3, 4)])
+def test_reshard_2byte_columns(rows, cols, unit, a, b):
+    _say(f"reshard 2-byte columns {rows}x{cols} unit={unit} {a}->{b}")
+    got, want, _ = _run(_logical(rows, cols, np.uint16), 1, unit, a, b)
+    for s in range(b):
+        assert np.array_equal(got[s], want[s]), f"dst rank {s}"
+
+
+def test_reshard_2byte_qkv_gqa():
+    _say("reshard 2-byte GQA columns")
+    n_q, n_kv, d = 16, 4, 8
+    G = _logical(96, (n_q + 2 * n_kv) * d, np.uint16)
+    for a, b in [(5, 7), (7, 5), (16, 3)]:
+        got, want, _ = _run(G, 1, d, a, b, O.QKV_GQA, n_q, n_kv)
+        for s in range(b):
+            assert np.array_equal(got[s], want[s])
+
+
 @pytest.mark.parametrize("pd", [0, 1])
 def test_reshard_qkv_gqa(pd):
     _say(f"reshard GQA pd={pd}")
