@@ -112,6 +112,7 @@ bool ring_combo(bool a_kc, bool b_kc, int epi) {
 // order and applies the epilogue.
 struct SplitChoice {
   int tile, splits, k_chunk;
+  bool deep;  // the deep-pipelined kernel
 };
 
 constexpr double kTileCycles = 2650.0;      // one 256 x 256 x 64 K tile on one compute unit at rate 1
@@ -132,7 +133,7 @@ double tile_time(int64_t M, int64_t N, int64_t ktiles, int layout, int i, int sp
 // ws_bytes: room for the partial sums (0: never split).
 SplitChoice choose_split(const ntp_handle* h, int64_t ws_bytes, int64_t M, int64_t N, int64_t K, int layout, int plain_tile,
                          int64_t ldw) {
-  SplitChoice best{plain_tile, 1, 0};
+  SplitChoice best{plain_tile, 1, 0, false};
   const int64_t ktiles = (K + 63) / 64;
   const int cus = h->compute_units;
   const int forced = int(h->opt[NTP_OPT_GEMM_SPLIT]);  // 1: never split; n > 1: n chunks if they fit
@@ -154,7 +155,7 @@ SplitChoice choose_split(const ntp_handle* h, int64_t ws_bytes, int64_t M, int64
       const double t = tile_time(M, N, ktiles, layout, i, sp, cus) + reduce;
       if (t < best_t) {
         best_t = t;
-        best = SplitChoice{i, sp, int(chunk_tiles * 64)};
+        best = SplitChoice{i, sp, int(chunk_tiles * 64), false};
       }
     }
   }
@@ -176,11 +177,42 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs g, co
   store4<EPI>(g, int(m), n0, acc);
 }
 
+constexpr int kDeepTile = 8;  // index of the deep-pipelined kernel's tile shape (128 x 128 on 8 wavefronts)
+constexpr int kMaxDeepSplits = 16;
+
+// Whether the deep-pipelined kernel takes over from `old`, and in how many K chunks.  Measured over 45 random shapes of up to one
+// 128 x 128 tile per compute unit, all layouts: against the persistent kernels on 128 x 128 tiles it is never slower (2 % at
+// five K tiles, 20-45 % at 10-60, up to 5.5 times where few tiles meet a long K axis that was not cut: 752 x 160 over K = 9544
+// 125 -> 22 us); against larger tiles with a cut K axis it is 15-45 % faster up to half as many tiles as compute units (224 x
+// 4344 over K = 6136: 50 -> 33 us) and slower above (280 x 7944 over K = 9152, 189 tiles: 75 -> 83 us).
+// Chunks: every one has a compute unit to itself.  A K tile takes 0.47 us (LDS reads: 96 KB a K tile and workgroup), the reduce launch 3.5 us
+// and its traffic at 4.4 TB/s; a chunk has at least four K tiles.
+SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int64_t M, int64_t N, int64_t K, int64_t ldw, const SplitChoice& old) {
+  const TileShape& ts = kTileShapes[old.tile];
+  const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), ktiles = (K + 63) / 64;
+  if (tiles > h->compute_units || (old.splits > 1 ? tiles * 2 > h->compute_units : ts.bm != 128 || ts.bn != 128)) return old;
+  SplitChoice best{kDeepTile, 1, int(ktiles * 64), true};
+  double best_t = 0.47 * double(ktiles);
+  for (int sp = 2; sp <= kMaxDeepSplits && tiles * sp <= h->compute_units; ++sp) {
+    const int64_t chunk_tiles = (ktiles + sp - 1) / sp;
+    if (chunk_tiles < 4 || int64_t(sp) * M * ldw * 4 > ws_bytes) break;
+    if ((sp - 1) * chunk_tiles * 64 >= K) continue;  // the last chunk would be empty
+    const double t = 0.47 * double(chunk_tiles) + 3.5 + double(M) * double(ldw) * (4.0 * sp + 4.0) / 4.4e6;
+    if (t < best_t) {
+      best_t = t;
+      best = SplitChoice{kDeepTile, sp, int(chunk_tiles * 64), true};
+    }
+  }
+  return best;
+}
+
 // Kernel variant (-1 generic, else a tile shape) and K chunks for a GEMM (g: M, N, K, n_store).
 SplitChoice plan_gemm(const ntp_handle* h, int64_t ws_bytes, const GemmArgs& g, int layout, bool ring_ok, bool split_ok,
-                      int64_t ldw) {
-  SplitChoice sc{choose_variant(h, g, ring_ok, layout), 1, 0};
+                      int64_t ldw, bool deep_ok) {
+  SplitChoice sc{choose_variant(h, g, ring_ok, layout), 1, 0, false};
   if (split_ok && int64_t(g.M) * g.N >= 128 * 128 * 8) sc = choose_split(h, ws_bytes, g.M, g.n_store, g.K, layout, sc.tile, ldw);
+  if (deep_ok && sc.tile >= 0 && !h->opt[NTP_OPT_GEMM_TILE] && !h->opt[NTP_OPT_GEMM_SPLIT] && !h->opt[NTP_OPT_GEMM_SCHEDULE])
+    sc = choose_deep(h, split_ok ? ws_bytes : 0, g.M, g.n_store, g.K, ldw, sc);
   return sc;
 }
 
@@ -206,7 +238,7 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 namespace ntp {
 
-int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t N, int64_t n_store, int64_t K) {
+int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t N, int64_t n_store, int64_t K, bool deep) {
   if (M < 1 || N < 1 || K < 1 || M > 0x7fffff00 || N > 0x7fffff00 || K > 0x7fffff00) return 0;
   GemmArgs g{};
   g.M = int32_t(M);
@@ -214,7 +246,7 @@ int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t 
   g.K = int32_t(K);
   g.n_store = int32_t(n_store);
   const int64_t ldw = (n_store + 15) / 16 * 16;
-  const SplitChoice sc = plan_gemm(h, INT64_MAX / 2, g, layout, true, true, ldw);
+  const SplitChoice sc = plan_gemm(h, INT64_MAX / 2, g, layout, true, true, ldw, deep);
   return sc.splits > 1 ? int64_t(sc.splits) * M * ldw * 4 : 0;
 }
 
@@ -314,19 +346,29 @@ int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
   const int64_t ldw = (n_store + 15) / 16 * 16;
   void* const ws_ptr = d.ws_override ? d.ws_override : h->workspace;
   const int64_t ws_bytes = d.ws_override ? d.ws_override_bytes : (h->workspace ? h->workspace_bytes : 0);
-  const SplitChoice sc = plan_gemm(h, ws_ptr ? ws_bytes : 0, g, layout, ring_ok, split_ok, ldw);
+  // deep-pipelined kernel: 32-bit byte offsets with room for one that lies past every operand, and a K tail of whole chunks
+  const int64_t k8 = (d.K + 7) / 8 * 8;
+  const bool deep_ok = ring_ok && a_rows * d.lda * 2 < (int64_t(1) << 31) && b_rows * d.ldb * 2 < (int64_t(1) << 31) &&
+                       (!d.a_kc || d.K % 8 == 0 || (d.a_k_pad_8 && !d.b_kc));
+  const SplitChoice sc = plan_gemm(h, ws_ptr ? ws_bytes : 0, g, layout, ring_ok, split_ok, ldw, deep_ok);
   const int variant = sc.tile;
   if (ntp::timing_on(h)) {
     char name[48], vn[16], sn[8] = "";
     variant_name(variant, vn, sizeof(vn));
     if (sc.splits > 1) snprintf(sn, sizeof(sn), "k%d", sc.splits);
-    const bool pp = sc.splits == 1 && use_pingpong(h, layout, variant, d.K) && !(layout == 2 && variant == 0 && ring_ok);
-    snprintf(name, sizeof(name), "gemm_%c%c_%s_%s%s%s", d.a_kc ? 'n' : 't', d.b_kc ? 't' : 'n', kEpiName[d.epilogue], vn, sn,
-             pp ? "pp" : "");
+    const bool pp = sc.splits == 1 && !sc.deep && use_pingpong(h, layout, variant, d.K) && !(layout == 2 && variant == 0 && ring_ok);
+    snprintf(name, sizeof(name), "gemm_%c%c_%s_%s%s%s%s", d.a_kc ? 'n' : 't', d.b_kc ? 't' : 'n', kEpiName[d.epilogue], vn,
+             sc.deep ? "d" : "", sn, pp ? "pp" : "");
     ntp::timing_begin(h, stream, name, 2.0 * double(d.M) * double(d.N) * double(d.K), 0.0);
   }
   int st;
-  if (layout == 2 && variant == 0 && sc.splits == 1 && ring_ok) {
+  if (sc.deep && sc.splits == 1) {
+    GemmArgs gp = g;
+    gp.a_extent = uint32_t(operand_extent_bytes(d.a_kc, d.M, d.a_kc ? k8 : d.K, d.lda, false));
+    gp.k_splits = 1;
+    gp.k_chunk = int32_t((d.K + 63) / 64 * 64);
+    st = launch_deep(gp, d.a_kc, d.b_kc, d.epilogue, s);
+  } else if (layout == 2 && variant == 0 && sc.splits == 1 && ring_ok) {
     // The 256 x 256 weight-gradient tile runs one workgroup per output tile: its persistent form is short of
     // registers (27 spilled, some inside the K loop) and measured 17 % slower (307 against 254 us at
     // 5376 x 12288 x 2048), more than the overlap of one tile's stores with the next tile's first loads gains.
@@ -337,14 +379,15 @@ int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
   } else if (sc.splits > 1) {
     GemmArgs gp = g;  // the partial-sum launch: fp32 to the workspace, no row segments
     gp.ring_tail = 0;
-    gp.a_extent = uint32_t(operand_extent_bytes(d.a_kc, d.M, d.K, d.lda, false));
+    gp.a_extent = uint32_t(operand_extent_bytes(d.a_kc, d.M, d.a_kc && sc.deep ? k8 : d.K, d.lda, false));
     gp.C = ws_ptr;
     gp.ldc = ldw;
     gp.n_segs = 0;
     gp.k_splits = sc.splits;
     gp.k_chunk = sc.k_chunk;
     gp.split_stride = int64_t(d.M) * ldw;
-    if (d.a_kc && d.b_kc) st = launch_ring_split_nt(gp, variant, s);
+    if (sc.deep) st = launch_deep(gp, d.a_kc, d.b_kc, EPI_F32, s);
+    else if (d.a_kc && d.b_kc) st = launch_ring_split_nt(gp, variant, s);
     else if (d.a_kc) st = launch_ring_split_nn(gp, variant, s);
     else st = launch_ring_split_tn(gp, EPI_F32, variant, s);
     if (st == NTP_OK) {
@@ -382,7 +425,7 @@ extern "C" int ntp_gemm_choice(const ntp_handle_t* h, int32_t layout, int64_t M,
   g.N = int32_t(N);
   g.K = int32_t(K);
   g.n_store = int32_t((N + 7) / 8 * 8);
-  const SplitChoice sc = plan_gemm(h, h->workspace ? h->workspace_bytes : 0, g, layout, true, true, (g.n_store + 15) / 16 * 16);
+  const SplitChoice sc = plan_gemm(h, h->workspace ? h->workspace_bytes : 0, g, layout, true, true, (g.n_store + 15) / 16 * 16, true);
   *out = ntp_gemm_choice_t{};
   out->k_splits = sc.splits;
   if (sc.tile < 0) {
@@ -395,7 +438,7 @@ extern "C" int ntp_gemm_choice(const ntp_handle_t* h, int32_t layout, int64_t M,
     out->wavefronts = kTileShapes[sc.tile].waves;
     out->ring = 1;
   }
-  out->persistent = sc.tile >= 0 && sc.splits == 1 && !(layout == 2 && sc.tile == 0) ? 1 : 0;
+  out->persistent = sc.tile >= 0 && !sc.deep && sc.splits == 1 && !(layout == 2 && sc.tile == 0) ? 1 : 0;
   out->pingpong = out->persistent && use_pingpong(h, layout, sc.tile, K) ? 1 : 0;
   return NTP_OK;
 }

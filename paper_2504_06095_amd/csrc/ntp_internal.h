@@ -98,6 +98,7 @@ struct GemmDesc {
   // A is K-contiguous, lda >= round_up(K, 64), and every row of A holds zeros in columns [K, round_up(K, 64)):
   // with B K-strided, the K tail can then go through the ring like a whole K tile
   bool a_k_pad_64;
+  bool a_k_pad_8;  // the same up to round_up(K, 8) (lda % 8 == 0 always holds)
   // fp32 epilogues: when n_segs > 0 the output rows go to these destinations instead of C
   // (host array; a row that no segment lists is not stored)
   const ntp_row_segment_t* segs;
@@ -113,7 +114,8 @@ int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream);
 // workspace were unlimited (0: it would not split).  layout as for ntp_gemm_choice; n_store: columns stored.
 // The same for the three attention core kernels of a shape (checked like the calls check it).
 int attn_core_workspace_wish(const ntp_handle* h, const ntp_attn_core_shape_t* shape, int64_t* bytes);
-int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t N, int64_t n_store, int64_t K);
+// deep: false for the choice without the deep-pipelined kernel.
+int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t N, int64_t n_store, int64_t K, bool deep = true);
 
 }  // namespace ntp
 

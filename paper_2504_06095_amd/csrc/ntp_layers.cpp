@@ -57,6 +57,7 @@ extern "C" int ntp_mlp_shard_fwd(ntp_handle_t* h, const ntp_mlp_shape_t* s, cons
   }
   // Zpart = Y B_i, contraction over the ragged shard width
   GemmDesc d2 = gemm(Y, ldy, true, B, ldb, false, s->M, s->H, s->n_r, ntp::EPI_BF16, Zpart, ldz);
+  d2.a_k_pad_8 = true;
   d2.a_k_pad_64 = pad64;  // Y's pad columns were zeroed just above
   return ntp::gemm_launch(h, d2, stream);
 }
@@ -101,6 +102,7 @@ int mlp_bwd(ntp_handle_t* h, const ntp_mlp_shape_t* s, const void* dZ, int64_t l
   if (s->M == 0) return NTP_OK;
   // dXpart = dP A_i^T, contraction over the ragged shard width
   GemmDesc dx = gemm(dP, lddp, true, A_t, lda, false, s->M, s->H, s->n_r, ntp::EPI_BF16, dXpart, lddx);
+  dx.a_k_pad_8 = s->n_r > 0;
   dx.a_k_pad_64 = pad64;  // dP's pad columns were zeroed above
   return ntp::gemm_launch(h, dx, stream);
 }
@@ -183,9 +185,13 @@ extern "C" int ntp_attn_proj_shard_fwd_static(ntp_handle_t* h, const ntp_attn_sh
   if (s->H % 8 || s->w_qkv % 8 || s->w_o % 8) return NTP_ERR_ALIGNMENT;
   if (h->device < 0 || !h->static_scratch) return NTP_ERR_NO_DEVICE;
   // a shape whose launches would want more partial-sum room than the array has is refused, not run unsplit
+  // (with the deep-pipelined kernel and without: its launches never want more than 16 MiB, but a shape that was
+  // refused before it existed stays refused)
   int64_t wish = 0;
-  if (QKV) wish = std::max(wish, ntp::gemm_workspace_wish(h, 0, s->M, s->w_qkv, s->w_qkv, s->H));
-  if (Zpart) wish = std::max(wish, ntp::gemm_workspace_wish(h, 1, s->M, s->H, s->H, s->w_o));
+  for (const bool deep : {false, true}) {
+    if (QKV) wish = std::max(wish, ntp::gemm_workspace_wish(h, 0, s->M, s->w_qkv, s->w_qkv, s->H, deep));
+    if (Zpart) wish = std::max(wish, ntp::gemm_workspace_wish(h, 1, s->M, s->H, s->H, s->w_o, deep));
+  }
   if (wish > int64_t(NTP_STATIC_SCRATCH_BYTES)) return NTP_ERR_SCRATCH_TOO_SMALL;
   return attn_fwd(h, s, X, ldx, Wqkv, ldwqkv, QKV, ldqkv, C, ldc, Wo, ldwo, Zpart, ldz, h->static_scratch,
                   int64_t(NTP_STATIC_SCRATCH_BYTES), stream);

@@ -1,0 +1,73 @@
+"""The deep-pipelined GEMM kernel (problems with few output tiles), whole and with a cut K axis, against the oracle: sizes at the edges of
+tiles, of K tiles and of the ring's five stages, in the three operand layouts and with every epilogue."""
+import sys
+
+import numpy as np
+import pytest
+
+from tests.helpers import TOL, AttnCase, MlpCase, rel_err
+
+pytestmark = pytest.mark.gpu
+MLP_NAMES = ("P", "Y", "Z", "dP", "dX", "dA_t", "dB")
+
+
+@pytest.fixture(params=[False, True], ids=["whole", "workspace"])
+def names(request):
+    import torch
+    import paper_2504_06095_amd as N
+    ws = torch.full((8 << 20,), float("nan"), dtype=torch.float32, device="cuda") if request.param else None
+    N.ntp_set_workspace(ws)
+    N.ntp_kernel_timing_enable(1)
+    N.ntp_kernel_timing_read()
+    yield lambda: [r["name"].split("_")[-1] for r in N.ntp_kernel_timing_read()]
+    N.ntp_kernel_timing_enable(0)
+    N.ntp_kernel_timing_read()
+    N.ntp_set_workspace(None)
+
+
+# every GEMM's K once below, at and above the five stages (320) and off the K tile; M and N around multiples of 128
+@pytest.mark.parametrize("M,H,n_r", [(256, 256, 256), (257, 264, 129), (513, 328, 320), (320, 384, 255), (130, 1288, 383), (1025, 520, 641), (129, 2056, 513),
+                                     (2048, 136, 257), (300, 4096, 131)])
+@pytest.mark.parametrize("mode", [0, 1], ids=["erf", "tanh"])
+def test_mlp_deep(names, M, H, n_r, mode):
+    print(f"[gpu-case] deep GEMM MLP M={M} H={H} n_r={n_r} mode={mode}", file=sys.stderr, flush=True)
+    case = MlpCase(M, H, n_r, 1, 0)
+    got, raw = case.run_gpu(mode=mode, accumulate_twice=True)
+    picked = names()
+    assert any("128x128w8d" in n for n in picked), picked
+    want = case.oracle(mode)
+    want["dA_t"], want["dB"] = 2 * want["dA_t"], 2 * want["dB"]
+    for k in MLP_NAMES:
+        assert np.isfinite(got[k]).all(), k
+        e = rel_err(got[k], want[k])
+        assert e <= TOL, f"{k}: rel err {e:.3e}"
+    pad = -(-n_r // 8) * 8
+    for k in ("P", "Y", "dP"):
+        assert (raw[k][:, n_r:pad].float().cpu().numpy() == 0).all(), k
+
+
+@pytest.mark.parametrize("M,H,n_q,n_kv,d,tp,rank", [(385, 520, 6, 2, 64, 2, 1), (129, 1544, 8, 4, 64, 3, 1), (700, 264, 4, 4, 128, 2, 0)])
+def test_attn_proj_deep(names, M, H, n_q, n_kv, d, tp, rank):
+    print(f"[gpu-case] deep GEMM attention projections M={M} H={H}", file=sys.stderr, flush=True)
+    case = AttnCase(M, H, n_q, n_kv, d, tp, rank)
+    got, want = case.run_gpu(), case.oracle()
+    picked = names()
+    assert any("128x128w8d" in n for n in picked), picked
+    for k in got:
+        e = rel_err(got[k], want[k])
+        assert e <= TOL, f"{k}: rel err {e:.3e}"
+
+
+def test_deep_matches_the_other_kernels_bit_for_bit(opts):
+    """Without a cut K axis both kernels add in the same order."""
+    import torch
+    from paper_2504_06095_amd import binding as K
+    print("[gpu-case] deep GEMM against the ring kernel", file=sys.stderr, flush=True)
+    for M, H, n_r in ((512, 1024, 586), (640, 776, 1000)):
+        case = MlpCase(M, H, n_r, 1, 0)
+        a, _ = case.run_gpu(pad_to=64)
+        opts(K.NTP_OPT_GEMM_SCHEDULE, 1)
+        b, _ = case.run_gpu(pad_to=64)
+        opts(K.NTP_OPT_GEMM_SCHEDULE, 0)
+        for k in MLP_NAMES:
+            assert np.array_equal(a[k], b[k]), k
