@@ -112,7 +112,7 @@ bool ring_combo(bool a_kc, bool b_kc, int epi) {
 // order and applies the epilogue.
 struct SplitChoice {
   int tile, splits, k_chunk;
-  bool deep;  // the deep-pipelined kernel
+  int deep;  // DeepForm
 };
 
 constexpr double kTileCycles = 2650.0;      // one 256 x 256 x 64 K tile on one compute unit at rate 1
@@ -133,7 +133,7 @@ double tile_time(int64_t M, int64_t N, int64_t ktiles, int layout, int i, int sp
 // ws_bytes: room for the partial sums (0: never split).
 SplitChoice choose_split(const ntp_handle* h, int64_t ws_bytes, int64_t M, int64_t N, int64_t K, int layout, int plain_tile,
                          int64_t ldw) {
-  SplitChoice best{plain_tile, 1, 0, false};
+  SplitChoice best{plain_tile, 1, 0, kNotDeep};
   const int64_t ktiles = (K + 63) / 64;
   const int cus = h->compute_units;
   const int forced = int(h->opt[NTP_OPT_GEMM_SPLIT]);  // 1: never split; n > 1: n chunks if they fit
@@ -155,7 +155,7 @@ SplitChoice choose_split(const ntp_handle* h, int64_t ws_bytes, int64_t M, int64
       const double t = tile_time(M, N, ktiles, layout, i, sp, cus) + reduce;
       if (t < best_t) {
         best_t = t;
-        best = SplitChoice{i, sp, int(chunk_tiles * 64), false};
+        best = SplitChoice{i, sp, int(chunk_tiles * 64), kNotDeep};
       }
     }
   }
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs g, co
   store4<EPI>(g, int(m), n0, acc);
 }
 
-constexpr int kDeepTile = 8;  // index of the deep-pipelined kernel's tile shape (128 x 128 on 8 wavefronts)
+constexpr int kDeepTile = 8, kDeepWideTile = 6;  // indices of the deep-pipelined kernel's tile shapes
 constexpr int kMaxDeepSplits = 16;
 
 // Whether the deep-pipelined kernel takes over from `old`, and in how many K chunks.  Measured over 45 random shapes of up to one
@@ -187,20 +187,37 @@ constexpr int kMaxDeepSplits = 16;
 // 4344 over K = 6136: 50 -> 33 us) and slower above (280 x 7944 over K = 9152, 189 tiles: 75 -> 83 us).
 // Chunks: every one has a compute unit to itself.  A K tile takes 0.47 us (LDS reads: 96 KB a K tile and workgroup), the reduce launch 3.5 us
 // and its traffic at 4.4 TB/s; a chunk has at least four K tiles.
-SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int64_t M, int64_t N, int64_t K, int64_t ldw, const SplitChoice& old) {
+//
+// Above one tile per compute unit, for a K axis that is not cut (32 random shapes):
+//  - weight gradients up to nine K tiles, any number of tiles: the time is the output's, and two workgroups on a compute unit keep storing
+//    while the next tile loads: 4456 x 7936 over K = 152 50 -> 43 us, 8072 x 3704 over 568 67 -> 60 us, 15520 x 11640 over 152
+//    267 -> 216 us and accumulating 502 -> 406 us (-14 to +1 %; at ten K tiles and more the larger tiles win);
+//  - 128 x 256 tiles that all fit on the device at once, from 20 K tiles on: 10160 x 432 over K = 1496 34 -> 27 us, 368 x 16040 over
+//    1584 34 -> 31 us, 1376 x 4672 over 3440 56 -> 54 us;
+//  - up to two 128 x 128 tiles per compute unit and 25 K tiles (weight gradients: 32): 1984 x 2664 over K = 328 16 -> 13.5 us, 584 x 7304
+//    over 1400 28 -> 25 us, 2192 x 2304 over 1888 38 -> 35 us; at 54 K tiles 10 % slower.
+SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int layout, int64_t M, int64_t N, int64_t K, int64_t ldw, const SplitChoice& old) {
   const TileShape& ts = kTileShapes[old.tile];
-  const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), ktiles = (K + 63) / 64;
-  if (tiles > h->compute_units || (old.splits > 1 ? tiles * 2 > h->compute_units : ts.bm != 128 || ts.bn != 128)) return old;
-  SplitChoice best{kDeepTile, 1, int(ktiles * 64), true};
+  const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), wide = ((M + 127) / 128) * ((N + 255) / 256), ktiles = (K + 63) / 64;
+  const int cus = h->compute_units;
+  if (tiles > cus) {
+    const SplitChoice deep2{kDeepTile, 1, int(ktiles * 64), kDeep2};
+    if (old.splits > 1) return old;
+    if (layout == 2 && ktiles <= 9) return deep2;
+    if (wide <= cus && ktiles >= 20) return SplitChoice{kDeepWideTile, 1, int(ktiles * 64), kDeepWide};
+    return tiles <= 2 * cus && ktiles <= (layout == 2 ? 32 : 25) ? deep2 : old;
+  }
+  if (old.splits > 1 ? tiles * 2 > cus : ts.bm != 128 || ts.bn != 128) return old;
+  SplitChoice best{kDeepTile, 1, int(ktiles * 64), kDeep5};
   double best_t = 0.47 * double(ktiles);
-  for (int sp = 2; sp <= kMaxDeepSplits && tiles * sp <= h->compute_units; ++sp) {
+  for (int sp = 2; sp <= kMaxDeepSplits && tiles * sp <= cus; ++sp) {
     const int64_t chunk_tiles = (ktiles + sp - 1) / sp;
     if (chunk_tiles < 4 || int64_t(sp) * M * ldw * 4 > ws_bytes) break;
     if ((sp - 1) * chunk_tiles * 64 >= K) continue;  // the last chunk would be empty
     const double t = 0.47 * double(chunk_tiles) + 3.5 + double(M) * double(ldw) * (4.0 * sp + 4.0) / 4.4e6;
     if (t < best_t) {
       best_t = t;
-      best = SplitChoice{kDeepTile, sp, int(chunk_tiles * 64), true};
+      best = SplitChoice{kDeepTile, sp, int(chunk_tiles * 64), kDeep5};
     }
   }
   return best;
@@ -209,10 +226,10 @@ SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int64_t M, int64_
 // Kernel variant (-1 generic, else a tile shape) and K chunks for a GEMM (g: M, N, K, n_store).
 SplitChoice plan_gemm(const ntp_handle* h, int64_t ws_bytes, const GemmArgs& g, int layout, bool ring_ok, bool split_ok,
                       int64_t ldw, bool deep_ok) {
-  SplitChoice sc{choose_variant(h, g, ring_ok, layout), 1, 0, false};
+  SplitChoice sc{choose_variant(h, g, ring_ok, layout), 1, 0, kNotDeep};
   if (split_ok && int64_t(g.M) * g.N >= 128 * 128 * 8) sc = choose_split(h, ws_bytes, g.M, g.n_store, g.K, layout, sc.tile, ldw);
   if (deep_ok && sc.tile >= 0 && !h->opt[NTP_OPT_GEMM_TILE] && !h->opt[NTP_OPT_GEMM_SPLIT] && !h->opt[NTP_OPT_GEMM_SCHEDULE])
-    sc = choose_deep(h, split_ok ? ws_bytes : 0, g.M, g.n_store, g.K, ldw, sc);
+    sc = choose_deep(h, split_ok ? ws_bytes : 0, layout, g.M, g.n_store, g.K, ldw, sc);
   return sc;
 }
 
@@ -358,7 +375,7 @@ int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
     if (sc.splits > 1) snprintf(sn, sizeof(sn), "k%d", sc.splits);
     const bool pp = sc.splits == 1 && !sc.deep && use_pingpong(h, layout, variant, d.K) && !(layout == 2 && variant == 0 && ring_ok);
     snprintf(name, sizeof(name), "gemm_%c%c_%s_%s%s%s%s", d.a_kc ? 'n' : 't', d.b_kc ? 't' : 'n', kEpiName[d.epilogue], vn,
-             sc.deep ? "d" : "", sn, pp ? "pp" : "");
+             sc.deep == kDeep2 ? "d2" : sc.deep ? "d" : "", sn, pp ? "pp" : "");
     ntp::timing_begin(h, stream, name, 2.0 * double(d.M) * double(d.N) * double(d.K), 0.0);
   }
   int st;
@@ -367,7 +384,7 @@ int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
     gp.a_extent = uint32_t(operand_extent_bytes(d.a_kc, d.M, d.a_kc ? k8 : d.K, d.lda, false));
     gp.k_splits = 1;
     gp.k_chunk = int32_t((d.K + 63) / 64 * 64);
-    st = launch_deep(gp, d.a_kc, d.b_kc, d.epilogue, s);
+    st = launch_deep(gp, d.a_kc, d.b_kc, d.epilogue, sc.deep, s);
   } else if (layout == 2 && variant == 0 && sc.splits == 1 && ring_ok) {
     // The 256 x 256 weight-gradient tile runs one workgroup per output tile: its persistent form is short of
     // registers (27 spilled, some inside the K loop) and measured 17 % slower (307 against 254 us at
@@ -386,7 +403,7 @@ int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
     gp.k_splits = sc.splits;
     gp.k_chunk = sc.k_chunk;
     gp.split_stride = int64_t(d.M) * ldw;
-    if (sc.deep) st = launch_deep(gp, d.a_kc, d.b_kc, EPI_F32, s);
+    if (sc.deep) st = launch_deep(gp, d.a_kc, d.b_kc, EPI_F32, sc.deep, s);
     else if (d.a_kc && d.b_kc) st = launch_ring_split_nt(gp, variant, s);
     else if (d.a_kc) st = launch_ring_split_nn(gp, variant, s);
     else st = launch_ring_split_tn(gp, EPI_F32, variant, s);

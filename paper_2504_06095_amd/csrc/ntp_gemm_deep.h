@@ -32,7 +32,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_deep_kernel(const GemmArg
   constexpr int NAI = BM_ * DK * 2 / 1024 / NW, NBI = BN_ * DK * 2 / 1024 / NW;  // DMA instructions per K tile and wavefront
   static_assert((BM_ * DK * 2 / 1024) % NW == 0 && (BN_ * DK * 2 / 1024) % NW == 0, "operands split evenly over the wavefronts");
   constexpr int WAIT = (STAGES - 2) * (NAI + NBI);
-  static_assert(STAGES >= 3 && WAIT <= 63, "the in-order counter holds 63 instructions");
+  static_assert(STAGES >= 2 && WAIT <= 63, "the in-order counter holds 63 instructions");
   constexpr int SA = BM_ * DK, SB = BN_ * DK, STAGE = SA + SB;  // elements
   static_assert(STAGES * STAGE * 2 <= 160 * 1024, "LDS of a compute unit");
   __shared__ __attribute__((aligned(1024))) uint16_t ring[STAGES * STAGE];

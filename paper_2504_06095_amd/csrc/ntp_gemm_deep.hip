@@ -1,4 +1,5 @@
-// Deep-pipelined GEMM instantiations: the 128 x 128 tile on 8 wavefronts with five K tiles in LDS, per operand layout and epilogue.
+// Deep-pipelined GEMM instantiations per operand layout and epilogue: the 128 x 128 tile on 8 wavefronts with five K tiles in LDS, the
+// same with two (64 KiB: two workgroups on a compute unit, one's stores and first loads under the other's products), and 128 x 256 with three.
 #include "ntp_gemm_launch.h"
 
 #include "ntp_gemm_deep.h"
@@ -7,37 +8,47 @@ namespace ntp_gemm {
 
 namespace {
 
-template <bool AKC, bool BKC, int EPI>
-int launch_one(GemmArgs g, hipStream_t s) {
+template <bool AKC, bool BKC, int EPI, int BN_, int STAGES>
+int launch_tile(GemmArgs g, hipStream_t s) {
   g.tiles_m = (g.M + 127) / 128;
-  g.tiles_n = (g.n_store + 127) / 128;
+  g.tiles_n = (g.n_store + BN_ - 1) / BN_;
   const int64_t per_split = (int64_t(g.tiles_m) * g.tiles_n + 7) / 8 * 8;
   if (g.k_splits < 1 || g.k_chunk < 64 || g.k_chunk % 64 || int64_t(g.k_splits - 1) * g.k_chunk >= g.K || per_split * g.k_splits > 0x7fffffff)
     return NTP_ERR_INVALID_ARG;
-  hipLaunchKernelGGL((gemm_deep_kernel<AKC, BKC, EPI, 128, 128, 2, 4, 5>), dim3(uint32_t(per_split * g.k_splits)), dim3(512), 0, s, g);
+  hipLaunchKernelGGL((gemm_deep_kernel<AKC, BKC, EPI, 128, BN_, 2, 4, STAGES>), dim3(uint32_t(per_split * g.k_splits)), dim3(512), 0, s, g);
   return hipGetLastError() == hipSuccess ? NTP_OK : NTP_ERR_LAUNCH;
+}
+
+template <bool AKC, bool BKC, int EPI>
+int launch_one(const GemmArgs& g, int form, hipStream_t s) {
+  switch (form) {
+    case kDeep5: return launch_tile<AKC, BKC, EPI, 128, 5>(g, s);
+    case kDeep2: return launch_tile<AKC, BKC, EPI, 128, 2>(g, s);
+    case kDeepWide: return launch_tile<AKC, BKC, EPI, 256, 3>(g, s);
+    default: return NTP_ERR_INVALID_ARG;
+  }
 }
 
 }  // namespace
 
-int launch_deep(const GemmArgs& g, bool a_kc, bool b_kc, int epilogue, hipStream_t s) {
+int launch_deep(const GemmArgs& g, bool a_kc, bool b_kc, int epilogue, int form, hipStream_t s) {
   if (g.k_splits > 1) epilogue = ntp::EPI_F32;  // partial sums
   if (a_kc && b_kc) {
     switch (epilogue) {
-      case ntp::EPI_BF16: return launch_one<true, true, ntp::EPI_BF16>(g, s);
-      case ntp::EPI_GELU: return launch_one<true, true, ntp::EPI_GELU>(g, s);
-      case ntp::EPI_DGELU: return launch_one<true, true, ntp::EPI_DGELU>(g, s);
-      case ntp::EPI_F32: return launch_one<true, true, ntp::EPI_F32>(g, s);
+      case ntp::EPI_BF16: return launch_one<true, true, ntp::EPI_BF16>(g, form, s);
+      case ntp::EPI_GELU: return launch_one<true, true, ntp::EPI_GELU>(g, form, s);
+      case ntp::EPI_DGELU: return launch_one<true, true, ntp::EPI_DGELU>(g, form, s);
+      case ntp::EPI_F32: return launch_one<true, true, ntp::EPI_F32>(g, form, s);
     }
   } else if (a_kc) {
     switch (epilogue) {
-      case ntp::EPI_BF16: return launch_one<true, false, ntp::EPI_BF16>(g, s);
-      case ntp::EPI_F32: return launch_one<true, false, ntp::EPI_F32>(g, s);
+      case ntp::EPI_BF16: return launch_one<true, false, ntp::EPI_BF16>(g, form, s);
+      case ntp::EPI_F32: return launch_one<true, false, ntp::EPI_F32>(g, form, s);
     }
   } else if (!b_kc) {
     switch (epilogue) {
-      case ntp::EPI_F32: return launch_one<false, false, ntp::EPI_F32>(g, s);
-      case ntp::EPI_F32_ACCUM: return launch_one<false, false, ntp::EPI_F32_ACCUM>(g, s);
+      case ntp::EPI_F32: return launch_one<false, false, ntp::EPI_F32>(g, form, s);
+      case ntp::EPI_F32_ACCUM: return launch_one<false, false, ntp::EPI_F32_ACCUM>(g, form, s);
     }
   }
   return NTP_ERR_UNSUPPORTED;

@@ -38,8 +38,9 @@ int launch_ring_tn(GemmArgs g, int epilogue, int tile, hipStream_t s);  // A [K 
 int launch_pp_nt(GemmArgs g, int epilogue, int tile, hipStream_t s);
 int launch_pp_nn(GemmArgs g, int epilogue, int tile, hipStream_t s);
 int launch_pp_tn(GemmArgs g, int epilogue, int tile, hipStream_t s);
-// Deep-pipelined kernel (ntp_gemm_deep.h), one workgroup per 128 x 128 tile and K chunk (g.k_splits, g.k_chunk as above).
-int launch_deep(const GemmArgs& g, bool a_kc, bool b_kc, int epilogue, hipStream_t s);
+// Deep-pipelined kernel (ntp_gemm_deep.h), one workgroup per tile and K chunk (g.k_splits, g.k_chunk as above).
+enum DeepForm : int { kNotDeep = 0, kDeep5, kDeep2, kDeepWide };  // 128 x 128 with five / two K tiles in LDS, 128 x 256 with three
+int launch_deep(const GemmArgs& g, bool a_kc, bool b_kc, int epilogue, int form, hipStream_t s);
 int launch_ring_split_nt(GemmArgs g, int tile, hipStream_t s);
 int launch_ring_split_nn(GemmArgs g, int tile, hipStream_t s);
 int launch_ring_split_tn(GemmArgs g, int epilogue, int tile, hipStream_t s);

@@ -58,6 +58,26 @@ def test_attn_proj_deep(names, M, H, n_q, n_kv, d, tp, rank):
         assert e <= TOL, f"{k}: rel err {e:.3e}"
 
 
+# the forms above one tile per compute unit: two K tiles in LDS ("d2"), and 128 x 256 tiles with three
+@pytest.mark.parametrize("M,H,n_r,form", [(129, 8200, 1090, "128x128w8d2"), (130, 4104, 2000, "128x128w8d2"), (2900, 1032, 1501, "128x128w8d2"),
+                                          (1290, 1288, 3300, "128x256d"), (577, 1000, 9001, "128x128w8d2")])
+def test_mlp_deep_more_tiles(M, H, n_r, form):
+    import paper_2504_06095_amd as N
+    print(f"[gpu-case] deep GEMM MLP, more tiles M={M} H={H} n_r={n_r}", file=sys.stderr, flush=True)
+    N.ntp_kernel_timing_enable(1)
+    N.ntp_kernel_timing_read()
+    case = MlpCase(M, H, n_r, 1, 0)
+    got, _ = case.run_gpu(accumulate_twice=True)
+    picked = [r["name"].split("_")[-1] for r in N.ntp_kernel_timing_read()]
+    N.ntp_kernel_timing_enable(0)
+    assert form in picked, picked
+    want = case.oracle()
+    want["dA_t"], want["dB"] = 2 * want["dA_t"], 2 * want["dB"]
+    for k in MLP_NAMES:
+        e = rel_err(got[k], want[k])
+        assert np.isfinite(got[k]).all() and e <= TOL, f"{k}: rel err {e:.3e}"
+
+
 def test_deep_matches_the_other_kernels_bit_for_bit(opts):
     """Without a cut K axis both kernels add in the same order."""
     import torch
