@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdint>
 #include <cstring>
@@ -267,7 +268,20 @@ int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t 
   return sc.splits > 1 ? int64_t(sc.splits) * M * ldw * 4 : 0;
 }
 
-int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
+namespace {
+
+// A checked GEMM: kernel arguments and the launcher's choice.
+struct Prepared {
+  GemmArgs g;
+  SplitChoice sc;
+  int layout;
+  bool ring_ok, nothing;  // nothing: no output, or none that has a destination
+  void* ws_ptr;
+  int64_t ldw, k8;
+};
+
+int prepare(ntp_handle* h, const GemmDesc& d, Prepared* out) {
+  out->nothing = true;
   if (!h || d.M < 0 || d.N < 0 || d.K < 0) return NTP_ERR_INVALID_ARG;
   if (d.M == 0 || d.N == 0) return NTP_OK;
   if (h->device < 0) return NTP_ERR_NO_DEVICE;
@@ -339,8 +353,6 @@ int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
   g.K = int32_t(d.K);
   g.n_store = int32_t(n_store);
   g.gelu_mode = d.gelu_mode;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  static const char* const kEpiName[] = {"bf16", "gelu", "dgelu", "f32", "f32acc"};
   // the ring kernel addresses each operand with 32-bit byte offsets from its base
   const int64_t a_rows = d.a_kc ? d.M : d.K, b_rows = d.b_kc ? d.N : d.K;
   const bool ring_ok = ring_combo(d.a_kc, d.b_kc, d.epilogue) && a_rows * d.lda * 2 < (int64_t(1) << 32) &&
@@ -368,6 +380,33 @@ int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
   const bool deep_ok = ring_ok && a_rows * d.lda * 2 < (int64_t(1) << 31) && b_rows * d.ldb * 2 < (int64_t(1) << 31) &&
                        (!d.a_kc || d.K % 8 == 0 || (d.a_k_pad_8 && !d.b_kc));
   const SplitChoice sc = plan_gemm(h, ws_ptr ? ws_bytes : 0, g, layout, ring_ok, split_ok, ldw, deep_ok);
+  *out = Prepared{g, sc, layout, ring_ok, false, ws_ptr, ldw, k8};
+  return NTP_OK;
+}
+
+// The arguments of a deep-pipelined launch without a cut K axis.
+GemmArgs deep_args(const Prepared& p, const GemmDesc& d) {
+  GemmArgs g = p.g;
+  g.a_extent = uint32_t(operand_extent_bytes(d.a_kc, d.M, d.a_kc ? p.k8 : d.K, d.lda, false));
+  g.k_splits = 1;
+  g.k_chunk = int32_t((d.K + 63) / 64 * 64);
+  return g;
+}
+
+}  // namespace
+
+int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
+  Prepared p;
+  int st = prepare(h, d, &p);
+  if (st != NTP_OK || p.nothing) return st;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  static const char* const kEpiName[] = {"bf16", "gelu", "dgelu", "f32", "f32acc"};
+  const GemmArgs& g = p.g;
+  const SplitChoice sc = p.sc;
+  const int layout = p.layout;
+  const bool ring_ok = p.ring_ok;
+  const int64_t n_store = g.n_store, ldw = p.ldw, k8 = p.k8;
+  void* const ws_ptr = p.ws_ptr;
   const int variant = sc.tile;
   if (ntp::timing_on(h)) {
     char name[48], vn[16], sn[8] = "";
@@ -378,13 +417,8 @@ int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
              sc.deep == kDeep2 ? "d2" : sc.deep ? "d" : "", sn, pp ? "pp" : "");
     ntp::timing_begin(h, stream, name, 2.0 * double(d.M) * double(d.N) * double(d.K), 0.0);
   }
-  int st;
   if (sc.deep && sc.splits == 1) {
-    GemmArgs gp = g;
-    gp.a_extent = uint32_t(operand_extent_bytes(d.a_kc, d.M, d.a_kc ? k8 : d.K, d.lda, false));
-    gp.k_splits = 1;
-    gp.k_chunk = int32_t((d.K + 63) / 64 * 64);
-    st = launch_deep(gp, d.a_kc, d.b_kc, d.epilogue, sc.deep, s);
+    st = launch_deep(deep_args(p, d), d.a_kc, d.b_kc, d.epilogue, sc.deep, s);
   } else if (layout == 2 && variant == 0 && sc.splits == 1 && ring_ok) {
     // The 256 x 256 weight-gradient tile runs one workgroup per output tile: its persistent form is short of
     // registers (27 spilled, some inside the K loop) and measured 17 % slower (307 against 254 us at
@@ -428,6 +462,80 @@ int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
   else if (d.a_kc && !d.b_kc) st = launch_generic<true, false>(g, d.epilogue, s);
   else if (!d.a_kc && !d.b_kc) st = launch_generic<false, false>(g, d.epilogue, s);
   else st = launch_generic<false, true>(g, d.epilogue, s);
+  ntp::timing_end(h, stream);
+  return st;
+}
+
+namespace {
+
+struct Span {
+  uintptr_t lo, hi;
+};
+
+// Whether what `a` writes touches anything that `b` reads or writes.
+bool writes_into(const GemmDesc& a, const GemmDesc& b) {
+  auto span = [](const void* p, int64_t rows, int64_t ld, int64_t cols, int64_t esz) {
+    const uintptr_t lo = reinterpret_cast<uintptr_t>(p);
+    return Span{lo, p && rows > 0 ? lo + uintptr_t(((rows - 1) * ld + cols) * esz) : lo};
+  };
+  auto outputs = [&](const GemmDesc& d, auto&& f) {
+    const bool f32 = d.epilogue == EPI_F32 || d.epilogue == EPI_F32_ACCUM;
+    if (d.n_segs > 0) {
+      for (int32_t i = 0; i < d.n_segs; ++i) f(span(d.segs[i].dst, d.segs[i].rows, d.segs[i].ld, d.N, 4));
+    } else {
+      f(span(d.C, d.M, d.ldc, d.ldc, f32 ? 4 : 2));
+    }
+  };
+  bool hit = false;
+  outputs(a, [&](Span x) {
+    auto test = [&](Span y) { hit = hit || (x.lo < y.hi && y.lo < x.hi); };
+    test(span(b.A, b.a_kc ? b.M : b.K, b.lda, b.lda, 2));
+    test(span(b.B, b.b_kc ? b.N : b.K, b.ldb, b.ldb, 2));
+    outputs(b, test);
+  });
+  return hit;
+}
+
+}  // namespace
+
+// GEMMs that do not need each other's results.  One launch where all of them would run on the deep-pipelined kernel anyway, nothing that one
+// writes is read or written by another (a caller may pass an output that overlaps a later product's operand: then they run in
+// order), and the estimate says so; else one after the other.  Estimate: a launch costs 6 us beside its K tiles (launch, first loads, stores);
+// the group's K tiles take as long as its longest problem, or as all its tiles dealt out over the device.
+int gemm_launch_group(ntp_handle* h, const GemmDesc* d, int n, void* stream) {
+  constexpr int kMax = 3;
+  Prepared p[kMax];
+  bool group = n >= 2 && n <= kMax;
+  double apart = 0.0, longest = 0.0, work = 0.0, flops = 0.0;
+  for (int i = 0; i < n && group; ++i) {
+    group = prepare(h, d[i], &p[i]) == NTP_OK && !p[i].nothing && p[i].sc.deep == kDeep5 &&
+            (p[i].layout == 2 ? d[i].epilogue == EPI_F32 || d[i].epilogue == EPI_F32_ACCUM : d[i].epilogue == EPI_BF16);
+    for (int j = 0; j < i && group; ++j) group = !writes_into(d[i], d[j]) && !writes_into(d[j], d[i]);
+    if (!group) break;
+    const GemmArgs& g = p[i].g;
+    const double tiles = double((g.M + 127) / 128) * double((g.n_store + 127) / 128), kt = double((g.K + 63) / 64), sp = p[i].sc.splits;
+    apart += 6.0 + 0.47 * std::ceil(kt / sp) + (sp > 1 ? 3.5 + double(g.M) * double(p[i].ldw) * (4.0 * sp + 4.0) / 4.4e6 : 0.0);
+    longest = std::max(longest, kt);
+    work += tiles * kt;
+    flops += 2.0 * double(g.M) * double(g.N) * double(g.K);
+  }
+  if (group) group = 6.0 + 0.47 * std::max(longest, 1.15 * work / h->compute_units) < apart;
+  if (!group) {
+    for (int i = 0; i < n; ++i) {
+      const int st = gemm_launch(h, d[i], stream);
+      if (st != NTP_OK) return st;
+    }
+    return NTP_OK;
+  }
+  GemmArgs g[kMax];
+  int layout[kMax], epi[kMax];
+  for (int i = 0; i < n; ++i) {
+    g[i] = deep_args(p[i], d[i]);
+    layout[i] = p[i].layout;
+    epi[i] = d[i].epilogue;
+  }
+  if (ntp::timing_on(h)) ntp::timing_begin(h, stream, "gemm_group_128x128w8d", flops, 0.0);
+  const int st = launch_deep_group(g, layout, epi, n, static_cast<hipStream_t>(stream));
   ntp::timing_end(h, stream);
   return st;
 }

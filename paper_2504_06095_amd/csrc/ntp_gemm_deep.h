@@ -23,8 +23,9 @@
 
 namespace ntp_gemm {
 
+// One (output tile, K chunk): workgroup `block` of problem g, with the ring in `ring`.
 template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, int STAGES>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_deep_kernel(const GemmArgs g) {
+__device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, uint16_t* const ring) {
   constexpr int NW = WGM * WGN;
   constexpr int TM = BM_ / WGM, TN = BN_ / WGN;  // wavefront tile
   constexpr int MI = TM / 16, NI = TN / 16;      // 16 x 16 accumulator blocks
@@ -35,14 +36,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_deep_kernel(const GemmArg
   static_assert(STAGES >= 2 && WAIT <= 63, "the in-order counter holds 63 instructions");
   constexpr int SA = BM_ * DK, SB = BN_ * DK, STAGE = SA + SB;  // elements
   static_assert(STAGES * STAGE * 2 <= 160 * 1024, "LDS of a compute unit");
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[STAGES * STAGE];
-
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
 
   const int nblk = g.tiles_m * g.tiles_n, per_split = (nblk + 7) & ~7;  // (keeps workgroup & 7 == tile & 7: the XCD)
-  const int split = blockIdx.x / per_split, vblk = blockIdx.x - split * per_split;
+  const int split = block / per_split, vblk = block - split * per_split;
   if (vblk >= nblk) return;  // padding workgroup (the whole workgroup leaves, before any barrier)
   const TilePos tp = place_tile(vblk, g.tiles_m, g.tiles_n);
   const int row0 = tp.tile_m * BM_, col0 = tp.tile_n * BN_;
@@ -154,6 +153,39 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_deep_kernel(const GemmArg
 #pragma unroll
       for (int j = 0; j < NI; ++j) store4<EPI>(g, m, col0 + wn * TN + j * 16 + (lane >> 4) * 4, acc[i][j]);
     }
+  }
+}
+
+template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, int STAGES>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_deep_kernel(const GemmArgs g) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[STAGES * (BM_ + BN_) * DK];
+  deep_tile<AKC, BKC, EPI, BM_, BN_, WGM, WGN, STAGES>(g, int(blockIdx.x), ring);
+}
+
+// Up to three problems that do not depend on each other in one launch (the 128 x 128 tile with five K tiles in LDS, no cut K axis):
+// a layer's small gradient GEMMs take 10-12 us each, of which launch, first loads and the last tiles' stores are the larger
+// part, and leave most of the device idle.  512 x 1024 x 586: dB, dA and dX 34 -> 14 us.
+constexpr int kMaxGroup = 3;
+struct GroupArgs {
+  GemmArgs g[kMaxGroup];
+  int32_t kind[kMaxGroup];   // GroupKind
+  int32_t first[kMaxGroup];  // first workgroup (a multiple of 8), ascending
+  int32_t n;
+};
+enum GroupKind : int32_t { kGroupNt = 0, kGroupNn, kGroupTn, kGroupTnAccum };  // layout and epilogue: bf16, bf16, fp32, fp32 accumulate
+
+__global__ __launch_bounds__(512) void gemm_deep_group_kernel(const GroupArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[5 * 256 * DK];
+  int p = 0;
+  for (int i = 1; i < a.n; ++i)
+    if (int(blockIdx.x) >= a.first[i]) p = i;
+  const GemmArgs& g = a.g[p];
+  const int block = int(blockIdx.x) - a.first[p];
+  switch (a.kind[p]) {
+    case kGroupNt: deep_tile<true, true, ntp::EPI_BF16, 128, 128, 2, 4, 5>(g, block, ring); break;
+    case kGroupNn: deep_tile<true, false, ntp::EPI_BF16, 128, 128, 2, 4, 5>(g, block, ring); break;
+    case kGroupTn: deep_tile<false, false, ntp::EPI_F32, 128, 128, 2, 4, 5>(g, block, ring); break;
+    default: deep_tile<false, false, ntp::EPI_F32_ACCUM, 128, 128, 2, 4, 5>(g, block, ring); break;
   }
 }
 

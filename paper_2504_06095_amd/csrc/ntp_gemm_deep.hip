@@ -54,4 +54,23 @@ int launch_deep(const GemmArgs& g, bool a_kc, bool b_kc, int epilogue, int form,
   return NTP_ERR_UNSUPPORTED;
 }
 
+int launch_deep_group(const GemmArgs* g, const int* layout, const int* epilogue, int n, hipStream_t s) {
+  if (n < 1 || n > kMaxGroup) return NTP_ERR_INVALID_ARG;
+  GroupArgs a{};
+  int64_t blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    a.g[i] = g[i];
+    a.g[i].tiles_m = (g[i].M + 127) / 128;
+    a.g[i].tiles_n = (g[i].n_store + 127) / 128;
+    if (layout[i] == 2 ? epilogue[i] != ntp::EPI_F32 && epilogue[i] != ntp::EPI_F32_ACCUM : epilogue[i] != ntp::EPI_BF16) return NTP_ERR_UNSUPPORTED;
+    a.kind[i] = layout[i] == 0 ? kGroupNt : layout[i] == 1 ? kGroupNn : epilogue[i] == ntp::EPI_F32 ? kGroupTn : kGroupTnAccum;
+    a.first[i] = int32_t(blocks);
+    blocks += (int64_t(a.g[i].tiles_m) * a.g[i].tiles_n + 7) / 8 * 8;
+    if (blocks > 0x7fffffff) return NTP_ERR_UNSUPPORTED;
+  }
+  a.n = n;
+  hipLaunchKernelGGL(gemm_deep_group_kernel, dim3(uint32_t(blocks)), dim3(512), 0, s, a);
+  return hipGetLastError() == hipSuccess ? NTP_OK : NTP_ERR_LAUNCH;
+}
+
 }  // namespace ntp_gemm

@@ -110,6 +110,8 @@ struct GemmDesc {
 
 // Validates and enqueues one GEMM on `stream`.  Returns an NTP_* status.
 int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream);
+// The same for up to three GEMMs that do not need each other's results: one launch where that is faster, else one after the other.
+int gemm_launch_group(ntp_handle* h, const GemmDesc* d, int n, void* stream);
 // Largest workspace (bytes) a GEMM of this shape could use, i.e. what the split-K choice would take if the
 // workspace were unlimited (0: it would not split).  layout as for ntp_gemm_choice; n_store: columns stored.
 // The same for the three attention core kernels of a shape (checked like the calls check it).

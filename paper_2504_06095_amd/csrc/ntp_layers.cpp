@@ -88,23 +88,24 @@ int mlp_bwd(ntp_handle_t* h, const ntp_mlp_shape_t* s, const void* dZ, int64_t l
     d.pad_n_64 = pad64;
     if ((st = ntp::gemm_launch(h, d, stream)) != NTP_OK) return st;
   }
+  GemmDesc rest[3];
+  int n = 0;
   if (s->n_r > 0) {
     // dB = Y^T dZ and dA_t = dP^T X: contraction over tokens, both operands token-major
-    GemmDesc db = gemm(Y, ldy, false, dZ, lddz, false, s->n_r, s->H, s->M, wepi, nullptr, 0);
+    GemmDesc& db = rest[n++] = gemm(Y, ldy, false, dZ, lddz, false, s->n_r, s->H, s->M, wepi, nullptr, 0);
     db.segs = dB_segs;
     db.n_segs = n_dB;
-    if ((st = ntp::gemm_launch(h, db, stream)) != NTP_OK) return st;
-    GemmDesc da = gemm(dP, lddp, false, X, ldx, false, s->n_r, s->H, s->M, wepi, nullptr, 0);
+    GemmDesc& da = rest[n++] = gemm(dP, lddp, false, X, ldx, false, s->n_r, s->H, s->M, wepi, nullptr, 0);
     da.segs = dA_segs;
     da.n_segs = n_dA;
-    if ((st = ntp::gemm_launch(h, da, stream)) != NTP_OK) return st;
   }
-  if (s->M == 0) return NTP_OK;
-  // dXpart = dP A_i^T, contraction over the ragged shard width
-  GemmDesc dx = gemm(dP, lddp, true, A_t, lda, false, s->M, s->H, s->n_r, ntp::EPI_BF16, dXpart, lddx);
-  dx.a_k_pad_8 = s->n_r > 0;
-  dx.a_k_pad_64 = pad64;  // dP's pad columns were zeroed above
-  return ntp::gemm_launch(h, dx, stream);
+  if (s->M > 0) {
+    // dXpart = dP A_i^T, contraction over the ragged shard width
+    GemmDesc& dx = rest[n++] = gemm(dP, lddp, true, A_t, lda, false, s->M, s->H, s->n_r, ntp::EPI_BF16, dXpart, lddx);
+    dx.a_k_pad_8 = s->n_r > 0;
+    dx.a_k_pad_64 = pad64;  // dP's pad columns were zeroed above
+  }
+  return ntp::gemm_launch_group(h, rest, n, stream);
 }
 
 }  // namespace
@@ -210,21 +211,19 @@ int attn_bwd(ntp_handle_t* h, const ntp_attn_shape_t* s, const void* dZ, int64_t
   int st = NTP_OK;
   if (dZ) {
     if (!Wo || !C || !dC || !dWo_segs || n_dWo < 1) return NTP_ERR_INVALID_ARG;
-    GemmDesc d = gemm(dZ, lddz, true, Wo, ldwo, true, s->M, s->w_o, s->H, ntp::EPI_BF16, dC, lddc);
-    if ((st = ntp::gemm_launch(h, d, stream)) != NTP_OK) return st;
-    GemmDesc w = gemm(C, ldc, false, dZ, lddz, false, s->w_o, s->H, s->M, wepi, nullptr, 0);
-    w.segs = dWo_segs;
-    w.n_segs = n_dWo;
-    if ((st = ntp::gemm_launch(h, w, stream)) != NTP_OK) return st;
+    GemmDesc d[2] = {gemm(dZ, lddz, true, Wo, ldwo, true, s->M, s->w_o, s->H, ntp::EPI_BF16, dC, lddc),
+                     gemm(C, ldc, false, dZ, lddz, false, s->w_o, s->H, s->M, wepi, nullptr, 0)};
+    d[1].segs = dWo_segs;
+    d[1].n_segs = n_dWo;
+    if ((st = ntp::gemm_launch_group(h, d, 2, stream)) != NTP_OK) return st;
   }
   if (dQKV) {
     if (!Wqkv || !X || !dXpart || !dWqkv_segs || n_dWqkv < 1) return NTP_ERR_INVALID_ARG;
-    GemmDesc d = gemm(dQKV, lddqkv, true, Wqkv, ldwqkv, false, s->M, s->H, s->w_qkv, ntp::EPI_BF16, dXpart, lddx);
-    if ((st = ntp::gemm_launch(h, d, stream)) != NTP_OK) return st;
-    GemmDesc w = gemm(dQKV, lddqkv, false, X, ldx, false, s->w_qkv, s->H, s->M, wepi, nullptr, 0);
-    w.segs = dWqkv_segs;
-    w.n_segs = n_dWqkv;
-    if ((st = ntp::gemm_launch(h, w, stream)) != NTP_OK) return st;
+    GemmDesc d[2] = {gemm(dQKV, lddqkv, true, Wqkv, ldwqkv, false, s->M, s->H, s->w_qkv, ntp::EPI_BF16, dXpart, lddx),
+                     gemm(dQKV, lddqkv, false, X, ldx, false, s->w_qkv, s->H, s->M, wepi, nullptr, 0)};
+    d[1].segs = dWqkv_segs;
+    d[1].n_segs = n_dWqkv;
+    if ((st = ntp::gemm_launch_group(h, d, 2, stream)) != NTP_OK) return st;
   }
   return NTP_OK;
 }

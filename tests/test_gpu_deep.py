@@ -79,13 +79,18 @@ def test_mlp_deep_more_tiles(M, H, n_r, form):
 
 
 def test_deep_matches_the_other_kernels_bit_for_bit(opts):
-    """Without a cut K axis both kernels add in the same order."""
-    import torch
+    """Without a cut K axis both kernels add in the same order; the three gradient GEMMs of the backward call share a launch."""
+    import paper_2504_06095_amd as N
     from paper_2504_06095_amd import binding as K
     print("[gpu-case] deep GEMM against the ring kernel", file=sys.stderr, flush=True)
-    for M, H, n_r in ((512, 1024, 586), (640, 776, 1000)):
+    for M, H, n_r in ((512, 1024, 586), (640, 776, 1000), (258, 264, 257)):
         case = MlpCase(M, H, n_r, 1, 0)
+        N.ntp_kernel_timing_enable(1)
+        N.ntp_kernel_timing_read()
         a, _ = case.run_gpu(pad_to=64)
+        picked = [r["name"] for r in N.ntp_kernel_timing_read()]
+        N.ntp_kernel_timing_enable(0)
+        assert "gemm_group_128x128w8d" in picked and len(picked) == 4, picked
         opts(K.NTP_OPT_GEMM_SCHEDULE, 1)
         b, _ = case.run_gpu(pad_to=64)
         opts(K.NTP_OPT_GEMM_SCHEDULE, 0)
