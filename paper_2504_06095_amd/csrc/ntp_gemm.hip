@@ -313,6 +313,7 @@ int prepare(ntp_handle* h, const GemmDesc& d, Prepared* out) {
   if (!to_segs && d.ldc < n_store) return NTP_ERR_INVALID_ARG;
 
   GemmArgs g{};
+  g.all_rows = 1;
   if (to_segs) {
     // destinations of the output rows: inside [0, M), aligned, wide enough, not overlapping in memory
     // (a row that no segment lists is not stored)
@@ -336,6 +337,16 @@ int prepare(ntp_handle* h, const GemmDesc& d, Prepared* out) {
       g.seg[g.n_segs].ld = r.ld;
       ++g.n_segs;
     }
+    int64_t covered = 0;  // rows [0, covered) have a destination
+    for (bool grown = true; grown;) {
+      grown = false;
+      for (int32_t i = 0; i < g.n_segs; ++i)
+        if (g.seg[i].begin <= covered && g.seg[i].end > covered) {
+          covered = g.seg[i].end;
+          grown = true;
+        }
+    }
+    g.all_rows = covered >= d.M;
     if (g.n_segs == 0) return NTP_OK;  // no row has a destination: nothing to compute
   }
   g.A = static_cast<const uint16_t*>(d.A);

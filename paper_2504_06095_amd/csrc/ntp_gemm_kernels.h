@@ -37,6 +37,8 @@ struct GemmArgs {
     float* ptr;
     int64_t ld;
   } seg[kMaxRowSegs];
+  // every row of [0, M) goes somewhere: the epilogue of a whole tile then issues a known number of instructions (at least)
+  int32_t all_rows;
   // split-K launches only: number of K chunks, chunk length (elements, a multiple of 64) and the
   // distance in floats between the partial-sum slices that start at C
   int32_t k_splits, k_chunk;

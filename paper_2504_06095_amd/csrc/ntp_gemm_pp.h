@@ -317,7 +317,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
     }
     const int erow0 = row0, ecol0 = col0;
     vblk = vnext;
-    stores_in_flight = NEPI <= 63 && erow0 + BM_ <= g.M && ecol0 + BN_ <= g.N;
+    stores_in_flight = NEPI <= 63 && g.all_rows != 0 && erow0 + BM_ <= g.M && ecol0 + BN_ <= g.N;
     if (more) {
       __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(0));
       __builtin_amdgcn_s_barrier();

@@ -473,8 +473,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_ring_kernel(const GemmArg
     // reads LDS and that every wavefront's DMA instructions of this tile have landed.
     const int erow0 = row0, ecol0 = col0;
     vblk = vnext;
-    // interior tile: no lane is masked in the epilogue, so its instruction count is the static one
-    stores_in_flight = NEPI <= 63 && erow0 + BM_ <= g.M && ecol0 + BN_ <= g.N;
+    // interior tile all of whose rows are stored: no lane is masked in the epilogue, so its instruction count is the static one
+    stores_in_flight = NEPI <= 63 && g.all_rows != 0 && erow0 + BM_ <= g.M && ecol0 + BN_ <= g.N;
     if (more) {
       __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(0));
       __builtin_amdgcn_s_barrier();

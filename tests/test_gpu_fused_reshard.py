@@ -226,3 +226,26 @@ def test_resharded_rejects_bad_segments():
     call(N.row_segments([(0, 10, buf, H), (30, 10, buf[30:], H)]))
     torch.cuda.synchronize()
     assert (buf[10:30] == SENTINEL).all() and (buf[:10] == 0).all() and (buf[30:40] == 0).all()
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_mlp_bwd_resharded_rows_without_a_destination(accumulate):
+    """Several output tiles per workgroup and only a few rows with a destination here (the others belong to other GPUs): a tile
+    whose rows are not stored must not let the next one start on operands that have not landed."""
+    import torch
+    import paper_2504_06095_amd as N
+    _say(f"mlp bwd resharded, few rows stored, accumulate {accumulate}")
+    M, H, n_r = 1024, 8192, 7000
+    g = torch.Generator("cuda").manual_seed(3)
+    mk = lambda r, c, s=1.0: torch.empty(r, c, device="cuda").normal_(0.0, s, generator=g).bfloat16()  # noqa: E731
+    dZ, X, At, B, P, Y = mk(M, H), mk(M, H), mk(n_r, H, 0.02), mk(n_r, H, 0.02), mk(M, n_r), mk(M, n_r)
+    dP, dX = torch.empty_like(P), torch.empty_like(X)
+    ref = [torch.zeros(n_r, H, device="cuda") for _ in range(2)]
+    got = [torch.zeros(300, H, device="cuda") for _ in range(2)]
+    segs = [N.row_segments([(6500, 300, t, H)]) for t in got]
+    for i in range(2):
+        N.ntp_mlp_shard_bwd(dZ, X, At, B, P, Y, dP, dX, *ref, n_r, accumulate=accumulate)
+        N.ntp_mlp_shard_bwd_resharded(dZ, X, At, B, P, Y, dP, dX, *segs, n_r, accumulate=accumulate)
+        torch.cuda.synchronize()
+        for a, b in zip(got, ref):
+            assert torch.equal(a, b[6500:6800])
