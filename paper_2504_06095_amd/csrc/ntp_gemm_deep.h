@@ -134,6 +134,9 @@ __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, ui
   }
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the clamped DMA instructions write LDS that this workgroup still owns
 
+  if constexpr (EPI == ntp::EPI_F32_ACCUM) {
+    if (g.k_splits == 1 && g.n_segs == 1) return accumulate_blocks<MI, NI>(g, row0 + wm * TM + (lane & 15), col0 + wn * TN + (lane >> 4) * 4, acc);
+  }
   constexpr bool PAIRED = EPI == ntp::EPI_BF16 || EPI == ntp::EPI_GELU || EPI == ntp::EPI_DGELU;
 #pragma unroll
   for (int i = 0; i < MI; ++i) {

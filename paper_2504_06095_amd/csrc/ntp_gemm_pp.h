@@ -328,6 +328,13 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
       first_dma();
     }
     __builtin_amdgcn_sched_barrier(0);  // the epilogue's memory instructions stay behind those DMA instructions
+    if constexpr (EPI == ntp::EPI_F32_ACCUM && NI <= 4) {  // (wider block rows would spill)
+      if (g.n_segs == 1) {
+        accumulate_blocks<MI, NI>(g, erow0 + wm * TM + (lane & 15), ecol0 + wn * TN + (lane >> 4) * 4, acc);
+        if (!more) break;
+        continue;
+      }
+    }
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
       const int m = erow0 + wm * TM + i * 16 + (lane & 15);

@@ -96,3 +96,24 @@ def test_deep_matches_the_other_kernels_bit_for_bit(opts):
         opts(K.NTP_OPT_GEMM_SCHEDULE, 0)
         for k in MLP_NAMES:
             assert np.array_equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("M,H,n_r", [(1000, 1288, 4000), (1040, 2056, 1300), (200, 4104, 3000), (4096, 3080, 1800)])
+def test_accumulating_epilogue_adds_exactly_once(M, H, n_r):
+    """Accumulating into a buffer gives, bit for bit, the buffer plus the overwriting call's result: same products, one fp32 addition."""
+    import torch
+    import paper_2504_06095_amd as N
+    print(f"[gpu-case] accumulating epilogue M={M} H={H} n_r={n_r}", file=sys.stderr, flush=True)
+    g = torch.Generator("cuda").manual_seed(1)
+    mk = lambda r, c: torch.empty(r, c, device="cuda").normal_(generator=g).bfloat16()  # noqa: E731
+    ld = -(-n_r // 8) * 8
+    dZ, X, At, B, P, Y = mk(M, H), mk(M, H), mk(n_r, H), mk(n_r, H), mk(M, ld)[:, :n_r], mk(M, ld)[:, :n_r]
+    dP, dX = torch.empty(M, ld, dtype=torch.bfloat16, device="cuda")[:, :n_r], torch.empty_like(X)
+    plain = [torch.full((n_r, H + 4), 7.0, device="cuda")[:, :H] for _ in range(2)]
+    start = [torch.empty(n_r, H + 4, device="cuda").normal_(generator=g) for _ in range(2)]
+    acc = [t.clone() for t in start]
+    N.ntp_mlp_shard_bwd(dZ, X, At, B, P, Y, dP, dX, *plain, n_r)
+    N.ntp_mlp_shard_bwd(dZ, X, At, B, P, Y, dP, dX, *[t[:, :H] for t in acc], n_r, accumulate=True)
+    torch.cuda.synchronize()
+    for s, p, a in zip(start, plain, acc):
+        assert torch.equal(a[:, :H], s[:, :H] + p) and torch.equal(a[:, H:], s[:, H:])
