@@ -1015,14 +1015,12 @@ __device__ __forceinline__ bf16x8 tr_frag(const uint16_t* tile, int ldt, int r0,
 }
 
 // dQ (and delta): a workgroup takes 64 QB query rows of one (sequence, head), a wavefront 16 QB of them.
+// (first: the workgroup's number in its launch, or in its share of a launch of `count`; sK, sV: kBKV rows of D + 16 each)
 template <int D, int QB, bool PAIRED>
-__global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads), amdgpu_waves_per_eu(QB == 1 ? 3 : 2, QB == 1 ? 3 : 2))) void
-attn_core_bwd_dq_kernel(const CoreBwdArgs a) {
+__device__ __forceinline__ void bwd_dq_body(const CoreBwdArgs& a, uint32_t first, uint32_t count, uint16_t* const sK, uint16_t* const sV) {
   constexpr int kRows = 64 * QB;
   constexpr int LDT = D + 16, KS = D / 32, DB = D / 16, CPR = D / 8, NLD = kBKV * CPR / kThreads;
-  __shared__ __attribute__((aligned(16))) uint16_t sK[kBKV * LDT];
-  __shared__ __attribute__((aligned(16))) uint16_t sV[kBKV * LDT];
-  const uint32_t bid = xcd_major(blockIdx.x, gridDim.x);
+  const uint32_t bid = xcd_major(first, count);
   const int piece = a.n_parts > 1 ? int(bid % a.n_parts) : 0;
   const int blk = a.n_parts > 1 ? int(bid / a.n_parts) : int(bid);
   const int per_seq = PAIRED ? a.pairs : a.tiles;
@@ -1071,7 +1069,7 @@ attn_core_bwd_dq_kernel(const CoreBwdArgs a) {
     }
     delta[qb] = xor_sum(part);
     lse2[qb] = a.LSE[int64_t(head) * Mtot + tok0 + qr] * 1.4426950408889634f;
-    if (lh == 0 && piece == 0 && q0 + qb * 16 + lq < S) a.Delta[int64_t(head) * Mtot + tok0 + qr] = delta[qb];
+    if (lh == 0 && piece == 0 && !a.delta_stored && q0 + qb * 16 + lq < S) a.Delta[int64_t(head) * Mtot + tok0 + qr] = delta[qb];
   }
 
   f32x4 acc[QB][DB];
@@ -1195,6 +1193,14 @@ attn_core_bwd_dq_kernel(const CoreBwdArgs a) {
     }
   }
   }  // the workgroup's passes
+}
+
+template <int D, int QB, bool PAIRED>
+__global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads), amdgpu_waves_per_eu(QB == 1 ? 3 : 2, QB == 1 ? 3 : 2))) void
+attn_core_bwd_dq_kernel(const CoreBwdArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t sK[kBKV * (D + 16)];
+  __shared__ __attribute__((aligned(16))) uint16_t sV[kBKV * (D + 16)];
+  bwd_dq_body<D, QB, PAIRED>(a, blockIdx.x, gridDim.x, sK, sV);
 }
 
 // The dQ kernel with the key / value tiles brought to LDS by DMA (see attn_core_fwd_dma_kernel: the same chunk-permuted
@@ -1454,13 +1460,10 @@ __device__ __forceinline__ void bwd_dq_dma_body(const CoreBwdArgs& a, const uint
 // the matrix work per LDS read but needs 440 registers (one wavefront per SIMD); KB = 1 fits in 256, two
 // workgroups share a compute unit and it measured 7-35 % faster at every size: only KB = 1 is built.
 template <int D, int KB, bool PAIRED>
-__global__ __launch_bounds__(kThreads, 2) void attn_core_bwd_dkv_kernel(const CoreBwdArgs a) {
+__device__ __forceinline__ void bwd_dkv_body(const CoreBwdArgs& a, uint32_t first, uint32_t count, uint16_t* const sQ, uint16_t* const sG, float* const sL,
+                                             float* const sD) {
   constexpr int LDT = D + 16, KS = D / 32, DB = D / 16, CPR = D / 8, NLD = kBKV * CPR / kThreads;
-  __shared__ __attribute__((aligned(16))) uint16_t sQ[kBKV * LDT];
-  __shared__ __attribute__((aligned(16))) uint16_t sG[kBKV * LDT];
-  __shared__ __attribute__((aligned(16))) float sL[kBKV];
-  __shared__ __attribute__((aligned(16))) float sD[kBKV];
-  const uint32_t bid = xcd_major(blockIdx.x, gridDim.x);
+  const uint32_t bid = xcd_major(first, count);
   const int part = a.n_parts > 1 ? int(bid % a.n_parts) : 0;
   const int blk = a.n_parts > 1 ? int(bid / a.n_parts) : int(bid);
   const int per_seq = PAIRED ? a.pairs : a.tiles;
@@ -1672,6 +1675,15 @@ __global__ __launch_bounds__(kThreads, 2) void attn_core_bwd_dkv_kernel(const Co
     }
   }
   }  // the workgroup's passes
+}
+
+template <int D, int KB, bool PAIRED>
+__global__ __launch_bounds__(kThreads, 2) void attn_core_bwd_dkv_kernel(const CoreBwdArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t sQ[kBKV * (D + 16)];
+  __shared__ __attribute__((aligned(16))) uint16_t sG[kBKV * (D + 16)];
+  __shared__ __attribute__((aligned(16))) float sL[kBKV];
+  __shared__ __attribute__((aligned(16))) float sD[kBKV];
+  bwd_dkv_body<D, KB, PAIRED>(a, blockIdx.x, gridDim.x, sQ, sG, sL, sD);
 }
 
 // The dK / dV kernel with the query and output-gradient tiles brought to LDS by DMA (the layout and the read
@@ -2100,24 +2112,39 @@ struct BothOrder {
   uint32_t n_dkv, paired, chunk;
 };
 
+// Kind of workgroup b (true: dK/dV) and its number among its kind.
+__device__ __forceinline__ bool both_place(const BothOrder& o, uint32_t& b) {
+  if (b < 2 * o.paired) {
+    const uint32_t c = b / o.chunk;
+    b = (c >> 1) * o.chunk + b % o.chunk;
+    return (c & 1) == 0;
+  }
+  b -= 2 * o.paired;
+  const bool dkv = b < o.n_dkv - o.paired;
+  b = dkv ? o.paired + b : o.paired + b - (o.n_dkv - o.paired);
+  return dkv;
+}
+
 template <bool PAIRED>
 __global__ __launch_bounds__(kThreads, 2) void attn_core_bwd_both_kernel(const CoreBwdArgs adq, const CoreBwdArgs adkv, const BothOrder o) {
   __shared__ __attribute__((aligned(1024))) uint16_t tiles[4 * kDmaTile];
   __shared__ __attribute__((aligned(16))) float row_values[2 * 2 * kBKV];
   uint32_t b = blockIdx.x;
-  bool dkv;
-  if (b < 2 * o.paired) {
-    const uint32_t c = b / o.chunk;
-    dkv = (c & 1) == 0;
-    b = (c >> 1) * o.chunk + b % o.chunk;
-  } else {
-    b -= 2 * o.paired;
-    dkv = b < o.n_dkv - o.paired;
-    b = dkv ? o.paired + b : o.paired + b - (o.n_dkv - o.paired);
-  }
+  const bool dkv = both_place(o, b);
   // (each kind renumbered by itself: its workgroups with equal b % 8 share an XCD whatever the other kind's count)
   if (dkv) bwd_dkv_dma_body<PAIRED>(adkv, b, o.n_dkv, tiles, row_values);
   else bwd_dq_dma_body<PAIRED>(adq, b, gridDim.x - o.n_dkv, tiles);
+}
+
+// The same for head dimension 64 (copies through registers, 21 KB of LDS a workgroup).
+template <bool PAIRED>
+__global__ __launch_bounds__(kThreads, 2) void attn_core_bwd_both64_kernel(const CoreBwdArgs adq, const CoreBwdArgs adkv, const BothOrder o) {
+  __shared__ __attribute__((aligned(16))) uint16_t t0[kBKV * (64 + 16)];
+  __shared__ __attribute__((aligned(16))) uint16_t t1[kBKV * (64 + 16)];
+  __shared__ __attribute__((aligned(16))) float row_values[2 * kBKV];
+  uint32_t b = blockIdx.x;
+  if (both_place(o, b)) bwd_dkv_body<64, 1, PAIRED>(adkv, b, o.n_dkv, t0, t1, row_values, row_values + kBKV);
+  else bwd_dq_body<64, 1, PAIRED>(adq, b, gridDim.x - o.n_dkv, t0, t1);
 }
 
 // delta[head][row] = sum_d dC[row][head D + d] C[row][head D + d]: 16 lanes per (row, head), 8 values each
@@ -2260,8 +2287,10 @@ CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_cor
   // Where it pays (the sweep above): wherever the two launches, uncut, have at most 3 workgroups per compute unit
   // between them (14 heads x 2048 causal: 98 -> 77 us; 8 heads x 4096 causal 175 -> 143; 4 heads x 4096 unmasked
   // 146 -> 122); larger launches fill the device on their own and lose 1-4 % to the extra kernel.
-  const bool pays = wq + wk <= 3 * cus;
-  c.bwd_both = c.dq_dma && c.dkv_dma && h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] != 1 && (pays || h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] == 2) &&
+  // Head dimension 64 (walks that are not cut): at every size measured (3 heads x 512 tokens of 4 sequences 28 -> 20 us, 15 heads
+  // x 389 30 -> 22 us, 28 heads x 6062 620 -> 589 us, 22 heads x 3801 no difference).
+  const bool pays = s->head_dim == 64 || wq + wk <= 3 * cus;
+  c.bwd_both = (dma || (s->head_dim == 64 && c.dq_parts == 1 && c.dkv_parts == 1)) && h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] != 1 && (pays || h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] == 2) &&
                (dkv_bytes == 0 || c.dkv_ws_offset + dkv_bytes <= ws_bytes);
   c.ws_bytes = std::max(c.ws_bytes, c.bwd_both ? (dkv_bytes ? c.dkv_ws_offset + dkv_bytes : dq_bytes) : std::max(dq_bytes, dkv_bytes));
   return c;
@@ -2443,7 +2472,7 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
       hipLaunchKernelGGL((attn_core_part_reduce_kernel<64, DKV>), rgrid, dim3(256), 0, hs, a, blocks);
     return hipGetLastError() == hipSuccess;
   };
-  const int64_t delta_wgs = (M * s->q_cnt * 16 + 255) / 256;
+  const int64_t delta_wgs = (M * s->q_cnt * (s->head_dim / 8) + 255) / 256;
   if (dq_wgs > 0x7fffffffll || dkv_wgs > 0x7fffffffll) return NTP_ERR_UNSUPPORTED;
   if (cc.bwd_both && bq > 0 && bk > 0 && dq_wgs + dkv_wgs <= 0x7fffffffll && delta_wgs <= 0x7fffffffll) {
     // one launch for both kernels, after the rows' delta values (5 algorithmic + 2 recomputed products per pair)
@@ -2456,7 +2485,8 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
     adkv.pairs = k_pairs;
     adkv.part_sums = a.part_sums + cc.dkv_ws_offset / 4;
     if (ntp::timing_on(h)) ntp::timing_begin(h, stream, cc.dq_parts > 1 || cc.dkv_parts > 1 ? "attn_core_bwd_both_cut" : "attn_core_bwd_both", 7.0 * pair_flops, 0.0);
-    hipLaunchKernelGGL((attn_core_delta_kernel<128>), dim3(uint32_t(delta_wgs)), dim3(256), 0, hs, a, M);
+    const bool wide = s->head_dim == 128;
+    hipLaunchKernelGGL(wide ? attn_core_delta_kernel<128> : attn_core_delta_kernel<64>, dim3(uint32_t(delta_wgs)), dim3(256), 0, hs, a, M);
     ok = hipGetLastError() == hipSuccess;
     const dim3 grid(uint32_t(dq_wgs + dkv_wgs));
     if (ok) {
@@ -2464,8 +2494,9 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
       order.n_dkv = uint32_t(dkv_wgs);
       order.chunk = uint32_t(std::max(h->compute_units, 1));
       order.paired = uint32_t(std::min(dq_wgs, dkv_wgs) / order.chunk * order.chunk);
-      if (s->causal) hipLaunchKernelGGL((attn_core_bwd_both_kernel<true>), grid, dim3(kThreads), 0, hs, adq, adkv, order);
-      else hipLaunchKernelGGL((attn_core_bwd_both_kernel<false>), grid, dim3(kThreads), 0, hs, adq, adkv, order);
+      const auto both = wide ? (s->causal ? attn_core_bwd_both_kernel<true> : attn_core_bwd_both_kernel<false>)
+                             : (s->causal ? attn_core_bwd_both64_kernel<true> : attn_core_bwd_both64_kernel<false>);
+      hipLaunchKernelGGL(both, grid, dim3(kThreads), 0, hs, adq, adkv, order);
       ok = hipGetLastError() == hipSuccess;
     }
     if (ok && cc.dq_parts > 1) {
