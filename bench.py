@@ -557,7 +557,7 @@ def mapped_reshard_stress(torch, N):
         sc, ss = shards(comp, t), shards(sync, tr)
         plans = (N.ntp_reshard_plan_create(spec, t, comp, tr, sync), N.ntp_reshard_plan_create(spec, tr, sync, t, comp))
         for pl in plans:
-            pl.ntp_reshard_plan_prepare()  # uploads the run table: the only allocation, outside the timed region
+            pl.ntp_reshard_plan_prepare()  # uploads the unit table: the only allocation, outside the timed region
         jobs.append((*plans, sc, ss))
         total += 2.0 * 4 * rows * cols
     out = {}

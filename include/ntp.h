@@ -414,8 +414,8 @@ int ntp_comp_sync_plan(int64_t k, int32_t full_tp, int32_t reduced_tp, int32_t* 
  * ntp_reshard_plan_table: for every destination unit, destination shards one
  *   after the other, the source rank and the local unit in its shard.
  * ntp_reshard_plan_prepare: makes the plan ready to run on the CURRENT device.
- *   Plans of column-partitioned tensors of 4-byte elements have a run table (2
- *   bytes per unit + 16 bytes per sub-shard) that one of the copy kernels reads
+ *   Plans of column-partitioned tensors of 4-byte elements and of row-partitioned
+ *   tensors have a unit table (4 bytes per unit) that the copy kernels read
  *   from device memory: this call allocates it (hipMalloc) and waits for its
  *   upload.  It is the only call of the library that allocates device memory or
  *   blocks; every plan needs it once before its first run (for plans without a

@@ -549,7 +549,7 @@ class ReshardPlan:
         return [(e.src_rank, e.src_unit) for e in buf[: n.value]]
 
     def ntp_reshard_plan_prepare(self) -> None:
-        """Make the plan ready to run on the current device (uploads its run table); needed once before the first run."""
+        """Make the plan ready to run on the current device (uploads its unit table); needed once before the first run."""
         _check(lib().ntp_reshard_plan_prepare(self._h), "ntp_reshard_plan_prepare")
 
     def ntp_reshard_plan_run(self, src_shards, dst_shards, handle=None) -> None:

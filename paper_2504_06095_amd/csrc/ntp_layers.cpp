@@ -262,7 +262,9 @@ extern "C" int ntp_workspace_bytes(const ntp_handle_t* h, int32_t call, const vo
   auto up = [](int64_t x, int64_t m) { return (x + m - 1) / m * m; };
   int64_t need = 0;
   auto gemm_wish = [&](int layout, int64_t M, int64_t N, int64_t n_store, int64_t K) {
-    if (M > 0 && N > 0 && K > 0) need = std::max(need, ntp::gemm_workspace_wish(h, layout, M, N, n_store, K));
+    // (also what the choice without the deep-pipelined kernel would use: operands of 2 GiB and more do not run on it)
+    if (M > 0 && N > 0 && K > 0)
+      for (const bool deep : {false, true}) need = std::max(need, ntp::gemm_workspace_wish(h, layout, M, N, n_store, K, deep));
   };
   if (call == NTP_CALL_MLP_SHARD) {
     const ntp_mlp_shape_t* s = static_cast<const ntp_mlp_shape_t*>(shape);
