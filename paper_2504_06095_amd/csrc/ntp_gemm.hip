@@ -275,13 +275,15 @@ struct Prepared {
   GemmArgs g;
   SplitChoice sc;
   int layout;
-  bool ring_ok, nothing;  // nothing: no output, or none that has a destination
+  bool ring_ok;
+  bool empty;    // no output element: nothing else is filled in
+  bool nothing;  // no output that has a destination
   void* ws_ptr;
   int64_t ldw, k8;
 };
 
 int prepare(ntp_handle* h, const GemmDesc& d, Prepared* out) {
-  out->nothing = true;
+  out->empty = out->nothing = true;
   if (!h || d.M < 0 || d.N < 0 || d.K < 0) return NTP_ERR_INVALID_ARG;
   if (d.M == 0 || d.N == 0) return NTP_OK;
   if (h->device < 0) return NTP_ERR_NO_DEVICE;
@@ -347,7 +349,6 @@ int prepare(ntp_handle* h, const GemmDesc& d, Prepared* out) {
         }
     }
     g.all_rows = covered >= d.M;
-    if (g.n_segs == 0) return NTP_OK;  // no row has a destination: nothing to compute
   }
   g.A = static_cast<const uint16_t*>(d.A);
   g.B = static_cast<const uint16_t*>(d.B);
@@ -391,7 +392,7 @@ int prepare(ntp_handle* h, const GemmDesc& d, Prepared* out) {
   const bool deep_ok = ring_ok && a_rows * d.lda * 2 < (int64_t(1) << 31) && b_rows * d.ldb * 2 < (int64_t(1) << 31) &&
                        (!d.a_kc || d.K % 8 == 0 || (d.a_k_pad_8 && !d.b_kc));
   const SplitChoice sc = plan_gemm(h, ws_ptr ? ws_bytes : 0, g, layout, ring_ok, split_ok, ldw, deep_ok);
-  *out = Prepared{g, sc, layout, ring_ok, false, ws_ptr, ldw, k8};
+  *out = Prepared{g, sc, layout, ring_ok, false, to_segs && g.n_segs == 0, ws_ptr, ldw, k8};
   return NTP_OK;
 }
 
@@ -404,12 +405,10 @@ GemmArgs deep_args(const Prepared& p, const GemmDesc& d) {
   return g;
 }
 
-}  // namespace
-
-int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
-  Prepared p;
-  int st = prepare(h, d, &p);
-  if (st != NTP_OK || p.nothing) return st;
+// Enqueues a checked GEMM by its choice.
+int launch_prepared(ntp_handle* h, const GemmDesc& d, const Prepared& p, void* stream) {
+  if (p.nothing) return NTP_OK;
+  int st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   static const char* const kEpiName[] = {"bf16", "gelu", "dgelu", "f32", "f32acc"};
   const GemmArgs& g = p.g;
@@ -477,6 +476,14 @@ int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
   return st;
 }
 
+}  // namespace
+
+int gemm_launch(ntp_handle* h, const GemmDesc& d, void* stream) {
+  Prepared p;
+  const int st = prepare(h, d, &p);
+  return st != NTP_OK ? st : launch_prepared(h, d, p, stream);
+}
+
 namespace {
 
 struct Span {
@@ -509,44 +516,56 @@ bool writes_into(const GemmDesc& a, const GemmDesc& b) {
 
 }  // namespace
 
-// GEMMs that do not need each other's results.  One launch where all of them would run on the deep-pipelined kernel anyway, nothing that one
-// writes is read or written by another (a caller may pass an output that overlaps a later product's operand: then they run in
-// order), and the estimate says so; else one after the other.  Estimate: a launch costs 6 us beside its K tiles (launch, first loads, stores);
-// the group's K tiles take as long as its longest problem, or as all its tiles dealt out over the device.
+// GEMMs that do not need each other's results.  One launch, without cutting a K axis, where all of them would run on the deep-pipelined
+// kernel anyway and the estimate says so; else one after the other by their own choices.  Estimate: a launch costs 6 us beside its K tiles
+// (launch, first loads, stores); the group's K tiles take as long as its longest problem, or as all its tiles dealt out over the device.
+// The numbers must not depend on where the outputs go, so the decision looks at shapes and workspace only: products without a destination
+// here count like the others, and where one product writes what another reads or writes (a caller may pass such buffers), the products run
+// one after the other in the form that they have in the shared launch.
 int gemm_launch_group(ntp_handle* h, const GemmDesc* d, int n, void* stream) {
   constexpr int kMax = 3;
+  if (n > kMax) return NTP_ERR_INVALID_ARG;
   Prepared p[kMax];
-  bool group = n >= 2 && n <= kMax;
+  int status[kMax] = {NTP_OK, NTP_OK, NTP_OK};
+  bool group = n >= 2, apart_only = false;
   double apart = 0.0, longest = 0.0, work = 0.0, flops = 0.0;
-  for (int i = 0; i < n && group; ++i) {
-    group = prepare(h, d[i], &p[i]) == NTP_OK && !p[i].nothing && p[i].sc.deep == kDeep5 &&
+  for (int i = 0; i < n; ++i) {
+    status[i] = prepare(h, d[i], &p[i]);
+    group = group && status[i] == NTP_OK && !p[i].empty && p[i].sc.deep == kDeep5 &&
             (p[i].layout == 2 ? d[i].epilogue == EPI_F32 || d[i].epilogue == EPI_F32_ACCUM : d[i].epilogue == EPI_BF16);
-    for (int j = 0; j < i && group; ++j) group = !writes_into(d[i], d[j]) && !writes_into(d[j], d[i]);
-    if (!group) break;
+    if (!group) continue;
     const GemmArgs& g = p[i].g;
     const double tiles = double((g.M + 127) / 128) * double((g.n_store + 127) / 128), kt = double((g.K + 63) / 64), sp = p[i].sc.splits;
     apart += 6.0 + 0.47 * std::ceil(kt / sp) + (sp > 1 ? 3.5 + double(g.M) * double(p[i].ldw) * (4.0 * sp + 4.0) / 4.4e6 : 0.0);
     longest = std::max(longest, kt);
     work += tiles * kt;
-    flops += 2.0 * double(g.M) * double(g.N) * double(g.K);
   }
-  if (group) group = 6.0 + 0.47 * std::max(longest, 1.15 * work / h->compute_units) < apart;
-  if (!group) {
+  group = group && 6.0 + 0.47 * std::max(longest, 1.15 * work / h->compute_units) < apart;
+  if (group) {
     for (int i = 0; i < n; ++i) {
-      const int st = gemm_launch(h, d[i], stream);
+      p[i].sc.splits = 1;
+      for (int j = 0; j < i; ++j) apart_only = apart_only || writes_into(d[i], d[j]) || writes_into(d[j], d[i]);
+    }
+  }
+  if (!group || apart_only) {
+    for (int i = 0; i < n; ++i) {
+      const int st = status[i] != NTP_OK ? status[i] : launch_prepared(h, d[i], p[i], stream);
       if (st != NTP_OK) return st;
     }
     return NTP_OK;
   }
   GemmArgs g[kMax];
-  int layout[kMax], epi[kMax];
+  int layout[kMax], epi[kMax], m = 0;
   for (int i = 0; i < n; ++i) {
-    g[i] = deep_args(p[i], d[i]);
-    layout[i] = p[i].layout;
-    epi[i] = d[i].epilogue;
+    if (p[i].nothing) continue;
+    g[m] = deep_args(p[i], d[i]);
+    layout[m] = p[i].layout;
+    epi[m++] = d[i].epilogue;
+    flops += 2.0 * double(d[i].M) * double(d[i].N) * double(d[i].K);
   }
+  if (m == 0) return NTP_OK;
   if (ntp::timing_on(h)) ntp::timing_begin(h, stream, "gemm_group_128x128w8d", flops, 0.0);
-  const int st = launch_deep_group(g, layout, epi, n, static_cast<hipStream_t>(stream));
+  const int st = launch_deep_group(g, layout, epi, m, static_cast<hipStream_t>(stream));
   ntp::timing_end(h, stream);
   return st;
 }

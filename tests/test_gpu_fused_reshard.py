@@ -249,3 +249,63 @@ def test_mlp_bwd_resharded_rows_without_a_destination(accumulate):
         torch.cuda.synchronize()
         for a, b in zip(got, ref):
             assert torch.equal(a, b[6500:6800])
+
+
+@pytest.fixture
+def big_workspace():
+    import torch
+    import paper_2504_06095_amd as N
+    N.ntp_set_workspace(torch.full((16 << 20,), float("nan"), dtype=torch.float32, device="cuda"))
+    yield
+    N.ntp_set_workspace(None)
+
+
+def _normal(torch, seed):
+    g = torch.Generator("cuda").manual_seed(seed)
+    return lambda r, c, s=1.0: torch.empty(r, c, device="cuda").normal_(0.0, s, generator=g).bfloat16()
+
+
+# gradient GEMMs that share a launch uncut, but would each be cut along K by themselves (a workspace is set)
+@pytest.mark.parametrize("M,H,n_r", [(1024, 1024, 400), (2048, 1024, 200)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_mlp_gradients_do_not_depend_on_their_destinations(big_workspace, M, H, n_r, accumulate):
+    """Rows without a destination, destinations side by side in one buffer (whose address ranges interleave): the same bits."""
+    import torch
+    import paper_2504_06095_amd as N
+    _say(f"mlp bwd, destinations of the gradients, M={M} H={H} n_r={n_r} accumulate {accumulate}")
+    assert N.ntp_gemm_choice(2, n_r, H, M)["k_splits"] > 1
+    mk = _normal(torch, 11)
+    dZ, X, At, B, P, Y = mk(M, H), mk(M, H), mk(n_r, H, 0.02), mk(n_r, H, 0.02), mk(M, n_r), mk(M, n_r)
+    start = [torch.empty(n_r, H, device="cuda").normal_() for _ in range(2)]
+    call = lambda f, *grads: (lambda dP, dX: (f(dZ, X, At, B, P, Y, dP, dX, *grads, n_r, accumulate=accumulate), (dP, dX))[1])(  # noqa: E731
+        torch.zeros_like(P), torch.zeros_like(X))
+    dA, dB = (t.clone() for t in start)
+    want = call(N.ntp_mlp_shard_bwd, dA, dB)
+    same = lambda got: all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(got, want))  # noqa: E731
+    # one gradient has no destination on this GPU
+    for keep in range(2):
+        grads = [t.clone() for t in start]
+        segs = [N.row_segments([(0, n_r if i == keep else 0, t, H)]) for i, t in enumerate(grads)]
+        assert same(call(N.ntp_mlp_shard_bwd_resharded, *segs))
+        assert torch.equal(grads[keep], (dA, dB)[keep]) and torch.equal(grads[1 - keep], start[1 - keep])
+    # neither has one
+    assert same(call(N.ntp_mlp_shard_bwd_resharded, *[N.row_segments([(0, 0, t, H)]) for t in start]))
+    # both in one buffer, row by row in turn
+    both = torch.cat(start, 1)
+    assert same(call(N.ntp_mlp_shard_bwd, both[:, :H], both[:, H:]))
+    assert torch.equal(both[:, :H], dA) and torch.equal(both[:, H:], dB)
+
+
+def test_attn_gradients_do_not_depend_on_their_destinations(big_workspace):
+    import torch
+    import paper_2504_06095_amd as N
+    M, H, wq, wo = 2048, 1024, 384, 128
+    _say(f"attn bwd, destinations of the gradients, M={M} H={H}")
+    mk = _normal(torch, 12)
+    dZ, dQKV, X, C, Wqkv, Wo = mk(M, H), mk(M, wq), mk(M, H), mk(M, wo), mk(wq, H, 0.02), mk(wo, H, 0.02)
+    dC, dX, dWqkv, dWo = torch.zeros_like(C), torch.zeros_like(X), torch.zeros(wq, H, device="cuda"), torch.zeros(wo, H, device="cuda")
+    N.ntp_attn_proj_shard_bwd(M, H, wq, wo, dZ, dQKV, X, C, Wqkv, Wo, dC, dX, dWqkv, dWo, False)
+    none = N.row_segments([(0, 0, dWo, H)])
+    dC2, dX2 = torch.zeros_like(C), torch.zeros_like(X)
+    N.ntp_attn_proj_shard_bwd_resharded(M, H, wq, wo, dZ, dQKV, X, C, Wqkv, Wo, dC2, dX2, none, none)
+    assert torch.equal(dC.view(torch.int16), dC2.view(torch.int16)) and torch.equal(dX.view(torch.int16), dX2.view(torch.int16))
