@@ -55,51 +55,25 @@ struct GemmArgs {
   int32_t resident;
 };
 
-// GeLU and its derivative, branch-free: the epilogues evaluate them for every output element (112 a lane on the 256 x 224 tile),
-// and the library's erff and tanhf, whose lanes go through both of their branches, cost as much as a K tile (2048 x 7022 over K = 12288:
-// fc1 292 -> 283 us, dY 301 -> 292 us; 4096 x 3511 over 6144 with two micro-batches, tanh form, whole shard 1986 -> 1950 us).
-//   erf form: Phi(-|x|) = exp(-x^2 / 2) R(t), t = 1 / (1 + 0.23 |x|), R the degree-8 polynomial with the least largest relative error
-//   (4.8e-8 for |x| <= 14, iteratively reweighted least squares on erfc; the substitution is Hastings'), then
-//   GeLU = x Phi(x), GeLU' = Phi(x) + x exp(-x^2 / 2) / sqrt(2 pi) with the same exponential.  Against 64 bits over normal x: GeLU 2.8e-8 (with
-//   erff 3.0e-8; in the negative tail, where 1 + erf cancels, better by orders), GeLU' 7.5e-8 (4.0e-8); the results are rounded to bf16 (2e-3).
-//   tanh form: (1 + tanh u) / 2 = 1 / (1 + exp(-2 u)): 3.6e-8 (2.9e-8), derivative 2.5e-7 (1.0e-7).
-struct NormalTail {
-  float cdf, e;  // Phi(x), exp(-x^2 / 2)
-};
-__device__ __forceinline__ NormalTail normal_tail(float x) {
-  const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.23f, __builtin_fabsf(x), 1.0f));
-  float r = -0.07846732110308453f;
-  r = __builtin_fmaf(r, t, 0.2904134561104405f);
-  r = __builtin_fmaf(r, t, -0.27812553352791003f);
-  r = __builtin_fmaf(r, t, 0.30147111038887736f);
-  r = __builtin_fmaf(r, t, -0.03291900102862229f);
-  r = __builtin_fmaf(r, t, 0.11951353549571861f);
-  r = __builtin_fmaf(r, t, 0.08576305381637472f);
-  r = __builtin_fmaf(r, t, 0.0923784373364247f);
-  r = __builtin_fmaf(r, t, -2.776129358586769e-05f);
-  const float e = __builtin_amdgcn_exp2f(x * x * -0.7213475204444817f);
-  const float q = r * e;
-  return NormalTail{x > 0.0f ? 1.0f - q : q, e};
-}
-
-// 1 / (1 + exp(-2 u)), u = sqrt(2 / pi) (x + 0.044715 x^3)
-__device__ __forceinline__ float gelu_sigmoid(float x) {
-  const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
-  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(u * -2.8853900817779268f));
-}
-
 __device__ __forceinline__ float gelu_fwd(float x, int mode) {
-  return x * (mode == NTP_GELU_TANH ? gelu_sigmoid(x) : normal_tail(x).cdf);
+  if (mode == NTP_GELU_TANH) {
+    const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
+    return 0.5f * x * (1.0f + tanhf(u));
+  }
+  return 0.5f * x * (1.0f + erff(x * 0.7071067811865476f));
 }
 
 __device__ __forceinline__ float gelu_bwd(float x, int mode) {
   if (mode == NTP_GELU_TANH) {
-    const float s = gelu_sigmoid(x);
-    const float du = 0.7978845608028654f * (1.0f + 3.0f * 0.044715f * x * x);
-    return s + 2.0f * x * (s * (1.0f - s)) * du;
+    const float c = 0.7978845608028654f;
+    const float u = c * (x + 0.044715f * x * x * x);
+    const float th = tanhf(u);
+    const float du = c * (1.0f + 3.0f * 0.044715f * x * x);
+    return 0.5f * (1.0f + th) + 0.5f * x * (1.0f - th * th) * du;
   }
-  const NormalTail n = normal_tail(x);
-  return n.cdf + x * (0.3989422804014327f * n.e);
+  const float cdf = 0.5f * (1.0f + erff(x * 0.7071067811865476f));
+  const float pdf = 0.3989422804014327f * __expf(-0.5f * x * x);
+  return cdf + x * pdf;
 }
 
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) {

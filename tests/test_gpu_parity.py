@@ -106,6 +106,42 @@ def test_gelu_mode_is_honoured_on_device():
         assert np.array_equal(got, want), f"mode {mode}: {np.count_nonzero(got != want)} of {len(want)} differ"
 
 
+@pytest.mark.parametrize("mode,std", [(0, 0.3), (0, 2.0), (1, 0.3), (1, 1.0)])
+def test_gelu_derivative_in_fp32_precision(mode, std):
+    """dP = (a b) GeLU'(P) with one product per element (exact in fp32): how often its bf16 result is not the one next to the
+    exact value says how large the fp32 evaluation's error is.  An error of rms relative size e moves a share of about
+    2 E|N(0, e)| v / ulp(v) of the values v over a rounding boundary; e must stay within half an fp32 ulp, 2^-24 (erff / tanhf and
+    the product: 4e-8; the estimate's own standard deviation here is 4-6 %)."""
+    import math
+    import torch
+    import paper_2504_06095_amd as N
+    _say(f"gelu derivative, mode {mode}, std {std}")
+    M, n, H = 8192, 4096, 8
+    g = torch.Generator("cuda").manual_seed(5)
+    P = torch.empty(M, n, device="cuda").normal_(0.0, std, generator=g).bfloat16()
+    dZ, B = torch.zeros(M, H, dtype=torch.bfloat16, device="cuda"), torch.zeros(n, H, dtype=torch.bfloat16, device="cuda")
+    dZ[:, 0] = torch.empty(M, device="cuda").uniform_(1.0, 2.0, generator=g).bfloat16()
+    B[:, 0] = torch.empty(n, device="cuda").uniform_(1.0, 2.0, generator=g).bfloat16()
+    dP, dX, dA, dB = torch.empty_like(P), torch.empty_like(dZ), torch.empty(n, H, device="cuda"), torch.empty(n, H, device="cuda")
+    N.ntp_mlp_shard_bwd(dZ, dZ, B, B, P, P, dP, dX, dA, dB, n, mode)
+    x = P.double()
+    if mode == 0:
+        d = 0.5 * torch.special.erfc(x / -math.sqrt(2.0)) + x * torch.exp(-0.5 * x * x) / math.sqrt(2.0 * math.pi)
+    else:
+        c = math.sqrt(2.0 / math.pi)
+        u = c * (x + 0.044715 * x ** 3)
+        s, r = torch.sigmoid(2.0 * u), torch.sigmoid(-2.0 * u)
+        d = s + 2.0 * x * s * r * c * (1.0 + 3.0 * 0.044715 * x * x)
+    v = (d * (dZ[:, :1].double() * B[:, 0].double())).abs()
+    ulp = torch.exp2(torch.floor(torch.log2(v)) - 7.0)
+    # near its zero the relative error of GeLU' says nothing; where it is 1 to within 2^-16, a b (16 bits) can lie on a boundary itself
+    keep = (d.abs() > 0.1) & ((d - 1.0).abs() > 2.0 ** -10)
+    wrong = ((dP.double().abs() - v).abs() > 0.5 * ulp) & keep
+    e = float(wrong.sum()) / float((v / ulp)[keep].sum()) / (2.0 * math.sqrt(2.0 / math.pi))
+    print(f"    {int(wrong.sum())} of {int(keep.sum())} on the far side of a boundary: rms error {e:.2e}", file=sys.stderr)
+    assert e <= 2.0 ** -24
+
+
 def test_mlp_gradient_accumulation():
     _say("mlp accumulate")
     case = MlpCase(192, 256, 600, 3, 2)
