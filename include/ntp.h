@@ -98,9 +98,9 @@ int ntp_device_info(const ntp_handle_t* h, int32_t* device, int32_t* compute_uni
 #define NTP_OPT_ATTN_PARTS 3         /* 1..16: parts per attention-core walk where the workspace holds them        */
 #define NTP_OPT_RESHARD_BLOCK 4      /* bytes per workgroup of the row-wise gather kernel                           */
 #define NTP_OPT_RESHARD_FLAT_BLOCK 5 /* bytes per workgroup of the flat-destination kernel                          */
-#define NTP_OPT_RESHARD_TABLE_BLOCK 6 /* bytes per block of the unit-table kernels                                  */
+#define NTP_OPT_RESHARD_TABLE_BLOCK 6 /* bytes per block of the unit-table and run-table kernels                    */
 #define NTP_OPT_RESHARD_NO_FLAT 7    /* 1: column-partitioned tensors never take the flat-destination kernel       */
-#define NTP_OPT_RESHARD_NO_TABLE 8   /* 1: plans never take the unit-table kernels                                 */
+#define NTP_OPT_RESHARD_NO_TABLE 8   /* 1: plans never take the unit-table and run-table kernels                   */
 #define NTP_OPT_GEMM_SCHEDULE 9      /* schedule of the ring kernel's K loop: 1 the default one everywhere, 2 the
                                         ping-pong one wherever it exists (8-wavefront tiles, persistent form)        */
 #define NTP_OPT_GEMM_WORKGROUPS 10   /* persistent GEMM launches use at most this many workgroups (rounded down to a
@@ -415,7 +415,7 @@ int ntp_comp_sync_plan(int64_t k, int32_t full_tp, int32_t reduced_tp, int32_t* 
  *   after the other, the source rank and the local unit in its shard.
  * ntp_reshard_plan_prepare: makes the plan ready to run on the CURRENT device.
  *   Plans of column-partitioned tensors of 4-byte elements and of row-partitioned
- *   tensors have a unit table (4 bytes per unit) that the copy kernels read
+ *   tensors have a table (4 bytes per unit, or 2 per unit and 16 per sub-shard) that the copy kernels read
  *   from device memory: this call allocates it (hipMalloc) and waits for its
  *   upload.  It is the only call of the library that allocates device memory or
  *   blocks; every plan needs it once before its first run (for plans without a
@@ -428,7 +428,7 @@ int ntp_comp_sync_plan(int64_t k, int32_t full_tp, int32_t reduced_tp, int32_t* 
  *   NTP_ERR_NOT_PREPARED, nothing is enqueued.  Column-partitioned tensors of
  *   4-byte elements whose source shards are all on this GPU, with dense 64-byte
  *   aligned destinations, and row-partitioned tensors of whole 16-byte rows with
- *   dense destinations go through the unit-table kernels; everything else is
+ *   dense destinations go through the unit-table and run-table kernels; everything else is
  *   copied sub-shard by sub-shard.
  * ntp_reshard_plan_destroy: frees the handle and its device table; no run of
  *   the plan may still be in flight.  NULL is accepted. */

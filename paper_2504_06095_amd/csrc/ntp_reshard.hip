@@ -23,6 +23,7 @@ namespace {
 
 constexpr int kMaxSegs = 56;          // per launch; the argument block stays below 4 KiB
 constexpr int kThreads = 256;         // 4 wavefronts
+constexpr int kWaves = kThreads / 64;
 constexpr int64_t kColChunk = 8192;   // bytes of a row handled by one workgroup
 constexpr int64_t kBlockBytes = 65536;  // target bytes per workgroup
 
@@ -611,6 +612,176 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
   }
 }
 
+// ---- the same through a run table, for rows of a few KB ------------------------------------------------------------------
+// A destination shard is a sequence of runs (units that follow each other in one source shard too); the plan keeps, in device
+// memory, the runs of every destination shard and for every destination unit the number of its run.  A workgroup copies both
+// tables into LDS (runs joined with this call's source pointers) and then takes one block of the shard, or walks over several
+// when the shard is very large.  Chunks that straddle a run boundary or a row end are put on a queue that each wavefront keeps in
+// LDS and are put together word by word when the loads of the others are done, with most lanes in use.
+// Where the line to the unit table lies (run_table_wanted): 170 layouts, fp32, both kernels in turn.  Rows up to 4.4 KB, tensors from 256 MB
+// on, layouts that are not copied in bands: this kernel takes 0.85 to 1.04 of the other's time, 0.95 on
+// average over 46 (13824 x 55296 from 67 to 60 ranks 1252 against 1440 us, 16384 x 53248 from 71 to 72 1399 against 1455).  Above 5 KB its
+// tables cost more per block than the unit table's lookups (14080 x 56320 from 33 to 25 ranks 1871 against 1357 us), in smaller tensors too
+// (4096 x 14336 from 48 to 47 191 against 178), and where lines go to several shards in turn the bands give more (up to 1.5 times).
+constexpr int kRunDsts = 16;               // destination shards per launch: few write streams at a time measured fastest
+constexpr uint32_t kQueueCap = 512;        // queued chunks per wavefront
+constexpr uint32_t kRunBlocksPerCu = 256;  // workgroups per compute unit and launch before they start to walk over several blocks
+constexpr int64_t kRunRowMax = 4480;       // bytes of a destination row: at most 1120 units and runs, 55 KB of LDS
+constexpr int64_t kRunTensorMin = int64_t(256) << 20;
+
+struct RunDev {      // one run of a destination shard (plan, device memory)
+  uint32_t begin, end;  // byte range in a destination row
+  uint32_t src_off;     // byte offset in a source row of what goes to `begin`
+  uint32_t rank;        // source rank
+};
+struct RunLds {      // the same, joined with the source pointers of this call
+  uint32_t begin, end, stride, pad_;
+  uint64_t adj;      // source base + src_off - begin: column c of row r is at adj + r * stride + c
+  uint64_t pad2_;
+};
+struct RunDst {
+  char* dst;
+  uint32_t idx_first, n_units;   // this shard's slice of the unit -> run numbers
+  uint32_t runs_first, n_runs;   // this shard's slice of the runs
+};
+struct RunBatch {
+  UnitSrc src[kMaxRanks];
+  RunDst dst[kRunDsts];
+  const RunDev* runs;
+  const uint16_t* run_of_unit;
+  uint32_t rows, unit_bytes, ndst, block_bytes;
+};
+
+__host__ __device__ inline uint32_t run_tables_bytes(uint32_t n_runs, uint32_t n_units) {
+  return n_runs * uint32_t(sizeof(RunLds)) + ((n_units * 2u + 15u) & ~15u);
+}
+__host__ __device__ inline uint32_t run_lds_bytes(uint32_t n_runs, uint32_t n_units) {
+  return run_tables_bytes(n_runs, n_units) + kWaves * kQueueCap * uint32_t(sizeof(uint2));
+}
+
+__global__ __launch_bounds__(kThreads) void reshard_runs_kernel(const RunBatch batch) {
+  extern __shared__ __align__(16) unsigned char run_lds[];
+  // consecutive workgroups take consecutive blocks of one destination shard
+  const uint32_t nslots = gridDim.x / batch.ndst;
+  const uint32_t di = blockIdx.x / nslots, slot = blockIdx.x - di * nslots;
+  const RunDst& dd = batch.dst[di];
+  const uint32_t ub = batch.unit_bytes, blk = batch.block_bytes;
+  const uint32_t W = dd.n_units * ub;
+  const int64_t T = int64_t(batch.rows) * W;
+  int64_t b0 = int64_t(slot) * blk;
+  if (b0 >= T) return;  // the whole workgroup leaves: nothing left for it in this shard
+  RunLds* const runs = reinterpret_cast<RunLds*>(run_lds);
+  uint16_t* const run_of = reinterpret_cast<uint16_t*>(run_lds + dd.n_runs * sizeof(RunLds));
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+  uint2* const queue = reinterpret_cast<uint2*>(run_lds + run_tables_bytes(dd.n_runs, dd.n_units)) + wave * kQueueCap;
+  for (uint32_t r = threadIdx.x; r < dd.n_runs; r += kThreads) {
+    const RunDev rd = batch.runs[dd.runs_first + r];
+    const UnitSrc sr = batch.src[rd.rank];
+    RunLds o;
+    o.begin = rd.begin;
+    o.end = rd.end;
+    o.stride = uint32_t(sr.stride);
+    o.pad_ = 0;
+    o.adj = uint64_t(reinterpret_cast<uintptr_t>(sr.base)) + rd.src_off - rd.begin;
+    o.pad2_ = 0;
+    runs[r] = o;
+  }
+  for (uint32_t j = threadIdx.x; j < dd.n_units; j += kThreads) run_of[j] = batch.run_of_unit[dd.idx_first + j];
+  __syncthreads();  // the only workgroup-wide wait: from here on the wavefronts run on their own
+
+  // W and the unit size are at least 4: the multiply-high division needs no special case
+  const uint32_t magic_w = div_magic(W), magic_u = div_magic(ub);
+  const char* const dummy = reinterpret_cast<const char*>(batch.runs);  // 16 readable bytes for lanes with nothing to load
+  // queued chunks of this wavefront, word by word
+  uint32_t nq = 0;  // chunks on this wavefront's queue (the same value in all lanes)
+  auto flush = [&]() {
+    // what other lanes have queued becomes visible
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (uint32_t i = lane; i < nq; i += 64) {
+      const uint2 e = queue[i];  // {row, byte column} of the chunk's first word
+      const int64_t at = int64_t(e.x) * W + e.y;
+      const uint32_t len = uint32_t(std::min<int64_t>(16, T - at));
+      u32x4 v;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const bool have = uint32_t(w) * 4 < len;
+        const uint32_t xw = e.y + (have ? 4u * w : 0u);
+        const uint32_t rw = __umulhi(xw, magic_w), cw = xw - rw * W;  // rows may be shorter than a chunk
+        const RunLds rn = runs[run_of[__umulhi(cw, magic_u)]];
+        v[w] = *reinterpret_cast<const uint32_t*>(rn.adj + (uint64_t(e.x + rw) * rn.stride + cw));
+      }
+      char* dp = dd.dst + at;
+      if (len == 16) {
+        __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dp));
+      } else {
+#pragma unroll
+        for (int w = 0; w < 3; ++w)
+          if (uint32_t(w) * 4 < len) reinterpret_cast<uint32_t*>(dp)[w] = v[w];
+      }
+    }
+    // the entries have been read before the queue is filled again
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    nq = 0;
+  };
+
+  // this workgroup's blocks: slot, slot + nslots, ...; (row0, c0) = position of the block's first byte
+  const int64_t step = int64_t(nslots) * blk;
+  const uint32_t step_rows = uint32_t(step / W), step_cols = uint32_t(step - int64_t(step_rows) * W);
+  uint32_t row0 = uint32_t(b0 / W);
+  uint32_t c0 = uint32_t(b0 - int64_t(row0) * W);
+  for (; b0 < T; b0 += step) {
+    const uint32_t nb = uint32_t(std::min<int64_t>(blk, T - b0));
+    char* __restrict__ d = dd.dst + b0;
+    const uint32_t nchunks = (nb + 15) >> 4;
+    // the loop bounds are the same for all lanes of a wavefront: every lane takes part in flush()
+    for (uint32_t wbase = wave << 6; wbase < nchunks; wbase += kThreads * kUnroll) {
+      const uint32_t base = wbase + lane;
+      u32x4 v[kUnroll];
+      bool ok[kUnroll], slow[kUnroll];
+      uint32_t rowq[kUnroll], colq[kUnroll];
+      // look every chunk up and start its load; lanes with no chunk, or with a chunk for the slow way,
+      // go through the same steps on chunk 0 and load the dummy bytes (no branches, four loads in flight)
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const uint32_t k = base + u * kThreads;
+        const bool valid = k < nchunks;
+        const uint32_t kb = valid ? k << 4 : 0u;
+        const uint32_t x = c0 + kb;
+        const uint32_t rr = __umulhi(x, magic_w), col = x - rr * W;
+        const RunLds rn = runs[run_of[__umulhi(col, magic_u)]];
+        ok[u] = valid && kb + 16u <= nb && col + 16u <= rn.end;
+        slow[u] = valid && !ok[u];
+        rowq[u] = row0 + rr;
+        colq[u] = col;
+        const char* p = reinterpret_cast<const char*>(rn.adj + (uint64_t(row0 + rr) * rn.stride + col));
+        v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_a4*>(ok[u] ? p : dummy));
+      }
+      // the chunks that need the slow way go on the queue, in lane order
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const uint64_t m = __ballot(slow[u]);
+        if (slow[u]) queue[nq + __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u))] = make_uint2(rowq[u], colq[u]);
+        nq += uint32_t(__popcll(m));
+      }
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u)
+        if (ok[u]) __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4*>(d + ((base + u * kThreads) << 4)));
+      // one pass of the loop queues at most 64 * kUnroll chunks per wavefront
+      if (nq > kQueueCap - 64 * kUnroll) flush();
+    }
+    row0 += step_rows;
+    c0 += step_cols;
+    if (c0 >= W) {
+      c0 -= W;
+      ++row0;
+    }
+  }
+  flush();
+}
+
 // Row-partitioned, rows a multiple of 16 bytes on 16-byte aligned addresses: every chunk lies in one unit.  A source shard
 // that is not on this GPU leaves its units' rows untouched.  Bound by HBM: 6.1 TB/s.  One launch for a whole tensor, where the dense
 // kernel takes one per 100 runs (a run is one row where several ranks are unloaded onto one): 4608 rows between TP 7 and TP 5,
@@ -1060,10 +1231,40 @@ struct ntp_reshard_plan {
   std::vector<ntp_unit_source_t> table;       // per destination unit, destination shards one after the other
   std::vector<int64_t> dst_first;             // first table entry of each destination shard
   std::vector<uint32_t> unit_src;             // `table` as the table kernels read it (empty: they cannot take this plan)
+  bool large = false;                         // column-partitioned, kRunTensorMin bytes and more
   bool interleaved = false;                   // column-partitioned, neighbouring source units often go to different shards
-  void* dev_table = nullptr;                  // `unit_src` on device `dev`, made by ntp_reshard_plan_prepare
+  // instead of `unit_src` where the run-table kernel takes the plan (run_table_wanted)
+  std::vector<RunDev> runs;                   // runs of all destination shards, one shard after the other
+  std::vector<int64_t> runs_first;            // first run of each destination shard
+  std::vector<uint16_t> run_of_unit;          // per destination unit (indexed like `table`): run number in its shard
+  void* dev_table = nullptr;                  // `unit_src`, or `runs` then `run_of_unit`, on device `dev`, made by ntp_reshard_plan_prepare
   int dev = -1;                               // device the plan was prepared on (-1: not prepared)
 };
+
+namespace {
+
+// Whether a column-partitioned plan of 4-byte elements goes through the run table (see reshard_runs_kernel).
+bool run_table_wanted(const ntp_reshard_plan* p) {
+  const ntp_tensor_spec_t& sp = p->spec;
+  const int64_t widest = *std::max_element(p->dst_units.begin(), p->dst_units.end()) * sp.unit * 4;
+  return p->large && !p->interleaved && widest <= kRunRowMax;
+}
+
+void build_run_table(ntp_reshard_plan* p) {
+  const uint32_t ub = uint32_t(p->spec.unit) * 4u;
+  p->runs_first.assign(size_t(p->dst_tp) + 1, 0);
+  p->run_of_unit.resize(p->table.size());
+  int32_t cur = 0;
+  for (const ntp_segment_t& g : p->segs) {
+    while (cur < g.dst_rank) p->runs_first[size_t(++cur)] = int64_t(p->runs.size());
+    const uint16_t number = uint16_t(int64_t(p->runs.size()) - p->runs_first[size_t(cur)]);
+    p->runs.push_back(RunDev{uint32_t(g.dst_unit) * ub, uint32_t(g.dst_unit + g.units) * ub, uint32_t(g.src_unit) * ub, uint32_t(g.src_rank)});
+    std::fill_n(p->run_of_unit.begin() + p->dst_first[size_t(g.dst_rank)] + g.dst_unit, g.units, number);
+  }
+  while (cur < p->dst_tp) p->runs_first[size_t(++cur)] = int64_t(p->runs.size());
+}
+
+}  // namespace
 
 extern "C" int ntp_reshard_plan_create(const ntp_tensor_spec_t* spec, int64_t map_len, int32_t src_tp,
                                        const int32_t* src_rank_of_unit, int32_t dst_tp,
@@ -1093,13 +1294,10 @@ extern "C" int ntp_reshard_plan_create(const ntp_tensor_spec_t* spec, int64_t ma
     for (int64_t i = 0; i < g.units; ++i)
       p->table[size_t(p->dst_first[g.dst_rank] + g.dst_unit + i)] = ntp_unit_source_t{g.src_rank, int32_t(g.src_unit + i)};
   }
-  if (n_units > 0 && n_units <= (int64_t(1) << kUnitBits) && src_tp <= kMaxRanks && (spec->partition_dim == 0 || spec->elem_size == 4)) {
-    p->unit_src.assign(size_t(n_units) + 3, 0);  // a chunk's four entries are read with one load
-    for (int64_t u = 0; u < n_units; ++u)
-      p->unit_src[size_t(u)] = uint32_t(p->table[size_t(u)].src_rank) << kUnitBits | uint32_t(p->table[size_t(u)].src_unit);
-  }
-  if (spec->partition_dim == 1) {
-    // how many times a 128-byte line of a source row changes its destination shard: from one time in four on, bands
+  if (spec->partition_dim == 1 && n_units > 0) {
+    // how many times a 128-byte line of a source row changes its destination shard.  More than once: bands; in tensors below 256 MiB from
+    // once in four on (3200 x 12800 from 40 to 33 ranks 156 us whole, 144 in bands; 16384 x 65536 from 71 to 55 1950 and 2053, 15104 x
+    // 60416 from 64 to 52 1653 and 1776)
     std::vector<int32_t> dst_of(size_t(n_units), 0);
     std::vector<int64_t> first(size_t(src_tp) + 1, 0);
     for (int32_t r = 0; r < src_tp; ++r) first[size_t(r) + 1] = first[size_t(r)] + p->src_units[size_t(r)];
@@ -1107,7 +1305,19 @@ extern "C" int ntp_reshard_plan_create(const ntp_tensor_spec_t* spec, int64_t ma
       std::fill_n(dst_of.begin() + first[size_t(g.src_rank)] + g.src_unit, g.units, g.dst_rank);
     int64_t turns = 0;
     for (int64_t u = 1; u < n_units; ++u) turns += dst_of[size_t(u)] != dst_of[size_t(u) - 1];
-    p->interleaved = turns * 4 * 128 > n_units * spec->unit * spec->elem_size;
+    const int64_t row_bytes = n_units * spec->unit * spec->elem_size;
+    p->large = spec->rows >= (kRunTensorMin + row_bytes - 1) / row_bytes;
+    p->interleaved = turns * 128 * (p->large ? 1 : 4) > row_bytes;
+  }
+  if (n_units > 0 && n_units <= (int64_t(1) << kUnitBits) && src_tp <= kMaxRanks && (spec->partition_dim == 0 || spec->elem_size == 4)) {
+    if (spec->partition_dim == 1 && run_table_wanted(p)) {
+      build_run_table(p);
+      *plan = p;
+      return NTP_OK;
+    }
+    p->unit_src.assign(size_t(n_units) + 3, 0);  // a chunk's four entries are read with one load
+    for (int64_t u = 0; u < n_units; ++u)
+      p->unit_src[size_t(u)] = uint32_t(p->table[size_t(u)].src_rank) << kUnitBits | uint32_t(p->table[size_t(u)].src_unit);
   }
   *plan = p;
   return NTP_OK;
@@ -1182,15 +1392,59 @@ bool table_path_ok(const ntp_handle* h, const ntp_reshard_plan* p, const void* c
 
 // The plan's table goes to the current device (allocates and waits for the copy).
 int upload_table(ntp_reshard_plan_t* plan) {
-  const size_t bytes = plan->unit_src.size() * sizeof(uint32_t);
-  if (hipMalloc(&plan->dev_table, bytes) != hipSuccess) {
+  const size_t runs_bytes = plan->runs.size() * sizeof(RunDev), idx_bytes = plan->run_of_unit.size() * sizeof(uint16_t);
+  const size_t units_bytes = plan->unit_src.size() * sizeof(uint32_t);
+  if (hipMalloc(&plan->dev_table, runs_bytes + idx_bytes + units_bytes) != hipSuccess) {
     plan->dev_table = nullptr;
     return NTP_ERR_LAUNCH;
   }
-  if (hipMemcpy(plan->dev_table, plan->unit_src.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
+  char* const at = static_cast<char*>(plan->dev_table);
+  auto put = [](char* to, const void* from, size_t n) { return n == 0 || hipMemcpy(to, from, n, hipMemcpyHostToDevice) == hipSuccess; };
+  if (!put(at, plan->runs.data(), runs_bytes) || !put(at + runs_bytes, plan->run_of_unit.data(), idx_bytes) ||
+      !put(at, plan->unit_src.data(), units_bytes)) {  // (a plan has one of the two tables)
     (void)hipFree(plan->dev_table);
     plan->dev_table = nullptr;
     return NTP_ERR_LAUNCH;
+  }
+  return NTP_OK;
+}
+
+// The launches of a checked call whose plan has a run table.
+int run_by_runs(ntp_handle* h, const ntp_reshard_plan* plan, const void* const* src_shards, const int64_t* src_ld, void* const* dst_shards,
+                int64_t block, void* stream) {
+  const ntp_tensor_spec_t& sp = plan->spec;
+  RunBatch batch{};
+  batch.runs = static_cast<const RunDev*>(plan->dev_table);
+  batch.run_of_unit = reinterpret_cast<const uint16_t*>(static_cast<const char*>(plan->dev_table) + plan->runs.size() * sizeof(RunDev));
+  batch.rows = uint32_t(sp.rows);
+  batch.unit_bytes = uint32_t(sp.unit) * 4u;
+  batch.block_bytes = uint32_t(block);
+  for (int32_t r = 0; r < plan->src_tp; ++r)
+    batch.src[r] = UnitSrc{static_cast<const char*>(src_shards[r]), uint64_t(src_ld[r]) * 4u};
+  for (int32_t s = 0; s < plan->dst_tp;) {
+    batch.ndst = 0;
+    int64_t nblk = 0;
+    uint32_t lds = 0;
+    double bytes = 0.0;
+    for (; s < plan->dst_tp && batch.ndst < uint32_t(kRunDsts); ++s) {
+      if (plan->dst_units[s] == 0 || !dst_shards[s]) continue;
+      const int64_t total = sp.rows * plan->dst_units[s] * sp.unit * 4;
+      const uint32_t n_runs = uint32_t(plan->runs_first[s + 1] - plan->runs_first[s]);
+      batch.dst[batch.ndst++] = RunDst{static_cast<char*>(dst_shards[s]), uint32_t(plan->dst_first[s]), uint32_t(plan->dst_units[s]),
+                                       uint32_t(plan->runs_first[s]), n_runs};
+      nblk = std::max(nblk, (total + block - 1) / block);
+      lds = std::max(lds, run_lds_bytes(n_runs, uint32_t(plan->dst_units[s])));
+      bytes += 2.0 * double(total);
+    }
+    if (batch.ndst == 0) break;
+    // workgroups per destination shard: one per block, or fewer that walk over several blocks each when
+    // the shards are very large (the tables are copied into LDS once per workgroup)
+    const int64_t slots = std::max<int64_t>(1, std::min<int64_t>(nblk, (int64_t(h->compute_units) * int64_t(kRunBlocksPerCu) + batch.ndst - 1) / batch.ndst));
+    if (ntp::timing_on(h)) ntp::timing_begin(h, stream, "reshard_runs", 0.0, bytes);
+    hipLaunchKernelGGL(reshard_runs_kernel, dim3(uint32_t(slots) * batch.ndst), dim3(kThreads), lds, static_cast<hipStream_t>(stream), batch);
+    const bool ok = hipGetLastError() == hipSuccess;
+    ntp::timing_end(h, stream);
+    if (!ok) return NTP_ERR_LAUNCH;
   }
   return NTP_OK;
 }
@@ -1205,7 +1459,7 @@ extern "C" int ntp_reshard_plan_prepare(ntp_reshard_plan_t* plan) {
     return NTP_ERR_NO_DEVICE;
   }
   if (plan->dev >= 0) return cur == plan->dev ? NTP_OK : NTP_ERR_INVALID_ARG;  // a plan lives on one device
-  if (!plan->unit_src.empty()) {
+  if (!plan->unit_src.empty() || !plan->runs.empty()) {
     const int st = upload_table(plan);
     if (st != NTP_OK) return st;
   }
@@ -1225,6 +1479,7 @@ extern "C" int ntp_reshard_plan_run(ntp_handle_t* h, ntp_reshard_plan_t* plan, c
   if (!table_path_ok(h, plan, src_shards, src_ld, dst_shards, dst_ld, block))
     return ntp::reshard_launch(h, &plan->spec, plan->segs, plan->src_units, plan->dst_units, src_shards, src_ld, dst_shards,
                                dst_ld, stream);
+  if (!plan->runs.empty()) return run_by_runs(h, plan, src_shards, src_ld, dst_shards, block, stream);
 
   const ntp_tensor_spec_t& sp = plan->spec;
   const bool by_rows = sp.partition_dim == 0;
@@ -1238,10 +1493,12 @@ extern "C" int ntp_reshard_plan_run(ntp_handle_t* h, ntp_reshard_plan_t* plan, c
   for (int32_t r = 0; r < plan->src_tp; ++r)
     batch.src[r] = UnitSrc{static_cast<const char*>(src_shards[r]), uint64_t(src_ld[r]) * uint64_t(sp.elem_size)};
   const int64_t per_unit = int64_t(sp.unit) * (by_rows ? sp.cols : sp.rows) * sp.elem_size;  // bytes
+  // columns that are not copied in bands: few write streams at a time (16384 x 53248 from 31 to 32 ranks 880 us in one launch, 854 in two)
+  const int32_t per_launch = by_rows || plan->interleaved ? kMaxRanks : kRunDsts;
   for (int32_t s = 0; s < plan->dst_tp;) {
     batch.ndst = 0;
     int64_t total = 0;
-    for (; s < plan->dst_tp && batch.ndst < kMaxRanks; ++s) {
+    for (; s < plan->dst_tp && batch.ndst < per_launch; ++s) {
       if (plan->dst_units[s] == 0 || !dst_shards[s]) continue;
       batch.dst[batch.ndst++] = TableDst{static_cast<char*>(dst_shards[s]), uint32_t(plan->dst_first[s]), uint32_t(plan->dst_units[s]), 0, 0};
       total += plan->dst_units[s] * per_unit;

@@ -264,3 +264,40 @@ def test_mlp_shard_on_the_comp_layout_sums_to_the_layer():
     for s in range(tr):
         off, w = O.shard_plan(n, tr, s)
         assert Hh.rel_err(dst[s].cpu().numpy().astype(np.float64), dBfull[off: off + w]) <= Hh.TOL, s
+
+
+# the run-table kernel (rows of at most 4480 bytes, tensors of 256 MiB and more, few lines shared by destination shards) and the shapes next to
+# it, which the unit table takes: rows that are no multiple of a chunk, shards that end inside a chunk and inside a block, runs of one unit,
+# units of 3 elements, walks over several blocks (many rows), destination shards in more than one launch (more than 16), padded sources
+@pytest.mark.parametrize("rows,k,unit,t,tr,back,pad,kernel", [
+    (16411, 4099, 1, 5, 4, False, 0, "runs"), (16411, 4099, 1, 5, 4, True, 3, "runs"), (2051, 33001, 1, 60, 54, False, 0, "runs"),
+    (19001, 1201, 3, 5, 4, False, 1, "runs"), (60000, 1120, 1, 2, 1, False, 0, "runs"), (59918, 1120, 1, 2, 1, False, 0, "table"),
+    (60001, 1121, 1, 2, 1, False, 0, "table"), (8192, 16384, 1, 23, 22, True, 0, "runs"), (5000, 20000, 1, 44, 30, True, 0, "table"),
+    (4000000, 19, 1, 3, 2, False, 0, "table")])
+def test_plan_run_large_column_tensors(rows, k, unit, t, tr, back, pad, kernel):
+    import torch
+    import paper_2504_06095_amd as N
+    _say(f"large column tensor rows={rows} k={k} unit={unit} t={t} t'={tr} back={back} pad={pad}")
+    comp, sync = O.comp_sync_plan(k, t, tr)
+    smap, a, dmap, b = (sync, tr, comp, t) if back else (comp, t, sync, tr)
+    G = torch.arange(rows * k * unit, dtype=torch.int32, device="cuda").view(rows, k * unit)
+    cols = lambda m, r: [u * unit + e for u in range(k) if m[u] == r for e in range(unit)]  # noqa: E731
+    src = []
+    for r in range(a):
+        c = cols(smap, r)
+        s = torch.full((rows, len(c) + pad), -7, dtype=torch.int32, device="cuda")[:, :len(c)]
+        s.copy_(G[:, c])
+        src.append(s)
+    dst = [torch.full((rows * len(cols(dmap, s)) + 16,), -1, dtype=torch.int32, device="cuda") for s in range(b)]
+    views = [d[:-16].view(rows, -1) for d in dst]
+    plan = N.ntp_reshard_plan_create(N.tensor_spec(rows, k * unit, 1, unit, 4), a, smap, b, dmap)
+    plan.ntp_reshard_plan_prepare()
+    N.ntp_kernel_timing_enable(1)
+    N.ntp_kernel_timing_read()
+    plan.ntp_reshard_plan_run(src, views)
+    names = {r["name"] for r in N.ntp_kernel_timing_read()}
+    N.ntp_kernel_timing_enable(0)
+    plan.destroy()
+    assert names == {"reshard_" + kernel}, names
+    for s in range(b):
+        assert torch.equal(views[s], G[:, cols(dmap, s)]) and (dst[s][-16:] == -1).all(), f"dst rank {s}"
