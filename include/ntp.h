@@ -88,7 +88,12 @@ int ntp_device_info(const ntp_handle_t* h, int32_t* device, int32_t* compute_uni
 /* Tuning overrides of one handle.  Every option is 0 by default = the library's
  * own choice.  They exist so that tests and tuning runs can reach every kernel
  * variant at any size; a forced variant computes the same result to within fp32
- * summation order (bit-identical for the reshard options).
+ * summation order (bit-identical for the reshard options).  GEMMs with few output
+ * tiles run on a kernel of their own (deep-pipelined; its K axis is cut into up to 16
+ * chunks where a workspace is set), and the gradient GEMMs of a small backward call may
+ * share one launch of it.  NTP_OPT_GEMM_TILE, _SPLIT, _SCHEDULE and _WORKGROUPS other
+ * than 0 are about the other kernels and switch both off; NTP_OPT_GEMM_NO_RING_TAIL does
+ * so for row-parallel GEMMs with K % 64 != 0.
  * Errors: unknown option or value out of range -> INVALID_ARG. */
 #define NTP_OPT_GEMM_TILE 0          /* 1: the small generic kernel; 2 + i: ring tile shape i in the order 256x256,
                                         256x224, 224x256, 256x192, 192x256, 256x128, 128x256, 128x128 (4 wavefronts),

@@ -229,7 +229,10 @@ SplitChoice plan_gemm(const ntp_handle* h, int64_t ws_bytes, const GemmArgs& g, 
                       int64_t ldw, bool deep_ok) {
   SplitChoice sc{choose_variant(h, g, ring_ok, layout), 1, 0, kNotDeep};
   if (split_ok && int64_t(g.M) * g.N >= 128 * 128 * 8) sc = choose_split(h, ws_bytes, g.M, g.n_store, g.K, layout, sc.tile, ldw);
-  if (deep_ok && sc.tile >= 0 && !h->opt[NTP_OPT_GEMM_TILE] && !h->opt[NTP_OPT_GEMM_SPLIT] && !h->opt[NTP_OPT_GEMM_SCHEDULE])
+  // (options that ask for a ring tile, a cut, a schedule, a cap on the persistent grid or a K tail through registers mean the ring kernels)
+  const bool ring_asked = h->opt[NTP_OPT_GEMM_TILE] || h->opt[NTP_OPT_GEMM_SPLIT] || h->opt[NTP_OPT_GEMM_SCHEDULE] || h->opt[NTP_OPT_GEMM_WORKGROUPS] ||
+                          (h->opt[NTP_OPT_GEMM_NO_RING_TAIL] && layout == 1 && g.K % 64 != 0);
+  if (deep_ok && sc.tile >= 0 && !ring_asked)
     sc = choose_deep(h, split_ok ? ws_bytes : 0, layout, g.M, g.n_store, g.K, ldw, sc);
   return sc;
 }

@@ -93,3 +93,16 @@ def test_schedule_choice_and_override():
     assert Bd.ntp_gemm_choice(2, 5376, 12288, 2048, handle=h)["pingpong"] == 0  # 256 x 256 weight-gradient tile: non-persistent
     assert Bd.lib().ntp_set_option(h.ptr, Bd.NTP_OPT_GEMM_SCHEDULE, 3) == Bd.NTP_ERR_INVALID_ARG
     Bd.ntp_destroy(h)
+
+
+def test_options_of_the_ring_kernels_reach_them_at_few_tiles():
+    """A cap on the persistent grid and a K tail through registers are about the ring kernels: problems with few tiles run on those then."""
+    h = Bd.ntp_create()
+    small, tail, whole = (0, 512, 586, 1024), (1, 777, 1096, 1001), (1, 777, 1096, 1024)
+    assert not any(Bd.ntp_gemm_choice(*s, handle=h)["persistent"] for s in (small, tail, whole))
+    Bd.ntp_set_option(Bd.NTP_OPT_GEMM_WORKGROUPS, 8, handle=h)
+    assert all(Bd.ntp_gemm_choice(*s, handle=h)["persistent"] for s in (small, tail, whole))
+    Bd.ntp_set_option(Bd.NTP_OPT_GEMM_WORKGROUPS, 0, handle=h)
+    Bd.ntp_set_option(Bd.NTP_OPT_GEMM_NO_RING_TAIL, 1, handle=h)
+    assert [Bd.ntp_gemm_choice(*s, handle=h)["persistent"] for s in (small, tail, whole)] == [0, 1, 0]
+    Bd.ntp_destroy(h)
