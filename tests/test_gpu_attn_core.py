@@ -231,6 +231,28 @@ def test_attn_core_bwd_one_or_two_launches(workspace, opts, n_q, n_kv, tp, rank,
     assert names == (["attn_core_bwd_both" + cut] if launches == 2 else ["attn_core_bwd_dq" + cut, "attn_core_bwd_dkv" + cut]), names
 
 
+# 64-row tiles: 1728 / 576 workgroups of the two kinds in pairs of 256 and what is left over (causal; full 3456 / 1152), 1728 / 576 over eight tiles
+# each (causal 864 / 288), and fewer than one chunk
+@pytest.mark.parametrize("launches", [0, 1, 2], ids=["auto", "two_launches", "one_launch"])
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+@pytest.mark.parametrize("n_q,n_kv,tp,rank,n_seq,S,pad", [(24, 8, 1, 0, 36, 200, 0), (24, 8, 1, 0, 9, 449, 8), (15, 5, 2, 1, 2, 449, 0)])
+def test_attn_core_bwd_head_dimension_64_launches(opts, n_q, n_kv, tp, rank, n_seq, S, pad, causal, launches):
+    """Head dimension 64, walks not cut (no workspace): the separate kernels, and the launch for both kinds of workgroup that the library
+    takes by itself, with grouped KV heads and ragged lengths."""
+    import paper_2504_06095_amd as N
+    _say(f"attn core bwd d=64, launches option {launches}: n_q={n_q} n_kv={n_kv} n_seq={n_seq} S={S} pad={pad} causal={causal}")
+    opts(K.NTP_OPT_ATTN_BWD_LAUNCHES, launches)
+    N.ntp_kernel_timing_enable(1)
+    N.ntp_kernel_timing_read()
+    try:
+        _bwd_case(n_q, n_kv, tp, rank, 64, n_seq, S, causal, seed=37, pad=pad)
+        names = [n for n in _core_names() if "bwd" in n]
+    finally:
+        N.ntp_kernel_timing_enable(0)
+        N.ntp_kernel_timing_read()
+    assert names == (["attn_core_bwd_dq", "attn_core_bwd_dkv"] if launches == 1 else ["attn_core_bwd_both"]), names
+
+
 def test_attn_core_bwd_one_launch_needs_room_for_both_kernels_parts(opts):
     """With a workspace that holds either kernel's parts but not both, the cut kernels go out as two launches."""
     import torch

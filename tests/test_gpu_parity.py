@@ -228,12 +228,15 @@ def test_mlp_every_tile_variant_ragged(variant, opts):
 
 
 @pytest.mark.parametrize("ring_tail", ["1", "0"], ids=["tail through the ring", "tail through registers"])
-@pytest.mark.parametrize("variant", ["auto"] + RING_TILES)
+@pytest.mark.parametrize("variant", ["auto", "auto ring"] + RING_TILES)
 def test_mlp_rows_padded_to_64_every_tile_variant(variant, ring_tail, opts):
     """P, Y, dP with leading dimensions that reach the next multiple of 64: their pad columns are zeroed that far
-    and the row-parallel GEMMs (fc2, dX: K = n_r = 1001 = 15 K tiles + 41) take the K tail through the ring."""
+    and the row-parallel GEMMs (fc2, dX: K = n_r = 1001 = 15 K tiles + 41) take the K tail through the ring.  (With so few tiles the
+    library's own choice is the deep-pipelined kernel, whose ring takes every tail, unless one through registers is asked for.)"""
     _say(f"mlp rows padded to 64, variant {variant}, ring tail {ring_tail}")
-    if variant != "auto":
+    if variant == "auto ring":
+        opts(K.NTP_OPT_GEMM_SCHEDULE, 1)
+    elif variant != "auto":
         opts(K.NTP_OPT_GEMM_TILE, variant)
     opts(K.NTP_OPT_GEMM_NO_RING_TAIL, 1 - int(ring_tail))
     case = MlpCase(777, 1096, 2003, 2, 1)
@@ -244,12 +247,19 @@ def test_mlp_rows_padded_to_64_every_tile_variant(variant, ring_tail, opts):
         assert (raw[name][:, 1001:1024].float().cpu().numpy() == 0).all(), name
 
 
-def test_mlp_ring_tail_needs_no_finite_values_past_the_weights():
+@pytest.mark.parametrize("tile,schedule,kernel", [("auto", 0, "128x128w8d"), ("auto", 1, "128x128w8"), ("256x256", 1, "256x256"), ("256x192", 2, "256x192pp"),
+                                                  ("128x128", 0, "128x128"), ("224x256", 2, "224x256pp")])
+def test_mlp_ring_tail_needs_no_finite_values_past_the_weights(tile, schedule, kernel, opts):
     """The weight shard B_i [n_r x H] ends exactly where its allocation ends: what the K tail tile would read past
     it comes back as zeros from the load's range check, not from memory.  NaN-filled neighbours must not leak in."""
     import torch
     import paper_2504_06095_amd as N
-    _say("mlp ring tail: weights at the end of a NaN-filled arena")
+    _say(f"mlp ring tail: weights at the end of a NaN-filled arena, tile {tile} schedule {schedule}")
+    if tile != "auto":
+        opts(K.NTP_OPT_GEMM_TILE, tile)
+    opts(K.NTP_OPT_GEMM_SCHEDULE, schedule)
+    N.ntp_kernel_timing_enable(1)
+    N.ntp_kernel_timing_read()
     case = MlpCase(520, 1032, 1500, 1, 0, seed=9, tag="arena")  # n_r = 1500 = 23 K tiles + 28
     from tests.helpers import dev_bf16_to_f64, to_dev_bf16
     M, H, n_r, ld = case.M, case.H, case.n_r, 1536
@@ -264,7 +274,10 @@ def test_mlp_ring_tail_needs_no_finite_values_past_the_weights():
     dA, dB = torch.zeros(n_r, H, device="cuda"), torch.zeros(n_r, H, device="cuda")
     N.ntp_mlp_shard_fwd(X, At, B, P[:, :n_r], Y[:, :n_r], Z, n_r, 0)
     N.ntp_mlp_shard_bwd(dZ, X, At, B, P[:, :n_r], Y[:, :n_r], dP[:, :n_r], dX, dA, dB, n_r, 0, False)
-    torch.cuda.synchronize()
+    names = [r["name"] for r in N.ntp_kernel_timing_read()]
+    N.ntp_kernel_timing_enable(0)
+    ran = [n for n in names if n.startswith("gemm_nn") or n.startswith("gemm_group")]  # fc2 and dX
+    assert len(ran) == 2 and all(n in ("gemm_nn_bf16_" + kernel, "gemm_group_" + kernel) for n in ran), names
     want = case.oracle()
     got = dict(Z=dev_bf16_to_f64(Z), dX=dev_bf16_to_f64(dX))
     _check_all(got, want, ["Z", "dX"])
