@@ -282,7 +282,7 @@ struct Prepared {
   bool empty;    // no output element: nothing else is filled in
   bool nothing;  // no output that has a destination
   void* ws_ptr;
-  int64_t ldw, k8;
+  int64_t ldw;
 };
 
 int prepare(ntp_handle* h, const GemmDesc& d, Prepared* out) {
@@ -391,18 +391,17 @@ int prepare(ntp_handle* h, const GemmDesc& d, Prepared* out) {
   void* const ws_ptr = d.ws_override ? d.ws_override : h->workspace;
   const int64_t ws_bytes = d.ws_override ? d.ws_override_bytes : (h->workspace ? h->workspace_bytes : 0);
   // deep-pipelined kernel: 32-bit byte offsets with room for one that lies past every operand, and a K tail of whole chunks
-  const int64_t k8 = (d.K + 7) / 8 * 8;
   const bool deep_ok = ring_ok && a_rows * d.lda * 2 < (int64_t(1) << 31) && b_rows * d.ldb * 2 < (int64_t(1) << 31) &&
                        (!d.a_kc || d.K % 8 == 0 || (d.a_k_pad_8 && !d.b_kc));
   const SplitChoice sc = plan_gemm(h, ws_ptr ? ws_bytes : 0, g, layout, ring_ok, split_ok, ldw, deep_ok);
-  *out = Prepared{g, sc, layout, ring_ok, false, to_segs && g.n_segs == 0, ws_ptr, ldw, k8};
+  *out = Prepared{g, sc, layout, ring_ok, false, to_segs && g.n_segs == 0, ws_ptr, ldw};
   return NTP_OK;
 }
 
 // The arguments of a deep-pipelined launch without a cut K axis.
 GemmArgs deep_args(const Prepared& p, const GemmDesc& d) {
   GemmArgs g = p.g;
-  g.a_extent = uint32_t(operand_extent_bytes(d.a_kc, d.M, d.a_kc ? p.k8 : d.K, d.lda, false));
+  g.a_extent = uint32_t(deep_extent_bytes(d.a_kc, d.M, d.K, d.lda));
   g.k_splits = 1;
   g.k_chunk = int32_t((d.K + 63) / 64 * 64);
   return g;
@@ -418,7 +417,7 @@ int launch_prepared(ntp_handle* h, const GemmDesc& d, const Prepared& p, void* s
   const SplitChoice sc = p.sc;
   const int layout = p.layout;
   const bool ring_ok = p.ring_ok;
-  const int64_t n_store = g.n_store, ldw = p.ldw, k8 = p.k8;
+  const int64_t n_store = g.n_store, ldw = p.ldw;
   void* const ws_ptr = p.ws_ptr;
   const int variant = sc.tile;
   if (ntp::timing_on(h)) {
@@ -443,7 +442,7 @@ int launch_prepared(ntp_handle* h, const GemmDesc& d, const Prepared& p, void* s
   } else if (sc.splits > 1) {
     GemmArgs gp = g;  // the partial-sum launch: fp32 to the workspace, no row segments
     gp.ring_tail = 0;
-    gp.a_extent = uint32_t(operand_extent_bytes(d.a_kc, d.M, d.a_kc && sc.deep ? k8 : d.K, d.lda, false));
+    gp.a_extent = uint32_t(sc.deep ? deep_extent_bytes(d.a_kc, d.M, d.K, d.lda) : operand_extent_bytes(d.a_kc, d.M, d.K, d.lda, false));
     gp.C = ws_ptr;
     gp.ldc = ldw;
     gp.n_segs = 0;

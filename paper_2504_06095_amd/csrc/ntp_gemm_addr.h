@@ -65,6 +65,21 @@ NTP_HD int64_t operand_extent_bytes(bool kc, int64_t rows, int64_t K, int64_t ld
   return ((K - 1) * ld + (rows + 7) / 8 * 8) * 2;
 }
 
+// ---- the deep-pipelined kernel (ntp_gemm_deep.h): the whole K range of a chunk, tail included, goes through the ring ----
+// A K chunk that starts at k_first has buffer views that start this many bytes into the operand and end where the operand ends.
+NTP_HD uint32_t deep_view_shift(bool kc, int64_t k_first, int64_t ld) { return uint32_t((kc ? k_first : k_first * ld) * 2); }
+// Bytes of the operand that the loads may touch: a K-contiguous A is read in whole chunks of 8 (the caller vouches for zeros from K on).
+NTP_HD int64_t deep_extent_bytes(bool kc, int64_t rows, int64_t K, int64_t ld) {
+  return operand_extent_bytes(kc, rows, kc ? (K + 7) / 8 * 8 : K, ld, false);
+}
+// Offset past every view (views are below 2 GiB): where the loads of a K-contiguous operand's chunks at k >= K of the last K tile go.
+constexpr uint32_t kNowhere = 0x80000000u;
+// Whether chunk `chunk` of the last of nk K tiles of a K range of K elements starts at or past K.
+template <bool KC>
+NTP_HD bool deep_cut(int nk, int chunk, int K) {
+  return KC && (nk - 1) * DK + chunk * 8 >= K;
+}
+
 // Virtual block v of nblk = tiles_m * tiles_n -> output tile.  Workgroups are dealt round-robin to the 8
 // XCDs (each with its own L2), so virtual block v belongs to XCD v & 7; every XCD walks a contiguous range
 // of tiles in groups of 8 tile rows, so that its workgroups share operands.

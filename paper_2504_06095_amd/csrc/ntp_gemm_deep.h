@@ -49,7 +49,7 @@ __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, ui
   const int K = min(g.k_chunk, g.K - int(k_first));
   const int nk = (K + DK - 1) / DK;
 
-  const uint32_t a_shift = uint32_t((AKC ? k_first : k_first * g.lda) * 2), b_shift = uint32_t((BKC ? k_first : k_first * g.ldb) * 2);
+  const uint32_t a_shift = deep_view_shift(AKC, k_first, g.lda), b_shift = deep_view_shift(BKC, k_first, g.ldb);
   const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(g.A) + a_shift / 2, 0, int(g.a_extent - a_shift), 0x00020000);
   const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(g.B) + b_shift / 2, 0, int(g.b_extent - b_shift), 0x00020000);
   const uint32_t astep_b = uint32_t(AKC ? DK : DK * g.lda) * 2, bstep_b = uint32_t(BKC ? DK : DK * g.ldb) * 2;
@@ -58,8 +58,7 @@ __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, ui
   fra.init(wm * TM, lane);
   frb.init(wn * TN, lane);
 
-  // DMA offsets; in the K tail the chunks at k >= K go past every buffer view (extents are below 2 GiB here)
-  constexpr uint32_t kNowhere = 0x80000000u;
+  // DMA offsets; in the K tail the chunks at k >= K go past every buffer view
   uint32_t offa[NAI], offb[NBI];
   bool cuta[NAI], cutb[NBI];
 #pragma unroll
@@ -67,14 +66,14 @@ __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, ui
     int line, chunk;
     slot_src<AKC, BM_>((wave * NAI + i) * 64 + lane, line, chunk);
     offa[i] = dma_offset<AKC>(g.lda, row0, g.M, line, chunk);
-    cuta[i] = AKC && (nk - 1) * DK + chunk * 8 >= K;
+    cuta[i] = deep_cut<AKC>(nk, chunk, K);
   }
 #pragma unroll
   for (int i = 0; i < NBI; ++i) {
     int line, chunk;
     slot_src<BKC, BN_>((wave * NBI + i) * 64 + lane, line, chunk);
     offb[i] = dma_offset<BKC>(g.ldb, col0, g.N, line, chunk);
-    cutb[i] = BKC && (nk - 1) * DK + chunk * 8 >= K;
+    cutb[i] = deep_cut<BKC>(nk, chunk, K);
   }
   auto dma = [&](int t, int slot) {
     const int kt = min(t, nk - 1);

@@ -7,6 +7,10 @@
 //   - a load lies wholly inside the operand, or
 //   - (K tail through the ring, B operand only) wholly outside the range-checked extent, where the hardware
 //     returns zeros, and then only for K lines >= K.
+// The deep-pipelined kernel's loads (ntp_gemm_deep.h) are enumerated the same way for its two tile sizes, 1 to 16 K chunks and
+// allocations that end with the operand: each lies wholly inside the operand and inside its view and starts at k < K, or wholly outside the
+// view, and then starts at k >= K.
+//
 // It also evaluates the schedule of a K loop padded to a multiple of five K tiles WITHOUT the clamp on the
 // tile index (a variant that was tried and faulted) and reports how far past the operand it reads.
 //
@@ -184,6 +188,70 @@ static bool run_gemm(bool akc, bool bkc, const Tile& t, const Shape& s, int spli
   return true;
 }
 
+// One operand of one output tile of the deep-pipelined kernel over one K chunk [first, first + Kc).
+template <bool KC, int R>
+static bool check_deep(const char* what, int64_t ld, int row0, int lim, int K_total, int64_t first, int Kc, int64_t extent, int64_t contract) {
+  const int nk = (Kc + DK - 1) / DK;
+  const int64_t shift = deep_view_shift(KC, first, ld), view = extent - shift, kstep = int64_t(KC ? DK : DK * ld) * 2;
+  if (shift != (KC ? first : first * ld) * 2 || view <= 0 || extent >= (int64_t(1) << 31)) {
+    printf("FAIL deep %s: view\n", what);
+    return false;
+  }
+  for (int pos = 0; pos < R * 8; ++pos) {  // every chunk position of a slot: all wavefronts, instructions, lanes
+    int line, chunk;
+    slot_src<KC, R>(pos, line, chunk);
+    const uint32_t off = dma_offset<KC>(ld, row0, lim, line, chunk);
+    const bool cut = deep_cut<KC>(nk, chunk, Kc);
+    for (int kt = 0; kt < nk; ++kt) {  // (the schedule clamps what it asks for past the end to the last K tile)
+      const int64_t voff = kt == nk - 1 && cut ? kNowhere : off, soff = int64_t(kt) * kstep, o = voff + soff;
+      const int64_t k = first + int64_t(kt) * DK + (KC ? chunk * 8 : line);  // where the 16 bytes start on the K axis
+      ++g_loads;
+      bool ok = soff <= 0xFFFFFFFFll && o <= 0xFFFFFFFFll;  // 32-bit sums
+      if (o + 16 <= view) ok = ok && shift + o + 16 <= contract && k < K_total;
+      else ok = ok && o >= view && k >= K_total;  // the range check returns zeros
+      if (ok) continue;
+      printf("FAIL deep %s: kc=%d R=%d ld=%lld row0=%d lim=%d K=%d first=%lld Kc=%d kt=%d k=%lld -> byte %lld of a view of %lld, contract %lld\n", what, int(KC), R,
+             (long long)ld, row0, lim, K_total, (long long)first, Kc, kt, (long long)k, (long long)o, (long long)view, (long long)contract);
+      return false;
+    }
+  }
+  return true;
+}
+
+static bool run_deep(bool akc, bool bkc, int bn, const Shape& s, int splits) {
+  const bool nn = akc && !bkc;
+  if (akc && s.K % 8 && !nn) return true;  // not this kernel's: only a row-parallel GEMM's A has its pad columns zeroed
+  const int a_cols = akc ? s.K : s.M, b_cols = bkc ? s.K : s.N;
+  const int64_t lda = (a_cols + 7) / 8 * 8 + s.pad_a, ldb = (b_cols + 7) / 8 * 8 + s.pad_b;
+  const int64_t a_ext = deep_extent_bytes(akc, s.M, s.K, lda), b_ext = operand_extent_bytes(bkc, s.N, s.K, ldb, false);
+  const int64_t a_con = contract_bytes(akc, s.M, s.K, lda, nn ? (s.K + 7) / 8 * 8 : s.K), b_con = contract_bytes(bkc, s.N, s.K, ldb, s.K);
+  if (a_ext > a_con || b_ext > b_con) {
+    printf("FAIL deep: extent beyond the contract\n");
+    return false;
+  }
+  const int chunk = ((s.K + 63) / 64 + splits - 1) / splits * 64;
+  if (int64_t(splits - 1) * chunk >= s.K) return true;  // the launcher never makes an empty chunk
+  for (int sp = 0; sp < splits; ++sp) {
+    const int64_t first = int64_t(sp) * chunk;
+    const int Kc = imin(chunk, s.K - int(first));
+    for (int side = 0; side < 2; ++side) {
+      const int b = side ? bn : 128, lim = side ? s.N : s.M, tiles = (lim + b - 1) / b;
+      const bool kc = side ? bkc : akc;
+      for (int tile : {0, tiles / 2, tiles - 1}) {
+        ++g_cases;
+        const int64_t ld = side ? ldb : lda, ext = side ? b_ext : a_ext, con = side ? b_con : a_con;
+        const char* const what = side ? "B" : "A";
+        const bool ok = b == 128 ? (kc ? check_deep<true, 128>(what, ld, tile * b, lim, s.K, first, Kc, ext, con)
+                                       : check_deep<false, 128>(what, ld, tile * b, lim, s.K, first, Kc, ext, con))
+                                 : (kc ? check_deep<true, 256>(what, ld, tile * b, lim, s.K, first, Kc, ext, con)
+                                       : check_deep<false, 256>(what, ld, tile * b, lim, s.K, first, Kc, ext, con));
+        if (!ok) return false;
+      }
+    }
+  }
+  return true;
+}
+
 int main(int argc, char** argv) {
   const bool padded = argc > 1 && !strcmp(argv[1], "padded");
   const Shape shapes[] = {
@@ -202,6 +270,14 @@ int main(int argc, char** argv) {
             if (padded && splits > 1) continue;
             if (!run_gemm(lay[0], lay[1], t, s, splits, pad64 != 0, padded)) return 1;
           }
+  const Shape deep_shapes[] = {{512, 586, 1024, 0, 0}, {257, 129, 264, 0, 0}, {1, 1, 8, 0, 0}, {130, 383, 1288, 8, 16}, {300, 131, 4096, 0, 0}, {520, 1032, 1500, 0, 0},
+                               {777, 1096, 1001, 0, 40}, {1001, 1096, 777, 0, 0}, {752, 160, 9544, 0, 0}, {129, 513, 2051, 64, 8}, {128, 256, 63, 0, 0}, {64, 8, 65, 0, 0}};
+  if (!padded)
+    for (const auto& lay : layouts)
+      for (int bn : {128, 256})
+        for (const Shape& s : deep_shapes)
+          for (int splits = 1; splits <= 16; ++splits)
+            if (!run_deep(lay[0], lay[1], bn, s, splits)) return 1;
   if (padded) printf("OVERRUN %lld\n", (long long)g_overrun);
   else printf("OK %lld %lld\n", (long long)g_cases, (long long)g_loads);
   return 0;
