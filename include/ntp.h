@@ -98,7 +98,8 @@ int ntp_device_info(const ntp_handle_t* h, int32_t* device, int32_t* compute_uni
 #define NTP_OPT_GEMM_TILE 0          /* 1: the small generic kernel; 2 + i: ring tile shape i in the order 256x256,
                                         256x224, 224x256, 256x192, 192x256, 256x128, 128x256, 128x128 (4 wavefronts),
                                         128x128 (8 wavefronts)                                                       */
-#define NTP_OPT_GEMM_SPLIT 1         /* 1: never cut the contraction axis; 2..8: that many chunks where they fit   */
+#define NTP_OPT_GEMM_SPLIT 1         /* 1: never cut the contraction axis; 2..8: that many chunks where they fit
+                                        (ring kernels)                                                               */
 #define NTP_OPT_GEMM_NO_RING_TAIL 2  /* 1: the K tail of row-parallel GEMMs goes through registers                 */
 #define NTP_OPT_ATTN_PARTS 3         /* 1..16: parts per attention-core walk where the workspace holds them        */
 #define NTP_OPT_RESHARD_BLOCK 4      /* bytes per workgroup of the row-wise gather kernel                           */
@@ -115,8 +116,9 @@ int ntp_device_info(const ntp_handle_t* h, int32_t* device, int32_t* compute_uni
                                         exist (head dimension 128; forward: 16 query rows per wavefront): 1 through
                                         registers, 2 by DMA into chunk-permuted rows; 0: the library's choice          */
 #define NTP_OPT_ATTN_BWD_LAUNCHES 12  /* the attention core's dQ and dK/dV kernels: 1 one launch each, 2 one launch for
-                                        both where both copy by DMA (they then share the compute units; a small
-                                        kernel stores the rows' delta values first); 0: the library's choice          */
+                                        both where both copy by DMA, or at head dimension 64 where neither walk is
+                                        cut (they then share the compute units; a small kernel stores the rows' delta
+                                        values first); 0: the library's choice                                         */
 #define NTP_OPT_COUNT_ 13
 int ntp_set_option(ntp_handle_t* h, int32_t option, int64_t value);
 
@@ -511,13 +513,14 @@ int ntp_set_workspace(ntp_handle_t* h, void* workspace, int64_t bytes);
 
 /* Diagnostic aid (host only, touches no device memory): which GEMM kernel a shard GEMM
  * of this shape would run on this handle (its compute units, workspace and options at
- * the time of the call), with tightly packed operands.  layout: 0 both operands K-contiguous (column-parallel
+ * the time of the call) if it is launched alone, with tightly packed operands (the gradient GEMMs of a
+ * backward call may share one launch, and are not cut then).  layout: 0 both operands K-contiguous (column-parallel
  * forward, activation gradients of row-parallel layers), 1 A K-contiguous and B
  * K-strided (row-parallel forward, partial input gradients), 2 both K-strided (weight
  * gradients).  M, N >= 1, K >= 0.
  *   tile_m, tile_n  output tile of a workgroup
  *   wavefronts      wavefronts per workgroup
- *   ring            1: the LDS-ring kernel; 0: the small generic kernel
+ *   ring            1: one of the kernels with an LDS ring (the deep-pipelined one included); 0: the small generic kernel
  *   k_splits        > 1: split-K with that many chunks, followed by the reduce kernel
  *   persistent      1: one workgroup per compute unit walks over the tiles
  *   pingpong        1: the K loop runs the ping-pong schedule (the two wavefronts of a SIMD alternate between
