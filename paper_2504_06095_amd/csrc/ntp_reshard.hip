@@ -463,10 +463,10 @@ __global__ __launch_bounds__(kThreads) void reshard_dense_kernel(const DenseBatc
 // 16-byte chunk stored whole and aligned.  The plan keeps in device memory, for every unit of every
 // destination shard (one shard after the other), where it comes from: rank << 24 | unit in that rank's shard.
 // The table is 4 bytes a unit and stays in the L2s; nothing about it has to fit in LDS, so every layout of a plan
-// takes one launch, whether a destination shard is two long runs or every unit comes from another rank.
-// (The earlier form kept a 32-byte record per run in LDS: layouts with more than about 1300 runs a shard, or with
-// rows above 57 KB, were copied sub-shard by sub-shard, 8 units a job: 93.8 ms for the gradients of a hidden-12800
-// layer between TP 7 and TP 5, which the table moves in 2.10 ms.)
+// goes through it, whether a destination shard is two long runs or every unit comes from another rank.
+// (The run table, reshard_runs_kernel, keeps a 32-byte record per run in LDS: without the unit table, layouts with more than about
+// 1300 runs a shard, or with rows above 57 KB, were copied sub-shard by sub-shard, 8 units a job: 93.8 ms for the gradients of a
+// hidden-12800 layer between TP 7 and TP 5, which this table moves in 2.10 ms.)
 constexpr int kMaxRanks = 96;       // source ranks, and destination shards per launch: the argument block stays below 4 KiB
 constexpr uint32_t kUnitBits = 24;  // of a table entry; the rank has the other 8
 
