@@ -2096,6 +2096,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_core_bwd_dkv_dma_kernel(cons
   bwd_dkv_dma_body<PAIRED>(a, blockIdx.x, gridDim.x, tiles, row_values);
 }
 
+#include "ntp_attn_bwd_wide.h"
+
 // Both backward kernels in one launch: the first n_dkv workgroups are dK/dV workgroups, the rest dQ workgroups.
 // Each kernel alone keeps the matrix pipe and the vector ALU busy in turn; at the launch sizes of a few heads
 // and a few thousand tokens either leaves most SIMDs with one wavefront, and nothing overlaps.  Launched together a
@@ -2241,11 +2243,12 @@ struct CoreChoice {
   int fwd_parts, dq_parts, dkv_parts;
   int64_t ws_bytes;  // workspace bytes the cut launches use (the largest of the three)
   bool dq_dma, dkv_dma;  // the dQ / the dK, dV kernel brings its tiles to LDS by DMA
+  bool bwd_wide;         // both with 32 owned rows per wavefront
   bool bwd_both;         // both backward kernels go out as one launch
   int64_t dkv_ws_offset; // then: byte offset of the dK/dV parts in the workspace (behind the dQ parts)
 };
 CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_core_shape_t* s) {
-  CoreChoice c{16, 1, 1, 1, 0, false, false, false, 0};
+  CoreChoice c{16, 1, 1, 1, 0, false, false, false, false, 0};
   const bool causal = s->causal != 0;
   const int64_t tiles = (s->seq_len + kBKV - 1) / kBKV;
   // under the causal mask a workgroup takes a pair of tiles, one from each end of the sequence
@@ -2272,6 +2275,22 @@ CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_cor
     c.fwd_parts = choose_parts_dma(h, ws_bytes, wq, bq, walk, bf, 2 * cus, wq * 4 >= cus * 3 ? 24 : 16, cus * 3 / 4);
     c.dq_parts = choose_parts_dma(h, ws_bytes, wq, bq, walk, bdq, cus, 10, cus * 3 / 8);
     c.dkv_parts = choose_parts_dma(h, ws_bytes, wk, bk, heads_per_kv * walk, bdkv, cus, 10, cus * 3 / 8);
+    // The backward kernels with 32 rows per wavefront (one workgroup of 128 rows per compute unit) need enough (128-row, 64-row) tile
+    // pairs per compute unit to pay for their way into and out of a walk, more where the walks are cut.  Both sides, one launch each,
+    // heads x tokens (pairs per unit): 14 x 8192 unmasked (448) 1583 -> 1275 us, causal (228) 895 -> 730; 14 x 2048 unmasked (28) 126 ->
+    // 101, causal (15) 72 -> 72; 28 x 1300 causal (13) 103 -> 71; 10 x 2048 causal (11) 67 -> 59; 16 x 1024 unmasked (8) 39 -> 36;
+    // cut: 3 on one KV head x 4096 unmasked (24) 108 -> 88, causal (12) 75 -> 77; 8 x 1024 causal (2) 36 -> 39.
+    const int64_t tiles2 = (tiles + 1) / 2;
+    const int64_t pairs = (causal ? tiles2 * tiles - tiles2 * (tiles2 - 1) : tiles2 * tiles) * s->n_seq * s->q_cnt;
+    const int64_t least = c.dq_parts > 1 || c.dkv_parts > 1 ? 16 : 8;
+    c.bwd_wide = h->opt[NTP_OPT_ATTN_COPY] == 3 || (h->opt[NTP_OPT_ATTN_COPY] == 0 && pairs >= least * cus);
+    if (c.bwd_wide && !h->opt[NTP_OPT_ATTN_PARTS]) {
+      // ... and a cut costs them more: no more parts than bring a walk to 1.5 times an even share of the launch's work
+      // (4 products a pair for dK/dV, 3 for dQ)
+      const double even = 7.0 * double(pairs) / double(cus);
+      while (c.dq_parts > 1 && 3.0 * double(tiles) <= 1.5 * even * (c.dq_parts - 1)) --c.dq_parts;
+      while (c.dkv_parts > 1 && 4.0 * double(heads_per_kv * tiles) <= 1.5 * even * (c.dkv_parts - 1)) --c.dkv_parts;
+    }
   } else {
     c.fwd_parts = choose_parts(h, ws_bytes, wq, bq, walk, bf, fill, 12, causal);
     c.dq_parts = choose_parts(h, ws_bytes, wq, bq, walk, bdq, fill, 12, causal);
@@ -2289,7 +2308,7 @@ CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_cor
   // 146 -> 122); larger launches fill the device on their own and lose 1-4 % to the extra kernel.
   // Head dimension 64 (walks that are not cut): at every size measured (3 heads x 512 tokens of 4 sequences 28 -> 20 us, 15 heads
   // x 389 30 -> 22 us, 28 heads x 6062 620 -> 589 us, 22 heads x 3801 no difference).
-  const bool pays = s->head_dim == 64 || wq + wk <= 3 * cus;
+  const bool pays = s->head_dim == 64 || c.bwd_wide || wq + wk <= 3 * cus;
   c.bwd_both = (dma || (s->head_dim == 64 && c.dq_parts == 1 && c.dkv_parts == 1)) && h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] != 1 && (pays || h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] == 2) &&
                (dkv_bytes == 0 || c.dkv_ws_offset + dkv_bytes <= ws_bytes);
   c.ws_bytes = std::max(c.ws_bytes, c.bwd_both ? (dkv_bytes ? c.dkv_ws_offset + dkv_bytes : dq_bytes) : std::max(dq_bytes, dkv_bytes));
@@ -2445,9 +2464,7 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
   a.kv_off = s->kv_off;
   a.group = s->group;
   a.causal = s->causal ? 1 : 0;
-  // the dQ kernel with 16 query rows per wavefront (three workgroups per CU, no register spills) measured
-  // faster than with 32 at almost every size: only that variant is built
-  constexpr int qbw = 1;
+  constexpr int qbw = 1;  // 16 query rows per wavefront, but for cc.bwd_wide (ntp_attn_bwd_wide.h)
   a.tiles = (s->seq_len + 64 * qbw - 1) / (64 * qbw);
   constexpr int kb = 1;  // 64 keys per workgroup of the dK/dV kernel
   const int32_t key_tiles = (s->seq_len + 64 * kb - 1) / (64 * kb);
@@ -2461,8 +2478,14 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
   a.part_sums = static_cast<float*>(h->workspace);
   const CoreChoice cc = choose_core(h, h->workspace ? h->workspace_bytes : 0, s);
   const int32_t q_pairs = s->causal ? (a.tiles + 1) / 2 : 0, k_pairs = s->causal ? (key_tiles + 1) / 2 : 0;
-  const int64_t dq_wgs = int64_t(q_pairs > 0 ? q_pairs : a.tiles) * s->n_seq * s->q_cnt * cc.dq_parts;
-  const int64_t dkv_wgs = int64_t(k_pairs > 0 ? k_pairs : key_tiles) * s->n_seq * s->kv_cnt * cc.dkv_parts;
+  int64_t dq_wgs = int64_t(q_pairs > 0 ? q_pairs : a.tiles) * s->n_seq * s->q_cnt * cc.dq_parts;
+  int64_t dkv_wgs = int64_t(k_pairs > 0 ? k_pairs : key_tiles) * s->n_seq * s->kv_cnt * cc.dkv_parts;
+  if (cc.bwd_wide) {  // workgroups of the launch's first section: tiles of 128 rows, under the mask the longer half of the walks
+    const int64_t own = (a.tiles + 1) / 2, first = s->causal ? (own + 1) / 2 : own;
+    dq_wgs = (first * s->n_seq * s->q_cnt * cc.dq_parts + 7) / 8 * 8;
+    dkv_wgs = (first * s->n_seq * s->kv_cnt * cc.dkv_parts + 7) / 8 * 8;
+  }
+  const int64_t sections = cc.bwd_wide && s->causal ? 2 : 1;
   auto reduce_parts = [&](auto dkv, int64_t blocks) {
     constexpr bool DKV = decltype(dkv)::value;
     const dim3 rgrid(uint32_t((blocks * 64 * ((DKV ? 2 : 1) * s->head_dim / 4) + 255) / 256));
@@ -2473,8 +2496,8 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
     return hipGetLastError() == hipSuccess;
   };
   const int64_t delta_wgs = (M * s->q_cnt * (s->head_dim / 8) + 255) / 256;
-  if (dq_wgs > 0x7fffffffll || dkv_wgs > 0x7fffffffll) return NTP_ERR_UNSUPPORTED;
-  if (cc.bwd_both && bq > 0 && bk > 0 && dq_wgs + dkv_wgs <= 0x7fffffffll && delta_wgs <= 0x7fffffffll) {
+  if (sections * dq_wgs > 0x7fffffffll || sections * dkv_wgs > 0x7fffffffll) return NTP_ERR_UNSUPPORTED;
+  if (cc.bwd_both && bq > 0 && bk > 0 && sections * (dq_wgs + dkv_wgs) <= 0x7fffffffll && delta_wgs <= 0x7fffffffll) {
     // one launch for both kernels, after the rows' delta values (5 algorithmic + 2 recomputed products per pair)
     CoreBwdArgs adq = a, adkv = a;
     adq.n_parts = cc.dq_parts;
@@ -2488,8 +2511,13 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
     const bool wide = s->head_dim == 128;
     hipLaunchKernelGGL(wide ? attn_core_delta_kernel<128> : attn_core_delta_kernel<64>, dim3(uint32_t(delta_wgs)), dim3(256), 0, hs, a, M);
     ok = hipGetLastError() == hipSuccess;
-    const dim3 grid(uint32_t(dq_wgs + dkv_wgs));
-    if (ok) {
+    const dim3 grid(uint32_t(sections * (dq_wgs + dkv_wgs)));
+    if (ok && cc.bwd_wide) {
+      // the longest of the short dK/dV walks against the longest dQ walk, in matrix products of tile pairs
+      const uint32_t kv_first = 2 * std::min<int64_t>(s->group, s->q_cnt) * cc.dq_parts > 3 * cc.dkv_parts;
+      hipLaunchKernelGGL(attn_core_bwd_both_wide_kernel, grid, dim3(kThreads), 0, hs, adq, adkv, uint32_t(dq_wgs), uint32_t(dkv_wgs), kv_first);
+      ok = hipGetLastError() == hipSuccess;
+    } else if (ok) {
       BothOrder order;
       order.n_dkv = uint32_t(dkv_wgs);
       order.chunk = uint32_t(std::max(h->compute_units, 1));
@@ -2516,8 +2544,10 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
     a.n_parts = cc.dq_parts;
     a.pairs = q_pairs;
     if (ntp::timing_on(h)) ntp::timing_begin(h, stream, a.n_parts > 1 ? "attn_core_bwd_dq_cut" : "attn_core_bwd_dq", 3.0 * pair_flops, 0.0);
-    const dim3 grid{uint32_t(dq_wgs)};
-    if (cc.dq_dma) {
+    const dim3 grid{uint32_t(sections * dq_wgs)};
+    if (cc.bwd_wide) {
+      hipLaunchKernelGGL(attn_core_bwd_dq_wide_kernel, grid, dim3(kThreads), 0, hs, a, uint32_t(dq_wgs));
+    } else if (cc.dq_dma) {
       if (a.pairs > 0) hipLaunchKernelGGL((attn_core_bwd_dq_dma_kernel<true>), grid, dim3(kThreads), 0, hs, a);
       else hipLaunchKernelGGL((attn_core_bwd_dq_dma_kernel<false>), grid, dim3(kThreads), 0, hs, a);
     } else if (s->head_dim == 128 && a.pairs > 0)
@@ -2540,8 +2570,10 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
     a.n_parts = cc.dkv_parts;
     a.pairs = k_pairs;
     if (ntp::timing_on(h)) ntp::timing_begin(h, stream, a.n_parts > 1 ? "attn_core_bwd_dkv_cut" : "attn_core_bwd_dkv", 4.0 * pair_flops, 0.0);
-    const dim3 grid{uint32_t(dkv_wgs)};
-    if (cc.dkv_dma) {
+    const dim3 grid{uint32_t(sections * dkv_wgs)};
+    if (cc.bwd_wide) {
+      hipLaunchKernelGGL(attn_core_bwd_dkv_wide_kernel, grid, dim3(kThreads), 0, hs, a, uint32_t(dkv_wgs));
+    } else if (cc.dkv_dma) {
       if (a.pairs > 0) hipLaunchKernelGGL((attn_core_bwd_dkv_dma_kernel<true>), grid, dim3(kThreads), 0, hs, a);
       else hipLaunchKernelGGL((attn_core_bwd_dkv_dma_kernel<false>), grid, dim3(kThreads), 0, hs, a);
     } else if (s->head_dim == 128 && a.pairs > 0)

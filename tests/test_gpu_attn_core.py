@@ -231,6 +231,22 @@ def test_attn_core_bwd_one_or_two_launches(workspace, opts, n_q, n_kv, tp, rank,
     assert names == (["attn_core_bwd_both" + cut] if launches == 2 else ["attn_core_bwd_dq" + cut, "attn_core_bwd_dkv" + cut]), names
 
 
+@pytest.mark.parametrize("launches", [1, 2], ids=["two_launches", "one_launch"])
+@pytest.mark.parametrize("parts", [1, 3])
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+@pytest.mark.parametrize("n_q,n_kv,tp,rank,n_seq,S,pad", [(4, 1, 4, 3, 1, 1, 0), (6, 6, 4, 1, 3, 64, 0), (8, 2, 3, 2, 1, 129, 0), (8, 2, 3, 0, 2, 200, 8),
+                                                        (64, 8, 30, 3, 2, 449, 0), (12, 3, 1, 0, 1, 640, 8), (6, 6, 4, 1, 1, 1100, 8)])
+def test_attn_core_bwd_32_rows_per_wavefront(workspace, opts, n_q, n_kv, tp, rank, n_seq, S, pad, causal, parts, launches):
+    """The backward kernels with 32 rows per wavefront at sizes below the launcher's own choice: 1, 2, 4, 5 and 9 tiles of 128 rows (the
+    middle one of an odd number has no partner under the mask), an odd and an even number of 64-row tiles, rows past the end in
+    the last one, walks shorter and longer than the ring, parts without a unit, grouped KV heads, several sequences."""
+    _say(f"attn core bwd, 32 rows per wavefront: heads {n_q}/{n_kv} tp {tp} rank {rank} n_seq={n_seq} S={S} pad={pad} causal={causal} parts={parts} launches={launches}")
+    opts(K.NTP_OPT_ATTN_COPY, 3)
+    opts(K.NTP_OPT_ATTN_PARTS, parts)
+    opts(K.NTP_OPT_ATTN_BWD_LAUNCHES, launches)
+    _bwd_case(n_q, n_kv, tp, rank, 128, n_seq, S, causal, seed=41, pad=pad)
+
+
 # 64-row tiles: 1728 / 576 workgroups of the two kinds in pairs of 256 and what is left over (causal; full 3456 / 1152), 1728 / 576 over eight tiles
 # each (causal 864 / 288), and fewer than one chunk
 @pytest.mark.parametrize("launches", [0, 1, 2], ids=["auto", "two_launches", "one_launch"])
