@@ -89,8 +89,8 @@ int ntp_device_info(const ntp_handle_t* h, int32_t* device, int32_t* compute_uni
  * own choice.  They exist so that tests and tuning runs can reach every kernel
  * variant at any size; a forced variant computes the same result to within fp32
  * summation order (bit-identical for the reshard options).  GEMMs with few output
- * tiles run on a kernel of their own (deep-pipelined; its K axis is cut into up to 16
- * chunks where a workspace is set), and the gradient GEMMs of a small backward call may
+ * tiles run on a kernel of their own (deep-pipelined; where a workspace is set its K axis
+ * is cut into up to 16 chunks or its tiles are 64 x 64), and the gradient GEMMs of a small backward call may
  * share one launch of it.  NTP_OPT_GEMM_TILE, _SPLIT, _SCHEDULE and _WORKGROUPS other
  * than 0 are about the other kernels and switch both off; NTP_OPT_GEMM_NO_RING_TAIL does
  * so for row-parallel GEMMs with K % 64 != 0.

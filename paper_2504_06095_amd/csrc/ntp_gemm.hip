@@ -180,6 +180,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs g, co
 
 constexpr int kDeepTile = 8, kDeepWideTile = 6;  // indices of the deep-pipelined kernel's tile shapes
 constexpr int kMaxDeepSplits = 16;
+constexpr double kSmallTileUs = 0.225;  // a K tile of the 64 x 64 form
+constexpr double kGroupSmallFrom = 24;  // K tiles
 
 // Whether the deep-pipelined kernel takes over from `old`, and in how many K chunks.  Measured over 45 random shapes of up to one
 // 128 x 128 tile per compute unit, all layouts: against the persistent kernels on 128 x 128 tiles it is never slower (2 % at
@@ -197,7 +199,7 @@ constexpr int kMaxDeepSplits = 16;
 //    1584 34 -> 31 us, 1376 x 4672 over 3440 56 -> 54 us;
 //  - up to two 128 x 128 tiles per compute unit and 25 K tiles (weight gradients: 32): 1984 x 2664 over K = 328 16 -> 13.5 us, 584 x 7304
 //    over 1400 28 -> 25 us, 2192 x 2304 over 1888 38 -> 35 us; at 54 K tiles 10 % slower.
-SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int layout, int64_t M, int64_t N, int64_t K, int64_t ldw, const SplitChoice& old) {
+SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int layout, int64_t M, int64_t N, int64_t K, int64_t ldw, const SplitChoice& old, bool small_ok) {
   const TileShape& ts = kTileShapes[old.tile];
   const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), wide = ((M + 127) / 128) * ((N + 255) / 256), ktiles = (K + 63) / 64;
   const int cus = h->compute_units;
@@ -221,19 +223,34 @@ SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int layout, int64
       best = SplitChoice{kDeepTile, sp, int(chunk_tiles * 64), kDeep5};
     }
   }
+  // Where the caller has set a workspace, the same with 64 x 64 tiles, which need a cut less often: up to three on a compute unit at a time,
+  // which share its rate (both sides in ntp_gemm_deep.h; without a workspace, and below six K tiles, whose launches are mostly fixed
+  // costs, the tiles stay 128 x 128)
+  if (!small_ok || ws_bytes <= 0 || ktiles < 6) return best;
+  const double small = double((M + 63) / 64) * double((N + 63) / 64) / double(cus);
+  for (int sp = 1; sp <= kMaxSplits; ++sp) {
+    const int64_t chunk_tiles = (ktiles + sp - 1) / sp;
+    if (sp > 1 && (chunk_tiles < 4 || int64_t(sp) * M * ldw * 4 > ws_bytes)) break;
+    if ((sp - 1) * chunk_tiles * 64 >= K) continue;  // the last chunk would be empty
+    const double t = kSmallTileUs * double(chunk_tiles) * std::max(1.0, small * sp) + (sp > 1 ? 3.5 + double(M) * double(ldw) * (4.0 * sp + 4.0) / 4.4e6 : 0.0);
+    if (t < best_t) {
+      best_t = t;
+      best = SplitChoice{kDeepTile, sp, int(chunk_tiles * 64), kDeepSmall};
+    }
+  }
   return best;
 }
 
 // Kernel variant (-1 generic, else a tile shape) and K chunks for a GEMM (g: M, N, K, n_store).
 SplitChoice plan_gemm(const ntp_handle* h, int64_t ws_bytes, const GemmArgs& g, int layout, bool ring_ok, bool split_ok,
-                      int64_t ldw, bool deep_ok) {
+                      int64_t ldw, bool deep_ok, bool small_ok = true) {
   SplitChoice sc{choose_variant(h, g, ring_ok, layout), 1, 0, kNotDeep};
   if (split_ok && int64_t(g.M) * g.N >= 128 * 128 * 8) sc = choose_split(h, ws_bytes, g.M, g.n_store, g.K, layout, sc.tile, ldw);
   // (options that ask for a ring tile, a cut, a schedule, a cap on the persistent grid or a K tail through registers mean the ring kernels)
   const bool ring_asked = h->opt[NTP_OPT_GEMM_TILE] || h->opt[NTP_OPT_GEMM_SPLIT] || h->opt[NTP_OPT_GEMM_SCHEDULE] || h->opt[NTP_OPT_GEMM_WORKGROUPS] ||
                           (h->opt[NTP_OPT_GEMM_NO_RING_TAIL] && layout == 1 && g.K % 64 != 0);
   if (deep_ok && sc.tile >= 0 && !ring_asked)
-    sc = choose_deep(h, split_ok ? ws_bytes : 0, layout, g.M, g.n_store, g.K, ldw, sc);
+    sc = choose_deep(h, split_ok ? ws_bytes : 0, layout, g.M, g.n_store, g.K, ldw, sc, small_ok);
   return sc;
 }
 
@@ -267,8 +284,10 @@ int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t 
   g.K = int32_t(K);
   g.n_store = int32_t(n_store);
   const int64_t ldw = (n_store + 15) / 16 * 16;
-  const SplitChoice sc = plan_gemm(h, INT64_MAX / 2, g, layout, true, true, ldw, deep);
-  return sc.splits > 1 ? int64_t(sc.splits) * M * ldw * 4 : 0;
+  // (what 128 x 128 tiles would be cut into counts where 64 x 64 tiles take their place uncut: those are for handles with a workspace)
+  const SplitChoice sc = plan_gemm(h, INT64_MAX / 2, g, layout, true, true, ldw, deep), wide = plan_gemm(h, INT64_MAX / 2, g, layout, true, true, ldw, deep, false);
+  const int splits = std::max(sc.splits, wide.splits);
+  return splits > 1 ? int64_t(splits) * M * ldw * 4 : 0;
 }
 
 namespace {
@@ -422,11 +441,13 @@ int launch_prepared(ntp_handle* h, const GemmDesc& d, const Prepared& p, void* s
   const int variant = sc.tile;
   if (ntp::timing_on(h)) {
     char name[48], vn[16], sn[8] = "";
-    variant_name(variant, vn, sizeof(vn));
+    if (sc.deep == kDeepSmall) snprintf(vn, sizeof(vn), "64x64");
+    else variant_name(variant, vn, sizeof(vn));
     if (sc.splits > 1) snprintf(sn, sizeof(sn), "k%d", sc.splits);
     const bool pp = sc.splits == 1 && !sc.deep && use_pingpong(h, layout, variant, d.K) && !(layout == 2 && variant == 0 && ring_ok);
     snprintf(name, sizeof(name), "gemm_%c%c_%s_%s%s%s%s", d.a_kc ? 'n' : 't', d.b_kc ? 't' : 'n', kEpiName[d.epilogue], vn,
              sc.deep == kDeep2 ? "d2" : sc.deep ? "d" : "", sn, pp ? "pp" : "");
+
     ntp::timing_begin(h, stream, name, 2.0 * double(d.M) * double(d.N) * double(d.K), 0.0);
   }
   if (sc.deep && sc.splits == 1) {
@@ -530,22 +551,29 @@ int gemm_launch_group(ntp_handle* h, const GemmDesc* d, int n, void* stream) {
   Prepared p[kMax];
   int status[kMax] = {NTP_OK, NTP_OK, NTP_OK};
   bool group = n >= 2, apart_only = false;
-  double apart = 0.0, longest = 0.0, work = 0.0, flops = 0.0;
+  double apart = 0.0, longest = 0.0, work = 0.0, work_small = 0.0, flops = 0.0;
   for (int i = 0; i < n; ++i) {
     status[i] = prepare(h, d[i], &p[i]);
-    group = group && status[i] == NTP_OK && !p[i].empty && p[i].sc.deep == kDeep5 &&
+    group = group && status[i] == NTP_OK && !p[i].empty && (p[i].sc.deep == kDeep5 || p[i].sc.deep == kDeepSmall) &&
             (p[i].layout == 2 ? d[i].epilogue == EPI_F32 || d[i].epilogue == EPI_F32_ACCUM : d[i].epilogue == EPI_BF16);
     if (!group) continue;
     const GemmArgs& g = p[i].g;
     const double tiles = double((g.M + 127) / 128) * double((g.n_store + 127) / 128), kt = double((g.K + 63) / 64), sp = p[i].sc.splits;
-    apart += 6.0 + 0.47 * std::ceil(kt / sp) + (sp > 1 ? 3.5 + double(g.M) * double(p[i].ldw) * (4.0 * sp + 4.0) / 4.4e6 : 0.0);
+    const double small = double((g.M + 63) / 64) * double((g.n_store + 63) / 64);
+    apart += 6.0 + (p[i].sc.deep == kDeep5 ? 0.47 : kSmallTileUs * std::max(1.0, small * sp / h->compute_units)) * std::ceil(kt / sp) + (sp > 1 ? 3.5 + double(g.M) * double(p[i].ldw) * (4.0 * sp + 4.0) / 4.4e6 : 0.0);
     longest = std::max(longest, kt);
     work += tiles * kt;
+    work_small += small * kt;
   }
-  group = group && 6.0 + 0.47 * std::max(longest, 1.15 * work / h->compute_units) < apart;
+  // 64 x 64 tiles on the terms of choose_deep, where a problem has a long K axis: its K tiles, 0.47 us each with 128 x 128, are then most of
+  // the launch's time (2048 x 192 over K = 1024 with 192 x 1024 over 2048 21.5 -> 14.7 us, 2048 x 1024 over 576 with 576 x 1024 over 2048 20.4 -> 14)
+  const double shared = 0.47 * std::max(longest, 1.15 * work / h->compute_units), shared_small = kSmallTileUs * std::max(longest, 1.15 * work_small / h->compute_units);
+  const bool by_small = h && h->workspace && longest >= kGroupSmallFrom && shared_small < shared;
+  group = group && 6.0 + (by_small ? shared_small : shared) < apart;
   if (group) {
     for (int i = 0; i < n; ++i) {
       p[i].sc.splits = 1;
+      p[i].sc.deep = by_small ? kDeepSmall : kDeep5;
       for (int j = 0; j < i; ++j) apart_only = apart_only || writes_into(d[i], d[j]) || writes_into(d[j], d[i]);
     }
   }
@@ -566,8 +594,8 @@ int gemm_launch_group(ntp_handle* h, const GemmDesc* d, int n, void* stream) {
     flops += 2.0 * double(d[i].M) * double(d[i].N) * double(d[i].K);
   }
   if (m == 0) return NTP_OK;
-  if (ntp::timing_on(h)) ntp::timing_begin(h, stream, "gemm_group_128x128w8d", flops, 0.0);
-  const int st = launch_deep_group(g, layout, epi, m, static_cast<hipStream_t>(stream));
+  if (ntp::timing_on(h)) ntp::timing_begin(h, stream, by_small ? "gemm_group_64x64d" : "gemm_group_128x128w8d", flops, 0.0);
+  const int st = launch_deep_group(g, layout, epi, m, by_small ? kDeepSmall : kDeep5, static_cast<hipStream_t>(stream));
   ntp::timing_end(h, stream);
   return st;
 }
@@ -590,9 +618,10 @@ extern "C" int ntp_gemm_choice(const ntp_handle_t* h, int32_t layout, int64_t M,
     out->wavefronts = 4;
     out->ring = 0;
   } else {
-    out->tile_m = kTileShapes[sc.tile].bm;
-    out->tile_n = kTileShapes[sc.tile].bn;
-    out->wavefronts = kTileShapes[sc.tile].waves;
+    const TileShape ts = sc.deep == kDeepSmall ? TileShape{64, 64, 4} : kTileShapes[sc.tile];
+    out->tile_m = ts.bm;
+    out->tile_n = ts.bn;
+    out->wavefronts = ts.waves;
     out->ring = 1;
   }
   out->persistent = sc.tile >= 0 && !sc.deep && sc.splits == 1 && !(layout == 2 && sc.tile == 0) ? 1 : 0;

@@ -19,15 +19,18 @@ constexpr int DK = 64;  // K extent of a tile
 
 NTP_HD int imin(int a, int b) { return a < b ? a : b; }
 
-// chunk permutation of a K-strided slot line
-NTP_HD constexpr int kline_swz(int k) { return ((k & 3) | (((k >> 3) & 1) << 2)) << 1; }
+// chunk permutation of a K-strided slot line of `rows` rows (a line of 64 rows is half of the 256 bytes that the LDS banks span, so
+// that two lines side by side take the place of the lowest bit)
+NTP_HD constexpr int kline_swz(int k, int rows) {
+  return rows == 64 ? (((k >> 1) & 1) | (((k >> 3) & 1) << 1)) << 1 : ((k & 3) | (((k >> 3) & 1) << 2)) << 1;
+}
 
 // Rows a tile side of `b` occupies in an LDS slot: whole DMA instructions of 64 rows (K-contiguous), or a
 // power-of-two number of 8-element chunks per K line (K-strided).
 constexpr int slot_rows(bool kc, int b) { return kc ? (b + 63) / 64 * 64 : (b <= 128 ? 128 : 256); }
 
 // chunk position `pos` of a slot -> (line, chunk) it holds.  K-contiguous [R rows][64 k]: chunk p of row r
-// holds k-chunk p ^ ((r >> 1) & 7).  K-strided [64 k][R rows]: chunk p of line k holds row-chunk p ^ kline_swz(k).
+// holds k-chunk p ^ ((r >> 1) & 7).  K-strided [64 k][R rows]: chunk p of line k holds row-chunk p ^ kline_swz(k, R).
 template <bool KC, int R>
 NTP_HD void slot_src(int pos, int& line, int& chunk) {
   if constexpr (KC) {
@@ -36,7 +39,7 @@ NTP_HD void slot_src(int pos, int& line, int& chunk) {
   } else {
     constexpr int CPL = R / 8;
     line = pos / CPL;
-    chunk = (pos % CPL) ^ kline_swz(line);
+    chunk = (pos % CPL) ^ kline_swz(line, R);
   }
 }
 

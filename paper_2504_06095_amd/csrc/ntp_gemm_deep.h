@@ -23,6 +23,13 @@
 
 namespace ntp_gemm {
 
+// Nothing that uses v moves ahead of this.
+__device__ __forceinline__ void pin(bf16x8& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(v)::"memory");
+#endif
+}
+
 // One (output tile, K chunk): workgroup `block` of problem g, with the ring in `ring`.
 template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, int STAGES>
 __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, uint16_t* const ring) {
@@ -91,45 +98,107 @@ __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, ui
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  constexpr int RDS = MI * (AKC ? 1 : 2) + NI * (BKC ? 1 : 2);  // LDS reads of a K-step
-  bf16x8 fa[2][MI], fb[2][NI];
   const uint32_t ring0 = lds_addr(ring);
-  auto read_frags = [&](auto kss, uint32_t sa, uint32_t sb) {
-    constexpr int ks = decltype(kss)::value;
-    static_for(std::make_integer_sequence<int, MI>{}, [&](auto i) { fa[ks][decltype(i)::value] = frag_read_asm<AKC, BM_, MI, decltype(i)::value, ks>(fra, sa); });
-    static_for(std::make_integer_sequence<int, NI>{}, [&](auto j) { fb[ks][decltype(j)::value] = frag_read_asm<BKC, BN_, NI, decltype(j)::value, ks>(frb, sb); });
-  };
-  auto multiply = [&](int ks) {
+  if constexpr (BM_ > 64) {
+    constexpr int RDS = MI * (AKC ? 1 : 2) + NI * (BKC ? 1 : 2);  // LDS reads of a K-step
+    bf16x8 fa[2][MI], fb[2][NI];
+    auto read_frags = [&](auto kss, uint32_t sa, uint32_t sb) {
+      constexpr int ks = decltype(kss)::value;
+      static_for(std::make_integer_sequence<int, MI>{}, [&](auto i) { fa[ks][decltype(i)::value] = frag_read_asm<AKC, BM_, MI, decltype(i)::value, ks>(fra, sa); });
+      static_for(std::make_integer_sequence<int, NI>{}, [&](auto j) { fb[ks][decltype(j)::value] = frag_read_asm<BKC, BN_, NI, decltype(j)::value, ks>(frb, sb); });
+    };
+    auto multiply = [&](int ks) {
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
-  };
-
+        for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+    };
 #pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s) dma(s, s);
-  int slot = 0, free_slot = STAGES - 1;
-  for (int t = 0; t < nk; ++t) {
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(WAIT));
+    for (int s = 0; s < STAGES - 1; ++s) dma(s, s);
+    int slot = 0, free_slot = STAGES - 1;
+    for (int t = 0; t < nk; ++t) {
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(WAIT));
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      const uint32_t sa = ring0 + uint32_t(slot) * (STAGE * 2), sb = sa + SA * 2;
+      read_frags(Int<0>{}, sa, sb);
+      __builtin_amdgcn_sched_barrier(0);
+      dma(t + STAGES - 1, free_slot);
+      __builtin_amdgcn_sched_barrier(0);
+      read_frags(Int<1>{}, sa, sb);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(lgkm_imm(RDS <= 15 ? RDS : 15));
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(0);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(lgkm_imm(0));
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(1);
+      __builtin_amdgcn_sched_barrier(0);
+      free_slot = slot;
+      slot = slot + 1 == STAGES ? 0 : slot + 1;
+    }
+  } else {
+    // 64 x 64: four wavefronts with 8 matrix instructions each have too little to do to hide a K tile's LDS reads, so the fragments of
+    // the next K tile are read under the products of the one in hand (weight gradients over K = 2048: 16.0 -> 14.0 us; on the larger
+    // tiles, whose two wavefronts per SIMD hide each other's reads, it costs 0.5 us a launch)
+    bf16x8 fa[2][2][MI], fb[2][2][NI];
+    auto read_frags = [&](auto setc, uint32_t sa, uint32_t sb) {
+      constexpr int set = decltype(setc)::value;
+      static_for(std::make_integer_sequence<int, 2 * MI>{}, [&](auto ic) {
+        constexpr int i = decltype(ic)::value % MI, ks = decltype(ic)::value / MI;
+        fa[set][ks][i] = frag_read_asm<AKC, BM_, MI, i, ks>(fra, sa);
+      });
+      static_for(std::make_integer_sequence<int, 2 * NI>{}, [&](auto jc) {
+        constexpr int j = decltype(jc)::value % NI, ks = decltype(jc)::value / NI;
+        fb[set][ks][j] = frag_read_asm<BKC, BN_, NI, j, ks>(frb, sb);
+      });
+    };
+    auto frags_arrived = [&](auto setc) {
+      constexpr int set = decltype(setc)::value;
+      __builtin_amdgcn_s_waitcnt(lgkm_imm(0));
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i) pin(fa[set][ks][i]);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) pin(fb[set][ks][j]);
+      }
+    };
+#pragma unroll
+    for (int s = 0; s < STAGES; ++s) dma(s, s);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(WAIT + NAI + NBI));
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    const uint32_t sa = ring0 + uint32_t(slot) * (STAGE * 2), sb = sa + SA * 2;
-    read_frags(Int<0>{}, sa, sb);
-    __builtin_amdgcn_sched_barrier(0);
-    dma(t + STAGES - 1, free_slot);
-    __builtin_amdgcn_sched_barrier(0);
-    read_frags(Int<1>{}, sa, sb);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(lgkm_imm(RDS <= 15 ? RDS : 15));
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(0);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(lgkm_imm(0));
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(1);
-    __builtin_amdgcn_sched_barrier(0);
-    free_slot = slot;
-    slot = slot + 1 == STAGES ? 0 : slot + 1;
+    read_frags(Int<0>{}, ring0, ring0 + SA * 2);
+    frags_arrived(Int<0>{});
+    int slot = 0;  // of the K tile in hand
+    auto step = [&](auto setc, int t) {
+      constexpr int set = decltype(setc)::value;
+      const int next = slot + 1 == STAGES ? 0 : slot + 1;
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(WAIT));  // this wavefront's share of the next K tile has landed ...
+      __builtin_amdgcn_s_barrier();                 // ... and everyone's; everyone has read the one in hand
+      __builtin_amdgcn_sched_barrier(0);
+      const uint32_t sa = ring0 + uint32_t(next) * (STAGE * 2);
+      read_frags(Int<1 - set>{}, sa, sa + SA * 2);
+      __builtin_amdgcn_sched_barrier(0);
+      dma(t + STAGES, slot);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][ks][j], fa[set][ks][i], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      frags_arrived(Int<1 - set>{});
+      __builtin_amdgcn_sched_barrier(0);
+      slot = next;
+    };
+    for (int t = 0; t < nk; t += 2) {
+      step(Int<0>{}, t);
+      if (t + 1 < nk) step(Int<1>{}, t + 1);
+    }
   }
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the clamped DMA instructions write LDS that this workgroup still owns
 
@@ -158,13 +227,18 @@ __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, ui
   }
 }
 
+// The 64 x 64 form (48 KB: three workgroups on a compute unit) for launches that leave most of the device idle with 128 x 128: a K tile takes
+// 0.225 us instead of 0.47 (16 DMA instructions, of which a compute unit takes one in 18 cycles, instead of 32), and there are four times as
+// many workgroups, so that the K axis needs no cut and no second launch.  512 x 584 over K = 1024 13.5 -> 9.6 us, 512 x 1024 over 584
+// 10.5 -> 8.0, 384 x 512 over 4096 in four chunks 18.9 -> 13.2.  Five K tiles in LDS are 0.3 us slower, seven 30 % where
+// a compute unit has more than one workgroup to take.
 template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, int STAGES>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_deep_kernel(const GemmArgs g) {
   __shared__ __attribute__((aligned(1024))) uint16_t ring[STAGES * (BM_ + BN_) * DK];
   deep_tile<AKC, BKC, EPI, BM_, BN_, WGM, WGN, STAGES>(g, int(blockIdx.x), ring);
 }
 
-// Up to three problems that do not depend on each other in one launch (the 128 x 128 tile with five K tiles in LDS, no cut K axis):
+// Up to three problems that do not depend on each other in one launch (the 128 x 128 tile with five K tiles in LDS or the 64 x 64 one, no cut K axis):
 // a layer's small gradient GEMMs take 10-12 us each, of which launch, first loads and the last tiles' stores are the larger
 // part, and leave most of the device idle.  512 x 1024 x 586: dB, dA and dX 34 -> 14 us.
 constexpr int kMaxGroup = 3;
@@ -176,18 +250,19 @@ struct GroupArgs {
 };
 enum GroupKind : int32_t { kGroupNt = 0, kGroupNn, kGroupTn, kGroupTnAccum };  // layout and epilogue: bf16, bf16, fp32, fp32 accumulate
 
-__global__ __launch_bounds__(512) void gemm_deep_group_kernel(const GroupArgs a) {
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[5 * 256 * DK];
+template <int B, int WG, int STAGES>
+__global__ __launch_bounds__(128 * WG) void gemm_deep_group_kernel(const GroupArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[STAGES * 2 * B * DK];
   int p = 0;
   for (int i = 1; i < a.n; ++i)
     if (int(blockIdx.x) >= a.first[i]) p = i;
   const GemmArgs& g = a.g[p];
   const int block = int(blockIdx.x) - a.first[p];
   switch (a.kind[p]) {
-    case kGroupNt: deep_tile<true, true, ntp::EPI_BF16, 128, 128, 2, 4, 5>(g, block, ring); break;
-    case kGroupNn: deep_tile<true, false, ntp::EPI_BF16, 128, 128, 2, 4, 5>(g, block, ring); break;
-    case kGroupTn: deep_tile<false, false, ntp::EPI_F32, 128, 128, 2, 4, 5>(g, block, ring); break;
-    default: deep_tile<false, false, ntp::EPI_F32_ACCUM, 128, 128, 2, 4, 5>(g, block, ring); break;
+    case kGroupNt: deep_tile<true, true, ntp::EPI_BF16, B, B, 2, WG, STAGES>(g, block, ring); break;
+    case kGroupNn: deep_tile<true, false, ntp::EPI_BF16, B, B, 2, WG, STAGES>(g, block, ring); break;
+    case kGroupTn: deep_tile<false, false, ntp::EPI_F32, B, B, 2, WG, STAGES>(g, block, ring); break;
+    default: deep_tile<false, false, ntp::EPI_F32_ACCUM, B, B, 2, WG, STAGES>(g, block, ring); break;
   }
 }
 

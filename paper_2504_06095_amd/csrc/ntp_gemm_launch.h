@@ -39,10 +39,10 @@ int launch_pp_nt(GemmArgs g, int epilogue, int tile, hipStream_t s);
 int launch_pp_nn(GemmArgs g, int epilogue, int tile, hipStream_t s);
 int launch_pp_tn(GemmArgs g, int epilogue, int tile, hipStream_t s);
 // Deep-pipelined kernel (ntp_gemm_deep.h), one workgroup per tile and K chunk (g.k_splits, g.k_chunk as above).
-enum DeepForm : int { kNotDeep = 0, kDeep5, kDeep2, kDeepWide };  // 128 x 128 with five / two K tiles in LDS, 128 x 256 with three
+enum DeepForm : int { kNotDeep = 0, kDeep5, kDeep2, kDeepWide, kDeepSmall };  // 128 x 128 with five / two K tiles in LDS, 128 x 256 and 64 x 64 with three
 int launch_deep(const GemmArgs& g, bool a_kc, bool b_kc, int epilogue, int form, hipStream_t s);
-// Up to three independent problems (no cut K axis; bf16 epilogue, fp32 ones for layout 2) in one launch of its 128 x 128 form.
-int launch_deep_group(const GemmArgs* g, const int* layout, const int* epilogue, int n, hipStream_t s);
+// Up to three independent problems (no cut K axis; bf16 epilogue, fp32 ones for layout 2) in one launch of its 128 x 128 or 64 x 64 form.
+int launch_deep_group(const GemmArgs* g, const int* layout, const int* epilogue, int n, int form, hipStream_t s);
 int launch_ring_split_nt(GemmArgs g, int tile, hipStream_t s);
 int launch_ring_split_nn(GemmArgs g, int tile, hipStream_t s);
 int launch_ring_split_tn(GemmArgs g, int epilogue, int tile, hipStream_t s);

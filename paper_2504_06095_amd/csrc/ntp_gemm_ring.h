@@ -137,7 +137,7 @@ struct FragAddr {
 #pragma unroll
       for (int i = 0; i < NF; ++i) {
         const int col = rbase + i * 16 + (s & 3) * 4;
-        o[i] = uint32_t(k * R + (((col >> 3) ^ kline_swz(k)) * 8) + (col & 7));
+        o[i] = uint32_t(k * R + (((col >> 3) ^ kline_swz(k, R)) * 8) + (col & 7));
       }
     }
   }

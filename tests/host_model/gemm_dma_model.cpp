@@ -20,6 +20,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "ntp_gemm_addr.h"
@@ -218,7 +219,7 @@ static bool check_deep(const char* what, int64_t ld, int row0, int lim, int K_to
   return true;
 }
 
-static bool run_deep(bool akc, bool bkc, int bn, const Shape& s, int splits) {
+static bool run_deep(bool akc, bool bkc, int bm, int bn, const Shape& s, int splits) {
   const bool nn = akc && !bkc;
   if (akc && s.K % 8 && !nn) return true;  // not this kernel's: only a row-parallel GEMM's A has its pad columns zeroed
   const int a_cols = akc ? s.K : s.M, b_cols = bkc ? s.K : s.N;
@@ -235,13 +236,15 @@ static bool run_deep(bool akc, bool bkc, int bn, const Shape& s, int splits) {
     const int64_t first = int64_t(sp) * chunk;
     const int Kc = imin(chunk, s.K - int(first));
     for (int side = 0; side < 2; ++side) {
-      const int b = side ? bn : 128, lim = side ? s.N : s.M, tiles = (lim + b - 1) / b;
+      const int b = side ? bn : bm, lim = side ? s.N : s.M, tiles = (lim + b - 1) / b;
       const bool kc = side ? bkc : akc;
       for (int tile : {0, tiles / 2, tiles - 1}) {
         ++g_cases;
         const int64_t ld = side ? ldb : lda, ext = side ? b_ext : a_ext, con = side ? b_con : a_con;
         const char* const what = side ? "B" : "A";
-        const bool ok = b == 128 ? (kc ? check_deep<true, 128>(what, ld, tile * b, lim, s.K, first, Kc, ext, con)
+        const bool ok = b == 64 ? (kc ? check_deep<true, 64>(what, ld, tile * b, lim, s.K, first, Kc, ext, con)
+                                      : check_deep<false, 64>(what, ld, tile * b, lim, s.K, first, Kc, ext, con))
+                        : b == 128 ? (kc ? check_deep<true, 128>(what, ld, tile * b, lim, s.K, first, Kc, ext, con)
                                        : check_deep<false, 128>(what, ld, tile * b, lim, s.K, first, Kc, ext, con))
                                  : (kc ? check_deep<true, 256>(what, ld, tile * b, lim, s.K, first, Kc, ext, con)
                                        : check_deep<false, 256>(what, ld, tile * b, lim, s.K, first, Kc, ext, con));
@@ -274,10 +277,10 @@ int main(int argc, char** argv) {
                                {777, 1096, 1001, 0, 40}, {1001, 1096, 777, 0, 0}, {752, 160, 9544, 0, 0}, {129, 513, 2051, 64, 8}, {128, 256, 63, 0, 0}, {64, 8, 65, 0, 0}};
   if (!padded)
     for (const auto& lay : layouts)
-      for (int bn : {128, 256})
+      for (const auto& t : {std::pair<int, int>{64, 64}, {128, 128}, {128, 256}})
         for (const Shape& s : deep_shapes)
           for (int splits = 1; splits <= 16; ++splits)
-            if (!run_deep(lay[0], lay[1], bn, s, splits)) return 1;
+            if (!run_deep(lay[0], lay[1], t.first, t.second, s, splits)) return 1;
   if (padded) printf("OVERRUN %lld\n", (long long)g_overrun);
   else printf("OK %lld %lld\n", (long long)g_cases, (long long)g_loads);
   return 0;

@@ -58,6 +58,36 @@ def test_attn_proj_deep(names, M, H, n_q, n_kv, d, tp, rank):
         assert e <= TOL, f"{k}: rel err {e:.3e}"
 
 
+# 64 x 64 tiles (where a workspace is set): M and N around multiples of 64, K at six K tiles and off them, cut and whole; the last two:
+# gradients over more than 24 K tiles, in the shared launch
+@pytest.mark.parametrize("M,H,n_r,group", [(65, 448, 513, False), (193, 1288, 450, False), (450, 1000, 385, False), (127, 4104, 383, False), (1601, 520, 193, True),
+                                           (1999, 264, 449, True)])
+def test_mlp_deep_small_tiles(M, H, n_r, group):
+    import torch
+    import paper_2504_06095_amd as N
+    print(f"[gpu-case] deep GEMM MLP, 64 x 64 tiles M={M} H={H} n_r={n_r}", file=sys.stderr, flush=True)
+    ws = torch.full((8 << 20,), float("nan"), dtype=torch.float32, device="cuda")
+    N.ntp_set_workspace(ws)
+    N.ntp_kernel_timing_enable(1)
+    N.ntp_kernel_timing_read()
+    try:
+        case = MlpCase(M, H, n_r, 1, 0)
+        got, raw = case.run_gpu(accumulate_twice=True)
+        picked = [r["name"] for r in N.ntp_kernel_timing_read()]
+    finally:
+        N.ntp_kernel_timing_enable(0)
+        N.ntp_set_workspace(None)
+    assert any("64x64d" in n for n in picked if "group" not in n) and ("gemm_group_64x64d" in picked) == group, picked
+    want = case.oracle()
+    want["dA_t"], want["dB"] = 2 * want["dA_t"], 2 * want["dB"]
+    for k in MLP_NAMES:
+        e = rel_err(got[k], want[k])
+        assert np.isfinite(got[k]).all() and e <= TOL, f"{k}: rel err {e:.3e}"
+    pad = -(-n_r // 8) * 8
+    for k in ("P", "Y", "dP"):
+        assert (raw[k][:, n_r:pad].float().cpu().numpy() == 0).all(), k
+
+
 # the forms above one tile per compute unit: two K tiles in LDS ("d2"), and 128 x 256 tiles with three
 @pytest.mark.parametrize("M,H,n_r,form", [(129, 8200, 1090, "128x128w8d2"), (130, 4104, 2000, "128x128w8d2"), (2900, 1032, 1501, "128x128w8d2"),
                                           (1290, 1288, 3300, "128x256d"), (577, 1000, 9001, "128x128w8d2")])
