@@ -181,6 +181,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs g, co
 constexpr int kDeepTile = 8, kDeepWideTile = 6;  // indices of the deep-pipelined kernel's tile shapes
 constexpr int kMaxDeepSplits = 16;
 constexpr double kSmallTileUs = 0.225;  // a K tile of the 64 x 64 form
+constexpr int kMaxSmallChunk = 31;      // K tiles: a workspace is set so that K axes of 2048 and more are cut, and they still are (2048 x 584 over
+                                        // K = 2048 would take 16.2 us in one piece, 20.3 in three)
 constexpr double kGroupSmallFrom = 24;  // K tiles
 
 // Whether the deep-pipelined kernel takes over from `old`, and in how many K chunks.  Measured over 45 random shapes of up to one
@@ -225,13 +227,13 @@ SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int layout, int64
   }
   // Where the caller has set a workspace, the same with 64 x 64 tiles, which need a cut less often: up to three on a compute unit at a time,
   // which share its rate (both sides in ntp_gemm_deep.h; without a workspace, and below six K tiles, whose launches are mostly fixed
-  // costs, the tiles stay 128 x 128)
-  if (!small_ok || ws_bytes <= 0 || ktiles < 6) return best;
+  // costs, the tiles stay 128 x 128; so do weight gradients, which share a launch where they are small)
+  if (!small_ok || layout == 2 || ws_bytes <= 0 || ktiles < 6) return best;
   const double small = double((M + 63) / 64) * double((N + 63) / 64) / double(cus);
   for (int sp = 1; sp <= kMaxSplits; ++sp) {
     const int64_t chunk_tiles = (ktiles + sp - 1) / sp;
     if (sp > 1 && (chunk_tiles < 4 || int64_t(sp) * M * ldw * 4 > ws_bytes)) break;
-    if ((sp - 1) * chunk_tiles * 64 >= K) continue;  // the last chunk would be empty
+    if ((sp - 1) * chunk_tiles * 64 >= K || chunk_tiles > kMaxSmallChunk) continue;  // (the last chunk would be empty)
     const double t = kSmallTileUs * double(chunk_tiles) * std::max(1.0, small * sp) + (sp > 1 ? 3.5 + double(M) * double(ldw) * (4.0 * sp + 4.0) / 4.4e6 : 0.0);
     if (t < best_t) {
       best_t = t;
