@@ -19,6 +19,11 @@
 
 constexpr int kWideRing = 4;                      // tile pairs in the LDS ring
 constexpr uint32_t kWideBuf = 2 * kDmaTile * 2;   // bytes of one: two 64-row tiles
+// Behind the ring of the dK/dV walk: zeros where the immediate offsets of the transposed reads (multiples of 4 KB below kWideBuf) lead from
+// the ring's end, 16 bytes each, and behind the first four of them the row values of the four buffers.
+constexpr uint32_t kWideStep = 4096;
+constexpr uint32_t kWideLds = kWideRing * kWideBuf + kWideBuf - kWideStep + 16;  // bytes
+static_assert(16 + 4 * kBKV * 4 <= kWideStep && kWideRing * kWideStep <= kWideBuf && kWideLds <= 160 * 1024, "LDS of the dK/dV walk");
 
 // f is called with 0 .. N - 1 as compile-time constants
 template <int N, typename F, int... I>
@@ -54,6 +59,12 @@ template <int N>
 __device__ __forceinline__ void wait_dma() {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+#endif
+}
+
+__device__ __forceinline__ void lds_stored() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #endif
 }
 
@@ -124,13 +135,17 @@ __device__ __forceinline__ attn_u32x4 negated(const attn_u32x4& v) { return v ^ 
 
 // Read addresses of a wavefront in buffer 0 of the ring: ak[s], the rows' (lane % 16) columns 32 s + 8 (lane / 16) ..; at[b],
 // transposed, the rows 4 (lane / 16) .. + 3 of column 16 b + lane % 16.  Other rows (multiples of 16) are immediates.
-__device__ __forceinline__ void wide_addresses(const uint16_t* ring, int lane, uint32_t (&ak)[4], uint32_t (&at)[8]) {
-  const uint32_t base = uint32_t(reinterpret_cast<uintptr_t>(ring));
+__device__ __forceinline__ void transposed_addresses(uint32_t base, int lane, uint32_t (&at)[8]) {
   const int lq = lane & 15, lh = lane >> 4, rv = lh * 4 + (lq >> 2);
 #pragma unroll
-  for (int s = 0; s < 4; ++s) ak[s] = base + uint32_t(lq) * 256u + ((uint32_t(s * 4 + lh) ^ row_swz(lq)) * 16u);
-#pragma unroll
   for (int b = 0; b < 8; ++b) at[b] = base + uint32_t(rv) * 256u + uint32_t(lq & 1) * 8u + ((uint32_t(b * 2 + ((lq & 3) >> 1)) ^ row_swz(rv)) * 16u);
+}
+__device__ __forceinline__ void wide_addresses(const uint16_t* ring, int lane, uint32_t (&ak)[4], uint32_t (&at)[8]) {
+  const uint32_t base = uint32_t(reinterpret_cast<uintptr_t>(ring));
+  const int lq = lane & 15, lh = lane >> 4;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) ak[s] = base + uint32_t(lq) * 256u + ((uint32_t(s * 4 + lh) ^ row_swz(lq)) * 16u);
+  transposed_addresses(base, lane, at);
 }
 // Bytes from the start of a tile in memory to what this lane's part of DMA instruction j of a wavefront brings: LDS chunk
 // (4 wave + j) 64 + lane of the tile.
@@ -156,9 +171,7 @@ __device__ __forceinline__ void store_wide_rows(const f32x4 (&acc)[8][2], float 
       for (int r = 0; r < 4; ++r) o[r] = ntp_gemm::f32_to_bf16(acc[b][rb][r] * factor);
       *reinterpret_cast<u16x4*>(lds + (rb * 16 + lq) * 128 + ((b * 2 + (lh >> 1)) ^ lq) * 8 + (lh & 1) * 4) = o;
     }
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#endif
+  lds_stored();
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int row = i * 4 + lh;
@@ -189,7 +202,7 @@ __device__ __forceinline__ bool wide_place(const CoreBwdArgs& a, uint32_t place,
   return true;
 }
 
-__device__ __forceinline__ void bwd_dkv_wide_body(const CoreBwdArgs& a, uint32_t place, bool is_short, uint16_t* ring, float* sLD) {
+__device__ __forceinline__ void bwd_dkv_wide_body(const CoreBwdArgs& a, uint32_t place, bool is_short, uint16_t* ring) {
   constexpr int D = 128;
   int sh, kt, part;
   if (!wide_place(a, place, is_short, true, uint32_t(a.n_seq) * uint32_t(a.kv_cnt), sh, kt, part)) return;
@@ -204,7 +217,10 @@ __device__ __forceinline__ void bwd_dkv_wide_body(const CoreBwdArgs& a, uint32_t
   wide_dma_offsets(a.lddc, wave, lane, voffg);
   uint32_t ak[4], at[8];
   wide_addresses(ring, lane, ak, at);
-  uint32_t al = uint32_t(reinterpret_cast<uintptr_t>(sLD)) + uint32_t(lh) * 16u;
+  uint16_t* const tail = ring + kWideRing * kWideBuf / 2;
+  const uint32_t zeros = uint32_t(reinterpret_cast<uintptr_t>(tail));
+  uint32_t al = zeros + 16u + uint32_t(lh) * 16u;
+  if (threadIdx.x < 8) *reinterpret_cast<attn_u32x4*>(tail + threadIdx.x * (kWideStep / 2)) = attn_u32x4{0, 0, 0, 0};
   // the local query heads that read this KV head are consecutive
   const int64_t group_first = int64_t(a.kv_off + g) * a.group - a.q_off;
   const int head_first = int(max(group_first, int64_t(0)));
@@ -240,7 +256,7 @@ __device__ __forceinline__ void bwd_dkv_wide_body(const CoreBwdArgs& a, uint32_t
     };
     auto fetch_part = [&](int to, int i) {
       if (i == 8) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsL, (ntp_gemm::lds_void*)(sLD + to * (4 * kBKV) + wave * kBKV), 4, uint32_t(lane) * 4u, uint32_t(f_t) * (kBKV * 4), 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsL, (ntp_gemm::lds_void*)(tail + to * (kWideStep / 2) + 8 + wave * (kBKV * 2)), 4, uint32_t(lane) * 4u, uint32_t(f_t) * (kBKV * 4), 0, 0);
         return;
       }
       uint16_t* dst = ring + to * (kWideBuf / 2) + (i & 1) * kDmaTile + (wave * 4 + (i >> 1)) * 512;
@@ -257,9 +273,9 @@ __device__ __forceinline__ void bwd_dkv_wide_body(const CoreBwdArgs& a, uint32_t
         }
       }
     };
-    // bytes from the buffer in hand to the next one, of the tiles and of the row values (a 32nd of it)
+    // bytes from the buffer in hand to the next one, of the tiles and of the row values (an eighth of it)
     auto to_next = [&]() { return buf == kWideRing - 1 ? -int32_t((kWideRing - 1) * kWideBuf) : int32_t(kWideBuf); };
-    static_assert(kWideBuf == 32 * (4 * kBKV * 4), "row values");
+    static_assert(kWideBuf == 8 * kWideStep, "row values");
 
     // the first unit first, then the owned rows, then two more units
     fetch_head();
@@ -289,6 +305,7 @@ __device__ __forceinline__ void bwd_dkv_wide_body(const CoreBwdArgs& a, uint32_t
 #pragma unroll
     for (int i = 0; i < 8; ++i) vf[i / 4][i % 4] = negated(vf[i / 4][i % 4]);
     wait_dma<18>();
+    lds_stored();
     __builtin_amdgcn_s_barrier();
     owned_ready(kf);
     owned_ready(vf);
@@ -337,8 +354,15 @@ __device__ __forceinline__ void bwd_dkv_wide_body(const CoreBwdArgs& a, uint32_t
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
               const int qrow = qbase + qb * 16 + lh * 4 + r, key = k0 + kb * 16 + lq;
-              sc[qb][kb][r] = qrow >= S || (a.causal && key > qrow) ? -INFINITY : sc[qb][kb][r];
+              const bool masked = qrow >= S || (a.causal && key > qrow);
+              sc[qb][kb][r] = masked ? -INFINITY : sc[qb][kb][r];
+              dp[qb][kb][r] = masked ? 0.f : dp[qb][kb][r];
             }
+        // (a row whose log-sum-exp is a NaN or an infinity has weights of zero all the same where it is masked)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) nl[qb][r] = fminf(nl[qb][r], FLT_MAX);
       }
       __builtin_amdgcn_sched_barrier(0);
       attn_u32x4 pf[2], dsf[2];
@@ -398,7 +422,7 @@ __device__ __forceinline__ void bwd_dkv_wide_body(const CoreBwdArgs& a, uint32_t
         if constexpr (i >= 48 && i % 2 == 0) f[(i - 48) / 2] = lds_frag_b128<CO + (((i - 48) / 2) & 1) * 4096>(ak[(i - 48) / 4]);  // of the half after the next
         if constexpr (i == 53 || i == 55) dl[(i - 53) / 2] = __builtin_bit_cast(f32x4, lds_frag_b128<256 + H * 128 + (i - 53) * 32>(al));
         // on to the next buffer
-        if constexpr (H == 0 && i == 47) al += uint32_t(step / 32);
+        if constexpr (H == 0 && i == 47) al += uint32_t(step / 8);
         if constexpr (H == 0 && i >= 47 && i < 60 && i % 4 == 3) ak[(i - 47) / 4] += uint32_t(step);
         if constexpr (H == 1 && i >= 48 && i < 56) at[i - 48] += uint32_t(step);
         // DMA
@@ -438,8 +462,18 @@ __device__ __forceinline__ void bwd_dkv_wide_body(const CoreBwdArgs& a, uint32_t
 
     for (int w = u_lo; w < u_hi; ++w) {
       step = to_next();
+      // Every query row of the tile comes before this wavefront's keys (the first unit of a head, the upper two wavefronts): all weights are
+      // zero, and the transposed fragments are read from zeros, so that they do not meet infinities and NaNs of rows that do not see these keys.
+      const bool unseen = a.causal && t * kBKV + kBKV - 1 < k0;
+      if (__builtin_expect(unseen, 0)) {
+#pragma unroll
+        for (int b = 0; b < 8; ++b) at[b] = zeros;
+      }
       half(std::integral_constant<int, 0>{}, s_a, p_a, s_b, p_b);
       half(std::integral_constant<int, 1>{}, s_b, p_b, s_a, p_a);
+      if (__builtin_expect(unseen, 0)) {
+        transposed_addresses(zeros - kWideRing * kWideBuf + uint32_t((buf + 1) & 3) * kWideBuf, lane, at);
+      }
       if (++t == q_tiles) t = q_first;
       buf = (buf + 1) & 3;
     }
@@ -660,7 +694,9 @@ __device__ __forceinline__ void bwd_dq_wide_body(const CoreBwdArgs& a, uint32_t 
       });
     };
 
-    for (int t = t_lo; t < t_hi; ++t) {
+    // under the mask the lower two wavefronts' rows see nothing of the last tile: no products there (see bwd_dkv_wide_body), only the others' barrier
+    const int t_own = a.causal ? min(t_hi, ((q0 + 31) >> 6) + 1) : t_hi;
+    for (int t = t_lo; t < t_own; ++t) {
       step = buf == kWideRing - 1 ? -int32_t((kWideRing - 1) * kWideBuf) : int32_t(kWideBuf);
       half(std::integral_constant<int, 0>{}, t, s_a, p_a, s_b, p_b);
       half(std::integral_constant<int, 1>{}, t, s_b, p_b, s_a, p_a);
@@ -670,6 +706,7 @@ __device__ __forceinline__ void bwd_dq_wide_body(const CoreBwdArgs& a, uint32_t 
     arrived<0>(f[0], f[1], f[2], f[3]);
     with(f[4], f[5], f[6], f[7]);
     wait_dma<0>();
+    for (int t = max(t_lo, t_own); t < t_hi; ++t) __builtin_amdgcn_s_barrier();
   }
   acc_settle(acc);
 
@@ -693,10 +730,9 @@ __device__ __forceinline__ void bwd_dq_wide_body(const CoreBwdArgs& a, uint32_t 
 // One kind of workgroups, `n_long` of them in the first section.
 __global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads), amdgpu_waves_per_eu(1, 1))) void
 attn_core_bwd_dkv_wide_kernel(const CoreBwdArgs a, const uint32_t n_long) {
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[kWideRing * kWideBuf / 2];
-  __shared__ __attribute__((aligned(1024))) float row_values[kWideRing * 4 * kBKV];
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[kWideLds / 2];
   const bool is_short = blockIdx.x >= n_long;
-  bwd_dkv_wide_body(a, is_short ? blockIdx.x - n_long : blockIdx.x, is_short, ring, row_values);
+  bwd_dkv_wide_body(a, is_short ? blockIdx.x - n_long : blockIdx.x, is_short, ring);
 }
 
 __global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads), amdgpu_waves_per_eu(1, 1))) void
@@ -710,8 +746,7 @@ attn_core_bwd_dq_wide_kernel(const CoreBwdArgs a, const uint32_t n_long) {
 // and the short dK/dV walks, these two in either order, and the short dQ walks.
 __global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads), amdgpu_waves_per_eu(1, 1))) void
 attn_core_bwd_both_wide_kernel(const CoreBwdArgs adq, const CoreBwdArgs adkv, const uint32_t n_dq, const uint32_t n_dkv, const uint32_t kv_first) {
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[kWideRing * kWideBuf / 2];
-  __shared__ __attribute__((aligned(1024))) float row_values[kWideRing * 4 * kBKV];
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[kWideLds / 2];
   uint32_t b = blockIdx.x;
   bool dkv = b < n_dkv, is_short = false;
   if (!dkv) {
@@ -730,6 +765,6 @@ attn_core_bwd_both_wide_kernel(const CoreBwdArgs adq, const CoreBwdArgs adkv, co
       }
     }
   }
-  if (dkv) bwd_dkv_wide_body(adkv, b, is_short, ring, row_values);
+  if (dkv) bwd_dkv_wide_body(adkv, b, is_short, ring);
   else bwd_dq_wide_body(adq, b, is_short, ring);
 }

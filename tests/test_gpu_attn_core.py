@@ -247,6 +247,46 @@ def test_attn_core_bwd_32_rows_per_wavefront(workspace, opts, n_q, n_kv, tp, ran
     _bwd_case(n_q, n_kv, tp, rank, 128, n_seq, S, causal, seed=41, pad=pad)
 
 
+@pytest.mark.parametrize("launches", [1, 2], ids=["two_launches", "one_launch"])
+@pytest.mark.parametrize("parts", [1, 3])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")], ids=["inf", "nan"])
+def test_attn_core_bwd_non_finite_rows_reach_no_further_with_32_rows(workspace, opts, value, parts, launches):
+    """Causal, an infinity or a NaN in one row of Q, K, V or dC (in each half of a 64-row tile, each tile of a 128-row one, the last row), or in
+    a row's log-sum-exp alone: whatever the kernels with 32 rows per wavefront return non-finite, those with 16 do too, and the
+    rest agrees with them."""
+    import torch
+    import paper_2504_06095_amd as N
+    _say(f"attn core bwd, one row {value}, parts={parts} launches={launches}")
+    opts(K.NTP_OPT_ATTN_PARTS, parts)
+    opts(K.NTP_OPT_ATTN_BWD_LAUNCHES, launches)
+    d, n_q, S = 128, 2, 333
+    plan = N.ntp_attn_shard_plan(n_q, 1, d, 1, 0)
+    shape = N.attn_core_shape(1, S, plan, n_q, True)
+    g = torch.Generator("cuda").manual_seed(7)
+    QKV0, dC0 = (torch.empty(S, w, device="cuda").normal_(generator=g).bfloat16() for w in (plan["w_qkv"], plan["w_o"]))
+    for what in ("Q", "K", "V", "dC", "LSE"):
+        for row in (0, 10, 40, 70, 127, 128, 161, 200, 255, 300, 332):
+            QKV, dC = QKV0.clone(), dC0.clone()
+            if what == "dC":
+                dC[row, 5] = value
+            elif what != "LSE":
+                QKV[row, {"Q": 0, "K": n_q, "V": n_q + 1}[what] * d + 5] = value
+            C, LSE, Delta = torch.empty_like(dC), torch.empty(n_q, S, device="cuda"), torch.empty(n_q, S, device="cuda")
+            N.ntp_attn_core_shard_fwd(shape, QKV, C, LSE)
+            if what == "LSE":
+                LSE[0, row] = value
+            got = {}
+            for copy in (2, 3):
+                opts(K.NTP_OPT_ATTN_COPY, copy)
+                got[copy] = torch.full_like(QKV, float("nan"))
+                N.ntp_attn_core_shard_bwd(shape, QKV, C, dC, LSE, Delta, got[copy])
+            bad, want_bad = (~torch.isfinite(got[c].float()) for c in (3, 2))
+            further = bad & ~want_bad
+            assert not further.any(), (what, row, sorted(set(torch.nonzero(further)[:, 0].tolist())))
+            a, b = (torch.where(want_bad, 0.0, got[c].double()) for c in (3, 2))
+            assert (a - b).norm() <= Hh.TOL * b.norm(), (what, row)
+
+
 # 64-row tiles: 1728 / 576 workgroups of the two kinds in pairs of 256 and what is left over (causal; full 3456 / 1152), 1728 / 576 over eight tiles
 # each (causal 864 / 288), and fewer than one chunk
 @pytest.mark.parametrize("launches", [0, 1, 2], ids=["auto", "two_launches", "one_launch"])
