@@ -71,9 +71,11 @@ __device__ __forceinline__ void lds_stored() {
 // One matrix instruction with the registers where these kernels want them (the compiler, left to itself, moves
 // accumulators between the two halves of the register file in the loop): scores in vector registers, owned operands and
 // gradient sums in accumulation registers.  The compiler does not know an instruction in assembly as a matrix
-// instruction, so the distances are kept by the order of the code: a vector instruction reads a result 16 matrix
-// instructions after its last one at the earliest, packed weights are ready a slot before they are read, and what an
-// accumulator starts from (mfma_from) comes from LDS or from before the loop and is not overwritten for 16 more.
+// instruction, so the distances that the hardware leaves to the program are kept here (and checked in the compiler's output by
+// tests/test_host_attn_schedule.py).  A vector instruction reads a result 16 matrix instructions after its last one at the earliest, but for the
+// first half of a walk, before which scores_settle waits.  Packed weights, which two wait states must follow, are ready (operand_ready) a
+// whole slot, at least a matrix instruction and an LDS read, before the one that reads them.  What an accumulator starts from
+// (mfma_from) comes from LDS or from before the loop and is not overwritten for 16 matrix instructions more.
 __device__ __forceinline__ void mfma_zero(f32x4& d, const attn_u32x4& x, const attn_u32x4& own) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(x), "a"(own));
@@ -103,11 +105,17 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
   v[1] = static_cast<__bf16>(hi);
   return __builtin_bit_cast(uint32_t, v);
 }
-// The packed weights are computed by here (and not next to the matrix instructions that read them)
+// What the vector unit makes for a matrix instruction is computed by here.
 template <typename V>
 __device__ __forceinline__ void operand_ready(V& w) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("" : "+v"(w));
+#endif
+}
+// Scores may be read by vector instructions after this.
+__device__ __forceinline__ void scores_settle(f32x4 (&s)[2][2], f32x4 (&p)[2][2]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_nop 15" : "+v"(s[0][0]), "+v"(s[0][1]), "+v"(s[1][0]), "+v"(s[1][1]), "+v"(p[0][0]), "+v"(p[0][1]), "+v"(p[1][0]), "+v"(p[1][1]));
 #endif
 }
 // The owned operands are in place before the first matrix instruction reads them
@@ -332,6 +340,7 @@ __device__ __forceinline__ void bwd_dkv_wide_body(const CoreBwdArgs& a, uint32_t
       else if constexpr (i < 20) mfma_from(p_a[qb][kb], f[i / 2], vf[kb][s], dl[qb]);
       else mfma_score(p_a[qb][kb], f[i / 2], vf[kb][s]);
     });
+    scores_settle(s_a, p_a);
     // what the steady state has in flight at the start of a half
     unrolled<4>([&](auto j) { f[j] = lds_frag_b128<8192 + (j & 1) * 4096>(ak[j / 2]); });
     unrolled<2>([&](auto j) { dl[j] = __builtin_bit_cast(f32x4, lds_frag_b128<256 + 128 + j * 64>(al)); });
@@ -408,8 +417,8 @@ __device__ __forceinline__ void bwd_dkv_wide_body(const CoreBwdArgs& a, uint32_t
           else if constexpr (i < 20) mfma_from(dn[qb][kb], f[i / 2], vf[kb][s], dl[qb]);  // starts as delta, the values' signs are flipped: delta - dP
           else mfma_score(dn[qb][kb], f[i / 2], vf[kb][s]);
         } else if constexpr (i < 48) {
-          constexpr int b = (i - 32) / 2;
-          mfma_grad(dv[b][i % 2], tg[2 * b], tg[2 * b + 1], pf[i % 2]);
+          constexpr int b = (i - 32) / 4 * 2 + i % 2, kb = (i / 2) % 2;  // (the first key block's weights in slots 32 and 33: the second's are packed in slot 32)
+          mfma_grad(dv[b][kb], tg[2 * b], tg[2 * b + 1], pf[kb]);
         } else {
           constexpr int b = (i - 48) / 2;
           mfma_grad(dk[b][i % 2], tq[2 * b], tq[2 * b + 1], dsf[i % 2]);
@@ -613,6 +622,7 @@ __device__ __forceinline__ void bwd_dq_wide_body(const CoreBwdArgs& a, uint32_t 
       else if constexpr (i < 20) mfma_from(p_a[kb][qb], f[i / 2], gf[qb][s], dl[qb]);
       else mfma_score(p_a[kb][qb], f[i / 2], gf[qb][s]);
     });
+    scores_settle(s_a, p_a);
     // what the steady state has in flight at the start of a half
     unrolled<8>([&](auto j) { f[j] = lds_frag_b128<8192 + (j & 1) * 4096>(ak[j / 2]); });
 
