@@ -542,6 +542,8 @@ typedef struct ntp_attn_core_choice {
   int32_t fwd_rows_per_wavefront, fwd_parts, dq_parts, dkv_parts;
 } ntp_attn_core_choice_t;
 int ntp_attn_core_choice(const ntp_handle_t* h, const ntp_attn_core_shape_t* shape, ntp_attn_core_choice_t* out);
+/* The same for the backward kernels: *rows_per_wavefront = 16 or 32 query rows (dQ) or keys (dK, dV) per wavefront. */
+int ntp_attn_core_bwd_rows(const ntp_handle_t* h, const ntp_attn_core_shape_t* shape, int32_t* rows_per_wavefront);
 
 /* Measurement aid: a plain dense device-to-device copy of `bytes` bytes (dst, src:
  * device, 16-byte aligned, bytes % 16 == 0, not overlapping) by a kernel named

@@ -7,7 +7,7 @@ if it has not been built.
 """
 from . import binding  # noqa: F401
 from .binding import (  # noqa: F401
-    NtpError, ReshardPlan, attn_core_shape, ntp_attn_core_shard_fwd, ntp_attn_core_shard_bwd, ntp_attn_core_choice, ntp_reshard_row_segments, row_segments, ntp_mlp_shard_bwd_resharded,
+    NtpError, ReshardPlan, attn_core_shape, ntp_attn_core_shard_fwd, ntp_attn_core_shard_bwd, ntp_attn_core_choice, ntp_attn_core_bwd_rows, ntp_reshard_row_segments, row_segments, ntp_mlp_shard_bwd_resharded,
     ntp_attn_proj_shard_bwd_resharded, ntp_comp_sync_plan, ntp_gemm_choice, ntp_reshard_plan_create, ntp_attn_proj_shard_bwd, ntp_attn_proj_shard_fwd, ntp_attn_shard_plan, ntp_calibration_copy,
     ntp_kernel_timing_enable, ntp_kernel_timing_read, ntp_mlp_shard_bwd,
     ntp_mlp_shard_fwd, ntp_reshard_grad, ntp_reshard_segments, ntp_set_workspace, ntp_shard_plan, ntp_version, tensor_spec,

@@ -61,7 +61,7 @@ EXPORTS = (
     "ntp_reshard_plan_table", "ntp_reshard_plan_prepare", "ntp_reshard_plan_run", "ntp_reshard_plan_destroy", "ntp_reshard_row_segments",
     "ntp_mlp_shard_bwd_resharded", "ntp_attn_proj_shard_bwd_resharded", "ntp_attn_core_shard_fwd", "ntp_attn_core_shard_bwd",
     "ntp_set_workspace", "ntp_gemm_choice", "ntp_attn_core_choice", "ntp_create", "ntp_destroy", "ntp_device_info",
-    "ntp_set_option", "ntp_workspace_bytes", "ntp_attn_proj_shard_fwd_static", "ntp_replica_sum", "ntp_probe_rates",
+    "ntp_set_option", "ntp_workspace_bytes", "ntp_attn_proj_shard_fwd_static", "ntp_replica_sum", "ntp_probe_rates", "ntp_attn_core_bwd_rows",
 )
 
 
@@ -185,6 +185,7 @@ def lib() -> C.CDLL:
         L.ntp_set_workspace.argtypes = [vp, vp, i64]
         L.ntp_gemm_choice.argtypes = [vp, C.c_int32, i64, i64, i64, C.POINTER(GemmChoice)]
         L.ntp_attn_core_choice.argtypes = [vp, C.POINTER(AttnCoreShape), C.POINTER(AttnCoreChoice)]
+        L.ntp_attn_core_bwd_rows.argtypes = [vp, C.POINTER(AttnCoreShape), C.POINTER(C.c_int32)]
         for name in EXPORTS:
             getattr(L, name)  # AttributeError if a declared symbol is not exported
         _lib = L
@@ -633,3 +634,10 @@ def ntp_attn_core_choice(shape, handle=None) -> dict:
     out = AttnCoreChoice()
     _check(lib().ntp_attn_core_choice(_h(handle), C.byref(shape), C.byref(out)), "ntp_attn_core_choice")
     return {n: getattr(out, n) for n, _ in AttnCoreChoice._fields_}
+
+
+def ntp_attn_core_bwd_rows(shape, handle=None) -> int:
+    """Rows per wavefront (16 or 32) of the attention core's backward kernels for an AttnCoreShape (host only)."""
+    rows = C.c_int32()
+    _check(lib().ntp_attn_core_bwd_rows(_h(handle), C.byref(shape), C.byref(rows)), "ntp_attn_core_bwd_rows")
+    return rows.value

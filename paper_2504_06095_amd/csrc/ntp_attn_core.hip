@@ -2248,6 +2248,37 @@ struct CoreChoice {
   bool bwd_both;         // both backward kernels go out as one launch
   int64_t dkv_ws_offset; // then: byte offset of the dK/dV parts in the workspace (behind the dQ parts)
 };
+// (128-row, 64-row) tile pairs of a launch of the backward kernels with 32 rows per wavefront
+int64_t wide_pairs(const ntp_attn_core_shape_t* s) {
+  const int64_t tiles = (s->seq_len + kBKV - 1) / kBKV, own = (tiles + 1) / 2;
+  return (s->causal ? own * tiles - own * (own - 1) : own * tiles) * s->n_seq * s->q_cnt;
+}
+// Whether the backward kernels with 32 rows per wavefront (one workgroup of 128 rows per compute unit) are the faster ones.  Their
+// products take two thirds of the time, but nothing overlaps a workgroup's way into and out of its walk (about 10 us; the 16-row kernels
+// have two workgroups per unit).  Measured over 225 shapes, with and without a workspace, as the ratio of the times, 32 rows to 16 rows; a launch's
+// work in products of tile pairs (4 a pair for dK/dV, 3 for dQ), a walk being those of one workgroup:
+//  - less than 8 pairs per unit (cut walks, whose parts are further ways in and out: 16, causal 20): 4 x 1024 causal cut 1.05, 28 x 900 causal 1.16,
+//    16 on 2 heads x 2048 causal cut 1.06; from there on 16 x 1024 unmasked 0.92, 3 on one x 4096 cut 0.80, causal 7 on 7 x 831 x 2 cut 0.85;
+//  - short walks, less than 24 products on average, causal 28 in launches of 4 and more workgroups per unit, 36 in those of 8 and more (whose ways
+//    in and out the 16-row kernels overlap best): 14 x 64 tokens of 150 sequences 1.65, 14 x 256 of 55 1.14, causal 14 x 512 of 22 1.19, 7 x 774
+//    of 16 1.16, 16 on 8 x 743 of 16 1.06; 14 x 512 of 5 0.92, 14 x 768 of 7 0.92, causal 14 x 768 of 4 0.89, 28 x 1300 0.69; from 18 on where the longest
+//    dK/dV walk, of grouped KV heads, is more than 1.5 even shares of the launch, and the 16-row kernels' pair of them longer still: 64 on 8 x 256 0.79;
+//  - fewer than 0.6 workgroups per unit: either form leaves units idle, 4 x 2048 1.06, 2 x 4096 1.03, one x 8192 1.01;
+//  - causal, ungrouped, up to 4 workgroups per unit with walks of less than 80 products: the 16-row kernels' workgroups are equal there, two per unit at
+//    a time, so that their rounds are full at 2 and 4 per unit: 14 x 2048 (1.75 per unit) 1.04, 16 x 1999 (2.0) 1.14, 8 x 2023 of 4 (4.0) 1.04;
+//    10 x 2048 (1.25) 0.89, 2 x 2113 of 8 (2.1) 0.68.
+// Over 385 shapes drawn afterwards the kernels taken are 9 % faster than 16 rows everywhere on the mean and at three shapes more than 4 % slower
+// (causal 28 on 14 x 809 of 2 1.19, 64 on 16 x 957 of 4 1.14, 7 x 1021 of 16 1.08).
+bool wide_pays(const ntp_attn_core_shape_t* s, int dq_parts, int dkv_parts, double cus) {
+  const double tiles = double((int64_t(s->seq_len) + kBKV - 1) / kBKV), own = std::ceil(tiles / 2), heads_per_kv = std::min(s->group, s->q_cnt);
+  const double per_unit = own * s->n_seq * (double(s->q_cnt) * dq_parts + double(s->kv_cnt) * dkv_parts) / cus, pairs = double(wide_pairs(s)) / cus;
+  if (pairs <= 0.0) return false;
+  const bool causal = s->causal != 0, cut = dq_parts > 1 || dkv_parts > 1;
+  const double walk = 7.0 * pairs / per_unit, longest = std::max(4.0 * heads_per_kv * tiles / dkv_parts, 3.0 * tiles / dq_parts);
+  if (pairs < (!cut ? 8.0 : causal ? 20.0 : 16.0) || per_unit < 0.6) return false;
+  if (!cut && causal && heads_per_kv == 1 && per_unit <= 4.0 && walk < 80.0 && per_unit / 2 >= 0.82 * std::ceil(per_unit / 2)) return false;
+  return walk >= (per_unit >= 8.0 ? 36.0 : causal && per_unit >= 4.0 ? 28.0 : 24.0) || (walk >= 18.0 && !cut && longest >= 1.5 * 7.0 * pairs);
+}
 CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_core_shape_t* s) {
   CoreChoice c{16, 1, 1, 1, 0, false, false, false, false, 0};
   const bool causal = s->causal != 0;
@@ -2276,21 +2307,14 @@ CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_cor
     c.fwd_parts = choose_parts_dma(h, ws_bytes, wq, bq, walk, bf, 2 * cus, wq * 4 >= cus * 3 ? 24 : 16, cus * 3 / 4);
     c.dq_parts = choose_parts_dma(h, ws_bytes, wq, bq, walk, bdq, cus, 10, cus * 3 / 8);
     c.dkv_parts = choose_parts_dma(h, ws_bytes, wk, bk, heads_per_kv * walk, bdkv, cus, 10, cus * 3 / 8);
-    // The backward kernels with 32 rows per wavefront (one workgroup of 128 rows per compute unit) need enough (128-row, 64-row) tile
-    // pairs per compute unit to pay for their way into and out of a walk, more where the walks are cut.  Both sides, one launch each,
-    // heads x tokens (pairs per unit): 14 x 8192 unmasked (448) 1583 -> 1275 us, causal (228) 895 -> 730; 14 x 2048 unmasked (28) 126 ->
-    // 101, causal (15) 72 -> 72; 28 x 1300 causal (13) 103 -> 71; 10 x 2048 causal (11) 67 -> 59; 16 x 1024 unmasked (8) 39 -> 36;
-    // cut: 3 on one KV head x 4096 unmasked (24) 108 -> 88, causal (12) 75 -> 77; 8 x 1024 causal (2) 36 -> 39.
-    const int64_t tiles2 = (tiles + 1) / 2;
-    const int64_t pairs = (causal ? tiles2 * tiles - tiles2 * (tiles2 - 1) : tiles2 * tiles) * s->n_seq * s->q_cnt;
-    const int64_t least = c.dq_parts > 1 || c.dkv_parts > 1 ? 16 : 8;
-    c.bwd_wide = h->opt[NTP_OPT_ATTN_COPY] == 3 || (h->opt[NTP_OPT_ATTN_COPY] == 0 && pairs >= least * cus);
+    c.bwd_wide = h->opt[NTP_OPT_ATTN_COPY] == 3 || (h->opt[NTP_OPT_ATTN_COPY] == 0 && wide_pays(s, c.dq_parts, c.dkv_parts, double(cus)));
     if (c.bwd_wide && !h->opt[NTP_OPT_ATTN_PARTS]) {
-      // ... and a cut costs them more: no more parts than bring a walk to 1.5 times an even share of the launch's work
-      // (4 products a pair for dK/dV, 3 for dQ)
-      const double even = 7.0 * double(pairs) / double(cus);
-      while (c.dq_parts > 1 && 3.0 * double(tiles) <= 1.5 * even * (c.dq_parts - 1)) --c.dq_parts;
-      while (c.dkv_parts > 1 && 4.0 * double(heads_per_kv * tiles) <= 1.5 * even * (c.dkv_parts - 1)) --c.dkv_parts;
+      // ... and a cut costs them more: no more parts than bring a walk to 1.3 times an even share of the launch's work
+      // (4 products a pair for dK/dV, 3 for dQ; to 1.5 times 8 heads on one KV head x 4096 causal took 1.03 of the 16-row kernels' time instead of
+      // 0.99, 14 on 2 x 4096 0.97 instead of 0.88, 32 on one x 2048 unmasked 0.80 instead of 0.75; to 1.1 times nothing changes)
+      const double even = 7.0 * double(wide_pairs(s)) / double(cus);
+      while (c.dq_parts > 1 && 3.0 * double(tiles) <= 1.3 * even * (c.dq_parts - 1)) --c.dq_parts;
+      while (c.dkv_parts > 1 && 4.0 * double(heads_per_kv * tiles) <= 1.3 * even * (c.dkv_parts - 1)) --c.dkv_parts;
     }
   } else {
     c.fwd_parts = choose_parts(h, ws_bytes, wq, bq, walk, bf, fill, 12, causal);
@@ -2344,6 +2368,14 @@ extern "C" int ntp_attn_core_choice(const ntp_handle_t* h, const ntp_attn_core_s
   if (!h || !out) return NTP_ERR_INVALID_ARG;
   const CoreChoice c = choose_core(h, h->workspace ? h->workspace_bytes : 0, s);
   *out = ntp_attn_core_choice_t{c.fwd_rows, c.fwd_parts, c.dq_parts, c.dkv_parts};
+  return NTP_OK;
+}
+
+extern "C" int ntp_attn_core_bwd_rows(const ntp_handle_t* h, const ntp_attn_core_shape_t* s, int32_t* out) {
+  const int st = check_core_shape(s);
+  if (st != NTP_OK) return st;
+  if (!h || !out) return NTP_ERR_INVALID_ARG;
+  *out = choose_core(h, h->workspace ? h->workspace_bytes : 0, s).bwd_wide ? 32 : 16;
   return NTP_OK;
 }
 
@@ -2487,6 +2519,11 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
     dkv_wgs = (first * s->n_seq * s->kv_cnt * cc.dkv_parts + 7) / 8 * 8;
   }
   const int64_t sections = cc.bwd_wide && s->causal ? 2 : 1;
+  auto timing_begin = [&](const char* which, bool cut, double products) {
+    char name[48];
+    snprintf(name, sizeof(name), "attn_core_bwd_%s%s%s", which, cc.bwd_wide ? "_r32" : "", cut ? "_cut" : "");
+    ntp::timing_begin(h, stream, name, products * pair_flops, 0.0);
+  };
   auto reduce_parts = [&](auto dkv, int64_t blocks) {
     constexpr bool DKV = decltype(dkv)::value;
     const dim3 rgrid(uint32_t((blocks * 64 * ((DKV ? 2 : 1) * s->head_dim / 4) + 255) / 256));
@@ -2508,7 +2545,7 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
     adkv.n_parts = cc.dkv_parts;
     adkv.pairs = k_pairs;
     adkv.part_sums = a.part_sums + cc.dkv_ws_offset / 4;
-    if (ntp::timing_on(h)) ntp::timing_begin(h, stream, cc.dq_parts > 1 || cc.dkv_parts > 1 ? "attn_core_bwd_both_cut" : "attn_core_bwd_both", 7.0 * pair_flops, 0.0);
+    if (ntp::timing_on(h)) timing_begin("both", cc.dq_parts > 1 || cc.dkv_parts > 1, 7.0);
     const bool wide = s->head_dim == 128;
     hipLaunchKernelGGL(wide ? attn_core_delta_kernel<128> : attn_core_delta_kernel<64>, dim3(uint32_t(delta_wgs)), dim3(256), 0, hs, a, M);
     ok = hipGetLastError() == hipSuccess;
@@ -2544,7 +2581,7 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
     // workgroups and each walks over up to seq_len / 64 key tiles: cut the walks then.
     a.n_parts = cc.dq_parts;
     a.pairs = q_pairs;
-    if (ntp::timing_on(h)) ntp::timing_begin(h, stream, a.n_parts > 1 ? "attn_core_bwd_dq_cut" : "attn_core_bwd_dq", 3.0 * pair_flops, 0.0);
+    if (ntp::timing_on(h)) timing_begin("dq", a.n_parts > 1, 3.0);
     const dim3 grid{uint32_t(sections * dq_wgs)};
     if (cc.bwd_wide) {
       hipLaunchKernelGGL(attn_core_bwd_dq_wide_kernel, grid, dim3(kThreads), 0, hs, a, uint32_t(dq_wgs));
@@ -2570,7 +2607,7 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
     a.tiles = key_tiles;
     a.n_parts = cc.dkv_parts;
     a.pairs = k_pairs;
-    if (ntp::timing_on(h)) ntp::timing_begin(h, stream, a.n_parts > 1 ? "attn_core_bwd_dkv_cut" : "attn_core_bwd_dkv", 4.0 * pair_flops, 0.0);
+    if (ntp::timing_on(h)) timing_begin("dkv", a.n_parts > 1, 4.0);
     const dim3 grid{uint32_t(sections * dkv_wgs)};
     if (cc.bwd_wide) {
       hipLaunchKernelGGL(attn_core_bwd_dkv_wide_kernel, grid, dim3(kThreads), 0, hs, a, uint32_t(dkv_wgs));

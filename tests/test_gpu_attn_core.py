@@ -245,6 +245,35 @@ def test_attn_core_bwd_32_rows_per_wavefront(workspace, opts, n_q, n_kv, tp, ran
     opts(K.NTP_OPT_ATTN_PARTS, parts)
     opts(K.NTP_OPT_ATTN_BWD_LAUNCHES, launches)
     _bwd_case(n_q, n_kv, tp, rank, 128, n_seq, S, causal, seed=41, pad=pad)
+    names = [n for n in _core_names() if "bwd" in n]
+    if (n_q, n_kv, tp, rank) != (4, 1, 4, 3) or S > 1:
+        assert names and all("_r32" in n for n in names), names
+
+
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+@pytest.mark.parametrize("copy,n_q,n_kv,n_seq,S,launch", [
+    # the launcher's own choice: long walks, grouped KV heads; short walks of many sequences, two launches (more than three workgroups per unit)
+    (0, 28, 28, 1, 1300, "_r32"), (0, 32, 8, 2, 1100, "_r32"), (0, 24, 8, 36, 200, ""),
+    # 16 rows where 32 is the choice: at the step's shape, 448 workgroups of each kind without the mask (one launch on request)
+    (2, 14, 14, 1, 2048, "")])
+def test_attn_core_bwd_rows_of_large_launches(opts, copy, n_q, n_kv, n_seq, S, launch, causal):
+    import paper_2504_06095_amd as N
+    _say(f"attn core bwd, copy option {copy}: heads {n_q}/{n_kv} n_seq={n_seq} S={S} causal={causal}")
+    opts(K.NTP_OPT_ATTN_COPY, copy)
+    if copy == 2:
+        opts(K.NTP_OPT_ATTN_BWD_LAUNCHES, 2)
+    shape = N.attn_core_shape(n_seq, S, N.ntp_attn_shard_plan(n_q, n_kv, 128, 1, 0), n_q // n_kv, causal)
+    assert N.ntp_attn_core_bwd_rows(shape) == (32 if launch else 16)
+    N.ntp_kernel_timing_enable(1)
+    N.ntp_kernel_timing_read()
+    try:
+        _bwd_case(n_q, n_kv, 1, 0, 128, n_seq, S, causal, seed=43)
+        names = [n for n in _core_names() if "bwd" in n]
+    finally:
+        N.ntp_kernel_timing_enable(0)
+        N.ntp_kernel_timing_read()
+    one = launch or copy == 2
+    assert names == [f"attn_core_bwd_{k}{launch}" for k in (("both",) if one else ("dq", "dkv"))], names
 
 
 @pytest.mark.parametrize("launches", [1, 2], ids=["two_launches", "one_launch"])

@@ -75,6 +75,56 @@ def test_short_walks_are_not_cut(workspace_1gib):
     assert (c["fwd_parts"], c["dq_parts"]) == (1, 1)
 
 
+# heads, KV heads, sequences, tokens, causal, rows of the backward kernels without and with a workspace (256 compute units): either side of
+# each line of the rule, at shapes that were measured with both kernels
+BWD_ROWS = [
+    # (128 x 64) tile pairs per unit, whole walks and cut ones
+    (16, 16, 1, 1024, 0, 32, 32), (16, 16, 1, 1024, 1, 16, 16), (12, 3, 1, 1700, 0, 32, 32), (12, 3, 1, 1700, 1, 32, 16),
+    (16, 2, 1, 2048, 1, 32, 16), (56, 7, 2, 831, 1, 32, 32), (8, 1, 1, 4096, 1, 32, 32), (32, 1, 1, 2048, 0, 32, 32), (3, 1, 1, 4096, 1, 16, 16),
+    # length of the walks: short sequences, many of them
+    (14, 14, 150, 33, 0, 16, 16), (14, 14, 439, 64, 1, 16, 16), (14, 14, 75, 128, 0, 16, 16), (14, 14, 55, 256, 0, 16, 16), (14, 14, 25, 384, 0, 16, 16),
+    (14, 14, 5, 512, 0, 32, 32), (14, 14, 22, 512, 1, 16, 16), (14, 14, 4, 768, 1, 32, 32), (7, 7, 16, 774, 1, 16, 16), (14, 14, 7, 768, 0, 32, 32), (18, 18, 2, 1024, 1, 32, 32),
+    (16, 8, 16, 743, 1, 16, 16), (16, 16, 16, 462, 0, 16, 16), (16, 16, 8, 1267, 1, 32, 32), (64, 8, 8, 256, 1, 32, 16), (16, 2, 96, 128, 0, 16, 16),
+    # workgroups per unit
+    (4, 4, 1, 2048, 0, 16, 16), (2, 2, 1, 4096, 0, 16, 32), (1, 1, 1, 8192, 0, 16, 32), (4, 4, 1, 4096, 0, 32, 32), (3, 1, 1, 4096, 0, 16, 32),
+    # full rounds of the 16-row kernels under the mask
+    (10, 10, 1, 2048, 1, 32, 32), (14, 14, 1, 2048, 1, 16, 16), (16, 16, 1, 1999, 1, 16, 16), (2, 2, 8, 2113, 1, 32, 32), (8, 8, 4, 2023, 1, 16, 16),
+    (14, 14, 1, 4096, 1, 32, 32), (14, 14, 1, 8192, 0, 32, 32), (14, 14, 1, 8192, 1, 32, 32)]
+
+
+@pytest.mark.parametrize("ws", [False, True], ids=["no_workspace", "workspace"])
+def test_rows_of_the_backward_kernels(ws):
+    assert Bd.lib().ntp_set_workspace(Bd.default_handle().ptr, FAKE_WS if ws else None, 1 << 30 if ws else 0) == 0
+    try:
+        got = [(*c[:5], N.ntp_attn_core_bwd_rows(_shape(c[0], c[1], 1, 0, *c[2:5]))) for c in BWD_ROWS]
+    finally:
+        assert Bd.lib().ntp_set_workspace(Bd.default_handle().ptr, None, 0) == 0
+    assert got == [(*c[:5], c[6 if ws else 5]) for c in BWD_ROWS]
+
+
+def test_rows_of_the_backward_kernels_by_option_and_head_dimension():
+    long, short = _shape(14, 14, 1, 0, 1, 8192, False), _shape(14, 14, 1, 0, 1, 64, False)
+    for copy, want in ((0, (32, 16)), (1, (16, 16)), (2, (16, 16)), (3, (32, 32))):
+        N.ntp_set_option(Bd.NTP_OPT_ATTN_COPY, copy)
+        try:
+            assert (N.ntp_attn_core_bwd_rows(long), N.ntp_attn_core_bwd_rows(short)) == want
+        finally:
+            N.ntp_set_option(Bd.NTP_OPT_ATTN_COPY, 0)
+    assert N.ntp_attn_core_bwd_rows(_shape(14, 14, 1, 0, 1, 8192, False, d=64)) == 16
+    assert N.ntp_attn_core_bwd_rows(_shape(14, 14, 1, 0, 0, 8192, False)) == 16
+
+
+def test_a_workspace_of_the_size_asked_for_gives_the_choice_of_an_unlimited_one():
+    for c in BWD_ROWS:
+        s = _shape(c[0], c[1], 1, 0, *c[2:5])
+        n, got = N.ntp_workspace_bytes(Bd.NTP_CALL_ATTN_CORE_SHARD, s), []
+        for size in (n, 1 << 40):
+            assert Bd.lib().ntp_set_workspace(Bd.default_handle().ptr, FAKE_WS if size else None, size) == 0
+            got.append((N.ntp_attn_core_bwd_rows(s), N.ntp_attn_core_choice(s)))
+        assert Bd.lib().ntp_set_workspace(Bd.default_handle().ptr, None, 0) == 0
+        assert got[0] == got[1], c
+
+
 def test_parts_respect_the_workspace_size():
     assert Bd.lib().ntp_set_workspace(Bd.default_handle().ptr, FAKE_WS, 16 << 20) == 0  # 16 MiB
     try:
