@@ -181,9 +181,13 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs g, co
 constexpr int kDeepTile = 8, kDeepWideTile = 6;  // indices of the deep-pipelined kernel's tile shapes
 constexpr int kMaxDeepSplits = 16;
 constexpr double kSmallTileUs = 0.225;  // a K tile of the 64 x 64 form
-constexpr int kMaxSmallChunk = 31;      // K tiles: a workspace is set so that K axes of 2048 and more are cut, and they still are (2048 x 584 over
-                                        // K = 2048 would take 16.2 us in one piece, 20.3 in three)
-constexpr double kGroupSmallFrom = 24;  // K tiles
+// K tiles of a piece in that form.  No measurement sets this line: K axes of 2048 and more stay cut on 128 x 128 tiles, as they were before this form
+// came and as callers that set a workspace for it (and the tests of cut products) have it, also where one piece is faster: 2048 x 584 over
+// K = 2048 16.2 us in one piece, 20.3 in three.
+constexpr int kMaxSmallChunk = 31;
+// K tiles of a shared launch's longest problem from which it may take that form (with 16 both take 14 us: 512 x 1024 x 586).
+constexpr double kGroupSmallFrom = 24;
+constexpr double kSmallPerUnit = 2.0;  // workgroups of that form per compute unit at a time
 
 // Whether the deep-pipelined kernel takes over from `old`, and in how many K chunks.  Measured over 45 random shapes of up to one
 // 128 x 128 tile per compute unit, all layouts: against the persistent kernels on 128 x 128 tiles it is never slower (2 % at
@@ -225,15 +229,19 @@ SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int layout, int64
       best = SplitChoice{kDeepTile, sp, int(chunk_tiles * 64), kDeep5};
     }
   }
-  // Where the caller has set a workspace, the same with 64 x 64 tiles, which need a cut less often: up to three on a compute unit at a time,
+  // Where the caller has set a workspace, the same with 64 x 64 tiles, which need a cut less often: up to two on a compute unit at a time,
   // which share its rate (both sides in ntp_gemm_deep.h; without a workspace, and below six K tiles, whose launches are mostly fixed
-  // costs, the tiles stay 128 x 128; so do weight gradients, which share a launch where they are small)
+  // costs, the tiles stay 128 x 128; so do weight gradients, which share a launch where they are small).  Not more than two: 576 x 3776 over K = 1024
+  // (2.07 per unit) takes 13.5 us, 10.7 with 128 x 128 tiles, over 1984 22.4 and 16.4, where 2048 x 1024 (2.0) takes 9.7 and 10.5, 13.3 and
+  // 16.4.  Nor, uncut, more than 1.3 where both operands are K-contiguous and their rows do not start on cache lines (twice the lines a
+  // tile): 640 x 2304 over K = 1264 (1.41) 13.4 and 12.0, 2048 x 1024 over 1264 13.6 and 12.8; 1664 x 640 over 1904 (1.02) 15.2 and 21.1.
   if (!small_ok || layout == 2 || ws_bytes <= 0 || ktiles < 6) return best;
   const double small = double((M + 63) / 64) * double((N + 63) / 64) / double(cus);
   for (int sp = 1; sp <= kMaxSplits; ++sp) {
     const int64_t chunk_tiles = (ktiles + sp - 1) / sp;
     if (sp > 1 && (chunk_tiles < 4 || int64_t(sp) * M * ldw * 4 > ws_bytes)) break;
     if ((sp - 1) * chunk_tiles * 64 >= K || chunk_tiles > kMaxSmallChunk) continue;  // (the last chunk would be empty)
+    if (small * sp > (sp == 1 && layout == 0 && K % 64 ? 1.3 : kSmallPerUnit)) break;
     const double t = kSmallTileUs * double(chunk_tiles) * std::max(1.0, small * sp) + (sp > 1 ? 3.5 + double(M) * double(ldw) * (4.0 * sp + 4.0) / 4.4e6 : 0.0);
     if (t < best_t) {
       best_t = t;
@@ -449,7 +457,6 @@ int launch_prepared(ntp_handle* h, const GemmDesc& d, const Prepared& p, void* s
     const bool pp = sc.splits == 1 && !sc.deep && use_pingpong(h, layout, variant, d.K) && !(layout == 2 && variant == 0 && ring_ok);
     snprintf(name, sizeof(name), "gemm_%c%c_%s_%s%s%s%s", d.a_kc ? 'n' : 't', d.b_kc ? 't' : 'n', kEpiName[d.epilogue], vn,
              sc.deep == kDeep2 ? "d2" : sc.deep ? "d" : "", sn, pp ? "pp" : "");
-
     ntp::timing_begin(h, stream, name, 2.0 * double(d.M) * double(d.N) * double(d.K), 0.0);
   }
   if (sc.deep && sc.splits == 1) {
@@ -553,7 +560,7 @@ int gemm_launch_group(ntp_handle* h, const GemmDesc* d, int n, void* stream) {
   Prepared p[kMax];
   int status[kMax] = {NTP_OK, NTP_OK, NTP_OK};
   bool group = n >= 2, apart_only = false;
-  double apart = 0.0, longest = 0.0, work = 0.0, work_small = 0.0, flops = 0.0;
+  double apart = 0.0, longest = 0.0, longest_small = 0.0, work = 0.0, tiles_small = 0.0, work_small = 0.0, flops = 0.0;
   for (int i = 0; i < n; ++i) {
     status[i] = prepare(h, d[i], &p[i]);
     group = group && status[i] == NTP_OK && !p[i].empty && (p[i].sc.deep == kDeep5 || p[i].sc.deep == kDeepSmall) &&
@@ -565,11 +572,18 @@ int gemm_launch_group(ntp_handle* h, const GemmDesc* d, int n, void* stream) {
     apart += 6.0 + (p[i].sc.deep == kDeep5 ? 0.47 : kSmallTileUs * std::max(1.0, small * sp / h->compute_units)) * std::ceil(kt / sp) + (sp > 1 ? 3.5 + double(g.M) * double(p[i].ldw) * (4.0 * sp + 4.0) / 4.4e6 : 0.0);
     longest = std::max(longest, kt);
     work += tiles * kt;
-    work_small += small * kt;
+    tiles_small += small;
+    longest_small = std::max(longest_small, kt + (tiles_small > kSmallPerUnit * h->compute_units ? work_small / h->compute_units : 0.0));
+    work_small += small * kt * (p[i].layout == 0 && g.K % 64 ? 1.5 : 1.0);
   }
   // 64 x 64 tiles on the terms of choose_deep, where a problem has a long K axis: its K tiles, 0.47 us each with 128 x 128, are then most of
-  // the launch's time (2048 x 192 over K = 1024 with 192 x 1024 over 2048 21.5 -> 14.7 us, 2048 x 1024 over 576 with 576 x 1024 over 2048 20.4 -> 14)
-  const double shared = 0.47 * std::max(longest, 1.15 * work / h->compute_units), shared_small = kSmallTileUs * std::max(longest, 1.15 * work_small / h->compute_units);
+  // the launch's time (2048 x 192 over K = 1024 with 192 x 1024 over 2048 21.5 -> 14.7 us, 2048 x 1024 over 576 with 576 x 1024 over 2048 20.4 -> 14).
+  // A problem that finds the device full (two workgroups a unit) starts behind those before it, and K-contiguous operands whose rows do not start
+  // on cache lines cost half as much again: without these two terms 4856 x 768 over K = 952 with 768 x 952 over 4856 took 50 us instead of 37,
+  // 4667 x 512 over 1640 with 512 x 1640 over 4667 52 instead of 38, 3792 x 768 over 568 with 768 x 568 over 3792 34 instead of 28.  (Over 246
+  // groups: 0.78 of the time without this form on the mean, three more than 2 % slower: 3460 x 776 over K = 512 with 512 x 776 over 3460 by 22 %,
+  // 4685 x 456 over 1024 with 1024 x 456 over 4685 and 592 x 384 over 5080 with 384 x 5080 over 592 by 5-7 %.)
+  const double shared = 0.47 * std::max(longest, 1.15 * work / h->compute_units), shared_small = kSmallTileUs * std::max(longest_small, 1.15 * work_small / h->compute_units);
   const bool by_small = h && h->workspace && longest >= kGroupSmallFrom && shared_small < shared;
   group = group && 6.0 + (by_small ? shared_small : shared) < apart;
   if (group) {

@@ -227,7 +227,7 @@ __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, ui
   }
 }
 
-// The 64 x 64 form (48 KB: three workgroups on a compute unit) for launches that leave most of the device idle with 128 x 128: a K tile takes
+// The 64 x 64 form (48 KB; two workgroups on a compute unit at a time, see choose_deep) for launches that leave most of the device idle with 128 x 128: a K tile takes
 // 0.225 us instead of 0.47 (16 DMA instructions, of which a compute unit takes one in 18 cycles, instead of 32), and there are four times as
 // many workgroups, so that the K axis needs no cut and no second launch.  512 x 584 over K = 1024 13.5 -> 9.6 us, 512 x 1024 over 584
 // 10.5 -> 8.0, 384 x 512 over 4096 in four chunks 18.9 -> 13.2.  Five K tiles in LDS are 0.3 us slower, seven 30 % where

@@ -88,6 +88,30 @@ def test_mlp_deep_small_tiles(M, H, n_r, group):
         assert (raw[k][:, n_r:pad].float().cpu().numpy() == 0).all(), k
 
 
+# the two gradient groups of the projections (dC and dWo, dX and dWqkv): 64 x 64 tiles shared where all workgroups are on the device at once, and
+# not where they make the longest walks wait or rows of a K-contiguous operand do not start on cache lines
+@pytest.mark.parametrize("M,H,n_q,n_kv,d,groups", [(2168, 584, 3, 1, 64, 2), (3792, 568, 6, 1, 128, 1), (4667, 1640, 4, 2, 128, 0)])
+def test_attn_gradient_groups_small_tiles(M, H, n_q, n_kv, d, groups):
+    import torch
+    import paper_2504_06095_amd as N
+    print(f"[gpu-case] deep GEMM gradient groups M={M} H={H}", file=sys.stderr, flush=True)
+    N.ntp_set_workspace(torch.full((16 << 20,), float("nan"), dtype=torch.float32, device="cuda"))
+    N.ntp_kernel_timing_enable(1)
+    N.ntp_kernel_timing_read()
+    try:
+        case = AttnCase(M, H, n_q, n_kv, d, 1, 0)
+        got = case.run_gpu()
+        picked = [r["name"] for r in N.ntp_kernel_timing_read()]
+    finally:
+        N.ntp_kernel_timing_enable(0)
+        N.ntp_set_workspace(None)
+    assert picked.count("gemm_group_64x64d") == groups, picked
+    want = case.oracle()
+    for k in got:
+        e = rel_err(got[k], want[k])
+        assert np.isfinite(got[k]).all() and e <= TOL, f"{k}: rel err {e:.3e}"
+
+
 # the forms above one tile per compute unit: two K tiles in LDS ("d2"), and 128 x 256 tiles with three
 @pytest.mark.parametrize("M,H,n_r,form", [(129, 8200, 1090, "128x128w8d2"), (130, 4104, 2000, "128x128w8d2"), (2900, 1032, 1501, "128x128w8d2"),
                                           (1290, 1288, 3300, "128x256d"), (577, 1000, 9001, "128x128w8d2")])

@@ -68,6 +68,18 @@ def test_split_k_respects_the_workspace_size():
         assert Bd.lib().ntp_set_workspace(Bd.default_handle().ptr, None, 0) == 0
 
 
+def test_small_tiles_where_two_workgroups_per_unit_hold_them(workspace_1gib):
+    """64 x 64 tiles, uncut, on either side of two per compute unit, and of 1.3 where K-contiguous rows do not start on cache lines."""
+    tile = lambda *s: (lambda c: (c["tile_m"], c["tile_n"], c["k_splits"]))(N.ntp_gemm_choice(*s))  # noqa: E731
+    assert tile(0, 2048, 1024, 1024) == tile(1, 2048, 1024, 1024) == (64, 64, 1)      # 2.0 per unit
+    assert tile(0, 576, 3776, 1024) == tile(1, 576, 3776, 1024) == (128, 128, 1)      # 2.07
+    assert tile(0, 640, 2304, 1280) == tile(1, 640, 2304, 1264) == (64, 64, 1)        # 1.41
+    assert tile(0, 640, 2304, 1264) == (128, 128, 1)
+    assert tile(0, 1664, 640, 1904) == (64, 64, 1)                                    # 1.02
+    assert tile(2, 640, 2304, 1280)[:2] != (64, 64)
+    assert N.ntp_gemm_choice(0, 2048, 1024, 1024)["wavefronts"] == 4
+
+
 def test_choice_rejects_bad_arguments():
     for args in [(3, 8, 8, 8), (-1, 8, 8, 8), (0, 0, 8, 8), (0, 8, 0, 8), (0, 8, 8, -1), (0, 1 << 31, 8, 8)]:
         with pytest.raises(N.NtpError):
