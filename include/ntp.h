@@ -77,7 +77,7 @@ const char* ntp_status_string(int status);
  * compute units, which the launchers size their grids by) and returns a handle
  * owned by the caller until ntp_destroy; it allocates host memory only.  With no
  * device visible the handle still serves the host-only calls (ntp_gemm_choice,
- * ntp_attn_core_choice, ntp_workspace_bytes) with an MI355X's 256 compute units.
+ * ntp_attn_core_choice, ntp_attn_core_bwd_rows, ntp_workspace_bytes) with an MI355X's 256 compute units.
  * Device calls must be made with the handle's device current.
  * ntp_device_info reports what was found (device -1: none). */
 typedef struct ntp_handle ntp_handle_t;
@@ -90,8 +90,8 @@ int ntp_device_info(const ntp_handle_t* h, int32_t* device, int32_t* compute_uni
  * variant at any size; a forced variant computes the same result to within fp32
  * summation order (bit-identical for the reshard options).  GEMMs with few output
  * tiles run on a kernel of their own (deep-pipelined; where a workspace is set its K axis
- * is cut into up to 16 chunks or its tiles are 64 x 64), and the gradient GEMMs of a small backward call may
- * share one launch of it.  NTP_OPT_GEMM_TILE, _SPLIT, _SCHEDULE and _WORKGROUPS other
+ * is cut into up to 16 chunks, or its tiles are 64 x 64 and its K axis whole or cut into up to 8), and the
+ * gradient GEMMs of a small backward call may share one launch of it.  NTP_OPT_GEMM_TILE, _SPLIT, _SCHEDULE and _WORKGROUPS other
  * than 0 are about the other kernels and switch both off; NTP_OPT_GEMM_NO_RING_TAIL does
  * so for row-parallel GEMMs with K % 64 != 0.
  * Errors: unknown option or value out of range -> INVALID_ARG. */
@@ -495,13 +495,14 @@ int ntp_kernel_timing_read(ntp_handle_t* h, ntp_kernel_time_t* out, int64_t max_
  * to the handle: calls on this handle that may use it must be ordered on the device
  * (one stream, or events between streams); to run shard calls concurrently on several
  * streams (the gradient sync beside the backward pass, Sec. 4.1), give each stream a
- * handle and a workspace of its own.  Without a workspace nothing is ever split.
+ * handle and a workspace of its own.  Without a workspace nothing is ever split.  With one, of
+ * any size, GEMMs with few output tiles may also run whole on 64 x 64 tiles, which use none of it.
  * Errors: NTP_ERR_INVALID_ARG (misaligned, negative size, NULL with bytes > 0).
  *
  * ntp_workspace_bytes (host only): the largest workspace that the forward or backward
  * call of a shape can use on this handle's device, i.e. what its launch decisions would
- * take if the workspace were unlimited (0: nothing would be split); a smaller workspace
- * is legal and leaves some launches unsplit.  call / shape:
+ * take if the workspace were unlimited (0: nothing would be split, though 64 x 64 tiles may be
+ * chosen once a workspace is set); a smaller workspace is legal and leaves some launches unsplit.  call / shape:
  *   NTP_CALL_MLP_SHARD        const ntp_mlp_shape_t*        ntp_mlp_shard_fwd, _bwd, _bwd_resharded
  *   NTP_CALL_ATTN_PROJ_SHARD  const ntp_attn_shape_t*       ntp_attn_proj_shard_fwd, _bwd, _bwd_resharded
  *   NTP_CALL_ATTN_CORE_SHARD  const ntp_attn_core_shape_t*  ntp_attn_core_shard_fwd, _bwd
