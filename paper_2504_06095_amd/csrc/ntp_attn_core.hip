@@ -2255,7 +2255,7 @@ int64_t wide_pairs(const ntp_attn_core_shape_t* s) {
 }
 // Whether the backward kernels with 32 rows per wavefront (one workgroup of 128 rows per compute unit) are the faster ones.  Their
 // products take two thirds of the time, but nothing overlaps a workgroup's way into and out of its walk (about 10 us; the 16-row kernels
-// have two workgroups per unit).  Measured over 225 shapes, with and without a workspace, as the ratio of the times, 32 rows to 16 rows; a launch's
+// have two workgroups per unit).  Measured with and without a workspace, as the ratio of the times, 32 rows to 16 rows; a launch's
 // work in products of tile pairs (4 a pair for dK/dV, 3 for dQ), a walk being those of one workgroup:
 //  - less than 8 pairs per unit (cut walks, whose parts are further ways in and out: 16, causal 20): 4 x 1024 causal cut 1.05, 28 x 900 causal 1.16,
 //    16 on 2 heads x 2048 causal cut 1.06; from there on 16 x 1024 unmasked 0.92, 3 on one x 4096 cut 0.80, causal 7 on 7 x 831 x 2 cut 0.85;
@@ -2267,8 +2267,8 @@ int64_t wide_pairs(const ntp_attn_core_shape_t* s) {
 //  - causal, ungrouped, up to 4 workgroups per unit with walks of less than 80 products: the 16-row kernels' workgroups are equal there, two per unit at
 //    a time, so that their rounds are full at 2 and 4 per unit: 14 x 2048 (1.75 per unit) 1.04, 16 x 1999 (2.0) 1.14, 8 x 2023 of 4 (4.0) 1.04;
 //    10 x 2048 (1.25) 0.89, 2 x 2113 of 8 (2.1) 0.68.
-// Over 385 shapes drawn afterwards the kernels taken are 9 % faster than 16 rows everywhere on the mean and at three shapes more than 4 % slower
-// (causal 28 on 14 x 809 of 2 1.19, 64 on 16 x 957 of 4 1.14, 7 x 1021 of 16 1.08).
+// Over 494 shapes, most of them drawn afterwards, the kernels taken are 9 % faster than 16 rows everywhere on the mean and at four shapes more than
+// 4 % slower (causal 28 on 14 x 809 of 2 1.19, 32 on 4 x 860 of 16 1.18, 64 on 16 x 957 of 4 1.14, 7 x 1021 of 16 1.07).
 bool wide_pays(const ntp_attn_core_shape_t* s, int dq_parts, int dkv_parts, double cus) {
   const double tiles = double((int64_t(s->seq_len) + kBKV - 1) / kBKV), own = std::ceil(tiles / 2), heads_per_kv = std::min(s->group, s->q_cnt);
   const double per_unit = own * s->n_seq * (double(s->q_cnt) * dq_parts + double(s->kv_cnt) * dkv_parts) / cus, pairs = double(wide_pairs(s)) / cus;
