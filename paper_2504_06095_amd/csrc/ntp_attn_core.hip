@@ -2257,8 +2257,8 @@ int64_t wide_pairs(const ntp_attn_core_shape_t* s) {
 // products take two thirds of the time, but nothing overlaps a workgroup's way into and out of its walk (about 10 us; the 16-row kernels
 // have two workgroups per unit).  Measured with and without a workspace, as the ratio of the times, 32 rows to 16 rows; a launch's
 // work in products of tile pairs (4 a pair for dK/dV, 3 for dQ), a walk being those of one workgroup:
-//  - less than 8 pairs per unit (cut walks, whose parts are further ways in and out: 16, causal 20): 4 x 1024 causal cut 1.05, 28 x 900 causal 1.16,
-//    16 on 2 heads x 2048 causal cut 1.06; from there on 16 x 1024 unmasked 0.92, 3 on one x 4096 cut 0.80, causal 7 on 7 x 831 x 2 cut 0.85;
+//  - less than 8 pairs per unit (cut walks, whose parts are further ways in and out: 16, causal 20): 4 x 2048 causal cut 1.05, 28 x 900 causal 1.16,
+//    16 on 2 heads x 2048 causal cut 1.06; from there on 16 x 1024 unmasked 0.92, 3 on one x 4096 cut 0.80, causal 56 on 7 x 831 of 2 cut 0.85;
 //  - short walks, less than 24 products on average, causal 28 in launches of 4 and more workgroups per unit, 36 in those of 8 and more (whose ways
 //    in and out the 16-row kernels overlap best): 14 x 64 tokens of 150 sequences 1.65, 14 x 256 of 55 1.14, causal 14 x 512 of 22 1.19, 7 x 774
 //    of 16 1.16, 16 on 8 x 743 of 16 1.06; 14 x 512 of 5 0.92, 14 x 768 of 7 0.92, causal 14 x 768 of 4 0.89, 28 x 1300 0.69; from 18 on where the longest
