@@ -93,6 +93,12 @@ __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, ui
     for (int i = 0; i < NBI; ++i) dma_issue(rb, sb + i * 512, last && cutb[i] ? kNowhere : offb[i], uint32_t(kt) * bstep_b);
   };
 
+  u16x4 aux[MI][NI];  // asked for before the first K tile: the epilogue finds them there
+  if constexpr (EPI == ntp::EPI_DGELU) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i) load_aux_row(g, row0 + wm * TM + i * 16 + (lane & 15), col0 + wn * TN + (lane >> 4) * 4, aux[i]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   f32x4 acc[MI][NI];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -219,7 +225,7 @@ __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, ui
     } else if constexpr (PAIRED) {
       static_assert(NI % 2 == 0, "blocks are stored in pairs");
 #pragma unroll
-      for (int j = 0; j < NI; j += 2) store8_pair<EPI>(g, m, col0 + wn * TN + j * 16, lane >> 4, acc[i][j], acc[i][j + 1]);
+      for (int j = 0; j < NI; j += 2) store8_pair<EPI>(g, m, col0 + wn * TN + j * 16, lane >> 4, acc[i][j], acc[i][j + 1], aux[i][j], aux[i][j + 1]);
     } else {
 #pragma unroll
       for (int j = 0; j < NI; ++j) store4<EPI>(g, m, col0 + wn * TN + j * 16 + (lane >> 4) * 4, acc[i][j]);

@@ -335,15 +335,21 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
         continue;
       }
     }
+    u16x4 aux[2][NI];
+    if constexpr (EPI == ntp::EPI_DGELU) load_aux_row(g, erow0 + wm * TM + (lane & 15), ecol0 + wn * TN + (lane >> 4) * 4, aux[0]);
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
       const int m = erow0 + wm * TM + i * 16 + (lane & 15);
+      if constexpr (EPI == ntp::EPI_DGELU) {
+        if (i + 1 < MI) load_aux_row(g, m + 16, ecol0 + wn * TN + (lane >> 4) * 4, aux[(i + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       if constexpr (PAIRED) {
 #pragma unroll
-        for (int j = 0; j + 1 < NI; j += 2) store8_pair<EPI>(g, m, ecol0 + wn * TN + j * 16, lane >> 4, acc[i][j], acc[i][j + 1]);
+        for (int j = 0; j + 1 < NI; j += 2) store8_pair<EPI>(g, m, ecol0 + wn * TN + j * 16, lane >> 4, acc[i][j], acc[i][j + 1], aux[i & 1][j], aux[i & 1][j + 1]);
       }
 #pragma unroll
-      for (int j = PAIRED ? NI - NODD : 0; j < NI; ++j) store4<EPI>(g, m, ecol0 + wn * TN + j * 16 + (lane >> 4) * 4, acc[i][j]);
+      for (int j = PAIRED ? NI - NODD : 0; j < NI; ++j) store4<EPI>(g, m, ecol0 + wn * TN + j * 16 + (lane >> 4) * 4, acc[i][j], aux[i & 1][j]);
     }
     if (!more) break;
   }

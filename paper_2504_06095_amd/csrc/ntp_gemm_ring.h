@@ -164,8 +164,10 @@ using Int = std::integral_constant<int, I>;
 // With several chunks the fp32 partial sums go to slice s of a workspace (g.C + s * g.split_stride
 // floats, rows of g.ldc); with one chunk the tile gets its normal epilogue.  Without the cross-tile state
 // of the persistent loop this form needs about 30 registers less.
+// (Two wavefronts on a SIMD, also with four of them in a workgroup: left free, the compiler gives accumulating weight gradients on the 128 x 128 tile 272
+// registers, so that a compute unit holds one workgroup instead of two: 3511 x 6144 over 4096 324-346 -> 247-258 us.)
 template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, bool SPLIT = false>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_ring_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_ring_kernel(const GemmArgs g) {
   static_assert(!SPLIT || EPI == ntp::EPI_F32 || EPI == ntp::EPI_F32_ACCUM, "partial sums are stored as fp32");
   constexpr int NW = WGM * WGN;
   constexpr int TM = BM_ / WGM, TN = BN_ / WGN;  // wavefront tile
@@ -498,7 +500,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_ring_kernel(const GemmArg
       const int m = erow0 + wm * TM + i * 16 + (lane & 15);
       if constexpr (PAIRED) {
 #pragma unroll
-        for (int j = 0; j + 1 < NI; j += 2) store8_pair<EPI>(g, m, ecol0 + wn * TN + j * 16, lane >> 4, acc[i][j], acc[i][j + 1]);
+        for (int j = 0; j + 1 < NI; j += 2) {
+          u16x4 aux[2] = {};  // (asked for a row ahead, as in the ping-pong kernels, the widest tiles would spill)
+          if constexpr (EPI == ntp::EPI_DGELU) load_aux_row(g, m, ecol0 + wn * TN + j * 16 + (lane >> 4) * 4, aux);
+          store8_pair<EPI>(g, m, ecol0 + wn * TN + j * 16, lane >> 4, acc[i][j], acc[i][j + 1], aux[0], aux[1]);
+        }
       }
 #pragma unroll
       for (int j = PAIRED ? NI - NODD : 0; j < NI; ++j) {

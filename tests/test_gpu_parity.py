@@ -142,6 +142,75 @@ def test_gelu_derivative_in_fp32_precision(mode, std):
     assert e <= 2.0 ** -24
 
 
+@pytest.mark.parametrize("M,n,H", [(8192, 4096, 8), (1000, 1096, 128), (4096, 4090, 192)])  # generic, deep-pipelined, ping-pong kernels
+@pytest.mark.parametrize("mode,scale", [(0, 0.125), (0, 0.5), (1, 0.125), (1, 0.5)])
+def test_gelu_functions_in_fp32_precision(M, n, H, mode, scale):
+    """Y = GeLU(x) and dP = (e f) GeLU'(P), judged as in test_gelu_derivative_in_fp32_precision: an rms relative error within half an fp32
+    ulp.  x = a b + c d is exact in 24 bits: a, b in [1, 2) have 8 bits each, c d 8 bits from 2^-22 on (x from one product alone takes too few values to lie near
+    rounding boundaries).  Left of -0.75 the result is a probability's tail, 2^q with q from -2 down to -36 at -6.5: q's half ulp (2^-23 up to
+    2^-19) times ln 2, with as much again for the steps before the last, bounds its relative error by 2.7e-6, which with the
+    rounding to bf16 is the closeness asked for there.  (0.5 (1 + erff) has 1.3e-6 at -2 and nothing right at -6.)  Then the ends of the number range:
+    infinite, NaN and the largest inputs give what the formulas give in their limits."""
+    import math
+    import torch
+    import paper_2504_06095_amd as N
+    _say(f"gelu functions, {M} x {n} over {H}, mode {mode}, scale {scale}")
+    g = torch.Generator("cuda").manual_seed(7)
+    P, Y, dP = (torch.zeros(M, -(-n // 64) * 64, dtype=torch.bfloat16, device="cuda")[:, :n] for _ in range(3))
+    X, At = torch.zeros(M, H, dtype=torch.bfloat16, device="cuda"), torch.zeros(n, H, dtype=torch.bfloat16, device="cuda")
+    whole = lambda lo, hi, k: torch.randint(lo, hi, (k,), device="cuda", generator=g).float()  # noqa: E731
+    X[:, 0] = (whole(128, 256, M) / 128 * (whole(0, 2, M) * 2 - 1) * scale).bfloat16()
+    At[:, 0] = (whole(128, 256, n) / 128).bfloat16()
+    X[:, 1], At[:, 1] = (whole(0, 16, M) * 2.0 ** -22 * scale).bfloat16(), whole(0, 16, n).bfloat16()
+    Z = torch.empty(M, H, dtype=torch.bfloat16, device="cuda")
+    N.ntp_mlp_shard_fwd(X, At, torch.zeros_like(At), P, Y, Z, n, mode)
+
+    def values(x):
+        if mode == 0:
+            return 0.5 * x * torch.special.erfc(x / -math.sqrt(2.0))
+        return x * torch.sigmoid(2.0 * math.sqrt(2.0 / math.pi) * (x + 0.044715 * x ** 3))
+
+    def slopes(x):
+        if mode == 0:
+            return 0.5 * torch.special.erfc(x / -math.sqrt(2.0)) + x * torch.exp(-0.5 * x * x) / math.sqrt(2.0 * math.pi)
+        c = math.sqrt(2.0 / math.pi)
+        u = c * (x + 0.044715 * x ** 3)
+        return torch.sigmoid(2.0 * u) + 2.0 * x * torch.sigmoid(2.0 * u) * torch.sigmoid(-2.0 * u) * c * (1.0 + 3.0 * 0.044715 * x * x)
+
+    def check(got, v, keep):  # no more on the far side of a boundary than half an ulp explains, and four standard deviations of that count
+        v, got = v.abs(), got.double().abs()
+        ulp = torch.exp2(torch.floor(torch.log2(v.clamp_min(1e-30))) - 7.0)
+        wrong = int(((got - v).abs() > 0.5 * ulp)[keep].sum())
+        most = 2.0 ** -24 * float((v / ulp)[keep].sum()) * 2.0 * math.sqrt(2.0 / math.pi)
+        print(f"    {wrong} on the far side of a boundary, expected at most {most:.0f}", file=sys.stderr)
+        assert wrong <= most + 4.0 * math.sqrt(most)
+
+    x = X[:, :2].double() @ At[:, :2].double().T
+    v = values(x)
+    check(Y, v, (x > -0.75) & (x < 2.5))  # (above, a value is x to within a few ulps, and those with c d = 0 can lie on a boundary)
+    assert ((Y.double() - v).abs() <= v.abs() * (2.0 ** -8 + 2.7e-6))[(x <= -0.75) & (x >= -6.5)].all()
+    dZ, B, xs = torch.zeros_like(X), torch.zeros_like(At), P.double()
+    dZ[:, 0] = torch.empty(M, device="cuda").uniform_(1.0, 2.0, generator=g).bfloat16()
+    B[:, 0] = torch.empty(n, device="cuda").uniform_(1.0, 2.0, generator=g).bfloat16()
+    dX, dA, dB = torch.empty_like(X), torch.empty(n, H, device="cuda"), torch.empty(n, H, device="cuda")
+    N.ntp_mlp_shard_bwd(dZ, X, At, B, P, Y, dP, dX, dA, dB, n, mode)
+    d = slopes(xs)
+    check(dP, d * (dZ[:, :1].double() * B[:, 0].double()), (d.abs() > 0.1) & ((d - 1.0).abs() > 2.0 ** -10))
+
+    big = torch.tensor([float("inf"), -float("inf"), float("nan"), 3e38, -3e38, 1e20, -1e20, 50.0, -50.0, 0.0, -0.0], device="cuda").bfloat16()
+    X[: len(big), 0], At[:, 0], dZ[:, 0], B[:, 0] = big, 1.0, 1.0, 1.0
+    X[: len(big), 1:] = 0.0
+    N.ntp_mlp_shard_fwd(X, At, B, P, Y, Z, n, mode)
+    N.ntp_mlp_shard_bwd(dZ, X, At, B, P, Y, dP, dX, dA, dB, n, mode)
+    nan, inf = float("nan"), float("inf")
+    want = torch.tensor([inf, nan, nan, big[3], -0.0, big[5], -0.0, 50.0, -0.0, 0.0, -0.0], dtype=torch.bfloat16, device="cuda")
+    slope = torch.tensor([nan, nan, nan, 1.0, 0.0, 1.0, 0.0, 1.0, 0.0, 0.5, 0.5], dtype=torch.bfloat16, device="cuda")
+    for got, w in ((Y, want), (dP, slope)):
+        rows = got[: len(big)]
+        assert torch.equal(rows.isnan(), w.isnan()[:, None].expand_as(rows))
+        assert torch.equal(rows.nan_to_num(0.0), w.nan_to_num(0.0)[:, None].expand_as(rows).contiguous())
+
+
 def test_mlp_gradient_accumulation():
     _say("mlp accumulate")
     case = MlpCase(192, 256, 600, 3, 2)
