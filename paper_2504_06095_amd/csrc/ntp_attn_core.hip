@@ -2171,6 +2171,8 @@ __global__ __launch_bounds__(256) void attn_core_delta_kernel(const CoreBwdArgs 
   if (c == 0 && row < rows) a.Delta[int64_t(head) * rows + row] = part;
 }
 
+#include "ntp_attn_small.h"
+
 // Adds the parts of a cut walk and stores the gradient as bf16.  `rows` rows per workgroup of the cut
 // kernel, `width` fp32 values per row: D (dQ) or 2 D ([dK | dV]).  One thread per 4 values.
 template <int D, bool DKV>
@@ -2247,7 +2249,51 @@ struct CoreChoice {
   bool bwd_wide;         // both with 32 owned rows per wavefront
   bool bwd_both;         // both backward kernels go out as one launch
   int64_t dkv_ws_offset; // then: byte offset of the dK/dV parts in the workspace (behind the dQ parts)
+  bool fwd_small, bwd_small;  // 16 rows per workgroup, whose wavefronts share out the walk (ntp_attn_small.h)
 };
+
+// Whether the kernels with 16 rows per workgroup are the faster ones (ntp_attn_small.h): by estimates (us) of both forms, fitted to 700 random launches
+// of 4 to 3000 16-row workgroups (1-14 KV heads, 1-8 query heads on each, 1-8 sequences of 40-6000 tokens, both masks) and right to 10 %
+// on the mean.  Each is what a launch costs anyhow, plus the larger of its longest walk and its workgroups' time dealt out over the device.  Taken where 10 %
+// faster by the estimates: over those launches 0.75 (forward) and 0.61 (backward) of the time without them at head dimension 64, 0.84 and 0.80 at 128; of
+// the 1400, eight lost more than 5 %.  16 heads of 64 over 7 ranks, four sequences of 512 causal tokens: 10.7 -> 6.3 us and 19.0 -> 13.2 us.
+struct SmallWalks {
+  double most, mean;  // steps of a wavefront: a quarter of its workgroup's walk
+};
+SmallWalks small_walks(int64_t tiles, int64_t heads, bool causal) {
+  const double t = double(tiles), h = double(heads), up = heads % 4 == 0 ? 0.0 : 0.375;  // (rounded up to whole tiles)
+  const double most = std::ceil(h * t / 4.0);
+  return {most, causal ? std::max(1.0, h * (t + 1.0) / 8.0 + up) : most};
+}
+bool small_fwd_pays(const ntp_attn_core_shape_t* s, const CoreChoice& c, double cus) {
+  const bool causal = s->causal != 0, d64 = s->head_dim == 64;
+  const int64_t tiles = (int64_t(s->seq_len) + kBKV - 1) / kBKV, heads = int64_t(s->n_seq) * s->q_cnt;
+  if (tiles < 1 || heads < 1) return false;
+  const SmallWalks w = small_walks(tiles, 1, causal);
+  const double small = double((s->seq_len + 15) / 16 * heads) / cus;
+  const double now = d64 ? 3.1 + std::max(0.84 * w.most, small / 2 * (1.02 + 1.5 * w.mean)) : 3.05 + std::max(1.71 * w.most, small * (1.47 + 1.96 * w.mean));
+  const double walk = std::ceil(double(causal ? tiles + 1 : tiles) / c.fwd_parts);
+  const double per_unit = double((causal ? (tiles + 1) / 2 : tiles) * heads * c.fwd_parts) / cus / (c.fwd_rows == 32 ? 2 : 1), cut = c.fwd_parts > 1;
+  const bool r32 = c.fwd_rows == 32;
+  const double other = d64 ? 3.0 + std::max((r32 ? 1.67 : 0.86) * walk, per_unit / 3 * (5.9 + (r32 ? 2.47 : 1.72) * walk)) + 5.8 * cut
+                           : 3.6 + std::max((r32 ? 2.66 : 1.15) * walk, per_unit / 2 * (3.1 + (r32 ? 5.2 : 1.47) * walk)) + 6.9 * cut;
+  return now < 0.9 * other;
+}
+bool small_bwd_pays(const ntp_attn_core_shape_t* s, const CoreChoice& c, double cus) {
+  const bool causal = s->causal != 0, d64 = s->head_dim == 64;
+  const int64_t tiles = (int64_t(s->seq_len) + kBKV - 1) / kBKV, q = int64_t(s->n_seq) * s->q_cnt, kv = int64_t(s->n_seq) * s->kv_cnt;
+  const int64_t heads_per_kv = std::min<int64_t>(s->group, s->q_cnt);
+  if (tiles < 1 || q < 1 || kv < 1 || c.bwd_wide) return false;  // (32 rows per wavefront: launches with work for every unit, 1.6 to 2.6 times as fast)
+  const SmallWalks wq = small_walks(tiles, 1, causal), wk = small_walks(tiles, heads_per_kv, causal);
+  const double t16 = double((int64_t(s->seq_len) + 15) / 16) / cus;
+  const double now = d64 ? 5.4 + std::max(1.4 * wk.most, t16 / 2 * (double(kv) * (2.2 + 2.14 * wk.mean) + double(q) * (2.2 + 1.0 * wq.mean)))
+                         : 6.2 + std::max(2.3 * wk.most, t16 * (double(kv) * (1.77 + 3.12 * wk.mean) + double(q) * (2.9 + 1.13 * wq.mean)));
+  const double walk = double(causal ? tiles + 1 : tiles), per = double(causal ? (tiles + 1) / 2 : tiles) / cus / 2;
+  const double dq = std::ceil(walk / c.dq_parts), dkv = std::ceil(walk * double(heads_per_kv) / c.dkv_parts), cuts = double(c.dq_parts > 1) + double(c.dkv_parts > 1);
+  const double other = d64 ? 5.1 + std::max(std::max(1.68 * dkv, 1.73 * dq), per * (double(kv * c.dkv_parts) * (11.0 + 2.46 * dkv) + double(q * c.dq_parts) * 3.7)) + 8.9 * cuts
+                           : 7.0 + std::max(std::max(1.72 * dkv, 1.23 * dq), per * (double(kv * c.dkv_parts) * (13.2 + 3.69 * dkv) + double(q * c.dq_parts) * 8.1)) + 6.7 * cuts;
+  return now < 0.9 * other;
+}
 // (128-row, 64-row) tile pairs of a launch of the backward kernels with 32 rows per wavefront
 int64_t wide_pairs(const ntp_attn_core_shape_t* s) {
   const int64_t tiles = (s->seq_len + kBKV - 1) / kBKV, own = (tiles + 1) / 2;
@@ -2280,7 +2326,7 @@ bool wide_pays(const ntp_attn_core_shape_t* s, int dq_parts, int dkv_parts, doub
   return walk >= (per_unit >= 8.0 ? 36.0 : causal && per_unit >= 4.0 ? 28.0 : 24.0) || (walk >= 18.0 && !cut && longest >= 1.5 * 7.0 * pairs);
 }
 CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_core_shape_t* s) {
-  CoreChoice c{16, 1, 1, 1, 0, false, false, false, false, 0};
+  CoreChoice c{16, 1, 1, 1, 0, false, false, false, false, 0, false, false};
   const bool causal = s->causal != 0;
   const int64_t tiles = (s->seq_len + kBKV - 1) / kBKV;
   // under the causal mask a workgroup takes a pair of tiles, one from each end of the sequence
@@ -2321,7 +2367,16 @@ CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_cor
     c.dq_parts = choose_parts(h, ws_bytes, wq, bq, walk, bdq, fill, 12, causal);
     c.dkv_parts = choose_parts(h, ws_bytes, wk, bk, heads_per_kv * walk, bdkv, 2.0, 16, false);
   }
-  if (c.fwd_parts > 1) c.fwd_rows = 16;
+  if (!h->opt[NTP_OPT_ATTN_PARTS] && !h->opt[NTP_OPT_ATTN_COPY] && !h->opt[NTP_OPT_ATTN_BWD_LAUNCHES]) {
+    c.fwd_small = small_fwd_pays(s, c, cus);
+    c.bwd_small = small_bwd_pays(s, c, cus);
+    if (c.fwd_small) c.fwd_parts = 1;
+    if (c.bwd_small) {
+      c.dq_parts = c.dkv_parts = 1;
+      c.bwd_wide = false;
+    }
+  }
+  if (c.fwd_parts > 1 || c.fwd_small) c.fwd_rows = 16;
   c.dq_dma = c.dkv_dma = dma;
   if (c.fwd_parts > 1) c.ws_bytes = std::max(c.ws_bytes, bq * c.fwd_parts * bf);
   const int64_t dq_bytes = c.dq_parts > 1 ? bq * c.dq_parts * bdq : 0, dkv_bytes = c.dkv_parts > 1 ? bk * c.dkv_parts * bdkv : 0;
@@ -2334,8 +2389,8 @@ CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_cor
   // Head dimension 64 (walks that are not cut): at every size measured (3 heads x 512 tokens of 4 sequences 28 -> 20 us, 15 heads
   // x 389 30 -> 22 us, 28 heads x 6062 620 -> 589 us, 22 heads x 3801 no difference).
   const bool pays = s->head_dim == 64 || c.bwd_wide || wq + wk <= 3 * cus;
-  c.bwd_both = (dma || (s->head_dim == 64 && c.dq_parts == 1 && c.dkv_parts == 1)) && h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] != 1 && (pays || h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] == 2) &&
-               (dkv_bytes == 0 || c.dkv_ws_offset + dkv_bytes <= ws_bytes);
+  c.bwd_both = c.bwd_small || ((dma || (s->head_dim == 64 && c.dq_parts == 1 && c.dkv_parts == 1)) && h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] != 1 && (pays || h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] == 2) &&
+               (dkv_bytes == 0 || c.dkv_ws_offset + dkv_bytes <= ws_bytes));
   c.ws_bytes = std::max(c.ws_bytes, c.bwd_both ? (dkv_bytes ? c.dkv_ws_offset + dkv_bytes : dq_bytes) : std::max(dq_bytes, dkv_bytes));
   return c;
 }
@@ -2415,8 +2470,8 @@ extern "C" int ntp_attn_core_shard_fwd(ntp_handle_t* h, const ntp_attn_core_shap
   const int qbw = cc.fwd_rows / 16;
   a.part_sums = static_cast<float*>(h->workspace);
   a.n_parts = cc.fwd_parts;
-  a.q_tiles = (s->seq_len + 64 * qbw - 1) / (64 * qbw);
-  a.pairs = s->causal ? (a.q_tiles + 1) / 2 : 0;
+  a.q_tiles = cc.fwd_small ? (s->seq_len + 15) / 16 : (s->seq_len + 64 * qbw - 1) / (64 * qbw);
+  a.pairs = s->causal && !cc.fwd_small ? (a.q_tiles + 1) / 2 : 0;
   a.scale_log2 = float(1.4426950408889634 / std::sqrt(double(s->head_dim)));
   const int64_t blocks = int64_t(a.q_tiles) * s->n_seq * s->q_cnt;  // query tiles
   const int64_t wgs = int64_t(a.pairs > 0 ? a.pairs : a.q_tiles) * s->n_seq * s->q_cnt;
@@ -2438,7 +2493,10 @@ extern "C" int ntp_attn_core_shard_fwd(ntp_handle_t* h, const ntp_attn_core_shap
     else launch(d, q, std::false_type{});
   };
   const bool by_dma = s->head_dim == 128 && qbw == 1 && h->opt[NTP_OPT_ATTN_COPY] != 1;
-  if (by_dma) {
+  if (cc.fwd_small) {
+    if (s->head_dim == 128) hipLaunchKernelGGL(attn_core_fwd_small_kernel<128>, grid, dim3(kThreads), 0, hs, a);
+    else hipLaunchKernelGGL(attn_core_fwd_small_kernel<64>, grid, dim3(kThreads), 0, hs, a);
+  } else if (by_dma) {
     if (a.pairs > 0) hipLaunchKernelGGL((attn_core_fwd_dma_kernel<true>), grid, dim3(kThreads), 0, hs, a);
     else hipLaunchKernelGGL((attn_core_fwd_dma_kernel<false>), grid, dim3(kThreads), 0, hs, a);
   } else if (s->head_dim == 128 && qbw == 2 && h->opt[NTP_OPT_ATTN_COPY] != 1) {
@@ -2550,7 +2608,14 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
     hipLaunchKernelGGL(wide ? attn_core_delta_kernel<128> : attn_core_delta_kernel<64>, dim3(uint32_t(delta_wgs)), dim3(256), 0, hs, a, M);
     ok = hipGetLastError() == hipSuccess;
     const dim3 grid(uint32_t(sections * (dq_wgs + dkv_wgs)));
-    if (ok && cc.bwd_wide) {
+    if (ok && cc.bwd_small) {
+      a.tiles = (s->seq_len + 15) / 16;
+      const int64_t n_dkv = int64_t(a.tiles) * s->n_seq * s->kv_cnt;
+      const dim3 small(uint32_t(n_dkv + int64_t(a.tiles) * s->n_seq * s->q_cnt));
+      if (wide) hipLaunchKernelGGL(attn_core_bwd_small_kernel<128>, small, dim3(kThreads), 0, hs, a, uint32_t(n_dkv));
+      else hipLaunchKernelGGL(attn_core_bwd_small_kernel<64>, small, dim3(kThreads), 0, hs, a, uint32_t(n_dkv));
+      ok = hipGetLastError() == hipSuccess;
+    } else if (ok && cc.bwd_wide) {
       // the longest of the short dK/dV walks against the longest dQ walk, in matrix products of tile pairs
       const uint32_t kv_first = 2 * std::min<int64_t>(s->group, s->q_cnt) * cc.dq_parts > 3 * cc.dkv_parts;
       hipLaunchKernelGGL(attn_core_bwd_both_wide_kernel, grid, dim3(kThreads), 0, hs, adq, adkv, uint32_t(dq_wgs), uint32_t(dkv_wgs), kv_first);

@@ -338,6 +338,46 @@ def test_attn_core_bwd_head_dimension_64_launches(opts, n_q, n_kv, tp, rank, n_s
     assert names == (["attn_core_bwd_dq", "attn_core_bwd_dkv"] if launches == 1 else ["attn_core_bwd_both"]), names
 
 
+# 16 rows per workgroup, whose wavefronts share out the walk: sequences at the edges of 16 rows, of a tile, of one tile per wavefront and of two;
+# grouped heads of which the rank holds a part; padded rows
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_q,n_kv,tp,rank,n_seq,S,pad", [(2, 2, 1, 0, 1, 15, 0), (3, 1, 1, 0, 2, 16, 8), (2, 2, 1, 0, 3, 17, 0), (8, 2, 3, 1, 1, 63, 0), (2, 1, 1, 0, 2, 65, 8),
+                                                          (3, 3, 1, 0, 1, 255, 0), (6, 2, 4, 1, 1, 257, 0), (2, 2, 1, 0, 2, 320, 0), (1, 1, 1, 0, 1, 577, 8)])
+def test_attn_core_few_workgroups(n_q, n_kv, tp, rank, d, n_seq, S, pad, causal):
+    _say(f"attn core, 16 rows per workgroup n_q={n_q} n_kv={n_kv} d={d} n_seq={n_seq} S={S} pad={pad} causal={causal}")
+    _case(n_q, n_kv, tp, rank, d, n_seq, S, causal, seed=4, pad=pad)
+    _bwd_case(n_q, n_kv, tp, rank, d, n_seq, S, causal, seed=5, pad=pad)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")], ids=["inf", "nan"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_attn_core_few_workgroups_non_finite_rows_reach_no_further(opts, value, d):
+    """A non-finite query, key, value or gradient row makes the same outputs non-finite as with 64 rows per workgroup, and the others agree."""
+    import torch
+    import paper_2504_06095_amd as N
+    _say(f"attn core, 16 rows per workgroup, a row of {value}, d={d}")
+    S, q = 300, 2
+    shape = N.attn_core_shape(1, S, N.ntp_attn_shard_plan(q, 1, d, 1, 0), 2, True)
+    g = torch.Generator("cuda").manual_seed(3)
+    for row, block in ((70, 0), (70, 1), (200, q), (130, q + 1), (70, -1)):  # query heads, key, value; -1: the gradient
+        QKV = torch.empty(S, (q + 2) * d, device="cuda").normal_(generator=g).bfloat16()
+        dC = torch.empty(S, q * d, device="cuda").normal_(generator=g).bfloat16()
+        (dC if block < 0 else QKV)[row, max(block, 0) * d + 5] = value
+        got = []
+        for copy in (0, 1):
+            opts(K.NTP_OPT_ATTN_COPY, copy)
+            C, dQKV, LSE, Delta = torch.zeros_like(dC), torch.zeros_like(QKV), torch.zeros(q, S, device="cuda"), torch.zeros(q, S, device="cuda")
+            N.ntp_attn_core_shard_fwd(shape, QKV, C, LSE)
+            N.ntp_attn_core_shard_bwd(shape, QKV, C, dC, LSE, Delta, dQKV)
+            got.append((C, LSE, dQKV))
+        torch.cuda.synchronize()
+        for a, b in zip(*got):
+            assert torch.equal(a.isfinite(), b.isfinite()), (row, block)
+            a, b = a.float().nan_to_num(0, 0, 0), b.float().nan_to_num(0, 0, 0)
+            assert (a - b).abs().max() <= 2e-2 * b.abs().max(), (row, block)
+
+
 def test_attn_core_bwd_one_launch_needs_room_for_both_kernels_parts(opts):
     """With a workspace that holds either kernel's parts but not both, the cut kernels go out as two launches."""
     import torch

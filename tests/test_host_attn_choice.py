@@ -75,6 +75,19 @@ def test_short_walks_are_not_cut(workspace_1gib):
     assert (c["fwd_parts"], c["dq_parts"]) == (1, 1)
 
 
+def test_small_launches_share_out_walks_inside_workgroups(workspace_1gib):
+    """Walks that would be cut into parts where the launch is small enough for 16 rows per workgroup, and the sizes from which they are."""
+    parts = lambda *a, **k: (lambda c: (c["fwd_parts"], c["dq_parts"], c["dkv_parts"]))(N.ntp_attn_core_choice(_shape(*a, **k)))  # noqa: E731
+    assert parts(4, 1, 1, 0, 1, 512, True, d=64) == parts(3, 3, 1, 0, 1, 1432, False, d=64) == (1, 1, 1)
+    assert parts(1, 1, 1, 0, 1, 1432, True) == (1, 1, 1)
+    N.ntp_set_option(Bd.NTP_OPT_ATTN_COPY, 2)
+    try:
+        assert max(parts(4, 1, 1, 0, 1, 512, True, d=64)) > 1 and max(parts(1, 1, 1, 0, 1, 1432, True)) > 1
+    finally:
+        N.ntp_set_option(Bd.NTP_OPT_ATTN_COPY, 0)
+    assert max(parts(4, 4, 1, 0, 1, 8192, True, d=64)) > 1 and max(parts(2, 1, 1, 0, 1, 4096, False)) > 1
+
+
 # heads, KV heads, sequences, tokens, causal, rows of the backward kernels without and with a workspace (256 compute units): either side of
 # each line of the rule, at shapes that were measured with both kernels
 BWD_ROWS = [
