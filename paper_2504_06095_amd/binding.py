@@ -201,8 +201,26 @@ def _check(status: int, where: str) -> None:
         raise NtpError(status, where)
 
 
-def _stream() -> int:
+# Enqueueing a call must not take longer than its kernels: two calls of a small MLP shard (512 x 1024 x 586) took 34 us on the host and 33 on
+# the device, six of a small attention shard (4 x 512 tokens, 3 heads of 64) 66 and 61, a layer's reshard of 9 to 7 shards a tensor 86 and 33; now 25,
+# 45 and 59.  So nothing is looked up twice: torch is bound once, the raw stream is asked for without a Stream object around it (2.9 -> 0.3 us a call), and a tensor's shape and
+# strides are fetched whole (0.65 -> 0.4 us a tensor).
+_torch = None
+_raw_stream = None  # device ordinal -> current stream, where this torch has it
+
+
+def _bind_torch():
+    global _torch, _raw_stream
     import torch
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _torch = torch
+    return torch
+
+
+def _stream() -> int:
+    torch = _torch or _bind_torch()
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch._C._cuda_getDevice())
     return int(torch.cuda.current_stream().cuda_stream)
 
 
@@ -210,13 +228,22 @@ def _mat(t, dtype=None):
     """(device pointer, leading dimension in elements) of a 2-D row-major tensor, or (None, 0)."""
     if t is None:
         return None, 0
-    if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
+    shape, stride = t.size(), t.stride()
+    if len(shape) != 2 or (stride[1] != 1 and shape[1] > 1):
         raise ValueError("expected a row-major 2-D tensor")
-    if dtype is not None and t.dtype != dtype:
+    if dtype is not None and t.dtype is not dtype:
         raise TypeError(f"expected {dtype}, got {t.dtype}")
     if not t.is_cuda:
         raise ValueError("expected a device tensor")
-    return t.data_ptr(), int(t.stride(0))
+    return t.data_ptr(), stride[0]
+
+
+def _mats(tensors, dtype):
+    """The same of several tensors, one after the other in one list."""
+    args = []
+    for t in tensors:
+        args += _mat(t, dtype)
+    return args
 
 
 # ---- handle ----------------------------------------------------------------------
@@ -323,60 +350,38 @@ def ntp_reshard_segments(spec: TensorSpec, src_tp: int, dst_tp: int) -> list[tup
 # ---- device calls ----------------------------------------------------------------
 def ntp_mlp_shard_fwd(X, A_t, B, P, Y, Zpart, n_r: int, gelu_mode: int = NTP_GELU_ERF, handle=None) -> None:
     """X [M,H], A_t [n_r,H], B [n_r,H] bf16 -> P, Y [M, >=n_r] and Zpart [M,H] bf16 (all preallocated)."""
-    import torch
-    bf = torch.bfloat16
     shape = MlpShape(X.shape[0], X.shape[1], n_r, gelu_mode)
-    args = []
-    for t in (X, A_t, B, P, Y, Zpart):
-        args += list(_mat(t, bf))
+    args = _mats((X, A_t, B, P, Y, Zpart), (_torch or _bind_torch()).bfloat16)
     _check(lib().ntp_mlp_shard_fwd(_h(handle), C.byref(shape), *args, _stream()), "ntp_mlp_shard_fwd")
 
 
 def ntp_mlp_shard_bwd(dZ, X, A_t, B, P, Y, dP, dXpart, dA_t, dB, n_r: int, gelu_mode: int = NTP_GELU_ERF,
                       accumulate: bool = False, handle=None) -> None:
-    import torch
-    bf, f32 = torch.bfloat16, torch.float32
+    torch = _torch or _bind_torch()
     shape = MlpShape(X.shape[0], X.shape[1], n_r, gelu_mode)
-    args = []
-    for t in (dZ, X, A_t, B, P, Y, dP, dXpart):
-        args += list(_mat(t, bf))
-    for t in (dA_t, dB):
-        args += list(_mat(t, f32))
+    args = _mats((dZ, X, A_t, B, P, Y, dP, dXpart), torch.bfloat16) + _mats((dA_t, dB), torch.float32)
     _check(lib().ntp_mlp_shard_bwd(_h(handle), C.byref(shape), *args, int(bool(accumulate)), _stream()), "ntp_mlp_shard_bwd")
 
 
 def ntp_attn_proj_shard_fwd(M, H, w_qkv, w_o, X=None, Wqkv=None, QKV=None, C_=None, Wo=None, Zpart=None, handle=None) -> None:
-    import torch
-    bf = torch.bfloat16
     shape = AttnShape(M, H, w_qkv, w_o)
-    args = []
-    for t in (X, Wqkv, QKV, C_, Wo, Zpart):
-        args += list(_mat(t, bf))
+    args = _mats((X, Wqkv, QKV, C_, Wo, Zpart), (_torch or _bind_torch()).bfloat16)
     _check(lib().ntp_attn_proj_shard_fwd(_h(handle), C.byref(shape), *args, _stream()), "ntp_attn_proj_shard_fwd")
 
 
 def ntp_attn_proj_shard_fwd_static(M, H, w_qkv, w_o, X=None, Wqkv=None, QKV=None, C_=None, Wo=None, Zpart=None,
                                    handle=None) -> None:
     """ntp_attn_proj_shard_fwd with the split-K partial sums in the library's static device array."""
-    import torch
-    bf = torch.bfloat16
     shape = AttnShape(M, H, w_qkv, w_o)
-    args = []
-    for t in (X, Wqkv, QKV, C_, Wo, Zpart):
-        args += list(_mat(t, bf))
+    args = _mats((X, Wqkv, QKV, C_, Wo, Zpart), (_torch or _bind_torch()).bfloat16)
     _check(lib().ntp_attn_proj_shard_fwd_static(_h(handle), C.byref(shape), *args, _stream()), "ntp_attn_proj_shard_fwd_static")
 
 
 def ntp_attn_proj_shard_bwd(M, H, w_qkv, w_o, dZ=None, dQKV=None, X=None, C_=None, Wqkv=None, Wo=None, dC=None,
                             dXpart=None, dWqkv=None, dWo=None, accumulate: bool = False, handle=None) -> None:
-    import torch
-    bf, f32 = torch.bfloat16, torch.float32
+    torch = _torch or _bind_torch()
     shape = AttnShape(M, H, w_qkv, w_o)
-    args = []
-    for t in (dZ, dQKV, X, C_, Wqkv, Wo, dC, dXpart):
-        args += list(_mat(t, bf))
-    for t in (dWqkv, dWo):
-        args += list(_mat(t, f32))
+    args = _mats((dZ, dQKV, X, C_, Wqkv, Wo, dC, dXpart), torch.bfloat16) + _mats((dWqkv, dWo), torch.float32)
     _check(lib().ntp_attn_proj_shard_bwd(_h(handle), C.byref(shape), *args, int(bool(accumulate)), _stream()),
            "ntp_attn_proj_shard_bwd")
 
@@ -389,7 +394,7 @@ def attn_core_shape(n_seq, seq_len, plan: dict, group: int, causal: bool = False
 
 def ntp_attn_core_shard_fwd(shape: AttnCoreShape, QKV, C_, LSE=None, handle=None) -> None:
     """QKV [M, (q_cnt + 2 kv_cnt) d] bf16 -> C_ [M, q_cnt d] bf16 and LSE [q_cnt, M] fp32 (optional)."""
-    import torch
+    torch = _torch or _bind_torch()
     q, ldq = _mat(QKV, torch.bfloat16)
     c, ldc = _mat(C_, torch.bfloat16)
     lse = None
@@ -403,7 +408,7 @@ def ntp_attn_core_shard_fwd(shape: AttnCoreShape, QKV, C_, LSE=None, handle=None
 def ntp_attn_core_shard_bwd(shape: AttnCoreShape, QKV, C_, dC, LSE, Delta, dQKV, handle=None) -> None:
     """Gradient of the attention core: dQKV (QKV's layout) from dC; LSE from the forward call, Delta scratch
     (both contiguous fp32 [q_cnt, M])."""
-    import torch
+    torch = _torch or _bind_torch()
     bf = torch.bfloat16
     q, ldq = _mat(QKV, bf)
     c, ldc = _mat(C_, bf)
@@ -452,12 +457,8 @@ def row_segments(items):
 def ntp_mlp_shard_bwd_resharded(dZ, X, A_t, B, P, Y, dP, dXpart, dA_segs, dB_segs, n_r: int,
                                 gelu_mode: int = NTP_GELU_ERF, accumulate: bool = False, handle=None) -> None:
     """As ntp_mlp_shard_bwd; dA_segs / dB_segs are ctypes arrays of RowSegment."""
-    import torch
-    bf = torch.bfloat16
     shape = MlpShape(X.shape[0], X.shape[1], n_r, gelu_mode)
-    args = []
-    for t in (dZ, X, A_t, B, P, Y, dP, dXpart):
-        args += list(_mat(t, bf))
+    args = _mats((dZ, X, A_t, B, P, Y, dP, dXpart), (_torch or _bind_torch()).bfloat16)
     _check(lib().ntp_mlp_shard_bwd_resharded(_h(handle), C.byref(shape), *args, dA_segs, len(dA_segs), dB_segs, len(dB_segs),
                                              int(bool(accumulate)), _stream()), "ntp_mlp_shard_bwd_resharded")
 
@@ -466,12 +467,8 @@ def ntp_attn_proj_shard_bwd_resharded(M, H, w_qkv, w_o, dZ=None, dQKV=None, X=No
                                       dXpart=None, dWqkv_segs=None, dWo_segs=None, accumulate: bool = False,
                                       handle=None) -> None:
     """As ntp_attn_proj_shard_bwd; dWqkv_segs / dWo_segs are ctypes arrays of RowSegment."""
-    import torch
-    bf = torch.bfloat16
     shape = AttnShape(M, H, w_qkv, w_o)
-    args = []
-    for t in (dZ, dQKV, X, C_, Wqkv, Wo, dC, dXpart):
-        args += list(_mat(t, bf))
+    args = _mats((dZ, dQKV, X, C_, Wqkv, Wo, dC, dXpart), (_torch or _bind_torch()).bfloat16)
     q = dWqkv_segs if dWqkv_segs is not None else (RowSegment * 0)()
     o = dWo_segs if dWo_segs is not None else (RowSegment * 0)()
     _check(lib().ntp_attn_proj_shard_bwd_resharded(_h(handle), C.byref(shape), *args, q, len(q), o, len(o), int(bool(accumulate)),
@@ -484,15 +481,14 @@ def _shard_arrays(spec: TensorSpec, src_tp: int, dst_tp: int, src_shards, dst_sh
     dp, dl = (vp * dst_tp)(), (i64 * dst_tp)()
     if len(src_shards) != src_tp or len(dst_shards) != dst_tp:
         raise ValueError("one entry per rank expected")
+    elem_size = spec.elem_size
     for arr_p, arr_l, shards in ((sp, sl, src_shards), (dp, dl, dst_shards)):
         for i, t in enumerate(shards):
             if t is None or t.numel() == 0:
-                arr_p[i], arr_l[i] = None, 0
-                continue
-            if t.element_size() != spec.elem_size:
+                continue  # (the arrays start as NULL and 0)
+            if t.element_size() != elem_size:
                 raise TypeError("element size of a shard differs from the spec")
-            p, ld = _mat(t)
-            arr_p[i], arr_l[i] = p, ld
+            arr_p[i], arr_l[i] = _mat(t)
     return sp, sl, dp, dl
 
 
