@@ -121,10 +121,15 @@ constexpr int kTileOverhead = 4;            // prologue and epilogue of an outpu
 constexpr double kReduceBytesPerCycle = 2000.0, kReduceFixedCycles = 6000.0;
 constexpr int kMaxSplits = 8, kMinSplitTiles = 8;
 
+// Workgroups of the busiest XCD's share of a launch with `splits` K chunks a tile: a tile and its chunks are on one XCD, so that 85 tiles in three
+// chunks are 33 workgroups on five of the XCDs and 30 on the others, whose 32 compute units take them in two rounds (2066 x 536 over K =
+// 3992: 43 us; in two chunks 31).
+int64_t xcd_load(int64_t tiles, int64_t splits) { return (tiles + 7) / 8 * splits; }
+
 double tile_time(int64_t M, int64_t N, int64_t ktiles, int layout, int i, int splits, int cus) {
   const TileShape& ts = kTileShapes[i];
   const int64_t tiles = ((M + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn);
-  const int64_t cu_load = (tiles * splits + cus - 1) / cus;
+  const int64_t units = std::max(cus / 8, 1), cu_load = splits == 1 ? (tiles + cus - 1) / cus : (xcd_load(tiles, splits) + units - 1) / units;
   const double rate = ts.waves == 4 && tiles <= cus ? kLoneSmallTileRate : kTileRate[layout][i];
   const int64_t kt = (ktiles + splits - 1) / splits + kTileOverhead;
   return double(cu_load) * double(kt) * kTileCycles * (ts.bm * ts.bn / 65536.0) / rate;
@@ -219,7 +224,7 @@ SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int layout, int64
   if (old.splits > 1 ? tiles * 2 > cus : ts.bm != 128 || ts.bn != 128) return old;
   SplitChoice best{kDeepTile, 1, int(ktiles * 64), kDeep5};
   double best_t = 0.47 * double(ktiles);
-  for (int sp = 2; sp <= kMaxDeepSplits && tiles * sp <= cus; ++sp) {
+  for (int sp = 2; sp <= kMaxDeepSplits && xcd_load(tiles, sp) * 8 <= cus; ++sp) {
     const int64_t chunk_tiles = (ktiles + sp - 1) / sp;
     if (chunk_tiles < 4 || int64_t(sp) * M * ldw * 4 > ws_bytes) break;
     if ((sp - 1) * chunk_tiles * 64 >= K) continue;  // the last chunk would be empty

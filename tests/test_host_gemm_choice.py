@@ -80,6 +80,18 @@ def test_small_tiles_where_two_workgroups_per_unit_hold_them(workspace_1gib):
     assert N.ntp_gemm_choice(0, 2048, 1024, 1024)["wavefronts"] == 4
 
 
+def test_chunks_fit_the_units_of_an_xcd(workspace_1gib):
+    """A tile and its K chunks are on one of the eight XCDs: 128 x 128 tiles are cut into no more chunks than the 32 units of the busiest one take at once."""
+    cut = 0
+    for layout, M, Nn, K in itertools.product((0, 1, 2), (130, 637, 1028, 2066, 3300), (136, 536, 1200, 2600), (2056, 3992, 9472, 13520)):
+        c = N.ntp_gemm_choice(layout, M, Nn, K)
+        if (c["tile_m"], c["tile_n"], c["wavefronts"]) == (128, 128, 8) and c["k_splits"] > 1:
+            cut += 1
+            assert -(-_tiles(c, M, Nn) // 8) * c["k_splits"] <= 32, (layout, M, Nn, K, c)
+    assert cut > 30
+    assert N.ntp_gemm_choice(0, 2066, 536, 3992)["k_splits"] == 2  # 85 tiles: three chunks would be 33 workgroups on five of the XCDs
+
+
 def test_choice_rejects_bad_arguments():
     for args in [(3, 8, 8, 8), (-1, 8, 8, 8), (0, 0, 8, 8), (0, 8, 0, 8), (0, 8, 8, -1), (0, 1 << 31, 8, 8)]:
         with pytest.raises(N.NtpError):
