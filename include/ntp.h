@@ -115,7 +115,8 @@ int ntp_device_info(const ntp_handle_t* h, int32_t* device, int32_t* compute_uni
 #define NTP_OPT_ATTN_COPY 11         /* how the attention kernels bring their 64-row tiles to LDS where both forms
                                         exist (head dimension 128; forward: 16 query rows per wavefront): 1 through
                                         registers, 2 by DMA into chunk-permuted rows, 3 as 2 and the backward kernels
-                                        with 32 instead of 16 rows per wavefront; 0: the library's choice              */
+                                        with 32 instead of 16 rows per wavefront (also at head dimension 64, where they
+                                        share a launch and walks are not cut); 0: the library's choice                */
 #define NTP_OPT_ATTN_BWD_LAUNCHES 12  /* the attention core's dQ and dK/dV kernels: 1 one launch each, 2 one launch for
                                         both where both copy by DMA, or at head dimension 64 where neither walk is
                                         cut (they then share the compute units; a small kernel stores the rows' delta

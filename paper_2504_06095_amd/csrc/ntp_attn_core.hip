@@ -2173,6 +2173,8 @@ __global__ __launch_bounds__(256) void attn_core_delta_kernel(const CoreBwdArgs 
 
 #include "ntp_attn_small.h"
 
+#include "ntp_attn_bwd64.h"
+
 // Adds the parts of a cut walk and stores the gradient as bf16.  `rows` rows per workgroup of the cut
 // kernel, `width` fp32 values per row: D (dQ) or 2 D ([dK | dV]).  One thread per 4 values.
 template <int D, bool DKV>
@@ -2249,6 +2251,7 @@ struct CoreChoice {
   bool bwd_wide;         // both with 32 owned rows per wavefront
   bool bwd_both;         // both backward kernels go out as one launch
   int64_t dkv_ws_offset; // then: byte offset of the dK/dV parts in the workspace (behind the dQ parts)
+  bool bwd64;            // the shared backward launch at head dimension 64 has 32 owned rows per wavefront and brings its tiles to LDS by DMA
   bool fwd_small, bwd_small;  // 16 rows per workgroup, whose wavefronts share out the walk (ntp_attn_small.h)
 };
 
@@ -2325,8 +2328,24 @@ bool wide_pays(const ntp_attn_core_shape_t* s, int dq_parts, int dkv_parts, doub
   if (!cut && causal && heads_per_kv == 1 && per_unit <= 4.0 && walk < 80.0 && per_unit / 2 >= 0.82 * std::ceil(per_unit / 2)) return false;
   return walk >= (per_unit >= 8.0 ? 36.0 : causal && per_unit >= 4.0 ? 28.0 : 24.0) || (walk >= 18.0 && !cut && longest >= 1.5 * 7.0 * pairs);
 }
+// Whether the backward launch at head dimension 64 with 32 rows per wavefront (ntp_attn_bwd64.h) is the faster one, by its 128-row dK/dV workgroups per compute unit,
+// of which one and a dQ workgroup run there at a time (64 rows: three): what it gains, up to a third, a nearly empty last round loses again.  192 random launches against
+// the choice without it, of those taken:
+//  - causal, a query head per KV head: 0.55 (above half: every unit has work) to 1, and from 1.5: 0.65-0.95 of the time (4 x 1747 tokens, 14 heads 135 -> 115 us; 6720
+//    tokens, 8 heads 268 -> 174, which was cut); between, 1.00-1.09 (1.17, 4 x 3647 tokens, 5 heads 204 -> 222);
+//  - causal, several query heads per KV head: from 0.65, 0.78-0.94 (dQ workgroups fill the last round); 0.41 and 0.48: 1.28 and 1.20;
+//  - unmasked, all walks equal: 0.65 to 1 0.73-0.88, above where the last round is filled to 0.85 0.81-0.95 (0.72, 2 x 5823 tokens, 4 heads 1.09); with several query heads per
+//    KV head from 0.95 on and to 0.79, 0.81-0.86 (4 x 2048 tokens, 16 heads on 4 277 -> 231 us; 0.71 1.04, 0.56 1.11-1.14).
+bool bwd64_pays(const ntp_attn_core_shape_t* s, double cus) {
+  const int64_t tiles = (int64_t(s->seq_len) + 127) / 128, wgs = (s->causal ? (tiles + 1) / 2 : tiles) * s->n_seq * s->kv_cnt;
+  const double load = double(wgs) / cus, filled = load / std::ceil(load);
+  const bool grouped = std::min<int64_t>(s->group, s->q_cnt) > 1;
+  if (tiles < 1 || wgs < 1 || s->q_cnt < 1 || int64_t(s->n_seq) * s->seq_len * s->q_cnt > (int64_t(1) << 33)) return false;  // (the delta kernel's grid)
+  if (s->causal) return grouped ? load >= 0.65 : load >= 1.5 || (load >= 0.55 && load <= 1.0);
+  return grouped ? load >= 0.95 && filled >= 0.79 : load >= 0.65 && filled >= (load > 1.0 ? 0.85 : 0.0);
+}
 CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_core_shape_t* s) {
-  CoreChoice c{16, 1, 1, 1, 0, false, false, false, false, 0, false, false};
+  CoreChoice c{16, 1, 1, 1, 0, false, false, false, false, 0, false, false, false};
   const bool causal = s->causal != 0;
   const int64_t tiles = (s->seq_len + kBKV - 1) / kBKV;
   // under the causal mask a workgroup takes a pair of tiles, one from each end of the sequence
@@ -2375,7 +2394,11 @@ CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_cor
       c.dq_parts = c.dkv_parts = 1;
       c.bwd_wide = false;
     }
+    c.bwd64 = s->head_dim == 64 && !c.bwd_small && bwd64_pays(s, cus);
+  } else if (s->head_dim == 64 && h->opt[NTP_OPT_ATTN_COPY] == 3 && h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] != 1) {
+    c.bwd64 = c.dq_parts == 1 && c.dkv_parts == 1;
   }
+  if (c.bwd64) c.dq_parts = c.dkv_parts = 1;
   if (c.fwd_parts > 1 || c.fwd_small) c.fwd_rows = 16;
   c.dq_dma = c.dkv_dma = dma;
   if (c.fwd_parts > 1) c.ws_bytes = std::max(c.ws_bytes, bq * c.fwd_parts * bf);
@@ -2555,10 +2578,11 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
   a.kv_off = s->kv_off;
   a.group = s->group;
   a.causal = s->causal ? 1 : 0;
-  constexpr int qbw = 1;  // 16 query rows per wavefront, but for cc.bwd_wide (ntp_attn_bwd_wide.h)
-  a.tiles = (s->seq_len + 64 * qbw - 1) / (64 * qbw);
-  constexpr int kb = 1;  // 64 keys per workgroup of the dK/dV kernel
-  const int32_t key_tiles = (s->seq_len + 64 * kb - 1) / (64 * kb);
+  const CoreChoice cc = choose_core(h, h->workspace ? h->workspace_bytes : 0, s);
+  constexpr int qbw = 1, kb = 1;  // of the kernels that go out one by one: 16 rows per wavefront, but for cc.bwd_wide (ntp_attn_bwd_wide.h)
+  const int32_t tile_rows = cc.bwd64 ? 128 : 64;  // of a workgroup (cc.bwd_wide, cc.bwd_small: below)
+  a.tiles = (s->seq_len + tile_rows - 1) / tile_rows;
+  const int32_t key_tiles = a.tiles;
   a.scale = float(1.0 / std::sqrt(double(s->head_dim)));
   a.scale_log2 = float(1.4426950408889634 / std::sqrt(double(s->head_dim)));
   hipStream_t hs = static_cast<hipStream_t>(stream);
@@ -2567,7 +2591,6 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
   const int64_t bq = int64_t(a.tiles) * s->n_seq * s->q_cnt, bk = int64_t(key_tiles) * s->n_seq * s->kv_cnt;
   if (bq > 0x7fffffffll || bk > 0x7fffffffll) return NTP_ERR_UNSUPPORTED;
   a.part_sums = static_cast<float*>(h->workspace);
-  const CoreChoice cc = choose_core(h, h->workspace ? h->workspace_bytes : 0, s);
   const int32_t q_pairs = s->causal ? (a.tiles + 1) / 2 : 0, k_pairs = s->causal ? (key_tiles + 1) / 2 : 0;
   int64_t dq_wgs = int64_t(q_pairs > 0 ? q_pairs : a.tiles) * s->n_seq * s->q_cnt * cc.dq_parts;
   int64_t dkv_wgs = int64_t(k_pairs > 0 ? k_pairs : key_tiles) * s->n_seq * s->kv_cnt * cc.dkv_parts;
@@ -2626,7 +2649,8 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
       order.chunk = uint32_t(std::max(h->compute_units, 1));
       order.paired = uint32_t(std::min(dq_wgs, dkv_wgs) / order.chunk * order.chunk);
       const auto both = wide ? (s->causal ? attn_core_bwd_both_kernel<true> : attn_core_bwd_both_kernel<false>)
-                             : (s->causal ? attn_core_bwd_both64_kernel<true> : attn_core_bwd_both64_kernel<false>);
+                             : cc.bwd64 ? (s->causal ? attn_core_bwd_both64_dma_kernel<true> : attn_core_bwd_both64_dma_kernel<false>)
+                                        : (s->causal ? attn_core_bwd_both64_kernel<true> : attn_core_bwd_both64_kernel<false>);
       hipLaunchKernelGGL(both, grid, dim3(kThreads), 0, hs, adq, adkv, order);
       ok = hipGetLastError() == hipSuccess;
     }

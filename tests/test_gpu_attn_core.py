@@ -338,6 +338,17 @@ def test_attn_core_bwd_head_dimension_64_launches(opts, n_q, n_kv, tp, rank, n_s
     assert names == (["attn_core_bwd_dq", "attn_core_bwd_dkv"] if launches == 1 else ["attn_core_bwd_both"]), names
 
 
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+@pytest.mark.parametrize("n_q,n_kv,tp,rank,n_seq,S,pad", [(4, 1, 4, 3, 1, 1, 0), (3, 3, 1, 0, 2, 64, 0), (8, 2, 3, 2, 1, 65, 0), (8, 2, 3, 1, 2, 129, 8),
+                                                          (12, 3, 1, 0, 1, 256, 8), (64, 8, 30, 3, 2, 449, 0), (6, 6, 4, 1, 1, 1100, 8)])
+def test_attn_core_bwd_head_dimension_64_32_rows_per_wavefront(opts, n_q, n_kv, tp, rank, n_seq, S, pad, causal):
+    """Below the launcher's own choice: one, two, four and nine tiles of 128 rows (the middle one of an odd number has no partner under the mask), one
+    or both 64-row halves in the last, odd and even walks through the two buffers, grouped heads of which the rank holds a part."""
+    _say(f"attn core bwd d=64, 32 rows per wavefront: heads {n_q}/{n_kv} tp {tp} rank {rank} n_seq={n_seq} S={S} pad={pad} causal={causal}")
+    opts(K.NTP_OPT_ATTN_COPY, 3)
+    _bwd_case(n_q, n_kv, tp, rank, 64, n_seq, S, causal, seed=43, pad=pad)
+
+
 # 16 rows per workgroup, whose wavefronts share out the walk: sequences at the edges of 16 rows, of a tile, of one tile per wavefront and of two;
 # grouped heads of which the rank holds a part; padded rows
 @pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
@@ -351,9 +362,10 @@ def test_attn_core_few_workgroups(n_q, n_kv, tp, rank, d, n_seq, S, pad, causal)
 
 
 @pytest.mark.parametrize("value", [float("inf"), float("nan")], ids=["inf", "nan"])
-@pytest.mark.parametrize("d", [64, 128])
-def test_attn_core_few_workgroups_non_finite_rows_reach_no_further(opts, value, d):
-    """A non-finite query, key, value or gradient row makes the same outputs non-finite as with 64 rows per workgroup, and the others agree."""
+@pytest.mark.parametrize("d,here", [(64, 0), (128, 0), (64, 3)])
+def test_attn_core_few_workgroups_non_finite_rows_reach_no_further(opts, value, d, here):
+    """A non-finite query, key, value or gradient row makes the same outputs non-finite as with 64 rows per workgroup, and the others agree.  (3: the
+    backward kernels with 32 rows per wavefront instead.)"""
     import torch
     import paper_2504_06095_amd as N
     _say(f"attn core, 16 rows per workgroup, a row of {value}, d={d}")
@@ -365,7 +377,7 @@ def test_attn_core_few_workgroups_non_finite_rows_reach_no_further(opts, value, 
         dC = torch.empty(S, q * d, device="cuda").normal_(generator=g).bfloat16()
         (dC if block < 0 else QKV)[row, max(block, 0) * d + 5] = value
         got = []
-        for copy in (0, 1):
+        for copy in (here, 1):
             opts(K.NTP_OPT_ATTN_COPY, copy)
             C, dQKV, LSE, Delta = torch.zeros_like(dC), torch.zeros_like(QKV), torch.zeros(q, S, device="cuda"), torch.zeros(q, S, device="cuda")
             N.ntp_attn_core_shard_fwd(shape, QKV, C, LSE)

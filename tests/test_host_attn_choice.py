@@ -149,6 +149,13 @@ def test_parts_respect_the_workspace_size():
         assert Bd.lib().ntp_set_workspace(Bd.default_handle().ptr, None, 0) == 0
 
 
+@pytest.mark.parametrize("n_q,n_kv,n_seq,S,cut", [(8, 8, 1, 6720, False), (5, 5, 2, 3702, False),  # 128-row workgroups for 0.84 and 0.59 of the units
+                                                  (7, 7, 1, 4194, True), (16, 4, 1, 3444, True)])  # 0.46; grouped, 0.22
+def test_head_dimension_64_walks_in_one_piece(workspace_1gib, n_q, n_kv, n_seq, S, cut):
+    c = N.ntp_attn_core_choice(_shape(n_q, n_kv, 1, 0, n_seq, S, True, d=64))
+    assert (c["dq_parts"] > 1, c["dkv_parts"] > 1) == (cut, cut)
+
+
 def test_choice_rejects_bad_shapes():
     s = _shape(8, 2, 3, 0, 1, 200, True, d=128)
     s.head_dim = 96
