@@ -2297,6 +2297,13 @@ bool small_bwd_pays(const ntp_attn_core_shape_t* s, const CoreChoice& c, double 
                            : 7.0 + std::max(std::max(1.72 * dkv, 1.23 * dq), per * (double(kv * c.dkv_parts) * (13.2 + 3.69 * dkv) + double(q * c.dq_parts) * 8.1)) + 6.7 * cuts;
   return now < 0.9 * other;
 }
+// Whether that backward launch also forms the rows' delta values, which saves a launch (3-4 us, 7 with the host's part where calls are short) and costs every step of a dK/dV walk
+// the rows of C: by the units of a workgroup's walk, of which a wavefront takes every fourth.  60 random small launches, head dimension 64: up to 12 units 0.68-1.01 of
+// the time (3 heads, four sequences of 222 tokens 25.7 -> 18.4 us with its call), 13 to 20 1.00-1.21; 128: up to 7 0.68-0.97, 8 1.02, 9 to 12 1.10-1.18.
+bool small_forms_delta(const ntp_attn_core_shape_t* s) {
+  const int64_t units = std::min<int64_t>(s->group, s->q_cnt) * ((int64_t(s->seq_len) + kBKV - 1) / kBKV);
+  return units <= (s->head_dim == 64 ? 12 : 7);
+}
 // (128-row, 64-row) tile pairs of a launch of the backward kernels with 32 rows per wavefront
 int64_t wide_pairs(const ntp_attn_core_shape_t* s) {
   const int64_t tiles = (s->seq_len + kBKV - 1) / kBKV, own = (tiles + 1) / 2;
@@ -2628,15 +2635,19 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
     adkv.part_sums = a.part_sums + cc.dkv_ws_offset / 4;
     if (ntp::timing_on(h)) timing_begin("both", cc.dq_parts > 1 || cc.dkv_parts > 1, 7.0);
     const bool wide = s->head_dim == 128;
-    hipLaunchKernelGGL(wide ? attn_core_delta_kernel<128> : attn_core_delta_kernel<64>, dim3(uint32_t(delta_wgs)), dim3(256), 0, hs, a, M);
-    ok = hipGetLastError() == hipSuccess;
+    const bool forms_delta = cc.bwd_small && small_forms_delta(s);
+    if (!forms_delta) {
+      hipLaunchKernelGGL(wide ? attn_core_delta_kernel<128> : attn_core_delta_kernel<64>, dim3(uint32_t(delta_wgs)), dim3(256), 0, hs, a, M);
+      ok = hipGetLastError() == hipSuccess;
+    }
     const dim3 grid(uint32_t(sections * (dq_wgs + dkv_wgs)));
     if (ok && cc.bwd_small) {
       a.tiles = (s->seq_len + 15) / 16;
       const int64_t n_dkv = int64_t(a.tiles) * s->n_seq * s->kv_cnt;
       const dim3 small(uint32_t(n_dkv + int64_t(a.tiles) * s->n_seq * s->q_cnt));
-      if (wide) hipLaunchKernelGGL(attn_core_bwd_small_kernel<128>, small, dim3(kThreads), 0, hs, a, uint32_t(n_dkv));
-      else hipLaunchKernelGGL(attn_core_bwd_small_kernel<64>, small, dim3(kThreads), 0, hs, a, uint32_t(n_dkv));
+      const auto kernel = wide ? (forms_delta ? attn_core_bwd_small_kernel<128, true> : attn_core_bwd_small_kernel<128, false>)
+                               : (forms_delta ? attn_core_bwd_small_kernel<64, true> : attn_core_bwd_small_kernel<64, false>);
+      hipLaunchKernelGGL(kernel, small, dim3(kThreads), 0, hs, a, uint32_t(n_dkv));
       ok = hipGetLastError() == hipSuccess;
     } else if (ok && cc.bwd_wide) {
       // the longest of the short dK/dV walks against the longest dQ walk, in matrix products of tile pairs

@@ -274,7 +274,7 @@ __device__ __forceinline__ void small_sum(unsigned char* lds, int wave, int lq, 
 }
 
 // dQ: workgroup `b` of `count` = 16 query rows of one (sequence, head).
-template <int D>
+template <int D, bool STORE_DELTA>
 __device__ __forceinline__ void bwd_dq_small_body(const CoreBwdArgs& a, const uint32_t b, const uint32_t count, unsigned char* const lds) {
   using T = SmallTile<D>;
   constexpr int KS = T::KS, DB = T::DB;
@@ -316,6 +316,7 @@ __device__ __forceinline__ void bwd_dq_small_body(const CoreBwdArgs& a, const ui
     }
     delta = xor_sum(part);
     lse2 = a.LSE[int64_t(head) * Mtot + tok0 + qr] * 1.4426950408889634f;
+    if (STORE_DELTA && wave == 0 && lh == 0 && qrow < S) a.Delta[int64_t(head) * Mtot + tok0 + qrow] = delta;
   }
   auto ask = [&](int t) {
     T::dma(srcK.rs, sK, voff, uint32_t(t) * srcK.step);
@@ -384,7 +385,8 @@ __device__ __forceinline__ void bwd_dq_small_body(const CoreBwdArgs& a, const ui
 }
 
 // dK and dV: workgroup `b` of `count` = 16 keys of one (sequence, KV head); the walk goes over the query tiles of every query head that reads it.
-template <int D>
+// (FORM_DELTA: the rows' delta values are formed from their rows of C, which are read with the tile; else a launch before this one has stored them.)
+template <int D, bool FORM_DELTA>
 __device__ __forceinline__ void bwd_dkv_small_body(const CoreBwdArgs& a, const uint32_t b, const uint32_t count, unsigned char* const lds, float (*const sLD)[2][kBKV]) {
   using T = SmallTile<D>;
   constexpr int KS = T::KS, DB = T::DB;
@@ -419,6 +421,7 @@ __device__ __forceinline__ void bwd_dkv_small_body(const CoreBwdArgs& a, const u
     }
   }
   float rl = 0.f, rd = 0.f;  // of the tile's row `lane`
+  bf16x8 cf[4 * KS];         // FORM_DELTA: the tile's rows of C, laid out as the fragments of dC
   auto ask = [&](int unit) {
     const int head = h_lo + unit / nt, t = t_lo + unit % nt;
     TileSrc<D> srcQ, srcG;
@@ -426,7 +429,16 @@ __device__ __forceinline__ void bwd_dkv_small_body(const CoreBwdArgs& a, const u
     srcG.init(a.dC + int64_t(head) * D + tok0 * a.lddc, a.lddc, S);
     const int64_t row = int64_t(head) * Mtot + tok0 + min(t * kBKV + lane, S - 1);
     rl = a.LSE[row] * 1.4426950408889634f;
-    rd = a.Delta[row];
+    if constexpr (FORM_DELTA) {
+#pragma unroll
+      for (int qb = 0; qb < 4; ++qb) {
+        const uint16_t* const cp = a.C + (tok0 + min(t * kBKV + qb * 16 + lq, S - 1)) * a.ldc + int64_t(head) * D + lh * 8;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) cf[qb * KS + ks] = *reinterpret_cast<const bf16x8*>(cp + ks * 32);
+      }
+    } else {
+      rd = a.Delta[row];
+    }
     T::dma(srcQ.rs, sQ, voffq, uint32_t(t) * srcQ.step);
     T::dma(srcG.rs, sG, voffg, uint32_t(t) * srcG.step);
   };
@@ -438,12 +450,23 @@ __device__ __forceinline__ void bwd_dkv_small_body(const CoreBwdArgs& a, const u
     const int qbase = (t_lo + unit % nt) * kBKV;
     dma_done();
     sLD[wave][0][lane] = rl;
-    sLD[wave][1][lane] = rd;
+    if constexpr (!FORM_DELTA) sLD[wave][1][lane] = rd;
     attn_u32x4 qf[4 * KS], gf[4 * KS];
     small_rows<D>(ad, lQ, qf);
     small_reads_done(qf);
     small_rows<D>(ad, lG, gf);
     small_reads_done(gf);
+    if constexpr (FORM_DELTA) {
+      // sum_d dC C is the diagonal of a product of 16-row blocks, row r of which is in the lanes with lane % 16 = r and lane / 16 = r / 4
+#pragma unroll
+      for (int qb = 0; qb < 4; ++qb) {
+        f32x4 dd = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) dd = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, gf[qb * KS + ks]), cf[qb * KS + ks], dd, 0, 0, 0);
+        const float lo = lq & 1 ? dd[1] : dd[0], hi = lq & 1 ? dd[3] : dd[2];
+        if ((lq >> 2) == lh) sLD[wave][1][qb * 16 + lq] = lq & 2 ? hi : lo;
+      }
+    }
     f32x4 l4[4], d4[4];
 #pragma unroll
     for (int qb = 0; qb < 4; ++qb) {
@@ -511,11 +534,12 @@ __device__ __forceinline__ void bwd_dkv_small_body(const CoreBwdArgs& a, const u
   });
 }
 
-// Both in one launch, after the rows' delta values: dK/dV workgroups first (their walks are the longer ones).
-template <int D>
+// Both in one launch: dK/dV workgroups first (their walks are the longer ones).  DELTA: they form the rows' delta values for themselves and the dQ workgroups store
+// them, instead of a launch before this one (small_forms_delta).
+template <int D, bool DELTA>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 128 ? 1 : 2, D == 128 ? 1 : 2))) void attn_core_bwd_small_kernel(const CoreBwdArgs a, const uint32_t n_dkv) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * 2 * SmallTile<D>::BYTES];
   __shared__ __attribute__((aligned(16))) float sLD[4][2][kBKV];
-  if (blockIdx.x < n_dkv) bwd_dkv_small_body<D>(a, blockIdx.x, n_dkv, lds, sLD);
-  else bwd_dq_small_body<D>(a, blockIdx.x - n_dkv, gridDim.x - n_dkv, lds);
+  if (blockIdx.x < n_dkv) bwd_dkv_small_body<D, DELTA>(a, blockIdx.x, n_dkv, lds, sLD);
+  else bwd_dq_small_body<D, DELTA>(a, blockIdx.x - n_dkv, gridDim.x - n_dkv, lds);
 }

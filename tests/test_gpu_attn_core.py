@@ -354,7 +354,8 @@ def test_attn_core_bwd_head_dimension_64_32_rows_per_wavefront(opts, n_q, n_kv, 
 @pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("n_q,n_kv,tp,rank,n_seq,S,pad", [(2, 2, 1, 0, 1, 15, 0), (3, 1, 1, 0, 2, 16, 8), (2, 2, 1, 0, 3, 17, 0), (8, 2, 3, 1, 1, 63, 0), (2, 1, 1, 0, 2, 65, 8),
-                                                          (3, 3, 1, 0, 1, 255, 0), (6, 2, 4, 1, 1, 257, 0), (2, 2, 1, 0, 2, 320, 0), (1, 1, 1, 0, 1, 577, 8)])
+                                                          (3, 3, 1, 0, 1, 255, 0), (6, 2, 4, 1, 1, 257, 0), (2, 2, 1, 0, 2, 320, 0), (1, 1, 1, 0, 1, 577, 8),
+                                                          (2, 1, 1, 0, 1, 250, 0), (3, 1, 1, 0, 1, 256, 8), (3, 1, 1, 0, 1, 321, 0)])  # walks of 8, 12 and 18 units
 def test_attn_core_few_workgroups(n_q, n_kv, tp, rank, d, n_seq, S, pad, causal):
     _say(f"attn core, 16 rows per workgroup n_q={n_q} n_kv={n_kv} d={d} n_seq={n_seq} S={S} pad={pad} causal={causal}")
     _case(n_q, n_kv, tp, rank, d, n_seq, S, causal, seed=4, pad=pad)
