@@ -2173,7 +2173,7 @@ __global__ __launch_bounds__(256) void attn_core_delta_kernel(const CoreBwdArgs 
 
 #include "ntp_attn_small.h"
 
-#include "ntp_attn_bwd64.h"
+#include "ntp_attn_d64.h"
 
 // Adds the parts of a cut walk and stores the gradient as bf16.  `rows` rows per workgroup of the cut
 // kernel, `width` fp32 values per row: D (dQ) or 2 D ([dK | dV]).  One thread per 4 values.
@@ -2335,7 +2335,7 @@ bool wide_pays(const ntp_attn_core_shape_t* s, int dq_parts, int dkv_parts, doub
   if (!cut && causal && heads_per_kv == 1 && per_unit <= 4.0 && walk < 80.0 && per_unit / 2 >= 0.82 * std::ceil(per_unit / 2)) return false;
   return walk >= (per_unit >= 8.0 ? 36.0 : causal && per_unit >= 4.0 ? 28.0 : 24.0) || (walk >= 18.0 && !cut && longest >= 1.5 * 7.0 * pairs);
 }
-// Whether the backward launch at head dimension 64 with 32 rows per wavefront (ntp_attn_bwd64.h) is the faster one, by its 128-row dK/dV workgroups per compute unit,
+// Whether the backward launch at head dimension 64 with 32 rows per wavefront (ntp_attn_d64.h) is the faster one, by its 128-row dK/dV workgroups per compute unit,
 // of which one and a dQ workgroup run there at a time (64 rows: three): what it gains, up to a third, a nearly empty last round loses again.  192 random launches against
 // the choice without it, of those taken:
 //  - causal, a query head per KV head: 0.55 (above half: every unit has work) to 1, and from 1.5: 0.65-0.95 of the time (4 x 1747 tokens, 14 heads 135 -> 115 us; 6720
@@ -2534,7 +2534,10 @@ extern "C" int ntp_attn_core_shard_fwd(ntp_handle_t* h, const ntp_attn_core_shap
     else hipLaunchKernelGGL((attn_core_fwd_dma2_kernel<false>), grid, dim3(kThreads), 0, hs, a);
   } else if (s->head_dim == 128 && qbw == 2) by_pairing(integral_constant<int, 128>{}, integral_constant<int, 2>{});
   else if (s->head_dim == 128) by_pairing(integral_constant<int, 128>{}, integral_constant<int, 1>{});
-  else if (qbw == 2) by_pairing(integral_constant<int, 64>{}, integral_constant<int, 2>{});
+  else if (qbw == 2 && h->opt[NTP_OPT_ATTN_COPY] != 1) {
+    if (a.pairs > 0) hipLaunchKernelGGL(attn_core_fwd64_dma_kernel<true>, grid, dim3(kThreads), 0, hs, a);
+    else hipLaunchKernelGGL(attn_core_fwd64_dma_kernel<false>, grid, dim3(kThreads), 0, hs, a);
+  } else if (qbw == 2) by_pairing(integral_constant<int, 64>{}, integral_constant<int, 2>{});
   else by_pairing(integral_constant<int, 64>{}, integral_constant<int, 1>{});
   bool ok = hipGetLastError() == hipSuccess;
   if (ok && a.n_parts > 1) {

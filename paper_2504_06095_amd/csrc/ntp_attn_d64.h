@@ -1,6 +1,6 @@
-// Attention core backward at head dimension 64 by DMA (included by ntp_attn_core.hip): dQ and dK/dV workgroups of one launch, 128 rows each, 32 per wavefront.
+// Attention core at head dimension 64 by DMA (included by ntp_attn_core.hip), 128 rows per workgroup, 32 per wavefront: backward (dQ and dK/dV workgroups of one launch) and forward.
 //
-// What bound the register-copy bodies (bwd_dq_body, bwd_dkv_body, 16 rows per wavefront) was the LDS: a (64 x 64) tile pair of either kind reads 96 and 128 KB of fragments, one
+// Backward: what bound the register-copy bodies (bwd_dq_body, bwd_dkv_body, 16 rows per wavefront) was the LDS: a (64 x 64) tile pair of either kind reads 96 and 128 KB of fragments, one
 // matrix instruction each, and writes 16 KB of copies, 2000 of the 2160 cycles that both took together.  With two blocks every fragment feeds two
 // matrix instructions; the tiles come by DMA into two buffers (rows of 128 bytes with permuted chunks, see ntp_attn_small.h), one barrier a tile, no staging
 // registers.  Products, masks and rounding are those of the other bodies, and so are the tiles that a row meets.  14 heads, 8192 tokens causal 541 -> 450 us, 2048
@@ -402,4 +402,147 @@ __global__ __launch_bounds__(kThreads, 2) void attn_core_bwd_both64_dma_kernel(c
   uint32_t b = blockIdx.x;
   if (both_place(o, b)) bwd_dkv64_body<PAIRED>(adkv, b, o.n_dkv, tiles, row_values);
   else bwd_dq64_body<PAIRED>(adq, b, gridDim.x - o.n_dkv, tiles);
+}
+
+// Forward: 128 query rows of one (sequence, head), or under the mask a pair of such tiles.  The register-copy kernel with 32 rows per wavefront waited at two barriers a
+// tile and spent vector instructions on its copies.  40 random launches: 0.79-0.92 of its time (2 x 6583 tokens, 14 heads causal 279 -> 223 us; 4 x 2655 unmasked 165 -> 150).
+// What bounds it is the softmax's vector work, 1000 of the 1400 cycles a tile takes on a unit with two workgroups or three.
+template <bool PAIRED>
+__global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads), amdgpu_waves_per_eu(2, 2))) void attn_core_fwd64_dma_kernel(const CoreArgs a) {
+  constexpr int D = 64, KS = 2, DB = 4, B = kBlocks64, kRows = 64 * B;
+  __shared__ __attribute__((aligned(1024))) uint16_t lds[4 * kTile64];  // key buffers 0 and 1, value buffers 0 and 1
+  const uint32_t bid = xcd_major(blockIdx.x, gridDim.x);
+  const int per_seq = PAIRED ? a.pairs : a.q_tiles;
+  const int u = int(bid) % per_seq, sh = int(bid) / per_seq;
+  const int seq = sh % a.n_seq, head = sh / a.n_seq;
+  const int g = (a.q_off + head) / a.group - a.kv_off;
+  const int S = a.seq_len;
+  const int64_t tok0 = int64_t(seq) * S;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lq = lane & 15, lh = lane >> 4;
+  const uint16_t* const Qp = a.QKV + int64_t(head) * D;
+  TileSrc<D> srcK, srcV;
+  srcK.init(a.QKV + int64_t(a.q_cnt + g) * D + tok0 * a.ld, a.ld, S);
+  srcV.init(a.QKV + int64_t(a.q_cnt + a.kv_cnt + g) * D + tok0 * a.ld, a.ld, S);
+  Dma64 dma;
+  dma.init(a.ld, wave, lane);
+  Addr64 ad;
+  ad.init(lds, lq, lh);
+  auto ask = [&](int t, int buf) {  // rows past the sequence end arrive as zeros (masked below)
+    dma.tile(srcK.rs, lds + buf * kTile64, wave, uint32_t(t) * srcK.step);
+    dma.tile(srcV.rs, lds + (2 + buf) * kTile64, wave, uint32_t(t) * srcV.step);
+  };
+
+  for (int seg = 0; seg < (PAIRED ? 2 : 1); ++seg) {
+    const int qt = PAIRED ? (seg == 0 ? a.q_tiles - 1 - u : u) : (a.causal ? a.q_tiles - 1 - u : u);
+    if (seg == 1) {
+      if (qt == a.q_tiles - 1 - u) break;  // odd tile count: the middle tile has no partner
+      __syncthreads();                     // the first pass's last tile has been read by everyone
+    }
+    const int q0 = qt * kRows + wave * (16 * B);
+    const int n_tiles = ((a.causal ? min(S, qt * kRows + kRows) : S) + kBKV - 1) / kBKV;
+    ask(0, 0);
+    bf16x8 qf[B][KS];
+    f32x4 acc[B][DB];
+    float m_run[B], l_run[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const int qr = min(q0 + b * 16 + lq, S - 1);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) qf[b][ks] = *reinterpret_cast<const bf16x8*>(Qp + (tok0 + qr) * a.ld + ks * 32 + lh * 8);
+#pragma unroll
+      for (int db = 0; db < DB; ++db) acc[b][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+      m_run[b] = -INFINITY;
+      l_run[b] = 0.f;
+    }
+
+    auto step = [&](auto bufc, int t) {
+      constexpr int BUF = decltype(bufc)::value;
+      dma_done();       // this wavefront's share of tile t has landed ...
+      __syncthreads();  // ... and everyone's; everyone has read the tile before
+      if (t + 1 < n_tiles) ask(t + 1, BUF ^ 1);
+      const int kv0 = t * kBKV;
+      if (a.causal && kv0 > q0 + 16 * B - 1) return;  // every key of the tile lies after this wavefront's last query row
+      attn_u32x4 kf[8];
+      ad.rows<BUF>(kf);
+      lds_reads_done(kf);
+      attn_u32x2 v0[8], v1[8];
+      ad.cols<2 + BUF, 0>(v0);
+      ad.cols<2 + BUF, 1>(v1);
+      // scores, transposed: [key kb*16 + (lane/16)*4 + r][query b*16 + lane%16]
+      f32x4 st[B][4];
+#pragma unroll
+      for (int b = 0; b < B; ++b)
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+          st[b][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) st[b][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[kb * KS + ks]), qf[b][ks], st[b][kb], 0, 0, 0);
+        }
+      const bool edge = kv0 + kBKV > S || (a.causal && kv0 + kBKV - 1 > q0);
+      bf16x8 pf[B][2];
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        if (edge) {
+          const int qrow = q0 + b * 16 + lq, last = (a.causal ? min(qrow, S - 1) : S - 1) - kv0 - lh * 4;
+#pragma unroll
+          for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (kb * 16 + r > last) st[b][kb][r] = -INFINITY;
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) mx = fmaxf(mx, st[b][kb][r]);
+        mx = xor_max(mx) * a.scale_log2;
+        const float m_new = fmaxf(m_run[b], mx);
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = fast_exp2(m_run[b] - m_use);
+        float ls = 0.f, p[4][4];
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            p[kb][r] = fast_exp2(fmaf(st[b][kb][r], a.scale_log2, -m_use));
+            ls += p[kb][r];
+          }
+        l_run[b] = l_run[b] * alpha + ls;
+        m_run[b] = m_new;
+        if (__any(alpha != 1.0f)) {
+#pragma unroll
+          for (int db = 0; db < DB; ++db) acc[b][db] *= alpha;
+        }
+        small_pack(p, pf[b]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      lds_reads_done(v0);
+      lds_reads_tied(v1);
+      products64<0>(v0, pf, acc);
+      products64<1>(v1, pf, acc);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int t = 0; t < n_tiles; t += 2) {
+      step(std::integral_constant<int, 0>{}, t);
+      if (t + 1 < n_tiles) step(std::integral_constant<int, 1>{}, t + 1);
+    }
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const int qrow = q0 + b * 16 + lq;
+      const float l = xor_sum(l_run[b]);
+      const float inv = 1.0f / l;
+      if (qrow >= S) continue;
+      uint16_t* const cp = a.C + (tok0 + qrow) * a.ldc + int64_t(head) * D + lh * 4;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        u16x4 o;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[r] = ntp_gemm::f32_to_bf16(acc[b][db][r] * inv);
+        *reinterpret_cast<u16x4*>(cp + db * 16) = o;
+      }
+      if (lh == 0 && a.LSE) a.LSE[int64_t(head) * (int64_t(a.n_seq) * S) + tok0 + qrow] = (m_run[b] + log2f(l)) * 0.6931471805599453f;
+    }
+  }  // the workgroup's passes
 }

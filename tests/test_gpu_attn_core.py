@@ -338,6 +338,18 @@ def test_attn_core_bwd_head_dimension_64_launches(opts, n_q, n_kv, tp, rank, n_s
     assert names == (["attn_core_bwd_dq", "attn_core_bwd_dkv"] if launches == 1 else ["attn_core_bwd_both"]), names
 
 
+@pytest.mark.parametrize("copy", [0, 1], ids=["dma", "registers"])
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+@pytest.mark.parametrize("n_q,n_kv,n_seq,S,pad", [(32, 32, 8, 129, 0), (64, 8, 1, 777, 8), (48, 48, 3, 300, 0), (40, 8, 10, 64, 8)])
+def test_attn_core_fwd_head_dimension_64_many_workgroups(opts, n_q, n_kv, n_seq, S, pad, causal, copy):
+    """384 and more tiles of 128 rows, the launcher's line for 32 query rows per wavefront: two, seven, three and one (half a tile) a sequence."""
+    import paper_2504_06095_amd as N
+    _say(f"attn core fwd d=64, 32 rows per wavefront: heads {n_q}/{n_kv} n_seq={n_seq} S={S} pad={pad} causal={causal} copy={copy}")
+    opts(K.NTP_OPT_ATTN_COPY, copy)
+    assert N.ntp_attn_core_choice(N.attn_core_shape(n_seq, S, N.ntp_attn_shard_plan(n_q, n_kv, 64, 1, 0), n_q // n_kv, causal))["fwd_rows_per_wavefront"] == 32
+    _case(n_q, n_kv, 1, 0, 64, n_seq, S, causal, seed=47, pad=pad)
+
+
 @pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
 @pytest.mark.parametrize("n_q,n_kv,tp,rank,n_seq,S,pad", [(4, 1, 4, 3, 1, 1, 0), (3, 3, 1, 0, 2, 64, 0), (8, 2, 3, 2, 1, 65, 0), (8, 2, 3, 1, 2, 129, 8),
                                                           (12, 3, 1, 0, 1, 256, 8), (64, 8, 30, 3, 2, 449, 0), (6, 6, 4, 1, 1, 1100, 8)])

@@ -108,9 +108,10 @@ def test_registers_are_left_alone_while_reads_are_in_flight(assembly, kernel):
     assert _in_flight_faults([c if c[0] != "s_waitcnt" else ("s_waitcnt", c[1], "s_waitcnt vmcnt(0)") for c in code], labels)
 
 
-def test_registers_are_left_alone_at_head_dimension_64(assembly):
-    code, labels = _code(assembly, "attn_core_bwd_both64_dma_kernel")  # (its matrix instructions are the compiler's own)
-    assert sum(op.startswith("ds_read") for op, _, _ in code) >= 128 and not any("scratch_" in text for _, _, text in code)
+@pytest.mark.parametrize("kernel,reads", [("attn_core_bwd_both64_dma_kernel", 128), ("attn_core_fwd64_dma_kernel", 48)])
+def test_registers_are_left_alone_at_head_dimension_64(assembly, kernel, reads):
+    code, labels = _code(assembly, kernel)  # (the matrix instructions are the compiler's own)
+    assert sum(op.startswith("ds_read") for op, _, _ in code) >= reads and not any("scratch_" in text for _, _, text in code)
     assert not _in_flight_faults(code, labels)
 
 
