@@ -2419,8 +2419,13 @@ CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_cor
   // Head dimension 64 (walks that are not cut): at every size measured (3 heads x 512 tokens of 4 sequences 28 -> 20 us, 15 heads
   // x 389 30 -> 22 us, 28 heads x 6062 620 -> 589 us, 22 heads x 3801 no difference).
   const bool pays = s->head_dim == 64 || c.bwd_wide || wq + wk <= 3 * cus;
-  c.bwd_both = c.bwd_small || ((dma || (s->head_dim == 64 && c.dq_parts == 1 && c.dkv_parts == 1)) && h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] != 1 && (pays || h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] == 2) &&
-               (dkv_bytes == 0 || c.dkv_ws_offset + dkv_bytes <= ws_bytes));
+  // (a launch of one kind has nothing to share; and the grids, which have at most four workgroups for every tile and part, must fit)
+  const int64_t delta_wgs = (int64_t(s->n_seq) * s->seq_len * s->q_cnt * (s->head_dim / 8) + 255) / 256;
+  const bool fits = bq > 0 && bk > 0 && bq * c.dq_parts + bk * c.dkv_parts <= 0x1fffff00ll && delta_wgs <= 0x7fffffffll;
+  c.bwd_both = fits && (c.bwd_small || ((dma || (s->head_dim == 64 && c.dq_parts == 1 && c.dkv_parts == 1)) && h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] != 1 &&
+                                        (pays || h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] == 2) && (dkv_bytes == 0 || c.dkv_ws_offset + dkv_bytes <= ws_bytes)));
+  c.bwd64 = c.bwd64 && c.bwd_both;  // (both are forms of that launch only)
+  c.bwd_small = c.bwd_small && c.bwd_both;
   c.ws_bytes = std::max(c.ws_bytes, c.bwd_both ? (dkv_bytes ? c.dkv_ws_offset + dkv_bytes : dq_bytes) : std::max(dq_bytes, dkv_bytes));
   return c;
 }
@@ -2626,7 +2631,7 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
   };
   const int64_t delta_wgs = (M * s->q_cnt * (s->head_dim / 8) + 255) / 256;
   if (sections * dq_wgs > 0x7fffffffll || sections * dkv_wgs > 0x7fffffffll) return NTP_ERR_UNSUPPORTED;
-  if (cc.bwd_both && bq > 0 && bk > 0 && sections * (dq_wgs + dkv_wgs) <= 0x7fffffffll && delta_wgs <= 0x7fffffffll) {
+  if (cc.bwd_both) {
     // one launch for both kernels, after the rows' delta values (5 algorithmic + 2 recomputed products per pair)
     CoreBwdArgs adq = a, adkv = a;
     adq.n_parts = cc.dq_parts;

@@ -361,6 +361,26 @@ def test_attn_core_bwd_head_dimension_64_32_rows_per_wavefront(opts, n_q, n_kv, 
     _bwd_case(n_q, n_kv, tp, rank, 64, n_seq, S, causal, seed=43, pad=pad)
 
 
+@pytest.mark.parametrize("copy", [0, 1, 2, 3])
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+@pytest.mark.parametrize("d,n_seq,S", [(64, 1, 129), (64, 2, 300), (64, 1, 64), (128, 2, 300)])
+def test_attn_core_bwd_without_query_heads(opts, d, n_seq, S, causal, copy):
+    """A shard that holds KV heads and no query head: every row of dK and dV is zero, whichever kernels are asked for."""
+    import torch
+    import paper_2504_06095_amd as N
+    _say(f"attn core bwd, no query heads: d={d} n_seq={n_seq} S={S} causal={causal} copy={copy}")
+    opts(K.NTP_OPT_ATTN_COPY, copy)
+    shape = N.attn_core_shape(n_seq, S, dict(q_cnt=0, kv_cnt=2, q_off=0, kv_off=0, head_dim=d), 1, causal)
+    M = n_seq * S
+    QKV = torch.randn(M, 4 * d, device="cuda").bfloat16()
+    dQKV = torch.full_like(QKV, float("nan"))
+    rows = torch.zeros(M, 8, dtype=torch.bfloat16, device="cuda")
+    none, values = rows[:, :0], torch.zeros(0, M, device="cuda")
+    N.ntp_attn_core_shard_bwd(shape, QKV, none, none, values, values, dQKV)
+    torch.cuda.synchronize()
+    assert (dQKV == 0).all(), torch.nonzero(~(dQKV == 0).all(1))[:4].flatten().tolist()
+
+
 # 16 rows per workgroup, whose wavefronts share out the walk: sequences at the edges of 16 rows, of a tile, of one tile per wavefront and of two;
 # grouped heads of which the rank holds a part; padded rows
 @pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
