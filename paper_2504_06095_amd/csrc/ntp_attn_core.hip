@@ -2465,7 +2465,8 @@ extern "C" int ntp_attn_core_bwd_rows(const ntp_handle_t* h, const ntp_attn_core
   const int st = check_core_shape(s);
   if (st != NTP_OK) return st;
   if (!h || !out) return NTP_ERR_INVALID_ARG;
-  *out = choose_core(h, h->workspace ? h->workspace_bytes : 0, s).bwd_wide ? 32 : 16;
+  const CoreChoice c = choose_core(h, h->workspace ? h->workspace_bytes : 0, s);
+  *out = c.bwd_wide || c.bwd64 ? 32 : 16;
   return NTP_OK;
 }
 
@@ -2617,7 +2618,7 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
   const int64_t sections = cc.bwd_wide && s->causal ? 2 : 1;
   auto timing_begin = [&](const char* which, bool cut, double products) {
     char name[48];
-    snprintf(name, sizeof(name), "attn_core_bwd_%s%s%s", which, cc.bwd_wide ? "_r32" : "", cut ? "_cut" : "");
+    snprintf(name, sizeof(name), "attn_core_bwd_%s%s%s", which, cc.bwd_wide || cc.bwd64 ? "_r32" : "", cut ? "_cut" : "");
     ntp::timing_begin(h, stream, name, products * pair_flops, 0.0);
   };
   auto reduce_parts = [&](auto dkv, int64_t blocks) {

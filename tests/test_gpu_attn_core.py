@@ -327,6 +327,8 @@ def test_attn_core_bwd_head_dimension_64_launches(opts, n_q, n_kv, tp, rank, n_s
     import paper_2504_06095_amd as N
     _say(f"attn core bwd d=64, launches option {launches}: n_q={n_q} n_kv={n_kv} n_seq={n_seq} S={S} pad={pad} causal={causal}")
     opts(K.NTP_OPT_ATTN_BWD_LAUNCHES, launches)
+    rows = N.ntp_attn_core_bwd_rows(N.attn_core_shape(n_seq, S, N.ntp_attn_shard_plan(n_q, n_kv, 64, tp, rank), n_q // n_kv, causal))
+    assert rows == (32 if (launches, causal, n_seq) == (0, True, 36) else 16)
     N.ntp_kernel_timing_enable(1)
     N.ntp_kernel_timing_read()
     try:
@@ -335,7 +337,7 @@ def test_attn_core_bwd_head_dimension_64_launches(opts, n_q, n_kv, tp, rank, n_s
     finally:
         N.ntp_kernel_timing_enable(0)
         N.ntp_kernel_timing_read()
-    assert names == (["attn_core_bwd_dq", "attn_core_bwd_dkv"] if launches == 1 else ["attn_core_bwd_both"]), names
+    assert names == (["attn_core_bwd_dq", "attn_core_bwd_dkv"] if launches == 1 else ["attn_core_bwd_both" + ("_r32" if rows == 32 else "")]), names
 
 
 @pytest.mark.parametrize("copy", [0, 1], ids=["dma", "registers"])
@@ -356,8 +358,10 @@ def test_attn_core_fwd_head_dimension_64_many_workgroups(opts, n_q, n_kv, n_seq,
 def test_attn_core_bwd_head_dimension_64_32_rows_per_wavefront(opts, n_q, n_kv, tp, rank, n_seq, S, pad, causal):
     """Below the launcher's own choice: one, two, four and nine tiles of 128 rows (the middle one of an odd number has no partner under the mask), one
     or both 64-row halves in the last, odd and even walks through the two buffers, grouped heads of which the rank holds a part."""
+    import paper_2504_06095_amd as N
     _say(f"attn core bwd d=64, 32 rows per wavefront: heads {n_q}/{n_kv} tp {tp} rank {rank} n_seq={n_seq} S={S} pad={pad} causal={causal}")
     opts(K.NTP_OPT_ATTN_COPY, 3)
+    assert N.ntp_attn_core_bwd_rows(N.attn_core_shape(n_seq, S, N.ntp_attn_shard_plan(n_q, n_kv, 64, tp, rank), n_q // n_kv, causal)) == 32
     _bwd_case(n_q, n_kv, tp, rank, 64, n_seq, S, causal, seed=43, pad=pad)
 
 

@@ -123,7 +123,15 @@ def test_rows_of_the_backward_kernels_by_option_and_head_dimension():
             assert (N.ntp_attn_core_bwd_rows(long), N.ntp_attn_core_bwd_rows(short)) == want
         finally:
             N.ntp_set_option(Bd.NTP_OPT_ATTN_COPY, 0)
-    assert N.ntp_attn_core_bwd_rows(_shape(14, 14, 1, 0, 1, 8192, False, d=64)) == 16
+    for copy, want in ((0, (32, 16)), (1, (16, 16)), (2, (16, 16)), (3, (32, 32))):  # (head dimension 64: where the launch is shared)
+        N.ntp_set_option(Bd.NTP_OPT_ATTN_COPY, copy)
+        try:
+            assert tuple(N.ntp_attn_core_bwd_rows(_shape(14, 14, 1, 0, 1, S, False, d=64)) for S in (8192, 64)) == want
+            N.ntp_set_option(Bd.NTP_OPT_ATTN_BWD_LAUNCHES, 1)
+            assert N.ntp_attn_core_bwd_rows(_shape(14, 14, 1, 0, 1, 8192, False, d=64)) == 16
+        finally:
+            N.ntp_set_option(Bd.NTP_OPT_ATTN_COPY, 0)
+            N.ntp_set_option(Bd.NTP_OPT_ATTN_BWD_LAUNCHES, 0)
     assert N.ntp_attn_core_bwd_rows(_shape(14, 14, 1, 0, 0, 8192, False)) == 16
 
 
