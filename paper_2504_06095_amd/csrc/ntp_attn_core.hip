@@ -2393,10 +2393,13 @@ CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_cor
     c.dq_parts = choose_parts(h, ws_bytes, wq, bq, walk, bdq, fill, 12, causal);
     c.dkv_parts = choose_parts(h, ws_bytes, wk, bk, heads_per_kv * walk, bdkv, 2.0, 16, false);
   }
-  if (!h->opt[NTP_OPT_ATTN_PARTS] && !h->opt[NTP_OPT_ATTN_COPY] && !h->opt[NTP_OPT_ATTN_BWD_LAUNCHES]) {
+  const bool own_choice = !h->opt[NTP_OPT_ATTN_PARTS] && !h->opt[NTP_OPT_ATTN_COPY];
+  if (own_choice) {
     c.fwd_small = small_fwd_pays(s, c, cus);
-    c.bwd_small = small_bwd_pays(s, c, cus);
     if (c.fwd_small) c.fwd_parts = 1;
+  }
+  if (own_choice && !h->opt[NTP_OPT_ATTN_BWD_LAUNCHES]) {
+    c.bwd_small = small_bwd_pays(s, c, cus);
     if (c.bwd_small) {
       c.dq_parts = c.dkv_parts = 1;
       c.bwd_wide = false;

@@ -88,6 +88,19 @@ def test_small_launches_share_out_walks_inside_workgroups(workspace_1gib):
     assert max(parts(4, 4, 1, 0, 1, 8192, True, d=64)) > 1 and max(parts(2, 1, 1, 0, 1, 4096, False)) > 1
 
 
+@pytest.mark.parametrize("d,S", [(64, 1432), (128, 1432)])
+def test_backward_launch_option_leaves_the_forward_call_alone(workspace_1gib, d, S):
+    s, got = _shape(2, 1, 1, 0, 1, S, True, d=d), []
+    for launches in (0, 1, 2):
+        N.ntp_set_option(Bd.NTP_OPT_ATTN_BWD_LAUNCHES, launches)
+        try:
+            c = N.ntp_attn_core_choice(s)
+        finally:
+            N.ntp_set_option(Bd.NTP_OPT_ATTN_BWD_LAUNCHES, 0)
+        got.append((c["fwd_rows_per_wavefront"], c["fwd_parts"]))
+    assert got == [(16, 1)] * 3  # (two heads' walks would be cut on the other kernels)
+
+
 # heads, KV heads, sequences, tokens, causal, rows of the backward kernels without and with a workspace (256 compute units): either side of
 # each line of the rule, at shapes that were measured with both kernels
 BWD_ROWS = [
