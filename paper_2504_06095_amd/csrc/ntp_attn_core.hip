@@ -2518,7 +2518,7 @@ extern "C" int ntp_attn_core_shard_fwd(ntp_handle_t* h, const ntp_attn_core_shap
   hipStream_t hs = static_cast<hipStream_t>(stream);
   if (ntp::timing_on(h)) {
     char name[48];
-    snprintf(name, sizeof(name), "attn_core_fwd%s%s", s->causal ? "_causal" : "", a.n_parts > 1 ? "_cut" : "");
+    snprintf(name, sizeof(name), "attn_core_fwd%s%s%s", cc.fwd_small ? "_small" : "", s->causal ? "_causal" : "", a.n_parts > 1 ? "_cut" : "");
     ntp::timing_begin(h, stream, name,
                       (s->causal ? 2.0 : 4.0) * double(s->n_seq) * double(s->seq_len) * double(s->seq_len) * s->head_dim * s->q_cnt, 0.0);
   }
@@ -2645,9 +2645,10 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
     adkv.n_parts = cc.dkv_parts;
     adkv.pairs = k_pairs;
     adkv.part_sums = a.part_sums + cc.dkv_ws_offset / 4;
-    if (ntp::timing_on(h)) timing_begin("both", cc.dq_parts > 1 || cc.dkv_parts > 1, 7.0);
     const bool wide = s->head_dim == 128;
     const bool forms_delta = cc.bwd_small && small_forms_delta(s);
+    // (small1: that launch alone; small2: the delta kernel before it)
+    if (ntp::timing_on(h)) timing_begin(forms_delta ? "small1" : cc.bwd_small ? "small2" : "both", cc.dq_parts > 1 || cc.dkv_parts > 1, 7.0);
     if (!forms_delta) {
       hipLaunchKernelGGL(wide ? attn_core_delta_kernel<128> : attn_core_delta_kernel<64>, dim3(uint32_t(delta_wgs)), dim3(256), 0, hs, a, M);
       ok = hipGetLastError() == hipSuccess;

@@ -142,6 +142,17 @@ def workspace():
     N.ntp_set_workspace(None)
 
 
+@pytest.fixture
+def kernels():
+    """Timing on; names of the attention core launches since the last call."""
+    import paper_2504_06095_amd as N
+    N.ntp_kernel_timing_enable(1)
+    N.ntp_kernel_timing_read()
+    yield _core_names
+    N.ntp_kernel_timing_enable(0)
+    N.ntp_kernel_timing_read()
+
+
 def _core_names():
     import paper_2504_06095_amd as N
     return [r["name"] for r in N.ntp_kernel_timing_read() if r["name"].startswith("attn_core")]
@@ -337,7 +348,8 @@ def test_attn_core_bwd_head_dimension_64_launches(opts, n_q, n_kv, tp, rank, n_s
     finally:
         N.ntp_kernel_timing_enable(0)
         N.ntp_kernel_timing_read()
-    assert names == (["attn_core_bwd_dq", "attn_core_bwd_dkv"] if launches == 1 else ["attn_core_bwd_both" + ("_r32" if rows == 32 else "")]), names
+    one = "attn_core_bwd_" + ("small2" if (launches, n_seq) == (0, 2) else "both_r32" if rows == 32 else "both")  # (the last shape: 16 rows per workgroup)
+    assert names == (["attn_core_bwd_dq", "attn_core_bwd_dkv"] if launches == 1 else [one]), names
 
 
 @pytest.mark.parametrize("copy", [0, 1], ids=["dma", "registers"])
@@ -392,22 +404,28 @@ def test_attn_core_bwd_without_query_heads(opts, d, n_seq, S, causal, copy):
 @pytest.mark.parametrize("n_q,n_kv,tp,rank,n_seq,S,pad", [(2, 2, 1, 0, 1, 15, 0), (3, 1, 1, 0, 2, 16, 8), (2, 2, 1, 0, 3, 17, 0), (8, 2, 3, 1, 1, 63, 0), (2, 1, 1, 0, 2, 65, 8),
                                                           (3, 3, 1, 0, 1, 255, 0), (6, 2, 4, 1, 1, 257, 0), (2, 2, 1, 0, 2, 320, 0), (1, 1, 1, 0, 1, 577, 8),
                                                           (2, 1, 1, 0, 1, 250, 0), (3, 1, 1, 0, 1, 256, 8), (3, 1, 1, 0, 1, 321, 0)])  # walks of 8, 12 and 18 units
-def test_attn_core_few_workgroups(n_q, n_kv, tp, rank, d, n_seq, S, pad, causal):
+def test_attn_core_few_workgroups(kernels, n_q, n_kv, tp, rank, d, n_seq, S, pad, causal):
+    import paper_2504_06095_amd as N
     _say(f"attn core, 16 rows per workgroup n_q={n_q} n_kv={n_kv} d={d} n_seq={n_seq} S={S} pad={pad} causal={causal}")
     _case(n_q, n_kv, tp, rank, d, n_seq, S, causal, seed=4, pad=pad)
     _bwd_case(n_q, n_kv, tp, rank, d, n_seq, S, causal, seed=5, pad=pad)
+    # (sequences of one tile leave nothing to share out: the rule may give them either form)
+    plan = N.ntp_attn_shard_plan(n_q, n_kv, d, tp, rank)
+    walk = min(n_q // n_kv, plan["q_cnt"]) * -(-S // 64)
+    fwd, bwd = "attn_core_fwd_small" + ("_causal" if causal else ""), "attn_core_bwd_small" + ("1" if walk <= (12 if d == 64 else 7) else "2")
+    assert S < 65 or kernels() == [fwd, fwd, bwd]
 
 
 @pytest.mark.parametrize("value", [float("inf"), float("nan")], ids=["inf", "nan"])
-@pytest.mark.parametrize("d,here", [(64, 0), (128, 0), (64, 3)])
-def test_attn_core_few_workgroups_non_finite_rows_reach_no_further(opts, value, d, here):
+@pytest.mark.parametrize("d,q,here,runs", [(64, 2, 0, "small1"), (64, 3, 0, "small2"), (128, 1, 0, "small1"), (128, 2, 0, "small2"), (64, 2, 3, "both_r32")])
+def test_attn_core_few_workgroups_non_finite_rows_reach_no_further(opts, kernels, value, d, q, here, runs):
     """A non-finite query, key, value or gradient row makes the same outputs non-finite as with 64 rows per workgroup, and the others agree.  (3: the
-    backward kernels with 32 rows per wavefront instead.)"""
+    backward kernels with 32 rows per wavefront instead.)  Walks of 5 units a query head, with and without the delta values formed in them."""
     import torch
     import paper_2504_06095_amd as N
-    _say(f"attn core, 16 rows per workgroup, a row of {value}, d={d}")
-    S, q = 300, 2
-    shape = N.attn_core_shape(1, S, N.ntp_attn_shard_plan(q, 1, d, 1, 0), 2, True)
+    _say(f"attn core, 16 rows per workgroup, a row of {value}, d={d} q={q}")
+    S = 300
+    shape = N.attn_core_shape(1, S, N.ntp_attn_shard_plan(q, 1, d, 1, 0), q, True)
     g = torch.Generator("cuda").manual_seed(3)
     for row, block in ((70, 0), (70, 1), (200, q), (130, q + 1), (70, -1)):  # query heads, key, value; -1: the gradient
         QKV = torch.empty(S, (q + 2) * d, device="cuda").normal_(generator=g).bfloat16()
@@ -420,6 +438,9 @@ def test_attn_core_few_workgroups_non_finite_rows_reach_no_further(opts, value, 
             N.ntp_attn_core_shard_fwd(shape, QKV, C, LSE)
             N.ntp_attn_core_shard_bwd(shape, QKV, C, dC, LSE, Delta, dQKV)
             got.append((C, LSE, dQKV))
+            ran = kernels()
+            assert copy or ran == ["attn_core_fwd_small_causal", "attn_core_bwd_" + runs], ran
+            assert copy != 3 or ran[1] == "attn_core_bwd_" + runs, ran
         torch.cuda.synchronize()
         for a, b in zip(*got):
             assert torch.equal(a.isfinite(), b.isfinite()), (row, block)
