@@ -2268,34 +2268,43 @@ SmallWalks small_walks(int64_t tiles, int64_t heads, bool causal) {
   const double most = std::ceil(h * t / 4.0);
   return {most, causal ? std::max(1.0, h * (t + 1.0) / 8.0 + up) : most};
 }
-bool small_fwd_pays(const ntp_attn_core_shape_t* s, const CoreChoice& c, double cus) {
-  const bool causal = s->causal != 0, d64 = s->head_dim == 64;
-  const int64_t tiles = (int64_t(s->seq_len) + kBKV - 1) / kBKV, heads = int64_t(s->n_seq) * s->q_cnt;
-  if (tiles < 1 || heads < 1) return false;
-  const SmallWalks w = small_walks(tiles, 1, causal);
-  const double small = double((s->seq_len + 15) / 16 * heads) / cus;
-  const double now = d64 ? 3.1 + std::max(0.84 * w.most, small / 2 * (1.02 + 1.5 * w.mean)) : 3.05 + std::max(1.71 * w.most, small * (1.47 + 1.96 * w.mean));
-  const double walk = std::ceil(double(causal ? tiles + 1 : tiles) / c.fwd_parts);
-  const double per_unit = double((causal ? (tiles + 1) / 2 : tiles) * heads * c.fwd_parts) / cus / (c.fwd_rows == 32 ? 2 : 1), cut = c.fwd_parts > 1;
-  const bool r32 = c.fwd_rows == 32;
-  const double other = d64 ? 3.0 + std::max((r32 ? 1.67 : 0.86) * walk, per_unit / 3 * (5.9 + (r32 ? 2.47 : 1.72) * walk)) + 5.8 * cut
-                           : 3.6 + std::max((r32 ? 2.66 : 1.15) * walk, per_unit / 2 * (3.1 + (r32 ? 5.2 : 1.47) * walk)) + 6.9 * cut;
-  return now < 0.9 * other;
+double small_fwd_time(const ntp_attn_core_shape_t* s, double cus) {
+  const bool d64 = s->head_dim == 64;
+  const int64_t heads = int64_t(s->n_seq) * s->q_cnt;
+  const SmallWalks w = small_walks((int64_t(s->seq_len) + kBKV - 1) / kBKV, 1, s->causal != 0);
+  const double small = double((int64_t(s->seq_len) + 15) / 16 * heads) / cus;
+  return d64 ? 3.1 + std::max(0.84 * w.most, small / 2 * (1.02 + 1.5 * w.mean)) : 3.05 + std::max(1.71 * w.most, small * (1.47 + 1.96 * w.mean));
 }
-bool small_bwd_pays(const ntp_attn_core_shape_t* s, const CoreChoice& c, double cus) {
+double other_fwd_time(const ntp_attn_core_shape_t* s, int rows, int parts, double cus) {
+  const bool causal = s->causal != 0, d64 = s->head_dim == 64, r32 = rows == 32;
+  const int64_t tiles = (int64_t(s->seq_len) + kBKV - 1) / kBKV, heads = int64_t(s->n_seq) * s->q_cnt;
+  const double walk = std::ceil(double(causal ? tiles + 1 : tiles) / parts);
+  const double per_unit = double((causal ? (tiles + 1) / 2 : tiles) * heads * parts) / cus / (r32 ? 2 : 1), cut = parts > 1;
+  return d64 ? 3.0 + std::max((r32 ? 1.67 : 0.86) * walk, per_unit / 3 * (5.9 + (r32 ? 2.47 : 1.72) * walk)) + 5.8 * cut
+             : 3.6 + std::max((r32 ? 2.66 : 1.15) * walk, per_unit / 2 * (3.1 + (r32 ? 5.2 : 1.47) * walk)) + 6.9 * cut;
+}
+double small_bwd_time(const ntp_attn_core_shape_t* s, double cus) {
   const bool causal = s->causal != 0, d64 = s->head_dim == 64;
   const int64_t tiles = (int64_t(s->seq_len) + kBKV - 1) / kBKV, q = int64_t(s->n_seq) * s->q_cnt, kv = int64_t(s->n_seq) * s->kv_cnt;
-  const int64_t heads_per_kv = std::min<int64_t>(s->group, s->q_cnt);
-  if (tiles < 1 || q < 1 || kv < 1 || c.bwd_wide) return false;  // (32 rows per wavefront: launches with work for every unit, 1.6 to 2.6 times as fast)
-  const SmallWalks wq = small_walks(tiles, 1, causal), wk = small_walks(tiles, heads_per_kv, causal);
+  const SmallWalks wq = small_walks(tiles, 1, causal), wk = small_walks(tiles, std::min<int64_t>(s->group, s->q_cnt), causal);
   const double t16 = double((int64_t(s->seq_len) + 15) / 16) / cus;
-  const double now = d64 ? 5.4 + std::max(1.4 * wk.most, t16 / 2 * (double(kv) * (2.2 + 2.14 * wk.mean) + double(q) * (2.2 + 1.0 * wq.mean)))
-                         : 6.2 + std::max(2.3 * wk.most, t16 * (double(kv) * (1.77 + 3.12 * wk.mean) + double(q) * (2.9 + 1.13 * wq.mean)));
+  return d64 ? 5.4 + std::max(1.4 * wk.most, t16 / 2 * (double(kv) * (2.2 + 2.14 * wk.mean) + double(q) * (2.2 + 1.0 * wq.mean)))
+             : 6.2 + std::max(2.3 * wk.most, t16 * (double(kv) * (1.77 + 3.12 * wk.mean) + double(q) * (2.9 + 1.13 * wq.mean)));
+}
+double other_bwd_time(const ntp_attn_core_shape_t* s, int dq_parts, int dkv_parts, double cus) {
+  const bool causal = s->causal != 0, d64 = s->head_dim == 64;
+  const int64_t tiles = (int64_t(s->seq_len) + kBKV - 1) / kBKV, q = int64_t(s->n_seq) * s->q_cnt, kv = int64_t(s->n_seq) * s->kv_cnt;
   const double walk = double(causal ? tiles + 1 : tiles), per = double(causal ? (tiles + 1) / 2 : tiles) / cus / 2;
-  const double dq = std::ceil(walk / c.dq_parts), dkv = std::ceil(walk * double(heads_per_kv) / c.dkv_parts), cuts = double(c.dq_parts > 1) + double(c.dkv_parts > 1);
-  const double other = d64 ? 5.1 + std::max(std::max(1.68 * dkv, 1.73 * dq), per * (double(kv * c.dkv_parts) * (11.0 + 2.46 * dkv) + double(q * c.dq_parts) * 3.7)) + 8.9 * cuts
-                           : 7.0 + std::max(std::max(1.72 * dkv, 1.23 * dq), per * (double(kv * c.dkv_parts) * (13.2 + 3.69 * dkv) + double(q * c.dq_parts) * 8.1)) + 6.7 * cuts;
-  return now < 0.9 * other;
+  const double dq = std::ceil(walk / dq_parts), dkv = std::ceil(walk * double(std::min<int64_t>(s->group, s->q_cnt)) / dkv_parts), cuts = double(dq_parts > 1) + double(dkv_parts > 1);
+  return d64 ? 5.1 + std::max(std::max(1.68 * dkv, 1.73 * dq), per * (double(kv * dkv_parts) * (11.0 + 2.46 * dkv) + double(q * dq_parts) * 3.7)) + 8.9 * cuts
+             : 7.0 + std::max(std::max(1.72 * dkv, 1.23 * dq), per * (double(kv * dkv_parts) * (13.2 + 3.69 * dkv) + double(q * dq_parts) * 8.1)) + 6.7 * cuts;
+}
+// Whether a small launch of `small` us is taken instead of one of `here` us, which with no workspace would be one of `whole` us and with an unlimited one of
+// `most` us.  What pays against the last and is not slower than the whole one is taken whatever the workspace is: the workspace that ntp_workspace_bytes asks for
+// has no room for the parts of a launch that is not wanted.  (2 x 1401 tokens, 9 heads of 64 causal: with no limit small, with the 0 bytes asked for not; 2 x 3139
+// tokens, 4 heads on 2: with the 21 MB asked for in other parts, 107 us for 89.)
+bool small_pays(double small, double here, double whole, double most) {
+  return (small < 0.9 * most && small <= whole) || (here != most && small < 0.9 * std::min(here, whole));
 }
 // Whether that backward launch also forms the rows' delta values, which saves a launch (3-4 us, 7 with the host's part where calls are short) and costs every step of a dK/dV walk
 // the rows of C: by the units of a workgroup's walk, of which a wavefront takes every fourth.  60 random small launches, head dimension 64: up to 12 units 0.68-1.01 of
@@ -2373,37 +2382,48 @@ CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_cor
   const int64_t cus = h->compute_units;
   // a dK/dV workgroup walks over the query tiles of every query head that reads its KV head
   const int64_t heads_per_kv = std::min<int64_t>(s->group, s->q_cnt);
-  if (dma) {
-    // (a launch that occupies 3/4 of the compute units uncut needs parts of 24 tiles to gain from a cut: 14 heads x
-    // 2048 tokens causal forward 42 us cut in two, 39 us whole; 8 heads x 2048 unmasked 36 and 33 us)
-    c.fwd_parts = choose_parts_dma(h, ws_bytes, wq, bq, walk, bf, 2 * cus, wq * 4 >= cus * 3 ? 24 : 16, cus * 3 / 4);
-    c.dq_parts = choose_parts_dma(h, ws_bytes, wq, bq, walk, bdq, cus, 10, cus * 3 / 8);
-    c.dkv_parts = choose_parts_dma(h, ws_bytes, wk, bk, heads_per_kv * walk, bdkv, cus, 10, cus * 3 / 8);
-    c.bwd_wide = h->opt[NTP_OPT_ATTN_COPY] == 3 || (h->opt[NTP_OPT_ATTN_COPY] == 0 && wide_pays(s, c.dq_parts, c.dkv_parts, double(cus)));
-    if (c.bwd_wide && !h->opt[NTP_OPT_ATTN_PARTS]) {
-      // ... and a cut costs them more: no more parts than bring a walk to 1.3 times an even share of the launch's work
-      // (4 products a pair for dK/dV, 3 for dQ; to 1.5 times 8 heads on one KV head x 4096 causal took 1.03 of the 16-row kernels' time instead of
-      // 0.99, 14 on 2 x 4096 0.97 instead of 0.88, 32 on one x 2048 unmasked 0.80 instead of 0.75; to 1.1 times nothing changes)
-      const double even = 7.0 * double(wide_pairs(s)) / double(cus);
-      while (c.dq_parts > 1 && 3.0 * double(tiles) <= 1.3 * even * (c.dq_parts - 1)) --c.dq_parts;
-      while (c.dkv_parts > 1 && 4.0 * double(heads_per_kv * tiles) <= 1.3 * even * (c.dkv_parts - 1)) --c.dkv_parts;
+  auto set_parts = [&](CoreChoice& c, int64_t ws) {
+    if (dma) {
+      // (a launch that occupies 3/4 of the compute units uncut needs parts of 24 tiles to gain from a cut: 14 heads x
+      // 2048 tokens causal forward 42 us cut in two, 39 us whole; 8 heads x 2048 unmasked 36 and 33 us)
+      c.fwd_parts = choose_parts_dma(h, ws, wq, bq, walk, bf, 2 * cus, wq * 4 >= cus * 3 ? 24 : 16, cus * 3 / 4);
+      c.dq_parts = choose_parts_dma(h, ws, wq, bq, walk, bdq, cus, 10, cus * 3 / 8);
+      c.dkv_parts = choose_parts_dma(h, ws, wk, bk, heads_per_kv * walk, bdkv, cus, 10, cus * 3 / 8);
+      c.bwd_wide = h->opt[NTP_OPT_ATTN_COPY] == 3 || (h->opt[NTP_OPT_ATTN_COPY] == 0 && wide_pays(s, c.dq_parts, c.dkv_parts, double(cus)));
+      if (c.bwd_wide && !h->opt[NTP_OPT_ATTN_PARTS]) {
+        // ... and a cut costs them more: no more parts than bring a walk to 1.3 times an even share of the launch's work
+        // (4 products a pair for dK/dV, 3 for dQ; to 1.5 times 8 heads on one KV head x 4096 causal took 1.03 of the 16-row kernels' time instead of
+        // 0.99, 14 on 2 x 4096 0.97 instead of 0.88, 32 on one x 2048 unmasked 0.80 instead of 0.75; to 1.1 times nothing changes)
+        const double even = 7.0 * double(wide_pairs(s)) / double(cus);
+        while (c.dq_parts > 1 && 3.0 * double(tiles) <= 1.3 * even * (c.dq_parts - 1)) --c.dq_parts;
+        while (c.dkv_parts > 1 && 4.0 * double(heads_per_kv * tiles) <= 1.3 * even * (c.dkv_parts - 1)) --c.dkv_parts;
+      }
+    } else {
+      c.fwd_parts = choose_parts(h, ws, wq, bq, walk, bf, fill, 12, causal);
+      c.dq_parts = choose_parts(h, ws, wq, bq, walk, bdq, fill, 12, causal);
+      c.dkv_parts = choose_parts(h, ws, wk, bk, heads_per_kv * walk, bdkv, 2.0, 16, false);
     }
-  } else {
-    c.fwd_parts = choose_parts(h, ws_bytes, wq, bq, walk, bf, fill, 12, causal);
-    c.dq_parts = choose_parts(h, ws_bytes, wq, bq, walk, bdq, fill, 12, causal);
-    c.dkv_parts = choose_parts(h, ws_bytes, wk, bk, heads_per_kv * walk, bdkv, 2.0, 16, false);
-  }
+  };
+  set_parts(c, ws_bytes);
   const bool own_choice = !h->opt[NTP_OPT_ATTN_PARTS] && !h->opt[NTP_OPT_ATTN_COPY];
-  if (own_choice) {
-    c.fwd_small = small_fwd_pays(s, c, cus);
+  if (own_choice && tiles > 0 && s->n_seq > 0 && s->q_cnt > 0) {
+    CoreChoice most = c;  // with a workspace of any size
+    set_parts(most, INT64_MAX / 2);
+    auto fwd = [&](int parts) { return other_fwd_time(s, c.fwd_rows, parts, cus); };
+    auto bwd = [&](int dq, int dkv) { return other_bwd_time(s, dq, dkv, cus); };
+    c.fwd_small = small_pays(small_fwd_time(s, cus), fwd(c.fwd_parts), fwd(1), fwd(most.fwd_parts));
     if (c.fwd_small) c.fwd_parts = 1;
+    // (32 rows per wavefront: launches with work for every unit, 1.6 to 2.6 times as fast)
+    if (!h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] && s->kv_cnt > 0 && !most.bwd_wide && !(dma && wide_pays(s, 1, 1, double(cus)))) {
+      const double whole = bwd(1, 1), all = bwd(most.dq_parts, most.dkv_parts);
+      c.bwd_small = small_pays(small_bwd_time(s, cus), c.bwd_wide ? all : bwd(c.dq_parts, c.dkv_parts), whole, all);
+      if (c.bwd_small) {
+        c.dq_parts = c.dkv_parts = 1;
+        c.bwd_wide = false;
+      }
+    }
   }
   if (own_choice && !h->opt[NTP_OPT_ATTN_BWD_LAUNCHES]) {
-    c.bwd_small = small_bwd_pays(s, c, cus);
-    if (c.bwd_small) {
-      c.dq_parts = c.dkv_parts = 1;
-      c.bwd_wide = false;
-    }
     c.bwd64 = s->head_dim == 64 && !c.bwd_small && bwd64_pays(s, cus);
   } else if (s->head_dim == 64 && h->opt[NTP_OPT_ATTN_COPY] == 3 && h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] != 1) {
     c.bwd64 = c.dq_parts == 1 && c.dkv_parts == 1;

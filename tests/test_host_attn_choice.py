@@ -1,4 +1,7 @@
 """Host logic of the attention core launcher (no GPU): rows per wavefront and how many parts the walks are cut into."""
+import math
+import random
+
 import pytest
 
 import paper_2504_06095_amd as N
@@ -151,6 +154,20 @@ def test_rows_of_the_backward_kernels_by_option_and_head_dimension():
 def test_a_workspace_of_the_size_asked_for_gives_the_choice_of_an_unlimited_one():
     for c in BWD_ROWS:
         s = _shape(c[0], c[1], 1, 0, *c[2:5])
+        n, got = N.ntp_workspace_bytes(Bd.NTP_CALL_ATTN_CORE_SHARD, s), []
+        for size in (n, 1 << 40):
+            assert Bd.lib().ntp_set_workspace(Bd.default_handle().ptr, FAKE_WS if size else None, size) == 0
+            got.append((N.ntp_attn_core_bwd_rows(s), N.ntp_attn_core_choice(s)))
+        assert Bd.lib().ntp_set_workspace(Bd.default_handle().ptr, None, 0) == 0
+        assert got[0] == got[1], c
+
+
+def test_a_workspace_of_the_size_asked_for_gives_the_choice_of_an_unlimited_one_over_sizes():
+    rng = random.Random(1)
+    for _ in range(4000):
+        kv = rng.randint(1, 14)
+        c = (kv * rng.choice((1, 1, 2, 4, 8)), kv, rng.choice((1, 1, 2, 4, 8)), round(math.exp(rng.uniform(math.log(16), math.log(9000)))), rng.random() < 0.5, rng.choice((64, 128)))
+        s = _shape(c[0], c[1], 1, 0, *c[2:5], d=c[5])
         n, got = N.ntp_workspace_bytes(Bd.NTP_CALL_ATTN_CORE_SHARD, s), []
         for size in (n, 1 << 40):
             assert Bd.lib().ntp_set_workspace(Bd.default_handle().ptr, FAKE_WS if size else None, size) == 0
