@@ -552,7 +552,7 @@ def test_attn_core_bwd_cut_chosen_for_few_heads(workspace):
     N.ntp_set_workspace(None)
     _bwd_case(64, 8, 30, 0, 128, 1, 1024, True, seed=5)
     names = _core_names()
-    assert names == ["attn_core_fwd_causal", "attn_core_bwd_both"], names
+    assert names == ["attn_core_fwd_small_causal", "attn_core_bwd_small2"], names
 
 
 def test_attn_core_bwd_padded_rows():
