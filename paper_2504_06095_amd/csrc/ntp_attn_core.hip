@@ -2313,6 +2313,13 @@ bool small_forms_delta(const ntp_attn_core_shape_t* s) {
   const int64_t units = std::min<int64_t>(s->group, s->q_cnt) * ((int64_t(s->seq_len) + kBKV - 1) / kBKV);
   return units <= (s->head_dim == 64 ? 12 : 7);
 }
+// Whether the 16-row tiles of so many (sequence, head)s are dealt out by length where a launch under the mask has more than one round of workgroups.  The tiles of
+// a head differ in length, and where the eight XCDs do not share the heads evenly, head by head leaves the long walks to some of them, whose compute units take two rounds
+// where others have none left.  5000 random launches (forward and backward, us): head dimension 128, 2 heads of 1500 tokens 27.1 -> 18.6 backward, 3 of 883 19.2 -> 14.8; four on
+// two of 1200 16.0 -> 11.2 forward; 64, 4 heads of 2500 18.6 -> 12.9 and 36.6 -> 29.3; by heads and rounds 0.57-0.97 of the time.  From 32 heads on an XCD has
+// heads enough, and their tiles are better off with their neighbours (1.02 of the time).  With less than a round there is nothing to share, and every XCD would read every
+// head for nothing: 7 KV heads under 56 x 237 tokens, 105 of 945 workgroups 17.6 -> 20.1 (so the keys ask for a round of their own).
+bool small_by_length(int64_t heads) { return heads < 32 && heads % 8 != 0; }
 // (128-row, 64-row) tile pairs of a launch of the backward kernels with 32 rows per wavefront
 int64_t wide_pairs(const ntp_attn_core_shape_t* s) {
   const int64_t tiles = (s->seq_len + kBKV - 1) / kBKV, own = (tiles + 1) / 2;
@@ -2553,6 +2560,7 @@ extern "C" int ntp_attn_core_shard_fwd(ntp_handle_t* h, const ntp_attn_core_shap
   };
   const bool by_dma = s->head_dim == 128 && qbw == 1 && h->opt[NTP_OPT_ATTN_COPY] != 1;
   if (cc.fwd_small) {
+    a.pairs = s->causal && wgs > h->compute_units && small_by_length(int64_t(s->n_seq) * s->q_cnt);
     if (s->head_dim == 128) hipLaunchKernelGGL(attn_core_fwd_small_kernel<128>, grid, dim3(kThreads), 0, hs, a);
     else hipLaunchKernelGGL(attn_core_fwd_small_kernel<64>, grid, dim3(kThreads), 0, hs, a);
   } else if (by_dma) {
@@ -2678,6 +2686,10 @@ extern "C" int ntp_attn_core_shard_bwd(ntp_handle_t* h, const ntp_attn_core_shap
       a.tiles = (s->seq_len + 15) / 16;
       const int64_t n_dkv = int64_t(a.tiles) * s->n_seq * s->kv_cnt;
       const dim3 small(uint32_t(n_dkv + int64_t(a.tiles) * s->n_seq * s->q_cnt));
+      if (s->causal && int64_t(small.x) * (wide ? 2 : 1) > 2 * int64_t(h->compute_units)) {
+        const bool keys = n_dkv * (wide ? 2 : 1) > h->compute_units;
+        a.pairs = (small_by_length(int64_t(s->n_seq) * s->q_cnt) ? 1 : 0) | (keys && small_by_length(int64_t(s->n_seq) * s->kv_cnt) ? 2 : 0);
+      }
       const auto kernel = wide ? (forms_delta ? attn_core_bwd_small_kernel<128, true> : attn_core_bwd_small_kernel<128, false>)
                                : (forms_delta ? attn_core_bwd_small_kernel<64, true> : attn_core_bwd_small_kernel<64, false>);
       hipLaunchKernelGGL(kernel, small, dim3(kThreads), 0, hs, a, uint32_t(n_dkv));

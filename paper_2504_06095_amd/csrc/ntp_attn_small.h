@@ -5,7 +5,7 @@
 // about 1 us).  Here a workgroup owns 16 rows, and its four wavefronts share out the walk: wavefront w takes tiles w, w + 4, ... in a part of
 // the LDS of its own, so that nothing but the end needs a barrier; the four partial results are put together through LDS (in the order of
 // the wavefronts).  Four times the workgroups, walks a quarter as long; what it costs is that a tile is read for 16 rows instead of 64, which is
-// why larger launches keep the other kernels (small_fwd_pays, small_bwd_pays).  Products, masks and rounding are those of the other kernels.  Head
+// why larger launches keep the other kernels (small_pays).  Products, masks and rounding are those of the other kernels.  Head
 // dimension 64, three heads, causal, forward and backward: 512 tokens 10.4 -> 5.0 and 18.8 -> 8.3 us, 1432 tokens 15.3 -> 8.6 and 35.5 -> 16.1; head dimension 128, 883
 // tokens 18.7 -> 9.9 and 31.3 -> 20.3.  What bounds it then is the way into and out of a workgroup (about 3 us), and at 128 the DMA of four tiles a step (1.1 us).
 //
@@ -35,6 +35,16 @@ struct SmallTile {
 template <int... Is, typename F>
 __device__ __forceinline__ void small_for(std::integer_sequence<int, Is...>, F&& f) {
   (f(std::integral_constant<int, Is>{}), ...);
+}
+
+// Workgroup b of a kind: its 16-row tile u and its (sequence, head) sh of `heads`.  Head by head, a head's tiles together on one XCD; or by length, the longest
+// tiles of all heads first (small_by_length).  (One division and no branch; called once, before the kernel's two bodies part: in either body the same lines
+// made launches of grouped heads 1.04-1.09 times as long.)
+__device__ __forceinline__ void small_place(uint32_t b, int tiles, int heads, bool by_length, int& u, int& sh) {
+  const uint32_t major = xcd_major(b, uint32_t(tiles) * uint32_t(heads));
+  const uint32_t bid = by_length ? b : major, n = uint32_t(by_length ? heads : tiles), quotient = bid / n, rest = bid - quotient * n;
+  u = int(by_length ? quotient : rest);
+  sh = int(by_length ? rest : quotient);
 }
 
 // This lane's read addresses in a tile at LDS address 0: rows (operand A, 16 rows a block) and transposed (operand A, 16 columns a block)
@@ -109,8 +119,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 1
   using T = SmallTile<D>;
   constexpr int KS = T::KS, DB = T::DB;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * 2 * T::BYTES];
-  const uint32_t bid = xcd_major(blockIdx.x, gridDim.x);
-  const int u = int(bid) % a.q_tiles, sh = int(bid) / a.q_tiles;
+  int u, sh;
+  small_place(blockIdx.x, a.q_tiles, a.n_seq * a.q_cnt, a.pairs != 0, u, sh);
   const int qt = a.causal ? a.q_tiles - 1 - u : u;  // the longest walks first
   const int seq = sh % a.n_seq, head = sh / a.n_seq;
   const int g = (a.q_off + head) / a.group - a.kv_off;
@@ -273,13 +283,11 @@ __device__ __forceinline__ void small_sum(unsigned char* lds, int wave, int lq, 
   }
 }
 
-// dQ: workgroup `b` of `count` = 16 query rows of one (sequence, head).
+// dQ: 16 query rows of one (sequence, head); u: their tile, the longest walk first.
 template <int D, bool STORE_DELTA>
-__device__ __forceinline__ void bwd_dq_small_body(const CoreBwdArgs& a, const uint32_t b, const uint32_t count, unsigned char* const lds) {
+__device__ __forceinline__ void bwd_dq_small_body(const CoreBwdArgs& a, const int u, const int sh, unsigned char* const lds) {
   using T = SmallTile<D>;
   constexpr int KS = T::KS, DB = T::DB;
-  const uint32_t bid = xcd_major(b, count);
-  const int u = int(bid) % a.tiles, sh = int(bid) / a.tiles;
   const int qt = a.causal ? a.tiles - 1 - u : u;
   const int seq = sh % a.n_seq, head = sh / a.n_seq;
   const int g = (a.q_off + head) / a.group - a.kv_off;
@@ -384,14 +392,12 @@ __device__ __forceinline__ void bwd_dq_small_body(const CoreBwdArgs& a, const ui
   });
 }
 
-// dK and dV: workgroup `b` of `count` = 16 keys of one (sequence, KV head); the walk goes over the query tiles of every query head that reads it.
+// dK and dV: the 16 keys of tile kt (early ones have the longest walks) of one (sequence, KV head); the walk goes over the query tiles of every query head that reads it.
 // (FORM_DELTA: the rows' delta values are formed from their rows of C, which are read with the tile; else a launch before this one has stored them.)
 template <int D, bool FORM_DELTA>
-__device__ __forceinline__ void bwd_dkv_small_body(const CoreBwdArgs& a, const uint32_t b, const uint32_t count, unsigned char* const lds, float (*const sLD)[2][kBKV]) {
+__device__ __forceinline__ void bwd_dkv_small_body(const CoreBwdArgs& a, const int kt, const int sh, unsigned char* const lds, float (*const sLD)[2][kBKV]) {
   using T = SmallTile<D>;
   constexpr int KS = T::KS, DB = T::DB;
-  const uint32_t bid = xcd_major(b, count);
-  const int kt = int(bid) % a.tiles, sh = int(bid) / a.tiles;
   const int seq = sh % a.n_seq, g = sh / a.n_seq;  // g: local KV head
   const int S = a.seq_len;
   const int64_t tok0 = int64_t(seq) * S, Mtot = int64_t(a.n_seq) * S;
@@ -540,6 +546,9 @@ template <int D, bool DELTA>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 128 ? 1 : 2, D == 128 ? 1 : 2))) void attn_core_bwd_small_kernel(const CoreBwdArgs a, const uint32_t n_dkv) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * 2 * SmallTile<D>::BYTES];
   __shared__ __attribute__((aligned(16))) float sLD[4][2][kBKV];
-  if (blockIdx.x < n_dkv) bwd_dkv_small_body<D, DELTA>(a, blockIdx.x, n_dkv, lds, sLD);
-  else bwd_dq_small_body<D, DELTA>(a, blockIdx.x - n_dkv, gridDim.x - n_dkv, lds);
+  const bool dkv = blockIdx.x < n_dkv;
+  int u, sh;
+  small_place(dkv ? blockIdx.x : blockIdx.x - n_dkv, a.tiles, a.n_seq * (dkv ? a.kv_cnt : a.q_cnt), (a.pairs & (dkv ? 2 : 1)) != 0, u, sh);
+  if (!dkv) bwd_dq_small_body<D, DELTA>(a, u, sh, lds);
+  else bwd_dkv_small_body<D, DELTA>(a, u, sh, lds, sLD);
 }

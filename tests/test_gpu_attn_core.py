@@ -416,6 +416,15 @@ def test_attn_core_few_workgroups(kernels, n_q, n_kv, tp, rank, d, n_seq, S, pad
     assert S < 65 or kernels() == [fwd, fwd, bwd]
 
 
+# walks dealt out by length: more than a round of 16-row workgroups on heads that eight XCDs do not share evenly (the queries' alone, the keys' as well)
+@pytest.mark.parametrize("n_q,n_kv,d,n_seq,S,pad", [(3, 3, 64, 1, 1409, 0), (6, 3, 64, 2, 700, 8), (3, 1, 128, 1, 1465, 0), (12, 3, 128, 1, 430, 0), (2, 2, 128, 1, 1169, 8)])
+def test_attn_core_few_workgroups_by_length(kernels, n_q, n_kv, d, n_seq, S, pad):
+    _say(f"attn core, 16 rows per workgroup by length n_q={n_q} n_kv={n_kv} d={d} n_seq={n_seq} S={S} pad={pad}")
+    _bwd_case(n_q, n_kv, 1, 0, d, n_seq, S, True, seed=6, pad=pad)
+    names = kernels()
+    assert names[0] == "attn_core_fwd_small_causal" and names[1].startswith("attn_core_bwd_small"), names
+
+
 @pytest.mark.parametrize("value", [float("inf"), float("nan")], ids=["inf", "nan"])
 @pytest.mark.parametrize("d,q,here,runs", [(64, 2, 0, "small1"), (64, 3, 0, "small2"), (128, 1, 0, "small1"), (128, 2, 0, "small2"), (64, 2, 3, "both_r32")])
 def test_attn_core_few_workgroups_non_finite_rows_reach_no_further(opts, kernels, value, d, q, here, runs):
