@@ -2256,10 +2256,12 @@ struct CoreChoice {
 };
 
 // Whether the kernels with 16 rows per workgroup are the faster ones (ntp_attn_small.h): by estimates (us) of both forms, fitted to 700 random launches
-// of 4 to 3000 16-row workgroups (1-14 KV heads, 1-8 query heads on each, 1-8 sequences of 40-6000 tokens, both masks) and right to 10 %
-// on the mean.  Each is what a launch costs anyhow, plus the larger of its longest walk and its workgroups' time dealt out over the device.  Taken where 10 %
-// faster by the estimates: over those launches 0.75 (forward) and 0.61 (backward) of the time without them at head dimension 64, 0.84 and 0.80 at 128; of
-// the 1400, eight lost more than 5 %.  16 heads of 64 over 7 ranks, four sequences of 512 causal tokens: 10.7 -> 6.3 us and 19.0 -> 13.2 us.
+// of 4 to 3000 16-row workgroups (1-14 KV heads, 1-8 query heads on each, 1-8 sequences of 40-6000 tokens, both masks; head dimension 64 with 32 rows per wavefront, whose tiles
+// come by DMA, to 540) and right to 10-15 %.  Each is what a launch costs anyhow, plus the larger of its longest walk and its workgroups' time dealt out over the device; without the
+// mask all walks are equal and a launch takes whole rounds (head dimension 128, 7 heads of 606 tokens, 266 workgroups for 256 units: 14.9 us, the other kernel
+// 12.2).  Taken where 10 % faster by the estimates.  Over 6000 random launches of up to 3000 workgroups: 0.80 (forward) and 0.56 (backward) of the time without them at head dimension
+// 64, 0.86 and 0.75 at 128; of the 12000, four lost more than 5 % (1 x 987 tokens, 16 heads on 4 unmasked forward 15.1 -> 17.5 us the most).  16 heads of 64 over 7 ranks, four
+// sequences of 512 causal tokens: 10.7 -> 6.3 us and 19.0 -> 13.2 us.
 struct SmallWalks {
   double most, mean;  // steps of a wavefront: a quarter of its workgroup's walk
 };
@@ -2269,25 +2271,32 @@ SmallWalks small_walks(int64_t tiles, int64_t heads, bool causal) {
   return {most, causal ? std::max(1.0, h * (t + 1.0) / 8.0 + up) : most};
 }
 double small_fwd_time(const ntp_attn_core_shape_t* s, double cus) {
-  const bool d64 = s->head_dim == 64;
+  const bool causal = s->causal != 0, d64 = s->head_dim == 64;
   const int64_t heads = int64_t(s->n_seq) * s->q_cnt;
-  const SmallWalks w = small_walks((int64_t(s->seq_len) + kBKV - 1) / kBKV, 1, s->causal != 0);
-  const double small = double((int64_t(s->seq_len) + 15) / 16 * heads) / cus;
-  return d64 ? 3.1 + std::max(0.84 * w.most, small / 2 * (1.02 + 1.5 * w.mean)) : 3.05 + std::max(1.71 * w.most, small * (1.47 + 1.96 * w.mean));
+  const SmallWalks w = small_walks((int64_t(s->seq_len) + kBKV - 1) / kBKV, 1, causal);
+  const double load = double((int64_t(s->seq_len) + 15) / 16 * heads) / cus, slots = d64 ? 2.0 : 1.0;  // workgroups per unit, and at a time
+  const double start = d64 ? 3.1 : 3.05, walk = (d64 ? 0.84 : 1.71) * w.most, each = d64 ? 1.02 + 1.5 * w.mean : 1.47 + 1.96 * w.mean;
+  if (causal) return start + std::max(walk, load / slots * each);
+  const double full = std::floor(load / slots), rest = load - slots * full;  // equal walks: whole rounds
+  return start + full * each + (rest > 0.0 ? std::max(walk + (full > 0.0 ? 1.0 : 0.0), rest / slots * each) : 0.0);
 }
 double other_fwd_time(const ntp_attn_core_shape_t* s, int rows, int parts, double cus) {
   const bool causal = s->causal != 0, d64 = s->head_dim == 64, r32 = rows == 32;
   const int64_t tiles = (int64_t(s->seq_len) + kBKV - 1) / kBKV, heads = int64_t(s->n_seq) * s->q_cnt;
   const double walk = std::ceil(double(causal ? tiles + 1 : tiles) / parts);
   const double per_unit = double((causal ? (tiles + 1) / 2 : tiles) * heads * parts) / cus / (r32 ? 2 : 1), cut = parts > 1;
-  return d64 ? 3.0 + std::max((r32 ? 1.67 : 0.86) * walk, per_unit / 3 * (5.9 + (r32 ? 2.47 : 1.72) * walk)) + 5.8 * cut
+  return d64 ? 3.0 + std::max((r32 ? 1.42 : 0.86) * walk, per_unit / 3 * (r32 ? 6.55 + 2.22 * walk : 5.9 + 1.72 * walk)) + 5.8 * cut
              : 3.6 + std::max((r32 ? 2.66 : 1.15) * walk, per_unit / 2 * (3.1 + (r32 ? 5.2 : 1.47) * walk)) + 6.9 * cut;
 }
 double small_bwd_time(const ntp_attn_core_shape_t* s, double cus) {
   const bool causal = s->causal != 0, d64 = s->head_dim == 64;
   const int64_t tiles = (int64_t(s->seq_len) + kBKV - 1) / kBKV, q = int64_t(s->n_seq) * s->q_cnt, kv = int64_t(s->n_seq) * s->kv_cnt;
   const SmallWalks wq = small_walks(tiles, 1, causal), wk = small_walks(tiles, std::min<int64_t>(s->group, s->q_cnt), causal);
-  const double t16 = double((int64_t(s->seq_len) + 15) / 16) / cus;
+  double t16 = double((int64_t(s->seq_len) + 15) / 16) / cus;
+  if (!causal && std::min<int64_t>(s->group, s->q_cnt) == 1) {  // equal walks: whole rounds
+    const double rounds = t16 * double(q + kv) / (d64 ? 2.0 : 1.0);
+    if (rounds > 1.0) t16 *= std::ceil(rounds) / rounds;
+  }
   return d64 ? 5.4 + std::max(1.4 * wk.most, t16 / 2 * (double(kv) * (2.2 + 2.14 * wk.mean) + double(q) * (2.2 + 1.0 * wq.mean)))
              : 6.2 + std::max(2.3 * wk.most, t16 * (double(kv) * (1.77 + 3.12 * wk.mean) + double(q) * (2.9 + 1.13 * wq.mean)));
 }
@@ -2418,7 +2427,8 @@ CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_cor
     set_parts(most, INT64_MAX / 2);
     auto fwd = [&](int parts) { return other_fwd_time(s, c.fwd_rows, parts, cus); };
     auto bwd = [&](int dq, int dkv) { return other_bwd_time(s, dq, dkv, cus); };
-    c.fwd_small = small_pays(small_fwd_time(s, cus), fwd(c.fwd_parts), fwd(1), fwd(most.fwd_parts));
+    // (head dimension 128, 17 to 20 tokens: a second workgroup for a few rows, 1.00 of the time on average, up to 1.06)
+    c.fwd_small = (s->head_dim == 64 || s->seq_len > 20) && small_pays(small_fwd_time(s, cus), fwd(c.fwd_parts), fwd(1), fwd(most.fwd_parts));
     if (c.fwd_small) c.fwd_parts = 1;
     // (32 rows per wavefront: launches with work for every unit, 1.6 to 2.6 times as fast)
     if (!h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] && s->kv_cnt > 0 && !most.bwd_wide && !(dma && wide_pays(s, 1, 1, double(cus)))) {

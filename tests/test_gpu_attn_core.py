@@ -416,6 +416,16 @@ def test_attn_core_few_workgroups(kernels, n_q, n_kv, tp, rank, d, n_seq, S, pad
     assert S < 65 or kernels() == [fwd, fwd, bwd]
 
 
+# Unmasked, all walks equal: whole rounds of the 16-row workgroups, of which a compute unit takes one (128) or two (64) at a time; short sequences
+@pytest.mark.parametrize("d,n_q,n_kv,n_seq,S,causal,small", [
+    (128, 8, 8, 1, 512, False, True), (128, 8, 2, 1, 568, False, False), (128, 7, 7, 1, 606, False, False), (128, 2, 2, 4, 613, False, False),
+    (64, 2, 2, 8, 512, False, True), (64, 4, 2, 4, 562, False, False), (64, 24, 3, 1, 387, False, False), (128, 4, 1, 4, 17, True, False), (128, 4, 1, 4, 64, True, True)])
+def test_attn_core_fwd_few_workgroups_rounds(kernels, d, n_q, n_kv, n_seq, S, causal, small):
+    _say(f"attn core fwd, rounds of 16-row workgroups d={d} n_q={n_q} n_kv={n_kv} n_seq={n_seq} S={S}")
+    _case(n_q, n_kv, 1, 0, d, n_seq, S, causal, seed=8)
+    assert kernels() == ["attn_core_fwd" + ("_small" if small else "") + ("_causal" if causal else "")]
+
+
 # walks dealt out by length: more than a round of 16-row workgroups on heads that eight XCDs do not share evenly (the queries' alone, the keys' as well)
 @pytest.mark.parametrize("n_q,n_kv,d,n_seq,S,pad", [(3, 3, 64, 1, 1409, 0), (6, 3, 64, 2, 700, 8), (3, 1, 128, 1, 1465, 0), (12, 3, 128, 1, 430, 0), (2, 2, 128, 1, 1169, 8)])
 def test_attn_core_few_workgroups_by_length(kernels, n_q, n_kv, d, n_seq, S, pad):
