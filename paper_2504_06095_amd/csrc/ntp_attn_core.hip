@@ -2427,8 +2427,8 @@ CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_cor
     set_parts(most, INT64_MAX / 2);
     auto fwd = [&](int parts) { return other_fwd_time(s, c.fwd_rows, parts, cus); };
     auto bwd = [&](int dq, int dkv) { return other_bwd_time(s, dq, dkv, cus); };
-    // (head dimension 128, 17 to 20 tokens: a second workgroup for a few rows, 1.00 of the time on average, up to 1.06)
-    c.fwd_small = (s->head_dim == 64 || s->seq_len > 20) && small_pays(small_fwd_time(s, cus), fwd(c.fwd_parts), fwd(1), fwd(most.fwd_parts));
+    // (17 and 18 tokens: a second workgroup for a row or two, 1.03-1.06 of the time)
+    c.fwd_small = (s->seq_len <= 16 || s->seq_len > 18) && small_pays(small_fwd_time(s, cus), fwd(c.fwd_parts), fwd(1), fwd(most.fwd_parts));
     if (c.fwd_small) c.fwd_parts = 1;
     // (32 rows per wavefront: launches with work for every unit, 1.6 to 2.6 times as fast)
     if (!h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] && s->kv_cnt > 0 && !most.bwd_wide && !(dma && wide_pays(s, 1, 1, double(cus)))) {

@@ -419,7 +419,7 @@ def test_attn_core_few_workgroups(kernels, n_q, n_kv, tp, rank, d, n_seq, S, pad
 # Unmasked, all walks equal: whole rounds of the 16-row workgroups, of which a compute unit takes one (128) or two (64) at a time; short sequences
 @pytest.mark.parametrize("d,n_q,n_kv,n_seq,S,causal,small", [
     (128, 8, 8, 1, 512, False, True), (128, 8, 2, 1, 568, False, False), (128, 7, 7, 1, 606, False, False), (128, 2, 2, 4, 613, False, False),
-    (64, 2, 2, 8, 512, False, True), (64, 4, 2, 4, 562, False, False), (64, 24, 3, 1, 387, False, False), (128, 4, 1, 4, 17, True, False), (128, 4, 1, 4, 64, True, True)])
+    (64, 2, 2, 8, 512, False, True), (64, 4, 2, 4, 562, False, False), (64, 24, 3, 1, 387, False, False), (128, 4, 1, 4, 17, True, False), (64, 8, 8, 1, 18, True, False), (128, 4, 1, 4, 64, True, True)])
 def test_attn_core_fwd_few_workgroups_rounds(kernels, d, n_q, n_kv, n_seq, S, causal, small):
     _say(f"attn core fwd, rounds of 16-row workgroups d={d} n_q={n_q} n_kv={n_kv} n_seq={n_seq} S={S}")
     _case(n_q, n_kv, 1, 0, d, n_seq, S, causal, seed=8)
