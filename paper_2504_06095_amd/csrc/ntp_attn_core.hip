@@ -2361,20 +2361,22 @@ bool wide_pays(const ntp_attn_core_shape_t* s, int dq_parts, int dkv_parts, doub
   return walk >= (per_unit >= 8.0 ? 36.0 : causal && per_unit >= 4.0 ? 28.0 : 24.0) || (walk >= 18.0 && !cut && longest >= 1.5 * 7.0 * pairs);
 }
 // Whether the backward launch at head dimension 64 with 32 rows per wavefront (ntp_attn_d64.h) is the faster one, by its 128-row dK/dV workgroups per compute unit,
-// of which one and a dQ workgroup run there at a time (64 rows: three): what it gains, up to a third, a nearly empty last round loses again.  192 random launches against
-// the choice without it, of those taken:
-//  - causal, a query head per KV head: 0.55 (above half: every unit has work) to 1, and from 1.5: 0.65-0.95 of the time (4 x 1747 tokens, 14 heads 135 -> 115 us; 6720
-//    tokens, 8 heads 268 -> 174, which was cut); between, 1.00-1.09 (1.17, 4 x 3647 tokens, 5 heads 204 -> 222);
-//  - causal, several query heads per KV head: from 0.65, 0.78-0.94 (dQ workgroups fill the last round); 0.41 and 0.48: 1.28 and 1.20;
-//  - unmasked, all walks equal: 0.65 to 1 0.73-0.88, above where the last round is filled to 0.85 0.81-0.95 (0.72, 2 x 5823 tokens, 4 heads 1.09); with several query heads per
-//    KV head from 0.95 on and to 0.79, 0.81-0.86 (4 x 2048 tokens, 16 heads on 4 277 -> 231 us; 0.71 1.04, 0.56 1.11-1.14).
+// of which one and a dQ workgroup run there at a time (64 rows: three): what it gains, up to a third, a nearly empty last round loses again.  With few rounds the longest
+// workgroups decide, and those of a sequence's last 128 keys are longer where the sequence ends inside them (every score of their walks is masked, and up to half of their rows
+// are past the end): such sequences ask for more.  2000 random launches and 150 on the lines, against the choice without it; of those taken, none above 1.02:
+//  - causal, a query head per KV head: from 0.58 (0.55 where 128 divides the sequence) to 1 0.65-1.01, from 1.52 (1.5) 0.74-1.01 (4 x 1747 tokens, 14 heads 135 -> 115 us; 6720
+//    tokens, 8 heads 268 -> 174, which was cut); below, 8 x 1294 tokens, 3 heads (0.56) 1.22; between, 0.92-1.35;
+//  - causal, several query heads per KV head: from 0.67, 0.72-1.02 (dQ workgroups fill the last round); at 0.656 8 x 1609 tokens, 24 heads on 3 1.11, below up to 1.8;
+//  - unmasked, all walks equal: from 0.78 (0.65) to 1 0.69-1.01, above where the last round is filled to 0.85 0.84-1.02; 4244 tokens, 5 heads (0.66) 1.12;
+//  - unmasked, several query heads per KV head: filled to 0.79 0.78-1.01; at 0.95 to 1 0.80-0.83 where 128 divides the sequence (4 x 2048 tokens, 16 heads on 4 274 -> 225 us; 2 x 4096
+//    548 -> 446), 0.98-1.16 where not (2 x 3996 534 -> 594).
 bool bwd64_pays(const ntp_attn_core_shape_t* s, double cus) {
   const int64_t tiles = (int64_t(s->seq_len) + 127) / 128, wgs = (s->causal ? (tiles + 1) / 2 : tiles) * s->n_seq * s->kv_cnt;
   const double load = double(wgs) / cus, filled = load / std::ceil(load);
-  const bool grouped = std::min<int64_t>(s->group, s->q_cnt) > 1;
+  const bool grouped = std::min<int64_t>(s->group, s->q_cnt) > 1, whole = s->seq_len % 128 == 0;
   if (tiles < 1 || wgs < 1 || s->q_cnt < 1 || int64_t(s->n_seq) * s->seq_len * s->q_cnt > (int64_t(1) << 33)) return false;  // (the delta kernel's grid)
-  if (s->causal) return grouped ? load >= 0.65 : load >= 1.5 || (load >= 0.55 && load <= 1.0);
-  return grouped ? load >= 0.95 && filled >= 0.79 : load >= 0.65 && filled >= (load > 1.0 ? 0.85 : 0.0);
+  if (s->causal) return grouped ? load >= 0.67 : load >= (whole ? 1.5 : 1.52) || (load >= (whole ? 0.55 : 0.58) && load <= 1.0);
+  return grouped ? load >= (whole ? 0.95 : 1.01) && filled >= 0.79 : load >= (whole ? 0.65 : 0.78) && filled >= (load > 1.0 ? 0.85 : 0.0);
 }
 CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_core_shape_t* s) {
   CoreChoice c{16, 1, 1, 1, 0, false, false, false, false, 0, false, false, false};

@@ -131,6 +131,16 @@ def test_rows_of_the_backward_kernels(ws):
     assert got == [(*c[:5], c[6 if ws else 5]) for c in BWD_ROWS]
 
 
+# the same at head dimension 64 (no workspace): causal and not, one and several query heads per KV head, sequences that 128 divides and others
+@pytest.mark.parametrize("n_q,n_kv,n_seq,S,causal,rows", [
+    (5, 5, 2, 3702, 1, 32), (3, 3, 8, 1294, 1, 16), (9, 9, 1, 4096, 1, 32), (9, 9, 1, 4095, 1, 16), (12, 12, 4, 2048, 1, 32), (8, 8, 8, 1371, 1, 16), (14, 14, 4, 1747, 1, 32),
+    (11, 11, 4, 1600, 1, 16), (24, 3, 8, 1609, 1, 16), (14, 7, 4, 1536, 1, 16), (24, 3, 8, 1900, 1, 32), (56, 7, 4, 4096, 1, 32),
+    (4, 4, 2, 2816, 0, 32), (5, 5, 1, 4244, 0, 16), (8, 8, 2, 1660, 0, 32), (4, 4, 2, 5823, 0, 16), (4, 4, 4, 3580, 0, 32),
+    (16, 4, 4, 2048, 0, 32), (16, 4, 4, 2047, 0, 16), (8, 4, 1, 8028, 0, 16), (16, 4, 4, 3300, 0, 32), (16, 4, 4, 3072, 0, 16)])
+def test_rows_of_the_backward_kernels_at_head_dimension_64(n_q, n_kv, n_seq, S, causal, rows):
+    assert N.ntp_attn_core_bwd_rows(_shape(n_q, n_kv, 1, 0, n_seq, S, causal, d=64)) == rows
+
+
 def test_rows_of_the_backward_kernels_by_option_and_head_dimension():
     long, short = _shape(14, 14, 1, 0, 1, 8192, False), _shape(14, 14, 1, 0, 1, 64, False)
     for copy, want in ((0, (32, 16)), (1, (16, 16)), (2, (16, 16)), (3, (32, 32))):
