@@ -1,7 +1,7 @@
-"""The assembly of the attention backward kernels with 32 rows per wavefront (no GPU).
+"""The assembly of the attention kernels whose LDS reads are inline assembly (no GPU): those with 32 rows per wavefront and those with 16 rows per workgroup.
 
-Their LDS reads and matrix instructions are inline assembly, of which the compiler knows neither when a read's registers are written nor
-that a matrix instruction is one.  What the source keeps by its order and its waits is checked in what the compiler makes of it."""
+The compiler does not know when such a read's registers are written, nor, in the backward kernels of head dimension 128, that a matrix instruction in assembly is
+one.  What the source keeps by its order and its waits is checked in what the compiler makes of it."""
 import os
 import re
 
@@ -22,9 +22,13 @@ def assembly(tmp_path_factory):
     return open(out).read().splitlines()
 
 
-def _code(assembly, kernel):
-    """(instructions of a kernel as (opcode, operand register sets, text), label -> index)"""
-    start = next(i for i, l in enumerate(assembly) if re.match(rf"_Z\w*{kernel}\w*:", l))
+def _symbols(assembly, kernel):
+    """Line numbers at which the instantiations of a kernel begin."""
+    return [i for i, l in enumerate(assembly) if re.match(rf"_Z\w*\d{kernel}(I\w*)?E\w*:", l)]
+
+
+def _code(assembly, start):
+    """(instructions of the kernel at a line as (opcode, operand register sets, text), label -> index)"""
     code, labels = [], {}
     for line in assembly[start + 1:]:
         line = line.split(";")[0].strip()
@@ -35,7 +39,7 @@ def _code(assembly, kernel):
         elif line and not line.startswith("."):
             op, _, rest = line.partition(" ")
             code.append((op, [_registers(p.strip().split(" ")[0]) for p in rest.split(",")], line))
-    raise AssertionError("no end of " + kernel)
+    raise AssertionError(f"no end of the kernel at line {start}")
 
 
 def _registers(operand):
@@ -77,6 +81,10 @@ def _in_flight_faults(code, labels):
     return faults
 
 
+def _without_waits(code):
+    return [c if c[0] != "s_waitcnt" else ("s_waitcnt", c[1], "s_waitcnt vmcnt(0)") for c in code]
+
+
 def _distance_faults(code):
     """Pairs closer than the hardware asks for, in the order of the text (one wait state an instruction, four a matrix instruction)."""
     at, vector, matrix, faults = 0, {}, {}, []
@@ -99,25 +107,30 @@ def _distance_faults(code):
 
 @pytest.mark.parametrize("kernel", KERNELS)
 def test_registers_are_left_alone_while_reads_are_in_flight(assembly, kernel):
-    code, labels = _code(assembly, kernel)
+    code, labels = _code(assembly, *_symbols(assembly, kernel))
     assert sum(op.startswith("v_mfma") for op, _, _ in code) >= 128 and sum(op.startswith("ds_read") for op, _, _ in code) >= 64
     assert not any("scratch_" in text for _, _, text in code)
     faults = _in_flight_faults(code, labels)
     assert not faults, list(faults.values())[:5]
-    # (the check sees a missing wait)
-    assert _in_flight_faults([c if c[0] != "s_waitcnt" else ("s_waitcnt", c[1], "s_waitcnt vmcnt(0)") for c in code], labels)
+    assert _in_flight_faults(_without_waits(code), labels)  # (the check sees a missing wait)
 
 
-@pytest.mark.parametrize("kernel,reads", [("attn_core_bwd_both64_dma_kernel", 128), ("attn_core_fwd64_dma_kernel", 48)])
-def test_registers_are_left_alone_at_head_dimension_64(assembly, kernel, reads):
-    code, labels = _code(assembly, kernel)  # (the matrix instructions are the compiler's own)
-    assert sum(op.startswith("ds_read") for op, _, _ in code) >= reads and not any("scratch_" in text for _, _, text in code)
-    assert not _in_flight_faults(code, labels)
+# paired and not; 16 rows per workgroup: both head dimensions, backward with and without the delta values formed in it (fewest LDS reads of them)
+@pytest.mark.parametrize("kernel,instantiations,reads", [("attn_core_bwd_both64_dma_kernel", 2, 128), ("attn_core_fwd64_dma_kernel", 2, 48), ("attn_core_fwd_small_kernel", 2, 24),
+                                                         ("attn_core_bwd_small_kernel", 4, 64)])
+def test_registers_are_left_alone_where_the_matrix_instructions_are_the_compilers(assembly, kernel, instantiations, reads):
+    starts = _symbols(assembly, kernel)
+    assert len(starts) == instantiations
+    for start in starts:
+        code, labels = _code(assembly, start)
+        assert sum(op.startswith("ds_read") for op, _, _ in code) >= reads and not any("scratch_" in text for _, _, text in code)
+        assert not _in_flight_faults(code, labels), assembly[start]
+        assert _in_flight_faults(_without_waits(code), labels)
 
 
 @pytest.mark.parametrize("kernel", KERNELS)
 def test_results_are_read_far_enough_behind_their_instructions(assembly, kernel):
-    code, _ = _code(assembly, kernel)
+    code, _ = _code(assembly, *_symbols(assembly, kernel))
     faults = _distance_faults(code)
     assert not faults, faults[:5]
     # (the check sees a vector instruction right before the matrix instruction that reads its result, and right behind one)
