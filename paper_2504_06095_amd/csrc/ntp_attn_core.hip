@@ -2363,10 +2363,10 @@ bool wide_pays(const ntp_attn_core_shape_t* s, int dq_parts, int dkv_parts, doub
 // Whether the backward launch at head dimension 64 with 32 rows per wavefront (ntp_attn_d64.h) is the faster one, by its 128-row dK/dV workgroups per compute unit,
 // of which one and a dQ workgroup run there at a time (64 rows: three): what it gains, up to a third, a nearly empty last round loses again.  With few rounds the longest
 // workgroups decide, and those of a sequence's last 128 keys are longer where the sequence ends inside them (every score of their walks is masked, and up to half of their rows
-// are past the end): such sequences ask for more.  2000 random launches and 150 on the lines, against the choice without it; of those taken, none above 1.02:
-//  - causal, a query head per KV head: from 0.58 (0.55 where 128 divides the sequence) to 1 0.65-1.01, from 1.52 (1.5) 0.74-1.01 (4 x 1747 tokens, 14 heads 135 -> 115 us; 6720
-//    tokens, 8 heads 268 -> 174, which was cut); below, 8 x 1294 tokens, 3 heads (0.56) 1.22; between, 0.92-1.35;
-//  - causal, several query heads per KV head: from 0.67, 0.72-1.02 (dQ workgroups fill the last round); at 0.656 8 x 1609 tokens, 24 heads on 3 1.11, below up to 1.8;
+// are past the end): such sequences ask for more without the mask.  2000 random launches and 150 on the lines, against the choice without it; of those taken, none above 1.02:
+//  - causal, a query head per KV head (a tile without a partner counted as half a workgroup): from 0.55, in one round, 0.65-1.01, from 1.5 0.74-1.01 (4 x 1747 tokens, 14 heads
+//    135 -> 115 us; 6720 tokens, 8 heads 268 -> 174, which was cut); below, 8 x 1294 tokens, 3 heads (0.52) 1.22; between, 0.92-1.35 (8 x 2350 tokens, 5 heads, 1.48: 1.09);
+//  - causal, several query heads per KV head: from 0.67, 0.72-1.02 (dQ workgroups fill the last round); at 0.61 8 x 1609 tokens, 24 heads on 3 1.11, below up to 1.8;
 //  - unmasked, all walks equal: from 0.78 (0.65) to 1 0.69-1.01, above where the last round is filled to 0.85 0.84-1.02; 4244 tokens, 5 heads (0.66) 1.12;
 //  - unmasked, several query heads per KV head: filled to 0.79 0.78-1.01; at 0.95 to 1 0.80-0.83 where 128 divides the sequence (4 x 2048 tokens, 16 heads on 4 274 -> 225 us; 2 x 4096
 //    548 -> 446), 0.98-1.16 where not (2 x 3996 534 -> 594).
@@ -2375,7 +2375,10 @@ bool bwd64_pays(const ntp_attn_core_shape_t* s, double cus) {
   const double load = double(wgs) / cus, filled = load / std::ceil(load);
   const bool grouped = std::min<int64_t>(s->group, s->q_cnt) > 1, whole = s->seq_len % 128 == 0;
   if (tiles < 1 || wgs < 1 || s->q_cnt < 1 || int64_t(s->n_seq) * s->seq_len * s->q_cnt > (int64_t(1) << 33)) return false;  // (the delta kernel's grid)
-  if (s->causal) return grouped ? load >= 0.67 : load >= (whole ? 1.5 : 1.52) || (load >= (whole ? 0.55 : 0.58) && load <= 1.0);
+  if (s->causal) {
+    const double pairs = double(tiles * s->n_seq * s->kv_cnt) / 2.0 / cus;
+    return grouped ? pairs >= 0.67 : pairs >= 1.5 || (pairs >= 0.55 && load <= 1.0);
+  }
   return grouped ? load >= (whole ? 0.95 : 1.01) && filled >= 0.79 : load >= (whole ? 0.65 : 0.78) && filled >= (load > 1.0 ? 0.85 : 0.0);
 }
 CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_core_shape_t* s) {
