@@ -88,7 +88,9 @@ int ntp_device_info(const ntp_handle_t* h, int32_t* device, int32_t* compute_uni
 /* Tuning overrides of one handle.  Every option is 0 by default = the library's
  * own choice.  They exist so that tests and tuning runs can reach every kernel
  * variant at any size; a forced variant computes the same result to within fp32
- * summation order (bit-identical for the reshard options).  GEMMs with few output
+ * summation order (bit-identical for the reshard options).  The attention kernels
+ * with 16 rows per workgroup are the exception: they are chosen by size alone, and NTP_OPT_ATTN_PARTS and
+ * NTP_OPT_ATTN_COPY other than 0 switch them off in both directions, NTP_OPT_ATTN_BWD_LAUNCHES in the backward call.  GEMMs with few output
  * tiles run on a kernel of their own (deep-pipelined; where a workspace is set its K axis
  * is cut into up to 16 chunks, or its tiles are 64 x 64 and its K axis whole or cut into up to 8), and the
  * gradient GEMMs of a small backward call may share one launch of it.  NTP_OPT_GEMM_TILE, _SPLIT, _SCHEDULE and _WORKGROUPS other
@@ -112,11 +114,11 @@ int ntp_device_info(const ntp_handle_t* h, int32_t* device, int32_t* compute_uni
 #define NTP_OPT_GEMM_WORKGROUPS 10   /* persistent GEMM launches use at most this many workgroups (rounded down to a
                                         multiple of 8, at least 8; 0: one per compute unit).  Fewer workgroups make
                                         each walk over more output tiles: tests and tuning                            */
-#define NTP_OPT_ATTN_COPY 11         /* how the attention kernels bring their 64-row tiles to LDS where both forms
-                                        exist (head dimension 128; forward: 16 query rows per wavefront): 1 through
-                                        registers, 2 by DMA into chunk-permuted rows, 3 as 2 and the backward kernels
-                                        with 32 instead of 16 rows per wavefront (also at head dimension 64, where they
-                                        share a launch and walks are not cut); 0: the library's choice                */
+#define NTP_OPT_ATTN_COPY 11         /* how the attention kernels bring their 64-row tiles to LDS where several forms
+                                        exist: 1 through registers; 2 by DMA into chunk-permuted rows (head dimension
+                                        128; 64: the forward kernel with 32 query rows per wavefront); 3 as 2 and the
+                                        backward kernels with 32 instead of 16 rows per wavefront (at head dimension 64
+                                        where they share a launch and walks are not cut); 0: the library's choice       */
 #define NTP_OPT_ATTN_BWD_LAUNCHES 12  /* the attention core's dQ and dK/dV kernels: 1 one launch each, 2 one launch for
                                         both where both copy by DMA, or at head dimension 64 where neither walk is
                                         cut (they then share the compute units; a small kernel stores the rows' delta
@@ -536,7 +538,8 @@ int ntp_gemm_choice(const ntp_handle_t* h, int32_t layout, int64_t M, int64_t N,
 
 /* Diagnostic aid (host only): launch decisions of the attention core kernels for a shape,
  * on this handle (its workspace and options at the time of the call).
- *   fwd_rows_per_wavefront  16 or 32 query rows per wavefront in the forward kernel
+ *   fwd_rows_per_wavefront  16 or 32 query rows per wavefront in the forward kernel (16 also where the four
+ *                           wavefronts of a workgroup share 16 rows: the timing names say so)
  *   fwd_parts, dq_parts, dkv_parts  > 1: every workgroup's walk is cut into that many parts
  *                                   (fp32 partial results in the workspace, merged by a second kernel)
  * Errors: as for ntp_attn_core_shard_fwd's shape checks. */

@@ -201,10 +201,10 @@ def _check(status: int, where: str) -> None:
         raise NtpError(status, where)
 
 
-# Enqueueing a call must not take longer than its kernels: two calls of a small MLP shard (512 x 1024 x 586) took 34 us on the host and 33 on
-# the device, six of a small attention shard (4 x 512 tokens, 3 heads of 64) 66 and 61, a layer's reshard of 9 to 7 shards a tensor 86 and 33; now 25,
-# 45 and 59.  So nothing is looked up twice: torch is bound once, the raw stream is asked for without a Stream object around it (2.9 -> 0.3 us a call), and a tensor's shape and
-# strides are fetched whole (0.65 -> 0.4 us a tensor).
+# Where kernels are short, enqueueing a call takes as long as they do or longer: two calls of a small MLP shard (512 x 1024 x 586) took 34 us on the host and 33 on
+# the device, six of a small attention shard (4 x 512 tokens, 3 heads of 64) 66 and 61, a layer's reshard of 9 to 7 shards a tensor 86 and 33; the host's part is now 25,
+# 45 and 59 (the reshard is still bound by it).  Nothing is looked up twice: torch is bound once, the raw stream is asked for without a Stream object around it (2.9 -> 0.3 us a call), and a
+# tensor's shape and strides are fetched whole (0.65 -> 0.4 us a tensor).
 _torch = None
 _raw_stream = None  # device ordinal -> current stream, where this torch has it
 

@@ -65,7 +65,10 @@ struct GemmArgs {
 //               negative arguments (0.5 (1 + erf) loses it to cancellation there), from one for positive ones.
 // The coefficients are least-maximum fits of the two functions (errors 1e-9 and 4.8e-9; logistic 2.4e-9), made for these ranges.  Error
 // against 64 bits, rms over N(0, 0.1) to N(0, 5) inputs: values 5.9e-9 to 5.7e-8 (with erff and tanhf 6.6e-9 to 6.4e-8), slopes 2.0e-8 to 2.7e-8 (2.0e-8 to
-// 1.1e-7).  MLP shard, both calls: 512 x 1024 x 586 35.5 -> 33.5 us, 4096 x 6144 x 3511 twice with the tanh form 1997 -> 1959, 2048 x 12288 x 7022 1837 -> 1818.
+// 1.1e-7); relative to the tail itself 1.9e-5 from -3 to -6.5 (0.5 (1 + erf) has nothing right there).  MLP shard, forward and backward: 512 x 1024 x 586 15.7 -> 15.2 and 20.9 -> 19.8 us,
+// 2048 x 4096 x 2341 98.3 -> 95.7 and 192.6 -> 186.4, 4096 x 6144 x 3511 with the tanh form 293.6 -> 285.8 and 632.6 -> 625.6.  What it costs: pre-activations so narrow that whole
+// wavefronts stay below erff's branch at sqrt(2) had the cheaper half of it alone, which launches of a few tiles show (rms 0.4, 143 x 384 x 68 forward 22.4 -> 23.3,
+// 2406 x 512 x 2163 34.2 -> 35.0; rms 1.4 and 2.0 26.4 -> 23.7 and 37.6 -> 35.1).
 __device__ __forceinline__ float normal_cdf(float x, float u) {  // u: x^2
   float p = -1.0864513569686096e-05f;
   p = fmaf(p, u, 0.00012061750021530315f);
@@ -293,7 +296,8 @@ __device__ __forceinline__ void accumulate_blocks(const GemmArgs& g, int m0, int
 
 // Pre-activations of a block row (EPI_DGELU): this lane's four values of each of its NI blocks, zeros where nothing is stored.  m: the lane's
 // row, n0: its first column of the first block.  They are asked for well before they are used (the pairs' stores would stand between them: the
-// memory counter is in order).
+// memory counter is in order).  Against a block row's loads right before its use, whole backward calls: 64 x 64 tiles 0.976-0.997 of the time (1024 x 768 x 512
+// 22.6 -> 22.2 us), ping-pong tiles 0.992-1.003, 128 x 128 and 128 x 256 tiles 0.986-1.012.
 template <int NI>
 __device__ __forceinline__ void load_aux_row(const GemmArgs& g, int m, int n0, u16x4 (&p)[NI]) {
   const uint16_t* const src = g.AUX + int64_t(m) * g.ldaux + n0;
