@@ -2435,7 +2435,7 @@ CoreChoice choose_core(const ntp_handle* h, int64_t ws_bytes, const ntp_attn_cor
     // (17 and 18 tokens: a second workgroup for a row or two, 1.03-1.06 of the time)
     c.fwd_small = (s->seq_len <= 16 || s->seq_len > 18) && small_pays(small_fwd_time(s, cus), fwd(c.fwd_parts), fwd(1), fwd(most.fwd_parts));
     if (c.fwd_small) c.fwd_parts = 1;
-    // (32 rows per wavefront: launches with work for every unit, 1.6 to 2.6 times as fast)
+    // (not where the launch has 32 rows per wavefront: up to 2.6 times as fast; without a workspace grouped heads can be the other way round, 16 heads on 2 x 1452 tokens 258 us for 153)
     if (!h->opt[NTP_OPT_ATTN_BWD_LAUNCHES] && s->kv_cnt > 0 && !most.bwd_wide && !(dma && wide_pays(s, 1, 1, double(cus)))) {
       const double whole = bwd(1, 1), all = bwd(most.dq_parts, most.dkv_parts);
       c.bwd_small = small_pays(small_bwd_time(s, cus), c.bwd_wide ? all : bwd(c.dq_parts, c.dkv_parts), whole, all);

@@ -39,8 +39,8 @@ __device__ __forceinline__ void small_for(std::integer_sequence<int, Is...>, F&&
 }
 
 // Workgroup b of a kind: its 16-row tile u and its (sequence, head) sh of `heads`.  Head by head, a head's tiles together on one XCD; or by length, the longest
-// tiles of all heads first (small_by_length).  (One division and no branch; called once, before the kernel's two bodies part: in either body the same lines
-// made launches of grouped heads 1.04-1.09 times as long.)
+// tiles of all heads first (small_by_length).  (One division and no branch; called once, before the backward kernel's two bodies part, of which the dQ body is the first in
+// the code: with the same lines in either body, or the other order, launches of grouped heads took 1.04-1.09 of the time.)
 __device__ __forceinline__ void small_place(uint32_t b, int tiles, int heads, bool by_length, int& u, int& sh) {
   const uint32_t major = xcd_major(b, uint32_t(tiles) * uint32_t(heads));
   const uint32_t bid = by_length ? b : major, n = uint32_t(by_length ? heads : tiles), quotient = bid / n, rest = bid - quotient * n;
@@ -115,6 +115,7 @@ __device__ __forceinline__ void small_pack(const float (&p)[4][4], bf16x8 (&f)[2
 }
 
 // Forward: workgroup = 16 query rows of one (sequence, head).
+// (a.pairs: nonzero where the tiles are dealt out by length)
 template <int D>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 128 ? 1 : 2, D == 128 ? 1 : 2))) void attn_core_fwd_small_kernel(const CoreArgs a) {
   using T = SmallTile<D>;
@@ -541,7 +542,7 @@ __device__ __forceinline__ void bwd_dkv_small_body(const CoreBwdArgs& a, const i
   });
 }
 
-// Both in one launch: dK/dV workgroups first (their walks are the longer ones).  DELTA: they form the rows' delta values for themselves and the dQ workgroups store
+// Both in one launch: dK/dV workgroups first (their walks are the longer ones).  a.pairs: 1 the queries', 2 the keys' tiles are dealt out by length.  DELTA: they form the rows' delta values for themselves and the dQ workgroups store
 // them, instead of a launch before this one (small_forms_delta).
 template <int D, bool DELTA>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 128 ? 1 : 2, D == 128 ? 1 : 2))) void attn_core_bwd_small_kernel(const CoreBwdArgs a, const uint32_t n_dkv) {
