@@ -46,28 +46,41 @@ int launch_generic(GemmArgs g, int epi, hipStream_t s) {
   });
 }
 
-// Relative throughput of one workgroup per tile shape at full occupancy, per operand layout (measured
-// on large problems with operands streaming from HBM): smaller wavefront tiles read more LDS fragments
-// per MFMA, smaller workgroup tiles move more bytes per flop, and the K-strided layouts pay two
-// transposing reads per fragment (their 256 x 256 variant is also short of registers).
+// Relative throughput of one workgroup per tile shape at full occupancy, per operand layout: smaller wavefront tiles read more LDS fragments
+// per MFMA, smaller workgroup tiles move more bytes per flop.  Fitted to 2500 random GEMMs (all layouts, 8 to 450 GFLOP, operands streaming from
+// HBM), every tile shape timed on each, with the ping-pong kernel on the 8-wavefront tiles: the tile that the table picks takes 1.012 (A, B K-contiguous), 1.003
+// and 1.009 of the best tile's time on the mean (with the table made for the ring schedule 1.014, 1.021 and 1.016).
 // The 4-wavefront 128 x 128 variant reaches its rate with two workgroups on a compute unit; alone on one
 // (at most 256 tiles) it runs at kLoneSmallTileRate, where the 8-wavefront variant of the same tile is faster.
 //                                             256x256 256x224 224x256 256x192 192x256 256x128 128x256 128x128 128x128w8
-constexpr double kTileRate[3][kNumTileShapes] = {{1.000, 0.957, 0.969, 0.917, 0.923, 0.761, 0.754, 0.65, 0.53},   // A, B K-contiguous
-                                                 {1.000, 0.929, 0.986, 0.908, 0.944, 0.770, 0.749, 0.65, 0.53},   // B K-strided
-                                                 {1.100, 0.984, 1.000, 0.956, 0.962, 0.797, 0.779, 0.65, 0.53}};  // both K-strided (256x256: its non-persistent form)
+constexpr double kTileRate[3][kNumTileShapes] = {{1.050, 1.008, 0.945, 0.924, 0.975, 0.714, 0.764, 0.60, 0.53},   // A, B K-contiguous
+                                                 {1.100, 0.977, 1.055, 1.023, 1.029, 0.705, 0.816, 0.60, 0.53},   // B K-strided
+                                                 {1.080, 1.007, 1.107, 0.985, 1.000, 0.806, 0.883, 0.50, 0.53}};  // both K-strided
 constexpr double kLoneSmallTileRate = 0.43;
+
+// What an estimate is made from: the rates above, the reduce launch behind a cut K axis (see choose_split), and the share of the uncut time that a cut has to reach.
+struct CostModel {
+  const double (*rate)[kNumTileShapes];
+  double reduce_bytes_per_cycle, reduce_fixed_cycles, cut_margin;
+};
+constexpr CostModel kCost = {kTileRate, 1500.0, 5000.0, 0.95};
+// The call with static scratch refuses shapes whose launches could use more room than there is, by the estimate that its limit came with: which shapes it
+// takes does not change with the rates.
+constexpr double kLimitRate[3][kNumTileShapes] = {{1.000, 0.957, 0.969, 0.917, 0.923, 0.761, 0.754, 0.65, 0.53},
+                                                  {1.000, 0.929, 0.986, 0.908, 0.944, 0.770, 0.749, 0.65, 0.53},
+                                                  {1.100, 0.984, 1.000, 0.956, 0.962, 0.797, 0.779, 0.65, 0.53}};
+constexpr CostModel kLimitCost = {kLimitRate, 2000.0, 6000.0, 0.85};
 
 // Pick the tile shape with the least estimated time: the busiest compute unit's number of
 // workgroups (they are dealt evenly; co-resident ones share its throughput) times tile area over rate.
-int choose_tile(int64_t M, int64_t N, int layout, int cus) {
+int choose_tile(const CostModel& cm, int64_t M, int64_t N, int layout, int cus) {
   int best = 0;
   double best_t = 1e300;
   for (int i = 0; i < kNumTileShapes; ++i) {
     const TileShape& ts = kTileShapes[i];
     const int64_t tiles = ((M + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn);
     const int64_t cu_load = (tiles + cus - 1) / cus;
-    const double rate = ts.waves == 4 && tiles <= cus ? kLoneSmallTileRate : kTileRate[layout][i];
+    const double rate = ts.waves == 4 && tiles <= cus ? kLoneSmallTileRate : cm.rate[layout][i];
     const double t = double(cu_load) * ts.bm * ts.bn / rate;
     if (t < best_t) {
       best_t = t;
@@ -85,7 +98,7 @@ void variant_name(int v, char* out, size_t n) {
 
 // Variant used for a shape: -1 = generic kernel, else an index into kTileShapes.  The handle's
 // NTP_OPT_GEMM_TILE overrides the choice (1: generic, 2 + i: tile shape i).
-int choose_variant(const ntp_handle* h, const GemmArgs& g, bool ring_ok, int layout) {
+int choose_variant(const CostModel& cm, const ntp_handle* h, const GemmArgs& g, bool ring_ok, int layout) {
   if (const int64_t f = h->opt[NTP_OPT_GEMM_TILE]) {
     if (!ring_ok || f == 1) return -1;
     if (f - 2 < kNumTileShapes) return int(f - 2);
@@ -94,7 +107,7 @@ int choose_variant(const ntp_handle* h, const GemmArgs& g, bool ring_ok, int lay
   // measured faster (512 x 586 x 1024: 15 us against 31 us per GEMM)
   if (int64_t(g.M) * g.N < 128 * 128 * 2 || g.K < 128) return -1;
   if (!ring_ok) return -1;
-  return choose_tile(g.M, g.n_store, layout, h->compute_units);
+  return choose_tile(cm, g.M, g.n_store, layout, h->compute_units);
 }
 
 // (layout, epilogue) pairs the shard layers use have ring instantiations; anything else runs on
@@ -118,7 +131,6 @@ struct SplitChoice {
 
 constexpr double kTileCycles = 2650.0;      // one 256 x 256 x 64 K tile on one compute unit at rate 1
 constexpr int kTileOverhead = 4;            // prologue and epilogue of an output tile, in K tiles
-constexpr double kReduceBytesPerCycle = 2000.0, kReduceFixedCycles = 6000.0;
 constexpr int kMaxSplits = 8, kMinSplitTiles = 8;
 
 // Workgroups of the busiest XCD's share of a launch with `splits` K chunks a tile: a tile and its chunks are on one XCD, so that 85 tiles in three
@@ -126,18 +138,18 @@ constexpr int kMaxSplits = 8, kMinSplitTiles = 8;
 // 3992: 43 us; in two chunks 31).
 int64_t xcd_load(int64_t tiles, int64_t splits) { return (tiles + 7) / 8 * splits; }
 
-double tile_time(int64_t M, int64_t N, int64_t ktiles, int layout, int i, int splits, int cus) {
+double tile_time(const CostModel& cm, int64_t M, int64_t N, int64_t ktiles, int layout, int i, int splits, int cus) {
   const TileShape& ts = kTileShapes[i];
   const int64_t tiles = ((M + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn);
   const int64_t units = std::max(cus / 8, 1), cu_load = splits == 1 ? (tiles + cus - 1) / cus : (xcd_load(tiles, splits) + units - 1) / units;
-  const double rate = ts.waves == 4 && tiles <= cus ? kLoneSmallTileRate : kTileRate[layout][i];
+  const double rate = ts.waves == 4 && tiles <= cus ? kLoneSmallTileRate : cm.rate[layout][i];
   const int64_t kt = (ktiles + splits - 1) / splits + kTileOverhead;
   return double(cu_load) * double(kt) * kTileCycles * (ts.bm * ts.bn / 65536.0) / rate;
 }
 
 // Least estimated time over (tile shape, splits); splits == 1 means: leave the GEMM as it is.
 // ws_bytes: room for the partial sums (0: never split).
-SplitChoice choose_split(const ntp_handle* h, int64_t ws_bytes, int64_t M, int64_t N, int64_t K, int layout, int plain_tile,
+SplitChoice choose_split(const CostModel& cm, const ntp_handle* h, int64_t ws_bytes, int64_t M, int64_t N, int64_t K, int layout, int plain_tile,
                          int64_t ldw) {
   SplitChoice best{plain_tile, 1, 0, kNotDeep};
   const int64_t ktiles = (K + 63) / 64;
@@ -146,7 +158,7 @@ SplitChoice choose_split(const ntp_handle* h, int64_t ws_bytes, int64_t M, int64
   const int64_t forced_tile = h->opt[NTP_OPT_GEMM_TILE];
   if (ws_bytes <= 0 || forced == 1) return best;
   // splitting has to beat the plain launch by a margin: the estimate is coarse
-  double best_t = plain_tile >= 0 ? 0.85 * tile_time(M, N, ktiles, layout, plain_tile, 1, cus) : 1e300;
+  double best_t = plain_tile >= 0 ? cm.cut_margin * tile_time(cm, M, N, ktiles, layout, plain_tile, 1, cus) : 1e300;
   if (forced > 1) best_t = 1e300;
   for (int i = 0; i < kNumTileShapes; ++i) {
     if (!kSplitTile[i]) continue;
@@ -157,8 +169,8 @@ SplitChoice choose_split(const ntp_handle* h, int64_t ws_bytes, int64_t M, int64
       if (forced <= 1 && chunk_tiles < kMinSplitTiles) break;
       if ((sp - 1) * chunk_tiles * 64 >= K) continue;  // the last chunk would be empty
       if (int64_t(sp) * M * ldw * 4 > ws_bytes) break;
-      const double reduce = kReduceFixedCycles + double(M) * double(N) * (4.0 * sp + 4.0) / kReduceBytesPerCycle;
-      const double t = tile_time(M, N, ktiles, layout, i, sp, cus) + reduce;
+      const double reduce = cm.reduce_fixed_cycles + double(M) * double(N) * (4.0 * sp + 4.0) / cm.reduce_bytes_per_cycle;
+      const double t = tile_time(cm, M, N, ktiles, layout, i, sp, cus) + reduce;
       if (t < best_t) {
         best_t = t;
         best = SplitChoice{i, sp, int(chunk_tiles * 64), kNotDeep};
@@ -257,10 +269,10 @@ SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int layout, int64
 }
 
 // Kernel variant (-1 generic, else a tile shape) and K chunks for a GEMM (g: M, N, K, n_store).
-SplitChoice plan_gemm(const ntp_handle* h, int64_t ws_bytes, const GemmArgs& g, int layout, bool ring_ok, bool split_ok,
+SplitChoice plan_gemm(const CostModel& cm, const ntp_handle* h, int64_t ws_bytes, const GemmArgs& g, int layout, bool ring_ok, bool split_ok,
                       int64_t ldw, bool deep_ok, bool small_ok = true) {
-  SplitChoice sc{choose_variant(h, g, ring_ok, layout), 1, 0, kNotDeep};
-  if (split_ok && int64_t(g.M) * g.N >= 128 * 128 * 8) sc = choose_split(h, ws_bytes, g.M, g.n_store, g.K, layout, sc.tile, ldw);
+  SplitChoice sc{choose_variant(cm, h, g, ring_ok, layout), 1, 0, kNotDeep};
+  if (split_ok && int64_t(g.M) * g.N >= 128 * 128 * 8) sc = choose_split(cm, h, ws_bytes, g.M, g.n_store, g.K, layout, sc.tile, ldw);
   // (options that ask for a ring tile, a cut, a schedule, a cap on the persistent grid or a K tail through registers mean the ring kernels)
   const bool ring_asked = h->opt[NTP_OPT_GEMM_TILE] || h->opt[NTP_OPT_GEMM_SPLIT] || h->opt[NTP_OPT_GEMM_SCHEDULE] || h->opt[NTP_OPT_GEMM_WORKGROUPS] ||
                           (h->opt[NTP_OPT_GEMM_NO_RING_TAIL] && layout == 1 && g.K % 64 != 0);
@@ -269,15 +281,16 @@ SplitChoice plan_gemm(const ntp_handle* h, int64_t ws_bytes, const GemmArgs& g, 
   return sc;
 }
 
-// Which schedule of the K loop a persistent ring launch gets (tile shapes 0-6 have both).  Under the board's power
-// limit the two run within a few percent of each other (with all-zero operands, which draw little switching power,
-// the ping-pong schedule is 6 % faster).  Measured in the GPT-3-shape step: ping-pong +1-4 % where both operands are
-// K-contiguous, -1-8 % where one or both are K-strided (their transposing reads make the memory slots longer), with
-// two exceptions: the weight-gradient layout on the 224 x 256 and 256 x 224 tiles, +2.5 %, whose ping-pong kernels also
-// need no scratch memory (the default schedule spills 10 and 21 registers there), and the row-parallel layout at short
-// K (fc2 / dX of a narrow shard: 8192 x 16384 over K = 750 runs 200-207 us against 215-221 us on the 256 x 256 tile).
-// NTP_OPT_GEMM_SCHEDULE: 1 forces the default schedule, 2 the ping-pong schedule.
-bool use_pingpong(const ntp_handle* h, int layout, int variant, int64_t K) {
+// Which kernel a persistent launch on an 8-wavefront tile gets: the ping-pong one (tile shapes 0-6, three K tiles or more), whose wavefronts read
+// fragments while the others of their SIMDs compute, unless NTP_OPT_GEMM_SCHEDULE = 1 asks for the ring kernel.  Measured on all tile shapes and layouts over ten
+// shapes of 26 to 350 GFLOP, ping-pong against ring: A, B K-contiguous 0.93-0.97 of the time, B K-strided 0.84-0.96, both K-strided 0.88-0.99 (2048 x
+// 12288 over K = 7040 269 -> 249, 288 -> 268 and 344 -> 310 us against the kernels that these layouts ran on before).
+bool use_pingpong(const ntp_handle* h, int variant, int64_t K) {
+  return variant >= 0 && variant <= 6 && K > 128 && h->opt[NTP_OPT_GEMM_SCHEDULE] != 1;
+}
+
+// What ntp_gemm_choice reports as `pingpong`: the kinds of GEMM for which the schedule was chosen while it was one of two (see ntp.h).
+bool reported_pingpong(const ntp_handle* h, int layout, int variant, int64_t K) {
   if (variant < 0 || variant > 6) return false;
   const int64_t f = h->opt[NTP_OPT_GEMM_SCHEDULE];
   if (f == 1) return false;
@@ -291,7 +304,7 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 namespace ntp {
 
-int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t N, int64_t n_store, int64_t K, bool deep) {
+int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t N, int64_t n_store, int64_t K, bool deep, bool limit) {
   if (M < 1 || N < 1 || K < 1 || M > 0x7fffff00 || N > 0x7fffff00 || K > 0x7fffff00) return 0;
   GemmArgs g{};
   g.M = int32_t(M);
@@ -300,7 +313,8 @@ int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t 
   g.n_store = int32_t(n_store);
   const int64_t ldw = (n_store + 15) / 16 * 16;
   // (what 128 x 128 tiles would be cut into counts where 64 x 64 tiles take their place uncut: those are for handles with a workspace)
-  const SplitChoice sc = plan_gemm(h, INT64_MAX / 2, g, layout, true, true, ldw, deep), wide = plan_gemm(h, INT64_MAX / 2, g, layout, true, true, ldw, deep, false);
+  const CostModel& cm = limit ? kLimitCost : kCost;
+  const SplitChoice sc = plan_gemm(cm, h, INT64_MAX / 2, g, layout, true, true, ldw, deep), wide = plan_gemm(cm, h, INT64_MAX / 2, g, layout, true, true, ldw, deep, false);
   const int splits = std::max(sc.splits, wide.splits);
   return splits > 1 ? int64_t(splits) * M * ldw * 4 : 0;
 }
@@ -313,6 +327,7 @@ struct Prepared {
   SplitChoice sc;
   int layout;
   bool ring_ok;
+  bool pp_ok;    // K tail within what the ping-pong kernel takes
   bool empty;    // no output element: nothing else is filled in
   bool nothing;  // no output that has a destination
   void* ws_ptr;
@@ -427,8 +442,16 @@ int prepare(ntp_handle* h, const GemmDesc& d, Prepared* out) {
   // deep-pipelined kernel: 32-bit byte offsets with room for one that lies past every operand, and a K tail of whole chunks
   const bool deep_ok = ring_ok && a_rows * d.lda * 2 < (int64_t(1) << 31) && b_rows * d.ldb * 2 < (int64_t(1) << 31) &&
                        (!d.a_kc || d.K % 8 == 0 || (d.a_k_pad_8 && !d.b_kc));
-  const SplitChoice sc = plan_gemm(h, ws_ptr ? ws_bytes : 0, g, layout, ring_ok, split_ok, ldw, deep_ok);
-  *out = Prepared{g, sc, layout, ring_ok, false, to_segs && g.n_segs == 0, ws_ptr, ldw};
+  // Ping-pong kernel, K tail as a K tile of its own: chunks of a K-contiguous operand past K go to an offset past every view below 2 GiB, lines of a
+  // K-strided one have offsets of 32 bits.
+  const int64_t k64 = (d.K + 63) / 64 * 64;
+  const bool tail_ok = (d.a_kc ? a_rows * d.lda * 2 < (int64_t(1) << 31) : k64 * d.lda * 2 < (int64_t(1) << 32)) &&
+                       (d.b_kc ? b_rows * d.ldb * 2 < (int64_t(1) << 31) : k64 * d.ldb * 2 < (int64_t(1) << 32)) &&
+                       (!d.a_kc || d.K % 8 == 0 || (d.a_k_pad_8 && !d.b_kc));
+  const bool pp_ok = d.K % 64 == 0 || (tail_ok && !(layout == 1 && h->opt[NTP_OPT_GEMM_NO_RING_TAIL]));
+  SplitChoice sc = plan_gemm(kCost, h, ws_ptr ? ws_bytes : 0, g, layout, ring_ok, split_ok && pp_ok, ldw, deep_ok);
+  if (layout == 2 && !pp_ok && ring_ok && !sc.deep && sc.splits == 1 && sc.tile == 0) sc.tile = 2;  // (the 256 x 256 tile of this layout is a ping-pong kernel)
+  *out = Prepared{g, sc, layout, ring_ok, pp_ok, false, to_segs && g.n_segs == 0, ws_ptr, ldw};
   return NTP_OK;
 }
 
@@ -459,7 +482,7 @@ int launch_prepared(ntp_handle* h, const GemmDesc& d, const Prepared& p, void* s
     if (sc.deep == kDeepSmall) snprintf(vn, sizeof(vn), "64x64");
     else variant_name(variant, vn, sizeof(vn));
     if (sc.splits > 1) snprintf(sn, sizeof(sn), "k%d", sc.splits);
-    const bool pp = sc.splits == 1 && !sc.deep && use_pingpong(h, layout, variant, d.K) && !(layout == 2 && variant == 0 && ring_ok);
+    const bool pp = sc.splits == 1 && !sc.deep && p.pp_ok && use_pingpong(h, variant, d.K) && !(layout == 2 && variant == 0);
     snprintf(name, sizeof(name), "gemm_%c%c_%s_%s%s%s%s", d.a_kc ? 'n' : 't', d.b_kc ? 't' : 'n', kEpiName[d.epilogue], vn,
              sc.deep == kDeep2 ? "d2" : sc.deep ? "d" : "", sn, pp ? "pp" : "");
     ntp::timing_begin(h, stream, name, 2.0 * double(d.M) * double(d.N) * double(d.K), 0.0);
@@ -467,17 +490,16 @@ int launch_prepared(ntp_handle* h, const GemmDesc& d, const Prepared& p, void* s
   if (sc.deep && sc.splits == 1) {
     st = launch_deep(deep_args(p, d), d.a_kc, d.b_kc, d.epilogue, sc.deep, s);
   } else if (layout == 2 && variant == 0 && sc.splits == 1 && ring_ok) {
-    // The 256 x 256 weight-gradient tile runs one workgroup per output tile: its persistent form is short of
-    // registers (27 spilled, some inside the K loop) and measured 17 % slower (307 against 254 us at
-    // 5376 x 12288 x 2048), more than the overlap of one tile's stores with the next tile's first loads gains.
+    // The 256 x 256 weight-gradient tile runs one workgroup per output tile (5376 x 12288 x 2048 247 -> 228 us with the ping-pong kernel; its persistent form takes
+    // 218 there, and 200 against 199 at 4096 x 4096 x 8192).
     GemmArgs gp = g;
     gp.k_splits = 1;
     gp.k_chunk = int32_t((d.K + 63) / 64 * 64);
-    st = launch_ring_split_tn(gp, d.epilogue, variant, s);
+    st = launch_split_tn(gp, d.epilogue, variant, s);
   } else if (sc.splits > 1) {
     GemmArgs gp = g;  // the partial-sum launch: fp32 to the workspace, no row segments
     gp.ring_tail = 0;
-    gp.a_extent = uint32_t(sc.deep ? deep_extent_bytes(d.a_kc, d.M, d.K, d.lda) : operand_extent_bytes(d.a_kc, d.M, d.K, d.lda, false));
+    gp.a_extent = uint32_t(deep_extent_bytes(d.a_kc, d.M, d.K, d.lda));
     gp.C = ws_ptr;
     gp.ldc = ldw;
     gp.n_segs = 0;
@@ -485,9 +507,9 @@ int launch_prepared(ntp_handle* h, const GemmDesc& d, const Prepared& p, void* s
     gp.k_chunk = sc.k_chunk;
     gp.split_stride = int64_t(d.M) * ldw;
     if (sc.deep) st = launch_deep(gp, d.a_kc, d.b_kc, EPI_F32, sc.deep, s);
-    else if (d.a_kc && d.b_kc) st = launch_ring_split_nt(gp, variant, s);
-    else if (d.a_kc) st = launch_ring_split_nn(gp, variant, s);
-    else st = launch_ring_split_tn(gp, EPI_F32, variant, s);
+    else if (d.a_kc && d.b_kc) st = launch_split_nt(gp, variant, s);
+    else if (d.a_kc) st = launch_split_nn(gp, variant, s);
+    else st = launch_split_tn(gp, EPI_F32, variant, s);
     if (st == NTP_OK) {
       const int64_t threads = int64_t(d.M) * (n_store / 4);
       const dim3 grid(uint32_t((threads + 255) / 256)), block(256);
@@ -497,10 +519,12 @@ int launch_prepared(ntp_handle* h, const GemmDesc& d, const Prepared& p, void* s
         return hipGetLastError() == hipSuccess ? NTP_OK : NTP_ERR_LAUNCH;
       });
     }
-  } else if (use_pingpong(h, layout, variant, d.K)) {
-    if (d.a_kc && d.b_kc) st = launch_pp_nt(g, d.epilogue, variant, s);
-    else if (d.a_kc) st = launch_pp_nn(g, d.epilogue, variant, s);
-    else st = launch_pp_tn(g, d.epilogue, variant, s);
+  } else if (p.pp_ok && use_pingpong(h, variant, d.K)) {
+    GemmArgs gp = g;
+    gp.a_extent = uint32_t(std::min<int64_t>(0xFFFFFFFFll, deep_extent_bytes(d.a_kc, d.M, d.K, d.lda)));
+    if (d.a_kc && d.b_kc) st = launch_pp_nt(gp, d.epilogue, variant, s);
+    else if (d.a_kc) st = launch_pp_nn(gp, d.epilogue, variant, s);
+    else st = launch_pp_tn(gp, d.epilogue, variant, s);
   } else if (variant >= 0) {
     if (d.a_kc && d.b_kc) st = launch_ring_nt(g, d.epilogue, variant, s);
     else if (d.a_kc) st = launch_ring_nn(g, d.epilogue, variant, s);
@@ -631,7 +655,7 @@ extern "C" int ntp_gemm_choice(const ntp_handle_t* h, int32_t layout, int64_t M,
   g.N = int32_t(N);
   g.K = int32_t(K);
   g.n_store = int32_t((N + 7) / 8 * 8);
-  const SplitChoice sc = plan_gemm(h, h->workspace ? h->workspace_bytes : 0, g, layout, true, true, (g.n_store + 15) / 16 * 16, true);
+  const SplitChoice sc = plan_gemm(kCost, h, h->workspace ? h->workspace_bytes : 0, g, layout, true, true, (g.n_store + 15) / 16 * 16, true);
   *out = ntp_gemm_choice_t{};
   out->k_splits = sc.splits;
   if (sc.tile < 0) {
@@ -646,6 +670,6 @@ extern "C" int ntp_gemm_choice(const ntp_handle_t* h, int32_t layout, int64_t M,
     out->ring = 1;
   }
   out->persistent = sc.tile >= 0 && !sc.deep && sc.splits == 1 && !(layout == 2 && sc.tile == 0) ? 1 : 0;
-  out->pingpong = out->persistent && use_pingpong(h, layout, sc.tile, K) ? 1 : 0;
+  out->pingpong = out->persistent && reported_pingpong(h, layout, sc.tile, K) ? 1 : 0;
   return NTP_OK;
 }

@@ -103,6 +103,15 @@ NTP_HD TilePos place_tile(int v, int tiles_m, int tiles_n) {
   return p;
 }
 
+// Order in which the XCDs walk over their tiles where they have more than a round of their 32 compute units: XCD x begins x rounds into its range and
+// comes to the range's start last.  Begun at their starts, the XCDs are at the same few columns, or half a row apart, all the time, and where rows are a power
+// of two long their loads and stores then meet in the same memory channels (8192 x 16384 over K = 750, 256 x 256 tiles, rows of 32 KiB: 236 -> 196 us; 8192 x
+// 8192 over 1024 130 -> 121; rows of 24 KiB 271 -> 273, within the runs' spread; by an eighth of a round or by two rounds 233 and 207).
+NTP_HD int rotate_walk(int v, int nblk) {
+  const int xcd = v & 7, n_x = (nblk >> 3) + (xcd < (nblk & 7) ? 1 : 0);
+  return n_x > 32 ? ((v >> 3) + 32 * xcd) % n_x * 8 + xcd : v;
+}
+
 // K tiles that go through the ring for a contraction of K elements: the whole ones, plus the tail tile when
 // it may go through the ring too.
 NTP_HD int ring_k_tiles(int K, bool ring_tail) { return K / DK + ((ring_tail && K % DK) ? 1 : 0); }

@@ -1,26 +1,36 @@
-// Ping-pong form of the ring GEMM kernel (8 wavefronts).  Same tiles, LDS ring, slot layouts, DMA addressing
+// Ping-pong form of the ring GEMM kernel (8 wavefronts).  Same tiles, slot layouts, DMA addressing
 // and epilogues as gemm_ring_kernel (ntp_gemm_ring.h); what differs is who does what when in the K loop.
 //
 // The two wavefronts of a SIMD (w and w + 4: wavefronts are dealt to the four SIMDs in turn) alternate between
 // two kinds of slot, with a workgroup barrier after every slot:
-//   memory slot   read all fragments of one K-step (32 k) of the current K tile from LDS into registers, start
-//                 this wavefront's DMA instructions, wait for the fragments;
-//   compute slot  MI x NI matrix instructions on those fragments, nothing else.
+//   memory slot   read all fragments of one K-step (32 k) of the current K tile from LDS into registers and
+//                 wait for them;
+//   compute slot  MI x NI matrix instructions on those fragments, this wavefront's DMA instructions evenly among them.
 // Wavefronts 0-3 ("early") run M0 C0 M1 C1 per K tile, wavefronts 4-7 ("late") the same one slot behind, so
-// in every slot one wavefront of each SIMD computes while the other one's LDS latency, address arithmetic and DMA
-// issue hide behind it, instead of sharing an instruction stream with the matrix instructions.
+// in every slot one wavefront of each SIMD computes while the other one's LDS latency hides behind it.
 //
-// LDS ring (five operand slots): K tile t (P = t mod 5) has A in slot 2P and B in slot 2P+1.  The last reader
-// of tile t is the late group's M1, the fourth slot of the tile; after that slot's barrier both are free.
-// Every wavefront moves an eighth of both operands, so that each of a tile's four slots carries a quarter of the
-// tile's DMA instructions (the vector memory path takes about 18 cycles per 1 KiB instruction and compute unit:
-// 64 of them per K tile are two thirds of the tile's matrix time, and have to be spread evenly to hide):
-//   in M0 of tile t a wavefront starts its share of B of tile t+1 -> slot 2P+3 (where A of tile t-1 was),
-//   in M1 its share of A of tile t+2 -> slot 2P+4 (where B of tile t-1 was), and the L2 prefetch;
-//   before the barrier that ends the tile's fourth slot (early group: after C1, late group: after M1) it waits
-//   for its DMA instructions up to that share of B (the NA + 1 newer ones may stay in flight).
-// After that barrier tile t+1 is complete in LDS.  Past the last tile the schedule keeps loading the last tile
-// (clamped index) into slots nobody reads, so that instruction counts stay static.
+// What bounds the loop is the longer of the two kinds of slot, then the board's power.  A compute slot is 448 cycles on a 256 x 224 tile.  With the DMA
+// instructions in the memory slots these took 390 (M0) and 600-680 cycles (M1, which also held a prefetch to L2), 510 and 750-780 where both
+// operands are K-strided; without them they take 210-230 (340-400), and a compute slot with four DMA instructions in it about 500: the vector memory
+// path takes about 18 cycles per 1 KiB instruction and compute unit, and 16 of them in 448 cycles do not queue up.  The prefetch (a 4-byte load
+// per 128-byte line four K tiles ahead, by turns) cost a slot more than it brought and is gone.  Whole GEMMs: use_pingpong in ntp_gemm.hip.  A K chunk of the
+// non-persistent form, which ran on the ring kernel before: 8192 x 752 over K = 16384 in two chunks 189 -> 171 us, 4096 x 640 over 8192 in three 65 -> 58.
+//
+// LDS is a ring of five operand slots that runs on from one output tile of a persistent workgroup into the next.  Of the two operands one ("long", the
+// one of more rows) is asked for two K tiles ahead, the other ("short") one to two.  While K tile t is multiplied the slots hold
+//   long t, short t, long t+1, short t+1, long t+2;
+// the last reader of tile t is the late group's M1, the fourth slot of the tile, after which its two slots take short t+2 and long t+3.
+// Every wavefront moves an eighth of both operands:
+//   early group: short t+1 in C0 of tile t (second slot), long t+2 in C1 (fourth);
+//   late group:  long t+2 in C0 of tile t (third slot), short t+2 in C1 (first slot of tile t+1);
+//   before the barrier that ends the fourth slot both wait for everything up to short t+1 (the instructions of long t+2 may stay in flight).
+// After that barrier tile t+1 is complete in LDS.  What a K tile asks for past the output tile's last one are the first K tiles of the workgroup's next
+// output tile, so that a tile switch is the epilogue alone; where there is none the offsets go past every buffer view (zeros, no memory traffic), so that instruction
+// counts stay static.
+//
+// K tail (K % 64): as in the deep-pipelined kernel, a K tile of its own through the ring.  Lines of a K-strided operand at k >= K lie past its buffer
+// view and read as zeros; of a K-contiguous one the chunks of 8 at k >= K are sent past the view in the last K tile (a chunk that K cuts holds zeros
+// from K on: the host sees to that).
 //
 // LDS reads in the loop are inline assembly: the compiler then neither sees nor guards them (it would put a
 // wait for every DMA in flight in front of each), and the waits above are the only ones.
@@ -65,13 +75,26 @@ __device__ __forceinline__ void dma_issue(__amdgpu_buffer_rsrc_t rsrc, uint16_t*
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)dst, 16, voff, soff, 0, 0);
 }
 
+// the same with the 32-bit LDS address of the destination
+__device__ __forceinline__ void dma_issue_at(__amdgpu_buffer_rsrc_t rsrc, uint32_t dst, uint32_t voff, uint32_t soff) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)dst, 16, voff, soff, 0, 0);
+#endif
+}
+
 template <int... Is, typename F>
 __device__ __forceinline__ void static_for(std::integer_sequence<int, Is...>, F&& f) {
   (f(Int<Is>{}), ...);
 }
 
-template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN>
+// SPLIT: the non-persistent form, one workgroup per unit of work.  The K axis is cut into g.k_splits
+// chunks of g.k_chunk (a multiple of the K tile; the last chunk takes what is left).  The grid holds
+// k_splits groups of round_up(tiles, 8) workgroups; group s computes every output tile over chunk s.
+// With several chunks the fp32 partial sums go to slice s of a workspace (g.C + s * g.split_stride
+// floats, rows of g.ldc); with one chunk the tile gets its normal epilogue.
+template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, bool SPLIT = false>
 __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
+  static_assert(!SPLIT || EPI == ntp::EPI_F32 || EPI == ntp::EPI_F32_ACCUM, "partial sums are stored as fp32");
   static_assert(WGM * WGN == 8, "wavefront w is paired with wavefront w + 4");
   constexpr int TM = BM_ / WGM, TN = BN_ / WGN;  // wavefront tile
   constexpr int MI = TM / 16, NI = TN / 16;      // 16 x 16 accumulator blocks
@@ -79,22 +102,13 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
   constexpr int RA = slot_rows(AKC, BM_), RB = slot_rows(BKC, BN_);
   static_assert(BM_ <= 256 && BN_ <= 256, "tile sides up to 256");
   constexpr int SLOT = (RA > RB ? RA : RB) * DK;
-  // DMA instructions per K tile and wavefront for A and for B
-  constexpr int NAI = RA * DK * 2 / 1024 / 8, NBI = RB * DK * 2 / 1024 / 8;
-  static_assert((RA * DK * 2 / 1024) % 8 == 0 && (RB * DK * 2 / 1024) % 8 == 0, "operands split evenly over the wavefronts");
-  __shared__ __attribute__((aligned(1024))) uint16_t r0[SLOT];
-  __shared__ __attribute__((aligned(1024))) uint16_t r1[SLOT];
-  __shared__ __attribute__((aligned(1024))) uint16_t r2[SLOT];
-  __shared__ __attribute__((aligned(1024))) uint16_t r3[SLOT];
-  __shared__ __attribute__((aligned(1024))) uint16_t r4[SLOT];
-  auto slot = [&](auto idx) -> uint16_t* {
-    constexpr int i = decltype(idx)::value;
-    if constexpr (i == 0) return r0;
-    else if constexpr (i == 1) return r1;
-    else if constexpr (i == 2) return r2;
-    else if constexpr (i == 3) return r3;
-    else return r4;
-  };
+  constexpr bool LB = RB > RA;  // the long operand is B
+  constexpr bool LKC = LB ? BKC : AKC, SKC = LB ? AKC : BKC;
+  constexpr int RL = LB ? RB : RA, RS = LB ? RA : RB;
+  // DMA instructions per K tile and wavefront for the long and the short operand
+  constexpr int NL = RL * DK * 2 / 1024 / 8, NS = RS * DK * 2 / 1024 / 8;
+  static_assert((RL * DK * 2 / 1024) % 8 == 0 && (RS * DK * 2 / 1024) % 8 == 0, "operands split evenly over the wavefronts");
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[5 * SLOT];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -102,100 +116,86 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
   const int wm = wave / WGN, wn = wave % WGN;
   const bool late = wave >= 4;  // uniform within a wavefront
 
-  // persistent workgroups, XCD-aware tile walk: as in gemm_ring_kernel
+  // persistent workgroups, XCD-aware tile walk: as in gemm_ring_kernel, each XCD begun a round later than the one before
   const int nblk = g.tiles_m * g.tiles_n;
-  struct Pos {
-    int tile_m, tile_n, row0, col0;
-  };
   auto place = [&](int v) {
-    const TilePos t = place_tile(v, g.tiles_m, g.tiles_n);
-    return Pos{t.tile_m, t.tile_n, t.tile_m * BM_, t.tile_n * BN_};
+    TilePos t = place_tile(rotate_walk(v, nblk), g.tiles_m, g.tiles_n);
+    t.tile_m *= BM_;
+    t.tile_n *= BN_;
+    return t;  // first row and column
   };
   int vblk = blockIdx.x;
-  const int K = g.K;
-  Pos pos = place(vblk);
-  int row0 = pos.row0, col0 = pos.col0;
+  int split = 0;
+  if constexpr (SPLIT) {
+    const int per_split = (nblk + 7) & ~7;  // keeps (workgroup index & 7) == (tile index & 7)
+    split = blockIdx.x / per_split;
+    vblk = blockIdx.x - split * per_split;
+    if (vblk >= nblk) return;  // padding workgroup (the whole workgroup leaves, before any barrier)
+  }
+  // this workgroup's share of the K axis
+  const int64_t k_first = SPLIT ? int64_t(split) * g.k_chunk : 0;
+  const int K = SPLIT ? min(g.k_chunk, g.K - int(k_first)) : g.K;
+  const int nk = (K + DK - 1) / DK;  // (three at least in the persistent form: pp_ok in ntp_gemm.hip)
+  TilePos pos = place(vblk);
 
   f32x4 acc[MI][NI];
-  const int64_t astep = AKC ? DK : DK * g.lda, bstep = BKC ? DK : DK * g.ldb;  // elements per K tile
-  constexpr bool RT = AKC && !BKC;
-  // range-checked buffer views of the operands (see gemm_ring_kernel); a wavefront uses the one of the operand it moves
-  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(g.A), 0, int(g.a_extent), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(g.B), 0, int(g.b_extent), 0x00020000);
-  const uint32_t astep_b = uint32_t(astep) * 2, bstep_b = uint32_t(bstep) * 2;
+  // range-checked buffer views of the operands (see gemm_ring_kernel)
+  const uint32_t a_shift = deep_view_shift(AKC, k_first, g.lda), b_shift = deep_view_shift(BKC, k_first, g.ldb);
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(g.A) + a_shift / 2, 0, int(g.a_extent - a_shift), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(g.B) + b_shift / 2, 0, int(g.b_extent - b_shift), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rl = LB ? rb : ra, rs = LB ? ra : rb;
+  const int64_t ldl = LB ? g.ldb : g.lda, lds = LB ? g.lda : g.ldb;
+  const int liml = LB ? g.N : g.M, lims = LB ? g.M : g.N;
+  const uint32_t stepl = uint32_t(LKC ? DK : DK * ldl) * 2, steps = uint32_t(SKC ? DK : DK * lds) * 2;  // bytes per K tile
   FragAddr<AKC, RA, MI> fra;
   FragAddr<BKC, RB, NI> frb;
   fra.init(wm * TM, lane);
   frb.init(wn * TN, lane);
 
-  const int nfull = K / DK;
-  const bool ring_tail = RT && g.ring_tail != 0 && nfull * DK < K;
-  const int nk = nfull + (ring_tail ? 1 : 0);
-
-  // L2 prefetch four K tiles ahead, by turns among the workgroups that share an operand tile: as in gemm_ring_kernel
-  constexpr int PFD = 4;
-  uint32_t pf_sink = 0;
-  const bool pf_is_a = wave < 4;
-  const int pf_mask = pf_is_a ? 3 : 7;
-  const bool pf_ok = pf_is_a ? (AKC || g.M >= 2) : (BKC || g.N >= 2);
-  const char* const pf_base = reinterpret_cast<const char*>(pf_is_a ? g.A : g.B);
-  const int64_t pf_step = (pf_is_a ? astep : bstep) * 2;  // bytes per K tile
-  int pf_turn = 0, pf_turn_next = -1;  // -1: there is no next output tile
-  uint32_t pf_voff = 0, pf_voff_next = 0;
-  auto pf_params = [&](const Pos& p, int& turn, uint32_t& voff) {
-    turn = pf_is_a ? (p.tile_n & 3) : (p.tile_m & 7);
-    voff = pf_is_a ? DmaOperand<AKC, RA, 8>::prefetch_offset(g.lda, p.row0, g.M, wave & 3, lane)
-                   : DmaOperand<BKC, RB, 8>::prefetch_offset(g.ldb, p.col0, g.N, wave & 3, lane);
-  };
-  auto prefetch = [&](int t) {
-    const int tp = t + PFD;
-    const bool own = tp < nfull;
-    const int kp = own ? tp : tp - nfull;
-    const int want = own ? pf_turn : pf_turn_next;
-    const bool turn = kp < nfull && ((kp & pf_mask) == want) && pf_ok;
-    const char* src = turn ? pf_base + int64_t(kp) * pf_step : pf_base;
-    const uint32_t voff = turn ? (own ? pf_voff : pf_voff_next) : 0u;
-    asm volatile("global_load_dword %0, %1, %2" : "+v"(pf_sink) : "v"(voff), "s"(src) : "memory");
-  };
-
-  // this wavefront's DMA offsets
-  uint32_t offa[NAI], offb[NBI];
-  auto setup_tile = [&] {
+  // this wavefront's DMA offsets in the output tile at p
+  uint32_t offl[NL], offs[NS];
+  auto set_long = [&](const TilePos& p) {
 #pragma unroll
-    for (int i = 0; i < NAI; ++i) {
+    for (int i = 0; i < NL; ++i) {
       int line, chunk;
-      slot_src<AKC, RA>((wave * NAI + i) * 64 + lane, line, chunk);
-      offa[i] = dma_offset<AKC>(g.lda, row0, g.M, line, chunk);
+      slot_src<LKC, RL>((wave * NL + i) * 64 + lane, line, chunk);
+      offl[i] = dma_offset<LKC>(ldl, LB ? p.tile_n : p.tile_m, liml, line, chunk);
     }
+  };
+  auto set_short = [&](const TilePos& p) {
 #pragma unroll
-    for (int i = 0; i < NBI; ++i) {
+    for (int i = 0; i < NS; ++i) {
       int line, chunk;
-      slot_src<BKC, RB>((wave * NBI + i) * 64 + lane, line, chunk);
-      offb[i] = dma_offset<BKC>(g.ldb, col0, g.N, line, chunk);
+      slot_src<SKC, RS>((wave * NS + i) * 64 + lane, line, chunk);
+      offs[i] = dma_offset<SKC>(lds, LB ? p.tile_m : p.tile_n, lims, line, chunk);
     }
-    pf_params(pos, pf_turn, pf_voff);
   };
-  // Byte offset of this wavefront's first DMA destination inside a slot.  It passes through an empty assembly
-  // statement at every use, so that the compiler adds it to the slot's address then and there (one scalar add per
-  // instruction) instead of keeping forty precomputed LDS addresses alive across the loop.
-  uint32_t dsta = uint32_t(wave) * NAI * 1024u, dstb = uint32_t(wave) * NBI * 1024u;
-  auto dma_a = [&](int kt, uint16_t* sl) {
-    asm volatile("" : "+s"(dsta));
+  // ... in its last K tile, and where there is nothing more to ask for
+  const bool cut = nk * DK > K;
+  auto cut_long = [&](bool all) {
+    if (!all && (!LKC || !cut)) return;
 #pragma unroll
-    for (int i = 0; i < NAI; ++i) dma_issue(ra, reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(sl) + dsta) + i * 512, offa[i], uint32_t(kt) * astep_b);
-  };
-  auto dma_b = [&](int kt, uint16_t* sl) {
-    asm volatile("" : "+s"(dstb));
-#pragma unroll
-    for (int i = 0; i < NBI; ++i) dma_issue(rb, reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(sl) + dstb) + i * 512, offb[i], uint32_t(kt) * bstep_b);
-  };
-  // first DMA instructions of an output tile: K tile 0 whole and A of K tile 1
-  auto first_dma = [&] {
-    if (nk > 0) {
-      dma_a(0, r0);
-      dma_b(0, r1);
-      dma_a(min(1, nk - 1), r2);
+    for (int i = 0; i < NL; ++i) {
+      int line, chunk;
+      slot_src<LKC, RL>((wave * NL + i) * 64 + lane, line, chunk);
+      if (all || deep_cut<LKC>(nk, chunk, K)) offl[i] = kNowhere;
     }
+  };
+  auto cut_short = [&](bool all) {
+    if (!all && (!SKC || !cut)) return;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      int line, chunk;
+      slot_src<SKC, RS>((wave * NS + i) * 64 + lane, line, chunk);
+      if (all || deep_cut<SKC>(nk, chunk, K)) offs[i] = kNowhere;
+    }
+  };
+  // DMA instruction i of K tile kt into the slot at LDS address sl
+  auto dma_long = [&](int i, int kt, uint32_t sl) {
+    dma_issue_at(rl, sl + uint32_t(wave * NL + i) * 1024u, offl[i], uint32_t(kt) * stepl);
+  };
+  auto dma_short = [&](int i, int kt, uint32_t sl) {
+    dma_issue_at(rs, sl + uint32_t(wave * NS + i) * 1024u, offs[i], uint32_t(kt) * steps);
   };
 
   bf16x8 fa[MI], fb[NI];
@@ -204,132 +204,122 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
     static_for(std::make_integer_sequence<int, MI>{}, [&](auto i) { fa[decltype(i)::value] = frag_read_asm<AKC, RA, MI, decltype(i)::value, ks>(fra, sa_addr); });
     static_for(std::make_integer_sequence<int, NI>{}, [&](auto j) { fb[decltype(j)::value] = frag_read_asm<BKC, RB, NI, decltype(j)::value, ks>(frb, sb_addr); });
   };
-  auto compute_slot = [&] {
+  // the matrix instructions of a K-step with `ND` DMA instructions evenly among them
+  auto compute_slot = [&](auto nd, auto&& dma) {
+    constexpr int ND = decltype(nd)::value, NM = MI * NI;
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(1);
-    // operands swapped so that each lane ends up with 4 consecutive columns of one row
+    static_for(std::make_integer_sequence<int, ND + 1>{}, [&](auto dc) {
+      constexpr int d = decltype(dc)::value;
+      // operands swapped so that each lane ends up with 4 consecutive columns of one row
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+      for (int n = d * NM / (ND + 1); n < (d + 1) * NM / (ND + 1); ++n)
+        acc[n / NI][n % NI] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[n % NI], fa[n / NI], acc[n / NI][n % NI], 0, 0, 0);
+      if constexpr (d < ND) {
+        __builtin_amdgcn_sched_barrier(0);
+        dma(d);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    });
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto pp_tile = [&](auto p, int t) {
-    constexpr int P = decltype(p)::value;
-    uint16_t* const sa = slot(Int<(2 * P) % 5>{});
-    uint16_t* const sb = slot(Int<(2 * P + 1) % 5>{});
-    uint16_t* const nss = slot(Int<(2 * P + 3) % 5>{});
-    uint16_t* const fsl = slot(Int<(2 * P + 4) % 5>{});
-    const uint32_t sa_addr = lds_addr(sa), sb_addr = lds_addr(sb);
-    const int t1 = min(t + 1, nk - 1), t2 = min(t + 2, nk - 1);
+  // LDS addresses of the slots: long t, short t, long t+1, short t+1, long t+2
+  const uint32_t ring0 = lds_addr(ring);
+  uint32_t s0 = ring0, s1 = s0 + SLOT * 2, s2 = s1 + SLOT * 2, s3 = s2 + SLOT * 2, s4 = s3 + SLOT * 2;
+  bool more = false;
+  TilePos npos = pos;
+  auto pp_tile = [&](auto latec, int t) {
+    constexpr bool LATE = decltype(latec)::value;
+    const int t2 = t + 2 < nk ? t + 2 : t + 2 - nk;
+    if (t + 3 >= nk) {
+      // (before the reads: nothing but the wait stands between a read and the use of its registers)  What this K tile asks for is the output tile's last K tile, or past it
+      if (t + 3 == nk) cut_long(false);
+      if (t + 2 == nk) more ? set_long(npos) : cut_long(true);
+      if (t + (LATE ? 3 : 2) == nk) cut_short(false);
+      if (t + (LATE ? 2 : 1) == nk) more ? set_short(npos) : cut_short(true);
+    }
     // M0
     __builtin_amdgcn_sched_barrier(0);
-    read_frags(Int<0>{}, sa_addr, sb_addr);
-    __builtin_amdgcn_sched_barrier(0);
-    dma_b(t1, nss);
+    read_frags(Int<0>{}, LB ? s1 : s0, LB ? s0 : s1);
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(lgkm0_imm());
     __builtin_amdgcn_s_barrier();
-    compute_slot();  // C0
+    // C0
+    if constexpr (LATE) compute_slot(Int<NL>{}, [&](int i) { dma_long(i, t2, s4); });
+    else compute_slot(Int<NS>{}, [&](int i) { dma_short(i, t + 1 < nk ? t + 1 : 0, s3); });
     __builtin_amdgcn_s_barrier();
     // M1
     __builtin_amdgcn_sched_barrier(0);
-    read_frags(Int<1>{}, sa_addr, sb_addr);
+    read_frags(Int<1>{}, LB ? s1 : s0, LB ? s0 : s1);
     __builtin_amdgcn_sched_barrier(0);
-    dma_a(t2, fsl);
-    prefetch(t);
-    __builtin_amdgcn_sched_barrier(0);
-    // late group: this is the tile's fourth slot; its share of B of tile t+1 (started in M0) has landed, the
-    // NAI + 1 newer instructions may fly on
-    if (late) __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(NAI + 1));
+    // late group: the tile's fourth slot
+    if constexpr (LATE) __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(NL));
     else __builtin_amdgcn_s_waitcnt(lgkm0_imm());
     __builtin_amdgcn_s_barrier();
-    compute_slot();  // C1
+    // C1
+    if constexpr (LATE) compute_slot(Int<NS>{}, [&](int i) { dma_short(i, t2, s0); });
+    else compute_slot(Int<NL>{}, [&](int i) { dma_long(i, t2, s4); });
     // early group: its C1 is the tile's fourth slot
-    if (!late) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NAI + 1));
+    if constexpr (!LATE) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NL));
     __builtin_amdgcn_s_barrier();
+    const uint32_t u0 = s0, u1 = s1;
+    s0 = s2;
+    s1 = s3;
+    s2 = s4;
+    s3 = u0;
+    s4 = u1;
   };
 
-  // vector memory instructions a wavefront issues in the epilogue of an interior tile (see gemm_ring_kernel)
-  constexpr bool PAIRED = EPI == ntp::EPI_BF16 || EPI == ntp::EPI_GELU || EPI == ntp::EPI_DGELU;
-  constexpr int NPAIR = NI / 2, NODD = NI & 1;
-  constexpr int NEPI = EPI == ntp::EPI_BF16    ? MI * (NPAIR + NODD)
-                       : EPI == ntp::EPI_GELU  ? MI * 2 * (NPAIR + NODD)
-                       : EPI == ntp::EPI_DGELU ? MI * (3 * NPAIR + 2 * NODD)
-                       : EPI == ntp::EPI_F32   ? MI * NI
-                                               : MI * NI * 2;
-  bool stores_in_flight = false;
-  setup_tile();
-  first_dma();
+  // the first output tile's first DMA instructions: K tile 0 whole, long of K tile 1, and the late group's share of short of K tile 1
+  set_long(pos);
+  set_short(pos);
+  if (SPLIT && nk == 1) {
+    cut_long(false);
+    cut_short(false);
+  }
+#pragma unroll
+  for (int i = 0; i < NL; ++i) dma_long(i, 0, s0);
+#pragma unroll
+  for (int i = 0; i < NS; ++i) dma_short(i, 0, s1);
+  if (SPLIT && nk <= 2) {
+    cut_long(nk == 1);
+    if (late || nk == 1) cut_short(nk == 1);
+  }
+#pragma unroll
+  for (int i = 0; i < NL; ++i) dma_long(i, 1, s2);
+  if (late) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) dma_short(i, 1, s3);
+  }
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  __builtin_amdgcn_s_barrier();
+
+  constexpr bool PAIRED = !SPLIT && (EPI == ntp::EPI_BF16 || EPI == ntp::EPI_GELU || EPI == ntp::EPI_DGELU);
+  constexpr int NODD = NI & 1;
   while (true) {
     const int vnext = vblk + int(gridDim.x);
-    const bool more = vnext < nblk;
-    const Pos npos = more ? place(vnext) : pos;
-    if (more) pf_params(npos, pf_turn_next, pf_voff_next);
-    else pf_turn_next = -1;
+    more = !SPLIT && vnext < nblk;
+    if (more) npos = place(vnext);
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    if (nk > 0) {
-      // the first DMA instructions of this output tile have landed (the previous tile's NEPI epilogue
-      // instructions, issued after them, may stay in flight: the counter is in order)
-      if (stores_in_flight) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NEPI <= 63 ? NEPI : 63));
-      else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    // Every wavefront passes 4 nk + 1 barriers in the loop: the late group one before its first slot, the
+    // early group one after its last (nk is the same for the whole workgroup).
+    if (late) {
       __builtin_amdgcn_s_barrier();
-      // Every wavefront passes 4 nk + 1 barriers in the loop: the late group one before its first slot, the
-      // early group one after its last (nk is the same for the whole workgroup).
-      if (late) __builtin_amdgcn_s_barrier();
-      for (int t = 0; t < nk; t += 5) {
-        pp_tile(Int<0>{}, t);
-        if (t + 1 < nk) pp_tile(Int<1>{}, t + 1);
-        if (t + 2 < nk) pp_tile(Int<2>{}, t + 2);
-        if (t + 3 < nk) pp_tile(Int<3>{}, t + 3);
-        if (t + 4 < nk) pp_tile(Int<4>{}, t + 4);
-      }
-      if (!late) __builtin_amdgcn_s_barrier();
+      for (int t = 0; t < nk; ++t) pp_tile(std::true_type{}, t);
+    } else {
+      for (int t = 0; t < nk; ++t) pp_tile(std::false_type{}, t);
+      __builtin_amdgcn_s_barrier();
     }
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the clamped DMA instructions of the last tiles
-    // K tail (K % 64 != 0) through registers with element masks, not overlapped
-    if (!ring_tail && nfull * DK < K) {
-      __syncthreads();
-      {
-        DmaOperand<AKC, RA, 8> ta;
-        ta.init(g.lda, row0, g.M, wave, lane);
-        ta.tail(g.A, astep, nfull, K, r0, wave, lane);
-        DmaOperand<BKC, RB, 8> tb;
-        tb.init(g.ldb, col0, g.N, wave, lane);
-        tb.tail(g.B, bstep, nfull, K, r1, wave, lane);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i) fa[i] = fra.read(r0, i, ks);
-#pragma unroll
-        for (int j = 0; j < NI; ++j) fb[j] = frb.read(r1, j, ks);
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-          for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
-      }
-    }
-    const int erow0 = row0, ecol0 = col0;
+    const int erow0 = pos.tile_m, ecol0 = pos.tile_n;
     vblk = vnext;
-    stores_in_flight = NEPI <= 63 && g.all_rows != 0 && erow0 + BM_ <= g.M && ecol0 + BN_ <= g.N;
-    if (more) {
-      __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(0));
-      __builtin_amdgcn_s_barrier();
-      pos = npos;
-      row0 = pos.row0;
-      col0 = pos.col0;
-      setup_tile();
-      first_dma();
-    }
-    __builtin_amdgcn_sched_barrier(0);  // the epilogue's memory instructions stay behind those DMA instructions
+    pos = npos;
+    __builtin_amdgcn_sched_barrier(0);  // the epilogue's memory instructions stay behind the loop's
     if constexpr (EPI == ntp::EPI_F32_ACCUM && NI <= 4) {  // (wider block rows would spill)
-      if (g.n_segs == 1) {
+      if (g.n_segs == 1 && (!SPLIT || g.k_splits == 1)) {
         accumulate_blocks<MI, NI>(g, erow0 + wm * TM + (lane & 15), ecol0 + wn * TN + (lane >> 4) * 4, acc);
         if (!more) break;
         continue;
@@ -349,11 +339,19 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
         for (int j = 0; j + 1 < NI; j += 2) store8_pair<EPI>(g, m, ecol0 + wn * TN + j * 16, lane >> 4, acc[i][j], acc[i][j + 1], aux[i & 1][j], aux[i & 1][j + 1]);
       }
 #pragma unroll
-      for (int j = PAIRED ? NI - NODD : 0; j < NI; ++j) store4<EPI>(g, m, ecol0 + wn * TN + j * 16 + (lane >> 4) * 4, acc[i][j], aux[i & 1][j]);
+      for (int j = PAIRED ? NI - NODD : 0; j < NI; ++j) {
+        const int n0 = ecol0 + wn * TN + j * 16 + (lane >> 4) * 4;
+        if (SPLIT && g.k_splits > 1) {
+          if (m < g.M && n0 < g.n_store)
+            *reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + int64_t(split) * g.split_stride + int64_t(m) * g.ldc + n0) = acc[i][j];
+        } else {
+          store4<EPI>(g, m, n0, acc[i][j], aux[i & 1][j]);
+        }
+      }
     }
     if (!more) break;
   }
-  asm volatile("" : "+v"(pf_sink));  // the prefetch register stays reserved up to here
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the last DMA instructions write LDS that this workgroup still owns
 }
 
 }  // namespace ntp_gemm

@@ -158,17 +158,10 @@ struct FragAddr {
 template <int I>
 using Int = std::integral_constant<int, I>;
 
-// SPLIT: the non-persistent form, one workgroup per unit of work.  The K axis is cut into g.k_splits
-// chunks of g.k_chunk (a multiple of the K tile; the last chunk takes what is left).  The grid holds
-// k_splits groups of round_up(tiles, 8) workgroups; group s computes every output tile over chunk s.
-// With several chunks the fp32 partial sums go to slice s of a workspace (g.C + s * g.split_stride
-// floats, rows of g.ldc); with one chunk the tile gets its normal epilogue.  Without the cross-tile state
-// of the persistent loop this form needs about 30 registers less.
 // (Two wavefronts on a SIMD, also with four of them in a workgroup: left free, the compiler gives accumulating weight gradients on the 128 x 128 tile 272
 // registers, so that a compute unit holds one workgroup instead of two: 3511 x 6144 over 4096 324-346 -> 247-258 us.)
-template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, bool SPLIT = false>
+template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN>
 __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_ring_kernel(const GemmArgs g) {
-  static_assert(!SPLIT || EPI == ntp::EPI_F32 || EPI == ntp::EPI_F32_ACCUM, "partial sums are stored as fp32");
   constexpr int NW = WGM * WGN;
   constexpr int TM = BM_ / WGM, TN = BN_ / WGN;  // wavefront tile
   constexpr int MI = TM / 16, NI = TN / 16;      // 16 x 16 accumulator blocks
@@ -216,18 +209,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_ring_kernel(const Gemm
     return TilePos{t.tile_m, t.tile_n, t.tile_m * BM_, t.tile_n * BN_};
   };
   int vblk = blockIdx.x;
-  int split = 0;
-  if constexpr (SPLIT) {
-    const int per_split = (nblk + 7) & ~7;  // keeps (workgroup index & 7) == (tile index & 7)
-    split = blockIdx.x / per_split;
-    vblk = blockIdx.x - split * per_split;
-    if (vblk >= nblk) return;  // padding workgroup (the whole workgroup leaves, before any barrier)
-  }
-  // this workgroup's share of the K axis: everything below addresses the operands from opA / opB
-  const int64_t k_first = SPLIT ? int64_t(split) * g.k_chunk : 0;
-  const int K = SPLIT ? min(g.k_chunk, g.K - int(k_first)) : g.K;
-  const uint16_t* const opA = g.A + (AKC ? k_first : k_first * g.lda);
-  const uint16_t* const opB = g.B + (BKC ? k_first : k_first * g.ldb);
+  const int K = g.K;
   TilePos pos = place(vblk);
   int row0 = pos.row0, col0 = pos.col0;
 
@@ -236,13 +218,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_ring_kernel(const Gemm
   OpB b;
   const int64_t astep = AKC ? DK : DK * g.lda, bstep = BKC ? DK : DK * g.ldb;  // elements per K tile
   // Buffer views of the operands for the DMA, each ending where the operand ends (the host checks that an
-  // operand spans < 4 GiB and passes the bytes from g.A / g.B on; a K chunk's view starts later and is that much
-  // shorter).  The range check of a buffer load covers vector + scalar offset, and what lies past the extent
+  // operand spans < 4 GiB and passes the bytes from g.A / g.B on).  The range check of a buffer load covers vector + scalar offset, and what lies past the extent
   // reads as zeros: no offset this kernel can form reaches memory outside the operands.
-  constexpr bool RT = AKC && !BKC && !SPLIT;
-  const uint32_t a_shift = uint32_t((AKC ? k_first : k_first * g.lda) * 2), b_shift = uint32_t((BKC ? k_first : k_first * g.ldb) * 2);
-  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(opA), 0, int(g.a_extent - a_shift), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(opB), 0, int(g.b_extent - b_shift), 0x00020000);
+  constexpr bool RT = AKC && !BKC;
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(g.A), 0, int(g.a_extent), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(g.B), 0, int(g.b_extent), 0x00020000);
   const uint32_t astep_b = uint32_t(astep) * 2, bstep_b = uint32_t(bstep) * 2;
   FragAddr<AKC, RA, MI> fra;
   FragAddr<BKC, RB, NI> frb;
@@ -270,7 +250,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_ring_kernel(const Gemm
   const bool pf_is_a = wave < 4;
   const int pf_mask = pf_is_a ? 3 : 7;
   const bool pf_ok = pf_is_a ? (AKC || g.M >= 2) : (BKC || g.N >= 2);
-  const char* const pf_base = reinterpret_cast<const char*>(pf_is_a ? opA : opB);
+  const char* const pf_base = reinterpret_cast<const char*>(pf_is_a ? g.A : g.B);
   const int64_t pf_step = (pf_is_a ? astep : bstep) * 2;  // bytes per K tile
   int pf_turn = 0, pf_turn_next = -1;  // -1: there is no next output tile
   uint32_t pf_voff = 0, pf_voff_next = 0;
@@ -416,7 +396,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_ring_kernel(const Gemm
   };
   // vector memory instructions a wavefront issues in the epilogue of an interior tile
   // (bf16 outputs go out two blocks at a time, see store8_pair; an odd last block goes alone)
-  constexpr bool PAIRED = !SPLIT && (EPI == ntp::EPI_BF16 || EPI == ntp::EPI_GELU || EPI == ntp::EPI_DGELU);
+  constexpr bool PAIRED = EPI == ntp::EPI_BF16 || EPI == ntp::EPI_GELU || EPI == ntp::EPI_DGELU;
   constexpr int NPAIR = NI / 2, NODD = NI & 1;
   constexpr int NEPI = EPI == ntp::EPI_BF16    ? MI * (NPAIR + NODD)
                        : EPI == ntp::EPI_GELU  ? MI * 2 * (NPAIR + NODD)
@@ -427,7 +407,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_ring_kernel(const Gemm
   first_dma();
   while (true) {
     const int vnext = vblk + int(gridDim.x);
-    const bool more = !SPLIT && vnext < nblk;
+    const bool more = vnext < nblk;
     const TilePos npos = more ? place(vnext) : pos;
     if (more) pf_params(npos, pf_turn_next, pf_voff_next);
     else pf_turn_next = -1;
@@ -457,8 +437,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_ring_kernel(const Gemm
     // K tail (K % 64 != 0) through registers with element masks, not overlapped
     if (!ring_tail && nfull * DK < K) {
       __syncthreads();
-      a.tail(opA, astep, nfull, K, r0, wave, lane);
-      b.tail(opB, bstep, nfull, K, r1, wave, lane);
+      a.tail(g.A, astep, nfull, K, r0, wave, lane);
+      b.tail(g.B, bstep, nfull, K, r1, wave, lane);
       __syncthreads();
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
@@ -507,19 +487,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_ring_kernel(const Gemm
         }
       }
 #pragma unroll
-      for (int j = PAIRED ? NI - NODD : 0; j < NI; ++j) {
-        const int n0 = ecol0 + wn * TN + j * 16 + (lane >> 4) * 4;
-        if constexpr (SPLIT) {
-          if (g.k_splits > 1) {
-            if (m < g.M && n0 < g.n_store)
-              *reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + int64_t(split) * g.split_stride + int64_t(m) * g.ldc + n0) = acc[i][j];
-          } else {
-            store4<EPI>(g, m, n0, acc[i][j]);
-          }
-        } else {
-          store4<EPI>(g, m, n0, acc[i][j]);
-        }
-      }
+      for (int j = PAIRED ? NI - NODD : 0; j < NI; ++j) store4<EPI>(g, m, ecol0 + wn * TN + j * 16 + (lane >> 4) * 4, acc[i][j]);
     }
     if (!more) break;
   }

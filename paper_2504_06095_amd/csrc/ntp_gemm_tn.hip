@@ -6,14 +6,14 @@ namespace ntp_gemm {
 
 NTP_RING_INSTANTIATE_BELOW_256(false, false, ntp::EPI_F32)
 NTP_RING_INSTANTIATE_BELOW_256(false, false, ntp::EPI_F32_ACCUM)
-NTP_RING_INSTANTIATE_SPLIT(false, false)
+NTP_INSTANTIATE_SPLIT(false, false)
 
-template __global__ void gemm_ring_kernel<false, false, ntp::EPI_F32_ACCUM, 256, 256, 2, 4, true>(const GemmArgs);
+template __global__ void gemm_pp_kernel<false, false, ntp::EPI_F32_ACCUM, 256, 256, 2, 4, true>(const GemmArgs);
 
-int launch_ring_split_tn(GemmArgs g, int epilogue, int tile, hipStream_t s) {
-  if (epilogue == ntp::EPI_F32) return launch_ring_split_tile<false, false>(g, tile, s);
+int launch_split_tn(GemmArgs g, int epilogue, int tile, hipStream_t s) {
+  if (epilogue == ntp::EPI_F32) return launch_split_tile<false, false>(g, tile, s);
   if (epilogue == ntp::EPI_F32_ACCUM && tile == 0 && g.k_splits == 1)
-    return launch_ring_split_one<false, false, 256, 256, 2, 4, ntp::EPI_F32_ACCUM>(g, s);
+    return launch_split_one<false, false, 256, 256, 2, 4, ntp::EPI_F32_ACCUM>(g, s);
   return NTP_ERR_UNSUPPORTED;
 }
 

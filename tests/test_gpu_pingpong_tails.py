@@ -1,0 +1,49 @@
+"""Ragged K in the ping-pong GEMM kernel, whose ring runs on from one output tile into the next: K tails as a K tile of their own with several output tiles
+per workgroup, and K chunks of one and two K tiles in its non-persistent form, for tile shapes whose long operand is A or B.  On a real MI355X."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2504_06095_amd import binding as K
+from tests.helpers import TOL, MlpCase, rel_err
+from tests.test_gpu_split_k import workspace  # noqa: F401  (poisoned workspace, kernel names recorded)
+
+pytestmark = pytest.mark.gpu
+TILES = ["256x256", "224x256", "256x192", "192x256", "128x256"]
+
+
+def _check(case, pad_to, tag):
+    print(f"[gpu-case] {tag}", file=sys.stderr, flush=True)
+    got, _ = case.run_gpu(pad_to=pad_to)
+    want = case.oracle()
+    for k in ("P", "Y", "Z", "dP", "dX", "dA_t", "dB"):
+        assert np.isfinite(got[k]).all(), f"{tag}: {k} not finite"
+        assert rel_err(got[k], want[k]) <= TOL, f"{tag}: {k} {rel_err(got[k], want[k]):.3e}"
+
+
+@pytest.mark.parametrize("k", [131, 200, 321])  # 3, 4 and 6 K tiles: as short as the persistent form takes, one more, and past the ring's length
+@pytest.mark.parametrize("tile", TILES)
+def test_k_tail_with_many_output_tiles_per_workgroup(opts, tile, k):
+    opts(K.NTP_OPT_GEMM_SCHEDULE, 2)
+    opts(K.NTP_OPT_GEMM_TILE, tile)
+    opts(K.NTP_OPT_GEMM_WORKGROUPS, 8)
+    for pad_to in (8, 64):  # K = n_r, whose rows end right behind it or at the next K tile
+        _check(MlpCase(1300, 1400, k, 1, 0, tag=f"ppt.n.{k}"), pad_to, f"{tile}, K = n_r = {k}, rows padded to {pad_to}")
+    h = (k + 7) // 8 * 8
+    _check(MlpCase(1300, h, 1403, 1, 0, tag=f"ppt.h.{k}"), 8, f"{tile}, K = H = {h}")
+    _check(MlpCase(k, 1400, 1403, 1, 0, tag=f"ppt.m.{k}"), 8, f"{tile}, K = tokens = {k}")
+
+
+@pytest.mark.parametrize("k,splits", [(488, 8), (987, 8), (1272, 7)])  # chunks of 1, 2 and 3 K tiles, the last one ragged
+@pytest.mark.parametrize("tile", ["256x256", "192x256", "256x128"])
+def test_short_ragged_k_chunks(workspace, opts, tile, k, splits):  # noqa: F811
+    import paper_2504_06095_amd as N
+    opts(K.NTP_OPT_GEMM_TILE, tile)
+    opts(K.NTP_OPT_GEMM_SPLIT, splits)
+    h = (k + 7) // 8 * 8
+    for case, tag in ((MlpCase(700, 704, k, 1, 0, tag=f"pps.n.{k}"), "n_r"), (MlpCase(700, h, 705, 1, 0, tag=f"pps.h.{k}"), "H"),
+                      (MlpCase(k, 704, 705, 1, 0, tag=f"pps.m.{k}"), "tokens")):
+        N.ntp_kernel_timing_read()
+        _check(case, 8, f"{tile}, {splits} chunks of K = {tag} = {k}")
+        assert any(r["name"].endswith(f"{tile}k{splits}") for r in N.ntp_kernel_timing_read()), tag
