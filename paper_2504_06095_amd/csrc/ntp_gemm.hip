@@ -62,14 +62,15 @@ constexpr double kLoneSmallTileRate = 0.43;
 struct CostModel {
   const double (*rate)[kNumTileShapes];
   double reduce_bytes_per_cycle, reduce_fixed_cycles, cut_margin;
+  bool follows_deep;  // a cut is weighed against the deep-pipelined kernel (choose_deep)
 };
-constexpr CostModel kCost = {kTileRate, 1500.0, 5000.0, 0.95};
+constexpr CostModel kCost = {kTileRate, 1500.0, 5000.0, 0.95, true};
 // The call with static scratch refuses shapes whose launches could use more room than there is, by the estimate that its limit came with: which shapes it
 // takes does not change with the rates.
 constexpr double kLimitRate[3][kNumTileShapes] = {{1.000, 0.957, 0.969, 0.917, 0.923, 0.761, 0.754, 0.65, 0.53},
                                                   {1.000, 0.929, 0.986, 0.908, 0.944, 0.770, 0.749, 0.65, 0.53},
                                                   {1.100, 0.984, 1.000, 0.956, 0.962, 0.797, 0.779, 0.65, 0.53}};
-constexpr CostModel kLimitCost = {kLimitRate, 2000.0, 6000.0, 0.85};
+constexpr CostModel kLimitCost = {kLimitRate, 2000.0, 6000.0, 0.85, false};
 
 // Pick the tile shape with the least estimated time: the busiest compute unit's number of
 // workgroups (they are dealt evenly; co-resident ones share its throughput) times tile area over rate.
@@ -131,6 +132,7 @@ struct SplitChoice {
 
 constexpr double kTileCycles = 2650.0;      // one 256 x 256 x 64 K tile on one compute unit at rate 1
 constexpr int kTileOverhead = 4;            // prologue and epilogue of an output tile, in K tiles
+constexpr double kCyclesPerUs = 1950.0;
 constexpr int kMaxSplits = 8, kMinSplitTiles = 8;
 
 // Workgroups of the busiest XCD's share of a launch with `splits` K chunks a tile: a tile and its chunks are on one XCD, so that 85 tiles in three
@@ -145,6 +147,11 @@ double tile_time(const CostModel& cm, int64_t M, int64_t N, int64_t ktiles, int 
   const double rate = ts.waves == 4 && tiles <= cus ? kLoneSmallTileRate : cm.rate[layout][i];
   const int64_t kt = (ktiles + splits - 1) / splits + kTileOverhead;
   return double(cu_load) * double(kt) * kTileCycles * (ts.bm * ts.bn / 65536.0) / rate;
+}
+
+// The same with the reduce launch.
+double cut_time(const CostModel& cm, int64_t M, int64_t N, int64_t ktiles, int layout, int i, int splits, int cus) {
+  return tile_time(cm, M, N, ktiles, layout, i, splits, cus) + cm.reduce_fixed_cycles + double(M) * double(N) * (4.0 * splits + 4.0) / cm.reduce_bytes_per_cycle;
 }
 
 // Least estimated time over (tile shape, splits); splits == 1 means: leave the GEMM as it is.
@@ -169,8 +176,7 @@ SplitChoice choose_split(const CostModel& cm, const ntp_handle* h, int64_t ws_by
       if (forced <= 1 && chunk_tiles < kMinSplitTiles) break;
       if ((sp - 1) * chunk_tiles * 64 >= K) continue;  // the last chunk would be empty
       if (int64_t(sp) * M * ldw * 4 > ws_bytes) break;
-      const double reduce = cm.reduce_fixed_cycles + double(M) * double(N) * (4.0 * sp + 4.0) / cm.reduce_bytes_per_cycle;
-      const double t = tile_time(cm, M, N, ktiles, layout, i, sp, cus) + reduce;
+      const double t = cut_time(cm, M, N, ktiles, layout, i, sp, cus);
       if (t < best_t) {
         best_t = t;
         best = SplitChoice{i, sp, int(chunk_tiles * 64), kNotDeep};
@@ -222,7 +228,7 @@ constexpr double kSmallPerUnit = 2.0;  // workgroups of that form per compute un
 //    1584 34 -> 31 us, 1376 x 4672 over 3440 56 -> 54 us;
 //  - up to two 128 x 128 tiles per compute unit and 25 K tiles (weight gradients: 32): 1984 x 2664 over K = 328 16 -> 13.5 us, 584 x 7304
 //    over 1400 28 -> 25 us, 2192 x 2304 over 1888 38 -> 35 us; at 54 K tiles 10 % slower.
-SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int layout, int64_t M, int64_t N, int64_t K, int64_t ldw, const SplitChoice& old, bool small_ok) {
+SplitChoice choose_deep(const CostModel& cm, const ntp_handle* h, int64_t ws_bytes, int layout, int64_t M, int64_t N, int64_t K, int64_t ldw, const SplitChoice& old, bool small_ok) {
   const TileShape& ts = kTileShapes[old.tile];
   const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), wide = ((M + 127) / 128) * ((N + 255) / 256), ktiles = (K + 63) / 64;
   const int cus = h->compute_units;
@@ -233,7 +239,10 @@ SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int layout, int64
     if (wide <= cus && ktiles >= 20) return SplitChoice{kDeepWideTile, 1, int(ktiles * 64), kDeepWide};
     return tiles <= 2 * cus && ktiles <= (layout == 2 ? 32 : 25) ? deep2 : old;
   }
-  if (old.splits > 1 ? tiles * 2 > cus : ts.bm != 128 || ts.bn != 128) return old;
+  // (above half as many tiles as units a cut that the rates found stays, unless one uncut piece a unit is clearly faster by this kernel's estimate: 397 x 4480 over K = 2584
+  // 22.7 us, 25.4 in three pieces of 128 x 256)
+  const bool cut_stays = tiles * 2 > cus && !(cm.follows_deep && 1.15 * (0.47 * double(ktiles) + 3.5) * kCyclesPerUs < cut_time(cm, M, N, ktiles, layout, old.tile, old.splits, cus));
+  if (old.splits > 1 ? cut_stays : ts.bm != 128 || ts.bn != 128) return old;
   SplitChoice best{kDeepTile, 1, int(ktiles * 64), kDeep5};
   double best_t = 0.47 * double(ktiles);
   for (int sp = 2; sp <= kMaxDeepSplits && xcd_load(tiles, sp) * 8 <= cus; ++sp) {
@@ -277,7 +286,7 @@ SplitChoice plan_gemm(const CostModel& cm, const ntp_handle* h, int64_t ws_bytes
   const bool ring_asked = h->opt[NTP_OPT_GEMM_TILE] || h->opt[NTP_OPT_GEMM_SPLIT] || h->opt[NTP_OPT_GEMM_SCHEDULE] || h->opt[NTP_OPT_GEMM_WORKGROUPS] ||
                           (h->opt[NTP_OPT_GEMM_NO_RING_TAIL] && layout == 1 && g.K % 64 != 0);
   if (deep_ok && sc.tile >= 0 && !ring_asked)
-    sc = choose_deep(h, split_ok ? ws_bytes : 0, layout, g.M, g.n_store, g.K, ldw, sc, small_ok);
+    sc = choose_deep(cm, h, split_ok ? ws_bytes : 0, layout, g.M, g.n_store, g.K, ldw, sc, small_ok);
   return sc;
 }
 
