@@ -10,11 +10,12 @@
 //
 // Per K tile, in step: wait for this wavefront's share of it, one barrier (now it is complete, and every wavefront has read its
 // fragments of the previous one), start the DMA of the K tile STAGES - 1 ahead into the previous one's slot, read all
-// fragments, multiply.  Where at least three K tiles are in LDS (128 x 256: where A is K-contiguous) the two wavefronts of a SIMD alternate instead: in one slot
+// fragments, multiply.  With five K tiles in LDS and 20 K tiles or more the two wavefronts of a SIMD alternate instead: in one slot
 // one of them reads a whole K tile's fragments while the other one multiplies, with its DMA instructions among the matrix instructions, in the next slot the
-// other way round.  1200 x 3272 over K = 1712 26.4 -> 24.1 us, 1376 x 4672 over 3440 47.3 -> 42.4, 1024 x 2048 and 2048 x 1024 over 2048 (a shared launch)
-// 31.0 -> 29.5; weight gradients on 128 x 256 tiles are 2 % slower so and stay in step, and so do launches
-// of fewer than 20 K tiles (the half tile between the groups is not won back: 512 x 1024 x 586 backward 19.1 -> 19.4 us, 278 x 2232 over K = 3248 in four chunks 18.1 -> 19.2).  (DMA among the matrix instructions alone, in step: 0.92-1.06 of the time, no gain on the
+// other way round.  1024 x 2048 and 2048 x 1024 over 2048 (a shared launch) 31.0 -> 29.5 us, 2000 x 1024 with 3000 columns 39.8 -> 38.4.  Shorter launches stay in step (the half tile
+// between the groups is not won back: 512 x 1024 x 586 backward 19.1 -> 19.4 us, 278 x 2232 over K = 3248 in four chunks 18.1 -> 19.2), and so does the 128 x 256
+// form: with three K tiles the late group's instructions have one tile's time to land, which is enough where operands are in the last-level cache (1376 x 4672 over 3440 47.3 ->
+// 42.4) and too little where they come from HBM (a layer shard of 2821 tokens, hidden 2816, 559 -> 569 us).  (DMA among the matrix instructions alone, in step: 0.92-1.06 of the time, no gain on the
 // mean.  What is left, 0.45-0.5 us a K tile with all compute units at it, is the 32 KB that each of them asks its L2 for: 64 GB/s a unit.)
 // Past the last K tile the schedule asks for the last one again (clamped index, slots nobody reads), so that the
 // instruction counts that the waits rely on stay static.  LDS reads are inline assembly (see ntp_gemm_pp.h).
@@ -37,7 +38,7 @@ __device__ __forceinline__ void pin(bf16x8& v) {
 }
 
 // Whether the wavefronts may alternate in a form.
-constexpr bool can_alternate(bool akc, int bm, int stages) { return bm > 64 && stages >= (akc ? 3 : 4); }
+constexpr bool can_alternate(int bm, int stages) { return bm > 64 && stages >= 4; }
 
 // One (output tile, K chunk): workgroup `block` of problem g, with the ring in `ring`.
 template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, int STAGES, bool ALT>
@@ -138,7 +139,7 @@ __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, ui
       free_slot = slot;
       slot = slot + 1 == STAGES ? 0 : slot + 1;
     };
-    if constexpr (ALT && can_alternate(AKC, BM_, STAGES)) {
+    if constexpr (ALT && can_alternate(BM_, STAGES)) {
       // The two wavefronts of a SIMD (w and w + 4) alternate, half a K tile apart: one reads a K tile's fragments while the other one multiplies.
       auto read_tile = [&] {
         __builtin_amdgcn_sched_barrier(0);

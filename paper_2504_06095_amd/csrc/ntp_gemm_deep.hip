@@ -22,7 +22,7 @@ int launch_tile(GemmArgs g, hipStream_t s) {
   if (g.k_splits < 1 || g.k_chunk < 64 || g.k_chunk % 64 || int64_t(g.k_splits - 1) * g.k_chunk >= g.K || per_split * g.k_splits > 0x7fffffff)
     return NTP_ERR_INVALID_ARG;
   const dim3 grid(uint32_t(per_split * g.k_splits)), block(64 * WGM * WGN);
-  if (can_alternate(AKC, BM_, STAGES) && k_tiles(g) >= kAlternateFrom) hipLaunchKernelGGL((gemm_deep_kernel<AKC, BKC, EPI, BM_, BN_, WGM, WGN, STAGES, can_alternate(AKC, BM_, STAGES)>), grid, block, 0, s, g);
+  if (can_alternate(BM_, STAGES) && k_tiles(g) >= kAlternateFrom) hipLaunchKernelGGL((gemm_deep_kernel<AKC, BKC, EPI, BM_, BN_, WGM, WGN, STAGES, can_alternate(BM_, STAGES)>), grid, block, 0, s, g);
   else hipLaunchKernelGGL((gemm_deep_kernel<AKC, BKC, EPI, BM_, BN_, WGM, WGN, STAGES, false>), grid, block, 0, s, g);
   return hipGetLastError() == hipSuccess ? NTP_OK : NTP_ERR_LAUNCH;
 }
