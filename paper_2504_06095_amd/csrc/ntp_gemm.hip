@@ -57,31 +57,25 @@ constexpr double kTileRate[3][kNumTileShapes] = {{1.050, 1.008, 0.945, 0.924, 0.
                                                  {1.100, 0.977, 1.055, 1.023, 1.029, 0.705, 0.816, 0.60, 0.53},   // B K-strided
                                                  {1.080, 1.007, 1.107, 0.985, 1.000, 0.806, 0.883, 0.50, 0.53}};  // both K-strided
 constexpr double kLoneSmallTileRate = 0.43;
-
-// What an estimate is made from: the rates above, the reduce launch behind a cut K axis (see choose_split), and the share of the uncut time that a cut has to reach.
-struct CostModel {
-  const double (*rate)[kNumTileShapes];
-  double reduce_bytes_per_cycle, reduce_fixed_cycles, cut_margin;
-  bool follows_deep;  // a cut is weighed against the deep-pipelined kernel (choose_deep)
-};
-constexpr CostModel kCost = {kTileRate, 1500.0, 5000.0, 0.95, true};
-// The call with static scratch refuses shapes whose launches could use more room than there is, by the estimate that its limit came with: which shapes it
-// takes does not change with the rates.
-constexpr double kLimitRate[3][kNumTileShapes] = {{1.000, 0.957, 0.969, 0.917, 0.923, 0.761, 0.754, 0.65, 0.53},
-                                                  {1.000, 0.929, 0.986, 0.908, 0.944, 0.770, 0.749, 0.65, 0.53},
-                                                  {1.100, 0.984, 1.000, 0.956, 0.962, 0.797, 0.779, 0.65, 0.53}};
-constexpr CostModel kLimitCost = {kLimitRate, 2000.0, 6000.0, 0.85, false};
+// The rates that decide what a GEMM is before it gets its tile: whether its K axis is cut and into how many chunks, and whether the deep-pipelined kernel takes it.
+// They and the constants of choose_split were measured with the ring schedule and stay: the chunks fix the order of a product's fp32 sums, what
+// ntp_workspace_bytes reports and which shapes the call with static scratch takes.  The rates above in their place, with a reduce refitted to them, gave 36 of
+// 20000 random products other chunks (4096 x 640 over K = 8192: five instead of three, 60.0 us instead of 63.6 with 52 MB of workspace instead of 31) and cut
+// products that run whole on 128 x 256 tiles without weighing that kernel.
+constexpr double kPlanRate[3][kNumTileShapes] = {{1.000, 0.957, 0.969, 0.917, 0.923, 0.761, 0.754, 0.65, 0.53},
+                                                 {1.000, 0.929, 0.986, 0.908, 0.944, 0.770, 0.749, 0.65, 0.53},
+                                                 {1.100, 0.984, 1.000, 0.956, 0.962, 0.797, 0.779, 0.65, 0.53}};
 
 // Pick the tile shape with the least estimated time: the busiest compute unit's number of
 // workgroups (they are dealt evenly; co-resident ones share its throughput) times tile area over rate.
-int choose_tile(const CostModel& cm, int64_t M, int64_t N, int layout, int cus) {
+int choose_tile(const double (&rates)[3][kNumTileShapes], int64_t M, int64_t N, int layout, int cus) {
   int best = 0;
   double best_t = 1e300;
   for (int i = 0; i < kNumTileShapes; ++i) {
     const TileShape& ts = kTileShapes[i];
     const int64_t tiles = ((M + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn);
     const int64_t cu_load = (tiles + cus - 1) / cus;
-    const double rate = ts.waves == 4 && tiles <= cus ? kLoneSmallTileRate : cm.rate[layout][i];
+    const double rate = ts.waves == 4 && tiles <= cus ? kLoneSmallTileRate : rates[layout][i];
     const double t = double(cu_load) * ts.bm * ts.bn / rate;
     if (t < best_t) {
       best_t = t;
@@ -99,7 +93,7 @@ void variant_name(int v, char* out, size_t n) {
 
 // Variant used for a shape: -1 = generic kernel, else an index into kTileShapes.  The handle's
 // NTP_OPT_GEMM_TILE overrides the choice (1: generic, 2 + i: tile shape i).
-int choose_variant(const CostModel& cm, const ntp_handle* h, const GemmArgs& g, bool ring_ok, int layout) {
+int choose_variant(const ntp_handle* h, const GemmArgs& g, bool ring_ok, int layout) {
   if (const int64_t f = h->opt[NTP_OPT_GEMM_TILE]) {
     if (!ring_ok || f == 1) return -1;
     if (f - 2 < kNumTileShapes) return int(f - 2);
@@ -108,7 +102,7 @@ int choose_variant(const CostModel& cm, const ntp_handle* h, const GemmArgs& g, 
   // measured faster (512 x 586 x 1024: 15 us against 31 us per GEMM)
   if (int64_t(g.M) * g.N < 128 * 128 * 2 || g.K < 128) return -1;
   if (!ring_ok) return -1;
-  return choose_tile(cm, g.M, g.n_store, layout, h->compute_units);
+  return choose_tile(kPlanRate, g.M, g.n_store, layout, h->compute_units);
 }
 
 // (layout, epilogue) pairs the shard layers use have ring instantiations; anything else runs on
@@ -132,7 +126,7 @@ struct SplitChoice {
 
 constexpr double kTileCycles = 2650.0;      // one 256 x 256 x 64 K tile on one compute unit at rate 1
 constexpr int kTileOverhead = 4;            // prologue and epilogue of an output tile, in K tiles
-constexpr double kCyclesPerUs = 1950.0;
+constexpr double kReduceBytesPerCycle = 2000.0, kReduceFixedCycles = 6000.0;
 constexpr int kMaxSplits = 8, kMinSplitTiles = 8;
 
 // Workgroups of the busiest XCD's share of a launch with `splits` K chunks a tile: a tile and its chunks are on one XCD, so that 85 tiles in three
@@ -140,23 +134,18 @@ constexpr int kMaxSplits = 8, kMinSplitTiles = 8;
 // 3992: 43 us; in two chunks 31).
 int64_t xcd_load(int64_t tiles, int64_t splits) { return (tiles + 7) / 8 * splits; }
 
-double tile_time(const CostModel& cm, int64_t M, int64_t N, int64_t ktiles, int layout, int i, int splits, int cus) {
+double tile_time(int64_t M, int64_t N, int64_t ktiles, int layout, int i, int splits, int cus) {
   const TileShape& ts = kTileShapes[i];
   const int64_t tiles = ((M + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn);
   const int64_t units = std::max(cus / 8, 1), cu_load = splits == 1 ? (tiles + cus - 1) / cus : (xcd_load(tiles, splits) + units - 1) / units;
-  const double rate = ts.waves == 4 && tiles <= cus ? kLoneSmallTileRate : cm.rate[layout][i];
+  const double rate = ts.waves == 4 && tiles <= cus ? kLoneSmallTileRate : kPlanRate[layout][i];
   const int64_t kt = (ktiles + splits - 1) / splits + kTileOverhead;
   return double(cu_load) * double(kt) * kTileCycles * (ts.bm * ts.bn / 65536.0) / rate;
 }
 
-// The same with the reduce launch.
-double cut_time(const CostModel& cm, int64_t M, int64_t N, int64_t ktiles, int layout, int i, int splits, int cus) {
-  return tile_time(cm, M, N, ktiles, layout, i, splits, cus) + cm.reduce_fixed_cycles + double(M) * double(N) * (4.0 * splits + 4.0) / cm.reduce_bytes_per_cycle;
-}
-
 // Least estimated time over (tile shape, splits); splits == 1 means: leave the GEMM as it is.
 // ws_bytes: room for the partial sums (0: never split).
-SplitChoice choose_split(const CostModel& cm, const ntp_handle* h, int64_t ws_bytes, int64_t M, int64_t N, int64_t K, int layout, int plain_tile,
+SplitChoice choose_split(const ntp_handle* h, int64_t ws_bytes, int64_t M, int64_t N, int64_t K, int layout, int plain_tile,
                          int64_t ldw) {
   SplitChoice best{plain_tile, 1, 0, kNotDeep};
   const int64_t ktiles = (K + 63) / 64;
@@ -165,7 +154,7 @@ SplitChoice choose_split(const CostModel& cm, const ntp_handle* h, int64_t ws_by
   const int64_t forced_tile = h->opt[NTP_OPT_GEMM_TILE];
   if (ws_bytes <= 0 || forced == 1) return best;
   // splitting has to beat the plain launch by a margin: the estimate is coarse
-  double best_t = plain_tile >= 0 ? cm.cut_margin * tile_time(cm, M, N, ktiles, layout, plain_tile, 1, cus) : 1e300;
+  double best_t = plain_tile >= 0 ? 0.85 * tile_time(M, N, ktiles, layout, plain_tile, 1, cus) : 1e300;
   if (forced > 1) best_t = 1e300;
   for (int i = 0; i < kNumTileShapes; ++i) {
     if (!kSplitTile[i]) continue;
@@ -176,7 +165,8 @@ SplitChoice choose_split(const CostModel& cm, const ntp_handle* h, int64_t ws_by
       if (forced <= 1 && chunk_tiles < kMinSplitTiles) break;
       if ((sp - 1) * chunk_tiles * 64 >= K) continue;  // the last chunk would be empty
       if (int64_t(sp) * M * ldw * 4 > ws_bytes) break;
-      const double t = cut_time(cm, M, N, ktiles, layout, i, sp, cus);
+      const double reduce = kReduceFixedCycles + double(M) * double(N) * (4.0 * sp + 4.0) / kReduceBytesPerCycle;
+      const double t = tile_time(M, N, ktiles, layout, i, sp, cus) + reduce;
       if (t < best_t) {
         best_t = t;
         best = SplitChoice{i, sp, int(chunk_tiles * 64), kNotDeep};
@@ -228,7 +218,7 @@ constexpr double kSmallPerUnit = 2.0;  // workgroups of that form per compute un
 //    1584 34 -> 31 us, 1376 x 4672 over 3440 56 -> 54 us;
 //  - up to two 128 x 128 tiles per compute unit and 25 K tiles (weight gradients: 32): 1984 x 2664 over K = 328 16 -> 13.5 us, 584 x 7304
 //    over 1400 28 -> 25 us, 2192 x 2304 over 1888 38 -> 35 us; at 54 K tiles 10 % slower.
-SplitChoice choose_deep(const CostModel& cm, const ntp_handle* h, int64_t ws_bytes, int layout, int64_t M, int64_t N, int64_t K, int64_t ldw, const SplitChoice& old, bool small_ok) {
+SplitChoice choose_deep(const ntp_handle* h, int64_t ws_bytes, int layout, int64_t M, int64_t N, int64_t K, int64_t ldw, const SplitChoice& old, bool small_ok) {
   const TileShape& ts = kTileShapes[old.tile];
   const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), wide = ((M + 127) / 128) * ((N + 255) / 256), ktiles = (K + 63) / 64;
   const int cus = h->compute_units;
@@ -239,10 +229,7 @@ SplitChoice choose_deep(const CostModel& cm, const ntp_handle* h, int64_t ws_byt
     if (wide <= cus && ktiles >= 20) return SplitChoice{kDeepWideTile, 1, int(ktiles * 64), kDeepWide};
     return tiles <= 2 * cus && ktiles <= (layout == 2 ? 32 : 25) ? deep2 : old;
   }
-  // (above half as many tiles as units a cut that the rates found stays, unless one uncut piece a unit is clearly faster by this kernel's estimate: 397 x 4480 over K = 2584
-  // 22.7 us, 25.4 in three pieces of 128 x 256)
-  const bool cut_stays = tiles * 2 > cus && !(cm.follows_deep && 1.15 * (0.47 * double(ktiles) + 3.5) * kCyclesPerUs < cut_time(cm, M, N, ktiles, layout, old.tile, old.splits, cus));
-  if (old.splits > 1 ? cut_stays : ts.bm != 128 || ts.bn != 128) return old;
+  if (old.splits > 1 ? tiles * 2 > cus : ts.bm != 128 || ts.bn != 128) return old;
   SplitChoice best{kDeepTile, 1, int(ktiles * 64), kDeep5};
   double best_t = 0.47 * double(ktiles);
   for (int sp = 2; sp <= kMaxDeepSplits && xcd_load(tiles, sp) * 8 <= cus; ++sp) {
@@ -278,15 +265,17 @@ SplitChoice choose_deep(const CostModel& cm, const ntp_handle* h, int64_t ws_byt
 }
 
 // Kernel variant (-1 generic, else a tile shape) and K chunks for a GEMM (g: M, N, K, n_store).
-SplitChoice plan_gemm(const CostModel& cm, const ntp_handle* h, int64_t ws_bytes, const GemmArgs& g, int layout, bool ring_ok, bool split_ok,
+SplitChoice plan_gemm(const ntp_handle* h, int64_t ws_bytes, const GemmArgs& g, int layout, bool ring_ok, bool split_ok,
                       int64_t ldw, bool deep_ok, bool small_ok = true) {
-  SplitChoice sc{choose_variant(cm, h, g, ring_ok, layout), 1, 0, kNotDeep};
-  if (split_ok && int64_t(g.M) * g.N >= 128 * 128 * 8) sc = choose_split(cm, h, ws_bytes, g.M, g.n_store, g.K, layout, sc.tile, ldw);
+  SplitChoice sc{choose_variant(h, g, ring_ok, layout), 1, 0, kNotDeep};
+  if (split_ok && int64_t(g.M) * g.N >= 128 * 128 * 8) sc = choose_split(h, ws_bytes, g.M, g.n_store, g.K, layout, sc.tile, ldw);
   // (options that ask for a ring tile, a cut, a schedule, a cap on the persistent grid or a K tail through registers mean the ring kernels)
   const bool ring_asked = h->opt[NTP_OPT_GEMM_TILE] || h->opt[NTP_OPT_GEMM_SPLIT] || h->opt[NTP_OPT_GEMM_SCHEDULE] || h->opt[NTP_OPT_GEMM_WORKGROUPS] ||
                           (h->opt[NTP_OPT_GEMM_NO_RING_TAIL] && layout == 1 && g.K % 64 != 0);
   if (deep_ok && sc.tile >= 0 && !ring_asked)
-    sc = choose_deep(cm, h, split_ok ? ws_bytes : 0, layout, g.M, g.n_store, g.K, ldw, sc, small_ok);
+    sc = choose_deep(h, split_ok ? ws_bytes : 0, layout, g.M, g.n_store, g.K, ldw, sc, small_ok);
+  // What stays whole on the persistent kernels takes the best tile by their own rates; the order of its sums is the same on every tile.
+  if (sc.tile >= 0 && sc.splits == 1 && !sc.deep && !h->opt[NTP_OPT_GEMM_TILE]) sc.tile = choose_tile(kTileRate, g.M, g.n_store, layout, h->compute_units);
   return sc;
 }
 
@@ -313,7 +302,7 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 namespace ntp {
 
-int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t N, int64_t n_store, int64_t K, bool deep, bool limit) {
+int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t N, int64_t n_store, int64_t K, bool deep) {
   if (M < 1 || N < 1 || K < 1 || M > 0x7fffff00 || N > 0x7fffff00 || K > 0x7fffff00) return 0;
   GemmArgs g{};
   g.M = int32_t(M);
@@ -322,8 +311,7 @@ int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t 
   g.n_store = int32_t(n_store);
   const int64_t ldw = (n_store + 15) / 16 * 16;
   // (what 128 x 128 tiles would be cut into counts where 64 x 64 tiles take their place uncut: those are for handles with a workspace)
-  const CostModel& cm = limit ? kLimitCost : kCost;
-  const SplitChoice sc = plan_gemm(cm, h, INT64_MAX / 2, g, layout, true, true, ldw, deep), wide = plan_gemm(cm, h, INT64_MAX / 2, g, layout, true, true, ldw, deep, false);
+  const SplitChoice sc = plan_gemm(h, INT64_MAX / 2, g, layout, true, true, ldw, deep), wide = plan_gemm(h, INT64_MAX / 2, g, layout, true, true, ldw, deep, false);
   const int splits = std::max(sc.splits, wide.splits);
   return splits > 1 ? int64_t(splits) * M * ldw * 4 : 0;
 }
@@ -458,7 +446,7 @@ int prepare(ntp_handle* h, const GemmDesc& d, Prepared* out) {
                        (d.b_kc ? b_rows * d.ldb * 2 < (int64_t(1) << 31) : k64 * d.ldb * 2 < (int64_t(1) << 32)) &&
                        (!d.a_kc || d.K % 8 == 0 || (d.a_k_pad_8 && !d.b_kc));
   const bool pp_ok = d.K % 64 == 0 || (tail_ok && !(layout == 1 && h->opt[NTP_OPT_GEMM_NO_RING_TAIL]));
-  SplitChoice sc = plan_gemm(kCost, h, ws_ptr ? ws_bytes : 0, g, layout, ring_ok, split_ok && pp_ok, ldw, deep_ok);
+  SplitChoice sc = plan_gemm(h, ws_ptr ? ws_bytes : 0, g, layout, ring_ok, split_ok && pp_ok, ldw, deep_ok);
   if (layout == 2 && !pp_ok && ring_ok && !sc.deep && sc.splits == 1 && sc.tile == 0) sc.tile = 2;  // (the 256 x 256 tile of this layout is a ping-pong kernel)
   *out = Prepared{g, sc, layout, ring_ok, pp_ok, false, to_segs && g.n_segs == 0, ws_ptr, ldw};
   return NTP_OK;
@@ -664,7 +652,7 @@ extern "C" int ntp_gemm_choice(const ntp_handle_t* h, int32_t layout, int64_t M,
   g.N = int32_t(N);
   g.K = int32_t(K);
   g.n_store = int32_t((N + 7) / 8 * 8);
-  const SplitChoice sc = plan_gemm(kCost, h, h->workspace ? h->workspace_bytes : 0, g, layout, true, true, (g.n_store + 15) / 16 * 16, true);
+  const SplitChoice sc = plan_gemm(h, h->workspace ? h->workspace_bytes : 0, g, layout, true, true, (g.n_store + 15) / 16 * 16, true);
   *out = ntp_gemm_choice_t{};
   out->k_splits = sc.splits;
   if (sc.tile < 0) {

@@ -116,8 +116,8 @@ int gemm_launch_group(ntp_handle* h, const GemmDesc* d, int n, void* stream);
 // workspace were unlimited (0: it would not split).  layout as for ntp_gemm_choice; n_store: columns stored.
 // The same for the three attention core kernels of a shape (checked like the calls check it).
 int attn_core_workspace_wish(const ntp_handle* h, const ntp_attn_core_shape_t* shape, int64_t* bytes);
-// deep: false for the choice without the deep-pipelined kernel; limit: by the estimate that the static scratch call's limit goes by.
-int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t N, int64_t n_store, int64_t K, bool deep = true, bool limit = false);
+// deep: false for the choice without the deep-pipelined kernel.
+int64_t gemm_workspace_wish(const ntp_handle* h, int layout, int64_t M, int64_t N, int64_t n_store, int64_t K, bool deep = true);
 
 }  // namespace ntp
 

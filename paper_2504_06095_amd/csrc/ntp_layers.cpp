@@ -190,8 +190,8 @@ extern "C" int ntp_attn_proj_shard_fwd_static(ntp_handle_t* h, const ntp_attn_sh
   // refused before it existed stays refused)
   int64_t wish = 0;
   for (const bool deep : {false, true}) {
-    if (QKV) wish = std::max(wish, ntp::gemm_workspace_wish(h, 0, s->M, s->w_qkv, s->w_qkv, s->H, deep, true));
-    if (Zpart) wish = std::max(wish, ntp::gemm_workspace_wish(h, 1, s->M, s->H, s->H, s->w_o, deep, true));
+    if (QKV) wish = std::max(wish, ntp::gemm_workspace_wish(h, 0, s->M, s->w_qkv, s->w_qkv, s->H, deep));
+    if (Zpart) wish = std::max(wish, ntp::gemm_workspace_wish(h, 1, s->M, s->H, s->H, s->w_o, deep));
   }
   if (wish > int64_t(NTP_STATIC_SCRATCH_BYTES)) return NTP_ERR_SCRATCH_TOO_SMALL;
   return attn_fwd(h, s, X, ldx, Wqkv, ldwqkv, QKV, ldqkv, C, ldc, Wo, ldwo, Zpart, ldz, h->static_scratch,
