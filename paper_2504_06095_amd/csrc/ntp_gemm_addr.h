@@ -75,12 +75,28 @@ NTP_HD uint32_t deep_view_shift(bool kc, int64_t k_first, int64_t ld) { return u
 NTP_HD int64_t deep_extent_bytes(bool kc, int64_t rows, int64_t K, int64_t ld) {
   return operand_extent_bytes(kc, rows, kc ? (K + 7) / 8 * 8 : K, ld, false);
 }
-// Offset past every view (views are below 2 GiB): where the loads of a K-contiguous operand's chunks at k >= K of the last K tile go.
+// Offset past every view of that kernel (its operands are below 2 GiB): where the loads of a K-contiguous operand's chunks at k >= K of the last K tile go.
 constexpr uint32_t kNowhere = 0x80000000u;
 // Whether chunk `chunk` of the last of nk K tiles of a K range of K elements starts at or past K.
 template <bool KC>
 NTP_HD bool deep_cut(int nk, int chunk, int K) {
   return KC && (nk - 1) * DK + chunk * 8 >= K;
+}
+
+// ---- the ping-pong kernel (ntp_gemm_pp.h): views, extents and K tails as above, operands up to 4 GiB, and a ring that runs on past an output tile ----
+// Offset at or past the end of every view: an operand is below 4 GiB and a whole number of 16-byte chunks (a multiple of 8 elements a row).  It goes with a scalar
+// offset of 0: no sum of the two overflows, and no scalar offset lies past the view that it is checked against.
+constexpr uint32_t kPastAll = 0xFFFFFFF0u;
+// K tile j of an output tile with nk of them: the scalar offset of its loads.  The last one of a ragged K (cut) has it in its vector offsets; past it come the
+// first K tiles of the next output tile (more), or nothing.
+NTP_HD uint32_t pp_scalar_offset(int j, int nk, bool cut, bool more, uint32_t step) {
+  if (j < nk) return cut && j == nk - 1 ? 0u : uint32_t(j) * step;
+  return more ? uint32_t(j - nk) * step : 0u;
+}
+// Vector offset of the chunk at slot position (line, chunk) in the last K tile of a ragged K, from its offset in K tile 0: past the view where it starts at or past K.
+template <bool KC>
+NTP_HD uint32_t pp_cut_offset(uint32_t off, uint32_t step, int nk, int line, int chunk, int K) {
+  return (nk - 1) * DK + (KC ? chunk * 8 : line) >= K ? kPastAll : off + uint32_t(nk - 1) * step;
 }
 
 // Virtual block v of nblk = tiles_m * tiles_n -> output tile.  Workgroups are dealt round-robin to the 8

@@ -25,12 +25,11 @@
 //   late group:  long t+2 in C0 of tile t (third slot), short t+2 in C1 (first slot of tile t+1);
 //   before the barrier that ends the fourth slot both wait for everything up to short t+1 (the instructions of long t+2 may stay in flight).
 // After that barrier tile t+1 is complete in LDS.  What a K tile asks for past the output tile's last one are the first K tiles of the workgroup's next
-// output tile, so that a tile switch is the epilogue alone; where there is none the offsets go past every buffer view (zeros, no memory traffic), so that instruction
+// output tile, so that a tile switch is the epilogue alone; where there is none the loads lie past their view (zeros, no memory traffic), so that instruction
 // counts stay static.
 //
-// K tail (K % 64): as in the deep-pipelined kernel, a K tile of its own through the ring.  Lines of a K-strided operand at k >= K lie past its buffer
-// view and read as zeros; of a K-contiguous one the chunks of 8 at k >= K are sent past the view in the last K tile (a chunk that K cuts holds zeros
-// from K on: the host sees to that).
+// K tail (K % 64): as in the deep-pipelined kernel, a K tile of its own through the ring.  Chunks at k >= K lie past the view in the last K tile and read as
+// zeros (a chunk that K cuts holds zeros from K on: the host sees to that).
 //
 // LDS reads in the loop are inline assembly: the compiler then neither sees nor guards them (it would put a
 // wait for every DMA in flight in front of each), and the waits above are the only ones.
@@ -170,33 +169,29 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
       offs[i] = dma_offset<SKC>(lds, LB ? p.tile_m : p.tile_n, lims, line, chunk);
     }
   };
-  // ... in its last K tile, and where there is nothing more to ask for
+  // ... in its last K tile (of a ragged K), and where there is nothing more to ask for
   const bool cut = nk * DK > K;
   auto cut_long = [&](bool all) {
-    if (!all && (!LKC || !cut)) return;
+    if (!all && !cut) return;
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       int line, chunk;
       slot_src<LKC, RL>((wave * NL + i) * 64 + lane, line, chunk);
-      if (all || deep_cut<LKC>(nk, chunk, K)) offl[i] = kNowhere;
+      offl[i] = all ? kPastAll : pp_cut_offset<LKC>(offl[i], stepl, nk, line, chunk, K);
     }
   };
   auto cut_short = [&](bool all) {
-    if (!all && (!SKC || !cut)) return;
+    if (!all && !cut) return;
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
       int line, chunk;
       slot_src<SKC, RS>((wave * NS + i) * 64 + lane, line, chunk);
-      if (all || deep_cut<SKC>(nk, chunk, K)) offs[i] = kNowhere;
+      offs[i] = all ? kPastAll : pp_cut_offset<SKC>(offs[i], steps, nk, line, chunk, K);
     }
   };
-  // DMA instruction i of K tile kt into the slot at LDS address sl
-  auto dma_long = [&](int i, int kt, uint32_t sl) {
-    dma_issue_at(rl, sl + uint32_t(wave * NL + i) * 1024u, offl[i], uint32_t(kt) * stepl);
-  };
-  auto dma_short = [&](int i, int kt, uint32_t sl) {
-    dma_issue_at(rs, sl + uint32_t(wave * NS + i) * 1024u, offs[i], uint32_t(kt) * steps);
-  };
+  // DMA instruction i of the K tile at scalar offset `at` into the slot at LDS address sl
+  auto dma_long = [&](int i, uint32_t at, uint32_t sl) { dma_issue_at(rl, sl + uint32_t(wave * NL + i) * 1024u, offl[i], at); };
+  auto dma_short = [&](int i, uint32_t at, uint32_t sl) { dma_issue_at(rs, sl + uint32_t(wave * NS + i) * 1024u, offs[i], at); };
 
   bf16x8 fa[MI], fb[NI];
   auto read_frags = [&](auto kss, uint32_t sa_addr, uint32_t sb_addr) {
@@ -231,7 +226,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
   TilePos npos = pos;
   auto pp_tile = [&](auto latec, int t) {
     constexpr bool LATE = decltype(latec)::value;
-    const int t2 = t + 2 < nk ? t + 2 : t + 2 - nk;
+    const uint32_t atl = pp_scalar_offset(t + 2, nk, cut, more, stepl), ats = pp_scalar_offset(t + (LATE ? 2 : 1), nk, cut, more, steps);
     if (t + 3 >= nk) {
       // (before the reads: nothing but the wait stands between a read and the use of its registers)  What this K tile asks for is the output tile's last K tile, or past it
       if (t + 3 == nk) cut_long(false);
@@ -246,8 +241,8 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
     __builtin_amdgcn_s_waitcnt(lgkm0_imm());
     __builtin_amdgcn_s_barrier();
     // C0
-    if constexpr (LATE) compute_slot(Int<NL>{}, [&](int i) { dma_long(i, t2, s4); });
-    else compute_slot(Int<NS>{}, [&](int i) { dma_short(i, t + 1 < nk ? t + 1 : 0, s3); });
+    if constexpr (LATE) compute_slot(Int<NL>{}, [&](int i) { dma_long(i, atl, s4); });
+    else compute_slot(Int<NS>{}, [&](int i) { dma_short(i, ats, s3); });
     __builtin_amdgcn_s_barrier();
     // M1
     __builtin_amdgcn_sched_barrier(0);
@@ -258,8 +253,8 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
     else __builtin_amdgcn_s_waitcnt(lgkm0_imm());
     __builtin_amdgcn_s_barrier();
     // C1
-    if constexpr (LATE) compute_slot(Int<NS>{}, [&](int i) { dma_short(i, t2, s0); });
-    else compute_slot(Int<NL>{}, [&](int i) { dma_long(i, t2, s4); });
+    if constexpr (LATE) compute_slot(Int<NS>{}, [&](int i) { dma_short(i, ats, s0); });
+    else compute_slot(Int<NL>{}, [&](int i) { dma_long(i, atl, s4); });
     // early group: its C1 is the tile's fourth slot
     if constexpr (!LATE) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NL));
     __builtin_amdgcn_s_barrier();
@@ -287,10 +282,10 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
     if (late || nk == 1) cut_short(nk == 1);
   }
 #pragma unroll
-  for (int i = 0; i < NL; ++i) dma_long(i, 1, s2);
+  for (int i = 0; i < NL; ++i) dma_long(i, pp_scalar_offset(1, nk, cut, false, stepl), s2);
   if (late) {
 #pragma unroll
-    for (int i = 0; i < NS; ++i) dma_short(i, 1, s3);
+    for (int i = 0; i < NS; ++i) dma_short(i, pp_scalar_offset(1, nk, cut, false, steps), s3);
   }
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
   __builtin_amdgcn_s_barrier();

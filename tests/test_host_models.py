@@ -1,6 +1,6 @@
 """Host-side models of the library's index arithmetic, built with g++ and run on the CPU (no GPU).
 
-* gemm_dma_model: every address the ring and the deep-pipelined GEMM kernels' operand DMA can form, for every tile
+* gemm_dma_model: every address the ring, the ping-pong and the deep-pipelined GEMM kernels' operand DMA can form, for every tile
   variant, operand layout, split-K chunk and a list of ragged shapes, checked against the operand as the caller's
   contract defines it; and the same schedule with the K loop padded to five K tiles and no clamp on the tile index (a variant that
   was tried on the GPU and faulted), which the model shows reading past the operand.
