@@ -324,7 +324,7 @@ struct Prepared {
   SplitChoice sc;
   int layout;
   bool ring_ok;
-  bool pp_ok;    // K tail within what the ping-pong kernel takes
+  bool pp_ok;    // a K tail that a persistent launch of the ping-pong kernel takes
   bool empty;    // no output element: nothing else is filled in
   bool nothing;  // no output that has a destination
   void* ws_ptr;
@@ -436,18 +436,11 @@ int prepare(ntp_handle* h, const GemmDesc& d, Prepared* out) {
   const int64_t ldw = (n_store + 15) / 16 * 16;
   void* const ws_ptr = d.ws_override ? d.ws_override : h->workspace;
   const int64_t ws_bytes = d.ws_override ? d.ws_override_bytes : (h->workspace ? h->workspace_bytes : 0);
-  // deep-pipelined kernel: 32-bit byte offsets with room for one that lies past every operand, and a K tail of whole chunks
-  const bool deep_ok = ring_ok && a_rows * d.lda * 2 < (int64_t(1) << 31) && b_rows * d.ldb * 2 < (int64_t(1) << 31) &&
-                       (!d.a_kc || d.K % 8 == 0 || (d.a_k_pad_8 && !d.b_kc));
-  // Ping-pong kernel, K tail as a K tile of its own: chunks of a K-contiguous operand past K go to an offset past every view below 2 GiB, lines of a
-  // K-strided one have offsets of 32 bits.
-  const int64_t k64 = (d.K + 63) / 64 * 64;
-  const bool tail_ok = (d.a_kc ? a_rows * d.lda * 2 < (int64_t(1) << 31) : k64 * d.lda * 2 < (int64_t(1) << 32)) &&
-                       (d.b_kc ? b_rows * d.ldb * 2 < (int64_t(1) << 31) : k64 * d.ldb * 2 < (int64_t(1) << 32)) &&
-                       (!d.a_kc || d.K % 8 == 0 || (d.a_k_pad_8 && !d.b_kc));
-  const bool pp_ok = d.K % 64 == 0 || (tail_ok && !(layout == 1 && h->opt[NTP_OPT_GEMM_NO_RING_TAIL]));
-  SplitChoice sc = plan_gemm(h, ws_ptr ? ws_bytes : 0, g, layout, ring_ok, split_ok && pp_ok, ldw, deep_ok);
-  if (layout == 2 && !pp_ok && ring_ok && !sc.deep && sc.splits == 1 && sc.tile == 0) sc.tile = 2;  // (the 256 x 256 tile of this layout is a ping-pong kernel)
+  // deep-pipelined and ping-pong kernels: a K tail of whole chunks; the former's 32-bit byte offsets with room for one that lies past every operand
+  const bool whole_chunks = !d.a_kc || d.K % 8 == 0 || (d.a_k_pad_8 && !d.b_kc);
+  const bool deep_ok = ring_ok && whole_chunks && a_rows * d.lda * 2 < (int64_t(1) << 31) && b_rows * d.ldb * 2 < (int64_t(1) << 31);
+  const bool pp_ok = d.K % 64 == 0 || (whole_chunks && !(layout == 1 && h->opt[NTP_OPT_GEMM_NO_RING_TAIL]));
+  const SplitChoice sc = plan_gemm(h, ws_ptr ? ws_bytes : 0, g, layout, ring_ok, split_ok && whole_chunks, ldw, deep_ok);
   *out = Prepared{g, sc, layout, ring_ok, pp_ok, false, to_segs && g.n_segs == 0, ws_ptr, ldw};
   return NTP_OK;
 }

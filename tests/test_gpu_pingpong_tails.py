@@ -47,3 +47,45 @@ def test_short_ragged_k_chunks(workspace, opts, tile, k, splits):  # noqa: F811
         N.ntp_kernel_timing_read()
         _check(case, 8, f"{tile}, {splits} chunks of K = {tag} = {k}")
         assert any(r["name"].endswith(f"{tile}k{splits}") for r in N.ntp_kernel_timing_read()), tag
+
+
+def _projections(M, H, w, X, Cc, W, handle=None):
+    """QKV = X W^T, Z = C W and dW = C^T dZ of one shard, and the names of the kernels."""
+    import torch
+    import paper_2504_06095_amd as N
+    QKV, Z = torch.zeros(M, w, dtype=torch.bfloat16, device="cuda"), torch.zeros(M, H, dtype=torch.bfloat16, device="cuda")
+    dC, dW = torch.zeros_like(QKV), torch.zeros(w, H, device="cuda")
+    N.ntp_kernel_timing_read()
+    N.ntp_attn_proj_shard_fwd(M, H, w, w, X=X, Wqkv=W, QKV=QKV, C_=Cc, Wo=W, Zpart=Z)
+    N.ntp_attn_proj_shard_bwd(M, H, w, w, dZ=X, C_=Cc, Wo=W, dC=dC, dWo=dW)
+    return (QKV, Z, dC, dW), [r["name"] for r in N.ntp_kernel_timing_read()]
+
+
+def test_ragged_k_of_operands_past_2_gib_is_cut(workspace, opts):  # noqa: F811
+    """A K-contiguous operand of more than 2 GiB (by its row length) and a ragged K, in three chunks: the bits of the same call on compact operands."""
+    import torch
+    print("[gpu-case] three ragged K chunks, operands past 2 GiB", file=sys.stderr, flush=True)
+    M, H, w, ld = 700, 1000, 712, 1600000
+    opts(K.NTP_OPT_GEMM_SPLIT, 3)
+    g = torch.Generator("cuda").manual_seed(3)
+    X, Cc, W = (torch.empty(r, c, device="cuda").normal_(generator=g).bfloat16() for r, c in ((M, H), (M, w), (w, H)))
+    far = torch.full((M, ld), float("nan"), dtype=torch.bfloat16, device="cuda")
+    assert M * ld * 2 > 2 << 30
+    far[:, :H], far[:, H:H + w] = X, Cc
+    want, names = _projections(M, H, w, X, Cc, W)
+    assert len(names) == 4 and all(n.split("_")[-1].split("x")[1].endswith("k3") for n in names), names
+    got, names = _projections(M, H, w, far[:, :H], far[:, H:H + w], W)
+    assert len(names) == 4 and all(n.split("_")[-1].split("x")[1].endswith("k3") for n in names), names
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+
+
+def test_k_tail_option_leaves_cut_axes_alone(workspace, opts):  # noqa: F811
+    """NTP_OPT_GEMM_NO_RING_TAIL is about persistent launches: a ragged row-parallel K is cut under it as without it."""
+    opts(K.NTP_OPT_GEMM_SPLIT, 3)
+    opts(K.NTP_OPT_GEMM_NO_RING_TAIL, 1)
+    import paper_2504_06095_amd as N
+    N.ntp_kernel_timing_read()
+    _check(MlpCase(700, 704, 987, 1, 0, tag="ppo"), 64, "three chunks, K tails through registers asked for")
+    names = [r["name"] for r in N.ntp_kernel_timing_read()]
+    assert len(names) == 6 and all(n.endswith("k3") for n in names), names
