@@ -287,6 +287,22 @@ bool use_pingpong(const ntp_handle* h, int variant, int64_t K) {
   return variant >= 0 && variant <= 6 && K > 128 && h->opt[NTP_OPT_GEMM_SCHEDULE] != 1;
 }
 
+// Compute units that a persistent launch uses.
+int32_t resident_units(const ntp_handle* h) {
+  const int64_t cap = h->opt[NTP_OPT_GEMM_WORKGROUPS];
+  return int32_t(cap ? std::min<int64_t>(cap, h->compute_units) : h->compute_units);
+}
+
+// Whether a weight gradient on 256 x 256 tiles runs the ping-pong kernel with one workgroup per output tile (which takes one and two K tiles too) instead of the
+// persistent one; the ring kernel does not have that tile.  A workgroup's next tile under its stores pays where there is one and a tile is short: with more tiles than
+// compute units and K up to 4096 the persistent form takes 0.961 of the time on the mean of sixteen shapes (0.89 to 1.00), accumulating 0.992 (0.97 to 1.03): 5376 x 12288
+// over 2048 259 -> 250 us, 8440 x 8072 over 720 150 -> 134.  With fewer tiles, or longer, it takes 1.001 on twenty-eight (0.95 to 1.03), accumulating 1.006 (0.98 to 1.07).
+bool one_tile_each(const ntp_handle* h, int layout, int variant, const GemmArgs& g) {
+  if (layout != 2 || variant != 0) return false;
+  const int64_t tiles = ((g.M + 255ll) / 256) * ((g.n_store + 255ll) / 256);
+  return !use_pingpong(h, variant, g.K) || tiles <= g.resident || g.K > 4096;
+}
+
 // What ntp_gemm_choice reports as `pingpong`: the kinds of GEMM for which the schedule was chosen while it was one of two (see ntp.h).
 bool reported_pingpong(const ntp_handle* h, int layout, int variant, int64_t K) {
   if (variant < 0 || variant > 6) return false;
@@ -428,8 +444,7 @@ int prepare(ntp_handle* h, const GemmDesc& d, Prepared* out) {
   // what the DMA loads are range-checked against (< 4 GiB when ring_ok)
   g.a_extent = uint32_t(std::min<int64_t>(0xFFFFFFFFll, operand_extent_bytes(d.a_kc, d.M, d.K, d.lda, g.ring_tail != 0)));
   g.b_extent = uint32_t(std::min<int64_t>(0xFFFFFFFFll, operand_extent_bytes(d.b_kc, d.N, d.K, d.ldb, false)));
-  g.resident = h->compute_units;
-  if (const int64_t cap = h->opt[NTP_OPT_GEMM_WORKGROUPS]) g.resident = int32_t(std::min<int64_t>(cap, h->compute_units));
+  g.resident = resident_units(h);
   // split-K: any (layout, epilogue) whose operands the ring kernel can address, except B K-contiguous
   // with A K-strided (no ring kernel)
   const bool split_ok = a_rows * d.lda * 2 < (int64_t(1) << 32) && b_rows * d.ldb * 2 < (int64_t(1) << 32) && (d.a_kc || !d.b_kc);
@@ -472,16 +487,14 @@ int launch_prepared(ntp_handle* h, const GemmDesc& d, const Prepared& p, void* s
     if (sc.deep == kDeepSmall) snprintf(vn, sizeof(vn), "64x64");
     else variant_name(variant, vn, sizeof(vn));
     if (sc.splits > 1) snprintf(sn, sizeof(sn), "k%d", sc.splits);
-    const bool pp = sc.splits == 1 && !sc.deep && p.pp_ok && use_pingpong(h, variant, d.K) && !(layout == 2 && variant == 0);
+    const bool pp = sc.splits == 1 && !sc.deep && p.pp_ok && use_pingpong(h, variant, d.K) && !one_tile_each(h, layout, variant, g);
     snprintf(name, sizeof(name), "gemm_%c%c_%s_%s%s%s%s", d.a_kc ? 'n' : 't', d.b_kc ? 't' : 'n', kEpiName[d.epilogue], vn,
              sc.deep == kDeep2 ? "d2" : sc.deep ? "d" : "", sn, pp ? "pp" : "");
     ntp::timing_begin(h, stream, name, 2.0 * double(d.M) * double(d.N) * double(d.K), 0.0);
   }
   if (sc.deep && sc.splits == 1) {
     st = launch_deep(deep_args(p, d), d.a_kc, d.b_kc, d.epilogue, sc.deep, s);
-  } else if (layout == 2 && variant == 0 && sc.splits == 1 && ring_ok) {
-    // The 256 x 256 weight-gradient tile runs one workgroup per output tile (5376 x 12288 x 2048 247 -> 228 us with the ping-pong kernel; its persistent form takes
-    // 218 there, and 200 against 199 at 4096 x 4096 x 8192).
+  } else if (one_tile_each(h, layout, variant, g) && sc.splits == 1 && ring_ok) {
     GemmArgs gp = g;
     gp.k_splits = 1;
     gp.k_chunk = int32_t((d.K + 63) / 64 * 64);
@@ -645,6 +658,7 @@ extern "C" int ntp_gemm_choice(const ntp_handle_t* h, int32_t layout, int64_t M,
   g.N = int32_t(N);
   g.K = int32_t(K);
   g.n_store = int32_t((N + 7) / 8 * 8);
+  g.resident = resident_units(h);
   const SplitChoice sc = plan_gemm(h, h->workspace ? h->workspace_bytes : 0, g, layout, true, true, (g.n_store + 15) / 16 * 16, true);
   *out = ntp_gemm_choice_t{};
   out->k_splits = sc.splits;
@@ -659,7 +673,7 @@ extern "C" int ntp_gemm_choice(const ntp_handle_t* h, int32_t layout, int64_t M,
     out->wavefronts = ts.waves;
     out->ring = 1;
   }
-  out->persistent = sc.tile >= 0 && !sc.deep && sc.splits == 1 && !(layout == 2 && sc.tile == 0) ? 1 : 0;
+  out->persistent = sc.tile >= 0 && !sc.deep && sc.splits == 1 && !one_tile_each(h, layout, sc.tile, g) ? 1 : 0;
   out->pingpong = out->persistent && reported_pingpong(h, layout, sc.tile, K) ? 1 : 0;
   return NTP_OK;
 }

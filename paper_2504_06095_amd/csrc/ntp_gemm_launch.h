@@ -30,19 +30,19 @@ constexpr int kNumTileShapes = int(sizeof(kTileShapes) / sizeof(kTileShapes[0]))
 int launch_ring_nt(GemmArgs g, int epilogue, int tile, hipStream_t s);  // A [M x K], B [N x K]
 int launch_ring_nn(GemmArgs g, int epilogue, int tile, hipStream_t s);  // A [M x K], B [K x N]
 int launch_ring_tn(GemmArgs g, int epilogue, int tile, hipStream_t s);  // A [K x M], B [K x N]
-// Non-persistent form (tile shapes with kSplitTile set; ping-pong kernel).  g.k_splits > 1: split-K, g.C is the fp32
-// workspace, g.ldc its row length, g.k_chunk / g.split_stride describe the chunks; partial sums only, no
-// epilogue.  g.k_splits == 1 (weight-gradient layout only): the whole GEMM with its fp32 epilogue; the
-// accumulating epilogue exists for the 256 x 256 tile only.
-// The same with the ping-pong schedule of the K loop (tile shapes 0-6, persistent form).
+// The same with the ping-pong kernel (tile shapes 0-6, K > 128).
 int launch_pp_nt(GemmArgs g, int epilogue, int tile, hipStream_t s);
 int launch_pp_nn(GemmArgs g, int epilogue, int tile, hipStream_t s);
 int launch_pp_tn(GemmArgs g, int epilogue, int tile, hipStream_t s);
-// Deep-pipelined kernel (ntp_gemm_deep.h), one workgroup per tile and K chunk (g.k_splits, g.k_chunk as above).
+// Deep-pipelined kernel (ntp_gemm_deep.h), one workgroup per tile and K chunk (g.k_splits, g.k_chunk as for the split launches below).
 enum DeepForm : int { kNotDeep = 0, kDeep5, kDeep2, kDeepWide, kDeepSmall };  // 128 x 128 with five / two K tiles in LDS, 128 x 256 and 64 x 64 with three
 int launch_deep(const GemmArgs& g, bool a_kc, bool b_kc, int epilogue, int form, hipStream_t s);
 // Up to three independent problems (no cut K axis; bf16 epilogue, fp32 ones for layout 2) in one launch of its 128 x 128 or 64 x 64 form.
 int launch_deep_group(const GemmArgs* g, const int* layout, const int* epilogue, int n, int form, hipStream_t s);
+// Ping-pong kernel with one workgroup per unit of work (tile shapes with kSplitTile set).  g.k_splits > 1: split-K, g.C is the fp32
+// workspace, g.ldc its row length, g.k_chunk / g.split_stride describe the chunks; partial sums only, no
+// epilogue.  g.k_splits == 1 (weight-gradient layout only): the whole GEMM with its fp32 epilogue; the
+// accumulating epilogue exists for the 256 x 256 tile only.
 int launch_split_nt(GemmArgs g, int tile, hipStream_t s);
 int launch_split_nn(GemmArgs g, int tile, hipStream_t s);
 int launch_split_tn(GemmArgs g, int epilogue, int tile, hipStream_t s);
@@ -111,7 +111,7 @@ template <bool AKC, bool BKC, int EPI>
 int launch_ring_tile(const GemmArgs& g, int tile, hipStream_t s) {
   switch (tile) {
     case 0:
-      // (the weight-gradient layout has this tile in the non-persistent form only)
+      // (the weight-gradient layout has this tile on the ping-pong kernel only)
       if constexpr (AKC || BKC) return launch_ring_one<AKC, BKC, EPI, 256, 256, 2, 4>(g, s);
       else return NTP_ERR_INVALID_ARG;
     case 1: return launch_ring_one<AKC, BKC, EPI, 256, 224, 4, 2>(g, s);

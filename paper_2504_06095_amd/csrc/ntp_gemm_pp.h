@@ -134,7 +134,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
   // this workgroup's share of the K axis
   const int64_t k_first = SPLIT ? int64_t(split) * g.k_chunk : 0;
   const int K = SPLIT ? min(g.k_chunk, g.K - int(k_first)) : g.K;
-  const int nk = (K + DK - 1) / DK;  // (three at least in the persistent form: pp_ok in ntp_gemm.hip)
+  const int nk = (K + DK - 1) / DK;  // (three at least in the persistent form: use_pingpong in ntp_gemm.hip)
   TilePos pos = place(vblk);
 
   f32x4 acc[MI][NI];

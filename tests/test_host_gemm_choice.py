@@ -39,9 +39,9 @@ def test_benchmark_configuration_choices():
     assert _tiles(N.ntp_gemm_choice(0, 2048, 7022, 12288), 2048, 7022) == 256
     c = N.ntp_gemm_choice(1, 2048, 12288, 7022)
     assert (c["tile_m"], c["tile_n"], c["persistent"]) == (256, 192, 1) and _tiles(c, 2048, 12288) == 512
-    # the 256 x 256 weight-gradient tile is the non-persistent one
+    # the weight gradient of QKV on 256 x 256 tiles
     c = N.ntp_gemm_choice(2, 5376, 12288, 2048)
-    assert (c["tile_m"], c["tile_n"], c["persistent"]) == (256, 256, 0)
+    assert (c["tile_m"], c["tile_n"], c["persistent"]) == (256, 256, 1)
     # a lone small tile set runs on 8 wavefronts per workgroup
     c = N.ntp_gemm_choice(0, 512, 586, 1024)
     assert (c["tile_m"], c["tile_n"], c["wavefronts"], c["ring"]) == (128, 128, 8, 1)
@@ -114,8 +114,22 @@ def test_schedule_choice_and_override():
     assert Bd.ntp_gemm_choice(0, 2048, 7022, 12288, handle=h)["pingpong"] == 0
     Bd.ntp_set_option(Bd.NTP_OPT_GEMM_SCHEDULE, 2, handle=h)
     assert Bd.ntp_gemm_choice(1, 2048, 12288, 7022, handle=h)["pingpong"] == 1
-    assert Bd.ntp_gemm_choice(2, 5376, 12288, 2048, handle=h)["pingpong"] == 0  # 256 x 256 weight-gradient tile: non-persistent
+    assert Bd.ntp_gemm_choice(2, 5376, 12288, 2048, handle=h)["pingpong"] == 1  # 256 x 256 weight-gradient tile
     assert Bd.lib().ntp_set_option(h.ptr, Bd.NTP_OPT_GEMM_SCHEDULE, 3) == Bd.NTP_ERR_INVALID_ARG
+    Bd.ntp_destroy(h)
+
+
+def test_weight_gradient_tile_that_the_ring_kernel_does_not_have():
+    """256 x 256: persistent where workgroups have several tiles of three to 64 K tiles; otherwise, and under the ring schedule, one workgroup per output tile."""
+    h = Bd.ntp_create()
+    Bd.ntp_set_option(Bd.NTP_OPT_GEMM_TILE, "256x256", handle=h)
+    one = lambda M, K: Bd.ntp_gemm_choice(2, M, 4096, K, handle=h)  # noqa: E731
+    assert [one(4097, K)["persistent"] for K in (8, 64, 128, 129, 192, 4096, 4097)] == [0, 0, 0, 1, 1, 1, 0]  # 272 tiles
+    assert one(4096, 2048)["persistent"] == 0  # 256
+    Bd.ntp_set_option(Bd.NTP_OPT_GEMM_WORKGROUPS, 8, handle=h)
+    assert one(4096, 2048)["persistent"] == one(257, 2048)["persistent"] == 1
+    Bd.ntp_set_option(Bd.NTP_OPT_GEMM_SCHEDULE, 1, handle=h)
+    assert one(4097, 2048)["persistent"] == 0 and one(4097, 2048)["tile_m"] == one(4097, 2048)["tile_n"] == 256
     Bd.ntp_destroy(h)
 
 
