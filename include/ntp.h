@@ -109,7 +109,8 @@ int ntp_device_info(const ntp_handle_t* h, int32_t* device, int32_t* compute_uni
 #define NTP_OPT_RESHARD_TABLE_BLOCK 6 /* bytes per block of the unit-table and run-table kernels                    */
 #define NTP_OPT_RESHARD_NO_FLAT 7    /* 1: column-partitioned tensors never take the flat-destination kernel       */
 #define NTP_OPT_RESHARD_NO_TABLE 8   /* 1: plans never take the unit-table and run-table kernels                   */
-#define NTP_OPT_GEMM_SCHEDULE 9      /* schedule of the persistent kernels' K loop: 1 the ring kernel's everywhere, 2 the
+#define NTP_OPT_GEMM_SCHEDULE 9      /* schedule of the persistent kernels' K loop: 1 the ring kernel's (cut products and
+                                        weight gradients on 256x256 tiles are not its own: ping-pong), 2 the
                                         ping-pong one wherever it exists (8-wavefront tiles, K > 128); 0 does the same
                                         and leaves problems with few tiles to the deep-pipelined kernel              */
 #define NTP_OPT_GEMM_WORKGROUPS 10   /* persistent GEMM launches use at most this many workgroups (rounded down to a
@@ -529,10 +530,10 @@ int ntp_set_workspace(ntp_handle_t* h, void* workspace, int64_t bytes);
  *   ring            1: one of the kernels with an LDS ring (the deep-pipelined one included); 0: the small generic kernel
  *   k_splits        > 1: split-K with that many chunks, followed by the reduce kernel
  *   persistent      1: one workgroup per compute unit walks over the tiles
- *   pingpong        1: a persistent launch of a kind that took the ping-pong schedule (the two wavefronts of a SIMD alternate
- *                   between matrix instructions and LDS reads) while it was one of two: both operands K-contiguous, row-parallel with K <= 1024,
- *                   weight gradients on 224-wide tiles, or any under NTP_OPT_GEMM_SCHEDULE = 2; 0: others.  Today the 8-wavefront
- *                   tiles of the other kinds run that schedule too (K > 128, no option against it); the timing names say which kernel ran ("pp")
+ *   pingpong        1: the ping-pong kernel (the two wavefronts of a SIMD alternate between matrix instructions and LDS reads): 8-wavefront
+ *                   tiles other than 128x128, cut, or whole with K > 128 and no option against it, and whole weight gradients on 256x256 tiles
+ *                   with any K; 0: another one.  In the timing names whole products on it end in "pp"; cut ones ("k" and the number of chunks
+ *                   behind the tile) are on it where no "d" stands between the two
  * Errors: NTP_ERR_INVALID_ARG. */
 typedef struct ntp_gemm_choice {
   int32_t tile_m, tile_n, wavefronts, ring, k_splits, persistent, pingpong;

@@ -303,13 +303,15 @@ bool one_tile_each(const ntp_handle* h, int layout, int variant, const GemmArgs&
   return !use_pingpong(h, variant, g.K) || tiles <= g.resident || g.K > 4096;
 }
 
-// What ntp_gemm_choice reports as `pingpong`: the kinds of GEMM for which the schedule was chosen while it was one of two (see ntp.h).
-bool reported_pingpong(const ntp_handle* h, int layout, int variant, int64_t K) {
-  if (variant < 0 || variant > 6) return false;
-  const int64_t f = h->opt[NTP_OPT_GEMM_SCHEDULE];
-  if (f == 1) return false;
-  if (f == 2) return true;
-  return layout == 0 || (layout == 2 && (variant == 1 || variant == 2)) || (layout == 1 && K <= 1024);
+// Whether a product runs on the ping-pong kernel: every cut one on an 8-wavefront tile, whole ones as above.  pp_ok: Prepared::pp_ok.
+bool on_pingpong(const ntp_handle* h, int layout, const SplitChoice& sc, const GemmArgs& g, bool pp_ok) {
+  if (sc.deep || sc.tile < 0 || sc.tile > 6) return false;
+  return sc.splits > 1 || one_tile_each(h, layout, sc.tile, g) || (pp_ok && use_pingpong(h, sc.tile, g.K));
+}
+
+// A K tail that a persistent launch of it takes (whole_chunks: see prepare).
+bool pingpong_takes(const ntp_handle* h, int layout, int64_t K, bool whole_chunks) {
+  return K % 64 == 0 || (whole_chunks && !(layout == 1 && h->opt[NTP_OPT_GEMM_NO_RING_TAIL]));
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -340,7 +342,7 @@ struct Prepared {
   SplitChoice sc;
   int layout;
   bool ring_ok;
-  bool pp_ok;    // a K tail that a persistent launch of the ping-pong kernel takes
+  bool pp_ok;    // pingpong_takes
   bool empty;    // no output element: nothing else is filled in
   bool nothing;  // no output that has a destination
   void* ws_ptr;
@@ -454,7 +456,7 @@ int prepare(ntp_handle* h, const GemmDesc& d, Prepared* out) {
   // deep-pipelined and ping-pong kernels: a K tail of whole chunks; the former's 32-bit byte offsets with room for one that lies past every operand
   const bool whole_chunks = !d.a_kc || d.K % 8 == 0 || (d.a_k_pad_8 && !d.b_kc);
   const bool deep_ok = ring_ok && whole_chunks && a_rows * d.lda * 2 < (int64_t(1) << 31) && b_rows * d.ldb * 2 < (int64_t(1) << 31);
-  const bool pp_ok = d.K % 64 == 0 || (whole_chunks && !(layout == 1 && h->opt[NTP_OPT_GEMM_NO_RING_TAIL]));
+  const bool pp_ok = pingpong_takes(h, layout, d.K, whole_chunks);
   const SplitChoice sc = plan_gemm(h, ws_ptr ? ws_bytes : 0, g, layout, ring_ok, split_ok && whole_chunks, ldw, deep_ok);
   *out = Prepared{g, sc, layout, ring_ok, pp_ok, false, to_segs && g.n_segs == 0, ws_ptr, ldw};
   return NTP_OK;
@@ -487,7 +489,7 @@ int launch_prepared(ntp_handle* h, const GemmDesc& d, const Prepared& p, void* s
     if (sc.deep == kDeepSmall) snprintf(vn, sizeof(vn), "64x64");
     else variant_name(variant, vn, sizeof(vn));
     if (sc.splits > 1) snprintf(sn, sizeof(sn), "k%d", sc.splits);
-    const bool pp = sc.splits == 1 && !sc.deep && p.pp_ok && use_pingpong(h, variant, d.K) && !one_tile_each(h, layout, variant, g);
+    const bool pp = sc.splits == 1 && on_pingpong(h, layout, sc, g, p.pp_ok);
     snprintf(name, sizeof(name), "gemm_%c%c_%s_%s%s%s%s", d.a_kc ? 'n' : 't', d.b_kc ? 't' : 'n', kEpiName[d.epilogue], vn,
              sc.deep == kDeep2 ? "d2" : sc.deep ? "d" : "", sn, pp ? "pp" : "");
     ntp::timing_begin(h, stream, name, 2.0 * double(d.M) * double(d.N) * double(d.K), 0.0);
@@ -674,6 +676,6 @@ extern "C" int ntp_gemm_choice(const ntp_handle_t* h, int32_t layout, int64_t M,
     out->ring = 1;
   }
   out->persistent = sc.tile >= 0 && !sc.deep && sc.splits == 1 && !one_tile_each(h, layout, sc.tile, g) ? 1 : 0;
-  out->pingpong = out->persistent && reported_pingpong(h, layout, sc.tile, K) ? 1 : 0;
+  out->pingpong = on_pingpong(h, layout, sc, g, pingpong_takes(h, layout, K, true)) ? 1 : 0;
   return NTP_OK;
 }

@@ -99,24 +99,39 @@ def test_choice_rejects_bad_arguments():
 
 
 def test_schedule_choice_and_override():
-    """K-contiguous layouts get the ping-pong schedule on the persistent 8-wavefront tiles; the option forces either."""
+    """Every layout gets the ping-pong kernel on the 8-wavefront tiles other than 128 x 128; the option forces either."""
     h = Bd.ntp_create()
     c = Bd.ntp_gemm_choice(0, 2048, 7022, 12288, handle=h)
     assert c["persistent"] == 1 and c["pingpong"] == 1
-    assert Bd.ntp_gemm_choice(1, 2048, 12288, 7022, handle=h)["pingpong"] == 0
-    assert Bd.ntp_gemm_choice(1, 8192, 16384, 750, handle=h)["pingpong"] == 1  # row-parallel layout at short K
-    c = Bd.ntp_gemm_choice(2, 7022, 12288, 2048, handle=h)  # weight gradient on the 224 x 256 tile: ping-pong too
+    assert Bd.ntp_gemm_choice(1, 2048, 12288, 7022, handle=h)["pingpong"] == 1  # row-parallel layout
+    assert Bd.ntp_gemm_choice(1, 8192, 16384, 750, handle=h)["pingpong"] == 1  # ... at short K
+    c = Bd.ntp_gemm_choice(2, 7022, 12288, 2048, handle=h)  # weight gradients on the 224 x 256 tile
     assert (c["tile_m"], c["tile_n"], c["pingpong"]) == (224, 256, 1)
-    c = Bd.ntp_gemm_choice(2, 1792, 12288, 2048, handle=h)  # ... on the 192 x 256 tile: default schedule
-    assert (c["tile_m"], c["tile_n"], c["pingpong"]) == (192, 256, 0)
-    assert Bd.ntp_gemm_choice(0, 512, 586, 1024, handle=h)["pingpong"] == 0  # the small 128 x 128 tile has one schedule
+    c = Bd.ntp_gemm_choice(2, 1792, 12288, 2048, handle=h)  # ... on the 192 x 256 tile
+    assert (c["tile_m"], c["tile_n"], c["pingpong"]) == (192, 256, 1)
+    assert Bd.ntp_gemm_choice(0, 512, 586, 1024, handle=h)["pingpong"] == 0  # the small 128 x 128 tile is the deep-pipelined kernel's
     Bd.ntp_set_option(Bd.NTP_OPT_GEMM_SCHEDULE, 1, handle=h)
     assert Bd.ntp_gemm_choice(0, 2048, 7022, 12288, handle=h)["pingpong"] == 0
+    assert Bd.ntp_gemm_choice(2, 5376, 12288, 2048, handle=h)["pingpong"] == 1  # the ring kernel has no 256 x 256 weight-gradient tile
     Bd.ntp_set_option(Bd.NTP_OPT_GEMM_SCHEDULE, 2, handle=h)
     assert Bd.ntp_gemm_choice(1, 2048, 12288, 7022, handle=h)["pingpong"] == 1
     assert Bd.ntp_gemm_choice(2, 5376, 12288, 2048, handle=h)["pingpong"] == 1  # 256 x 256 weight-gradient tile
     assert Bd.lib().ntp_set_option(h.ptr, Bd.NTP_OPT_GEMM_SCHEDULE, 3) == Bd.NTP_ERR_INVALID_ARG
     Bd.ntp_destroy(h)
+
+
+def test_choice_says_where_the_pingpong_kernel_runs(workspace_1gib):
+    pp = lambda *s: (lambda c: (c["k_splits"], c["persistent"], c["pingpong"]))(N.ntp_gemm_choice(*s))  # noqa: E731
+    assert pp(0, 4096, 640, 8192) == (3, 0, 1)      # cut, on 256 x 128 tiles
+    assert pp(2, 384, 512, 4096)[2] == 0            # few tiles: the deep-pipelined kernel
+    assert pp(0, 8192, 8192, 128) == (1, 1, 0) and pp(0, 8192, 8192, 136) == (1, 1, 1)  # two K tiles: the ring kernel
+    assert pp(0, 100, 100, 4096)[2] == 0            # the generic kernel
+    h = Bd.default_handle()
+    try:
+        Bd.ntp_set_option(Bd.NTP_OPT_GEMM_NO_RING_TAIL, 1, handle=h)
+        assert pp(1, 8192, 16384, 750) == (1, 1, 0) and pp(1, 8192, 16384, 768) == (1, 1, 1) and pp(0, 8192, 16384, 752) == (1, 1, 1)
+    finally:
+        Bd.ntp_set_option(Bd.NTP_OPT_GEMM_NO_RING_TAIL, 0, handle=h)
 
 
 def test_weight_gradient_tile_that_the_ring_kernel_does_not_have():
