@@ -8,17 +8,14 @@
 // (bound by LDS reads, 96 KB a K tile, and the barrier); with four wavefronts of 64 x 64 it is a third less LDS traffic and 20-50 %
 // slower, because nothing overlaps a wavefront's reads.  512 x 586 x 1024: 16 -> 12 us; 1200 x 1712 x 3272: 46 -> 34 us.
 //
-// Per K tile, in step: wait for this wavefront's share of it, one barrier (now it is complete, and every wavefront has read its
+// Per K tile: wait for this wavefront's share of it, one barrier (now it is complete, and every wavefront has read its
 // fragments of the previous one), start the DMA of the K tile STAGES - 1 ahead into the previous one's slot, read all
-// fragments, multiply.  With five K tiles in LDS and 20 K tiles or more the two wavefronts of a SIMD alternate instead: in one slot
-// one of them reads a whole K tile's fragments while the other one multiplies, with its DMA instructions among the matrix instructions, in the next slot the
-// other way round.  1024 x 2048 and 2048 x 1024 over 2048 (a shared launch) 31.0 -> 29.5 us, 2000 x 1024 with 3000 columns 39.8 -> 38.4.  Shorter launches stay in step (the half tile
-// between the groups is not won back: 512 x 1024 x 586 backward 19.1 -> 19.4 us, 278 x 2232 over K = 3248 in four chunks 18.1 -> 19.2), and so does the 128 x 256
-// form: with three K tiles the late group's instructions have one tile's time to land, which is enough where operands are in the last-level cache (1376 x 4672 over 3440 47.3 ->
-// 42.4) and too little where they come from HBM (a layer shard of 2821 tokens, hidden 2816, 559 -> 569 us).  (DMA among the matrix instructions alone, in step: 0.92-1.06 of the time, no gain on the
-// mean.  What is left, 0.45-0.5 us a K tile with all compute units at it, is the 32 KB that each of them asks its L2 for: 64 GB/s a unit.)
-// Past the last K tile the schedule asks for the last one again (clamped index, slots nobody reads), so that the
+// fragments, multiply.  Past the last K tile the schedule asks for the last one again (clamped index, slots nobody reads), so that the
 // instruction counts that the waits rely on stay static.  LDS reads are inline assembly (see ntp_gemm_pp.h).
+//
+// (The two wavefronts of a SIMD alternating, one reading a whole K tile while the other one multiplies, from 20 K tiles on: over 170 random projections of 2 to
+// 40 GFLOP 1.003 of the time with cold operands, shared launches 1.005 (0.98 to 1.04), and 0.996 with cached ones.  DMA instructions among the matrix instructions, in
+// step: 0.92-1.06 of the time, no gain on the mean.  What is left, 0.45-0.5 us a K tile with all compute units at it, is the 32 KB that each of them asks its L2 for: 64 GB/s a unit.)
 //
 // K tail (K % 64): K-contiguous operands are read in chunks of 8, and chunks at k >= K are sent past the end of the buffer view, where
 // loads read zeros; lines of a K-strided operand at k >= K lie past its end by themselves.  A chunk that K cuts must
@@ -37,11 +34,8 @@ __device__ __forceinline__ void pin(bf16x8& v) {
 #endif
 }
 
-// Whether the wavefronts may alternate in a form.
-constexpr bool can_alternate(int bm, int stages) { return bm > 64 && stages >= 4; }
-
 // One (output tile, K chunk): workgroup `block` of problem g, with the ring in `ring`.
-template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, int STAGES, bool ALT>
+template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, int STAGES>
 __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, uint16_t* const ring) {
   constexpr int NW = WGM * WGN;
   constexpr int TM = BM_ / WGM, TN = BN_ / WGN;  // wavefront tile
@@ -92,15 +86,6 @@ __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, ui
     offb[i] = dma_offset<BKC>(g.ldb, col0, g.N, line, chunk);
     cutb[i] = deep_cut<BKC>(nk, chunk, K);
   }
-  constexpr int NDMA = NAI + NBI;
-  // DMA instruction i of K tile t into a slot
-  auto dma_one = [&](auto ic, int t, int slot) {
-    constexpr int i = decltype(ic)::value;
-    const int kt = min(t, nk - 1);
-    const bool last = kt == nk - 1;
-    if constexpr (i < NAI) dma_issue(ra, ring + slot * STAGE + (wave * NAI + i) * 512, last && cuta[i] ? kNowhere : offa[i], uint32_t(kt) * astep_b);
-    else dma_issue(rb, ring + slot * STAGE + SA + (wave * NBI + i - NAI) * 512, last && cutb[i - NAI] ? kNowhere : offb[i - NAI], uint32_t(kt) * bstep_b);
-  };
   auto dma = [&](int t, int slot) {
     const int kt = min(t, nk - 1);
     const bool last = kt == nk - 1;
@@ -132,95 +117,36 @@ __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, ui
       static_for(std::make_integer_sequence<int, MI>{}, [&](auto i) { fa[ks][decltype(i)::value] = frag_read_asm<AKC, BM_, MI, decltype(i)::value, ks>(fra, sa); });
       static_for(std::make_integer_sequence<int, NI>{}, [&](auto j) { fb[ks][decltype(j)::value] = frag_read_asm<BKC, BN_, NI, decltype(j)::value, ks>(frb, sb); });
     };
+    auto multiply = [&](int ks) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+    };
 #pragma unroll
     for (int s = 0; s < STAGES - 1; ++s) dma(s, s);
     int slot = 0, free_slot = STAGES - 1;
-    auto next_slot = [&] {
-      free_slot = slot;
-      slot = slot + 1 == STAGES ? 0 : slot + 1;
-    };
-    if constexpr (ALT && can_alternate(BM_, STAGES)) {
-      // The two wavefronts of a SIMD (w and w + 4) alternate, half a K tile apart: one reads a K tile's fragments while the other one multiplies.
-      auto read_tile = [&] {
-        __builtin_amdgcn_sched_barrier(0);
-        const uint32_t sa = ring0 + uint32_t(slot) * (STAGE * 2), sb = sa + SA * 2;
-        read_frags(Int<0>{}, sa, sb);
-        read_frags(Int<1>{}, sa, sb);
-        __builtin_amdgcn_sched_barrier(0);
-      };
-      auto multiply_tile = [&](int t) {
-        constexpr int NM = 2 * MI * NI;
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(1);
-        static_for(std::make_integer_sequence<int, NDMA + 1>{}, [&](auto dc) {
-          constexpr int d = decltype(dc)::value;
-#pragma unroll
-          for (int n = d * NM / (NDMA + 1); n < (d + 1) * NM / (NDMA + 1); ++n) {
-            const int ks = n / (MI * NI), i = n / NI % MI, j = n % NI;
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-          if constexpr (d < NDMA) dma_one(Int<d>{}, t + STAGES - 1, free_slot);
-          __builtin_amdgcn_sched_barrier(0);
-        });
-        __builtin_amdgcn_s_setprio(0);
-        __builtin_amdgcn_sched_barrier(0);
-      };
-      // Every wavefront passes 2 nk + 2 barriers.  K tile t + 1 is complete at the barrier that ends the late group's reads of tile t: both groups have
-      // waited for it by then, the early one behind the DMA instructions of tile t + STAGES - 1, the late one before it issues those; the slot that
-      // they fill is that of tile t - 1, which the late group has read by the barrier before.
+    for (int t = 0; t < nk; ++t) {
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(WAIT));
       __builtin_amdgcn_s_barrier();
-      if (wave < NW / 2) {
-        for (int t = 0; t < nk; ++t) {
-          read_tile();
-          __builtin_amdgcn_s_waitcnt(lgkm_imm(0));
-          __builtin_amdgcn_s_barrier();
-          multiply_tile(t);
-          __builtin_amdgcn_s_waitcnt(vmcnt_imm(WAIT));
-          __builtin_amdgcn_s_barrier();
-          next_slot();
-        }
-        __builtin_amdgcn_s_barrier();
-      } else {
-        __builtin_amdgcn_s_barrier();
-        for (int t = 0; t < nk; ++t) {
-          read_tile();
-          __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm((STAGES - 3) * NDMA));
-          __builtin_amdgcn_s_barrier();
-          multiply_tile(t);
-          __builtin_amdgcn_s_barrier();
-          next_slot();
-        }
-      }
-    } else {
-      auto multiply = [&](int ks) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-          for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
-      };
-      for (int t = 0; t < nk; ++t) {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(WAIT));
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        const uint32_t sa = ring0 + uint32_t(slot) * (STAGE * 2), sb = sa + SA * 2;
-        read_frags(Int<0>{}, sa, sb);
-        __builtin_amdgcn_sched_barrier(0);
-        dma(t + STAGES - 1, free_slot);
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(Int<1>{}, sa, sb);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(lgkm_imm(RDS <= 15 ? RDS : 15));
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(0);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(lgkm_imm(0));
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(1);
-        __builtin_amdgcn_sched_barrier(0);
-        next_slot();
-      }
+      __builtin_amdgcn_sched_barrier(0);
+      const uint32_t sa = ring0 + uint32_t(slot) * (STAGE * 2), sb = sa + SA * 2;
+      read_frags(Int<0>{}, sa, sb);
+      __builtin_amdgcn_sched_barrier(0);
+      dma(t + STAGES - 1, free_slot);
+      __builtin_amdgcn_sched_barrier(0);
+      read_frags(Int<1>{}, sa, sb);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(lgkm_imm(RDS <= 15 ? RDS : 15));
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(0);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(lgkm_imm(0));
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(1);
+      __builtin_amdgcn_sched_barrier(0);
+      free_slot = slot;
+      slot = slot + 1 == STAGES ? 0 : slot + 1;
     }
   } else {
     // 64 x 64: four wavefronts with 8 matrix instructions each have too little to do to hide a K tile's LDS reads, so the fragments of
@@ -316,10 +242,10 @@ __device__ __forceinline__ void deep_tile(const GemmArgs& g, const int block, ui
 // many workgroups, so that the K axis needs no cut and no second launch.  512 x 584 over K = 1024 13.5 -> 9.6 us, 512 x 1024 over 584
 // 10.5 -> 8.0, 384 x 512 over 4096 in four chunks 18.9 -> 13.2.  Five K tiles in LDS are 0.3 us slower, seven 30 % where
 // a compute unit has more than one workgroup to take.
-template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, int STAGES, bool ALT>
+template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, int STAGES>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_deep_kernel(const GemmArgs g) {
   __shared__ __attribute__((aligned(1024))) uint16_t ring[STAGES * (BM_ + BN_) * DK];
-  deep_tile<AKC, BKC, EPI, BM_, BN_, WGM, WGN, STAGES, ALT>(g, int(blockIdx.x), ring);
+  deep_tile<AKC, BKC, EPI, BM_, BN_, WGM, WGN, STAGES>(g, int(blockIdx.x), ring);
 }
 
 // Up to three problems that do not depend on each other in one launch (the 128 x 128 tile with five K tiles in LDS or the 64 x 64 one, no cut K axis):
@@ -334,7 +260,7 @@ struct GroupArgs {
 };
 enum GroupKind : int32_t { kGroupNt = 0, kGroupNn, kGroupTn, kGroupTnAccum };  // layout and epilogue: bf16, bf16, fp32, fp32 accumulate
 
-template <int B, int WG, int STAGES, bool ALT>
+template <int B, int WG, int STAGES>
 __global__ __launch_bounds__(128 * WG) void gemm_deep_group_kernel(const GroupArgs a) {
   __shared__ __attribute__((aligned(1024))) uint16_t ring[STAGES * 2 * B * DK];
   int p = 0;
@@ -343,10 +269,10 @@ __global__ __launch_bounds__(128 * WG) void gemm_deep_group_kernel(const GroupAr
   const GemmArgs& g = a.g[p];
   const int block = int(blockIdx.x) - a.first[p];
   switch (a.kind[p]) {
-    case kGroupNt: deep_tile<true, true, ntp::EPI_BF16, B, B, 2, WG, STAGES, ALT>(g, block, ring); break;
-    case kGroupNn: deep_tile<true, false, ntp::EPI_BF16, B, B, 2, WG, STAGES, ALT>(g, block, ring); break;
-    case kGroupTn: deep_tile<false, false, ntp::EPI_F32, B, B, 2, WG, STAGES, ALT>(g, block, ring); break;
-    default: deep_tile<false, false, ntp::EPI_F32_ACCUM, B, B, 2, WG, STAGES, ALT>(g, block, ring); break;
+    case kGroupNt: deep_tile<true, true, ntp::EPI_BF16, B, B, 2, WG, STAGES>(g, block, ring); break;
+    case kGroupNn: deep_tile<true, false, ntp::EPI_BF16, B, B, 2, WG, STAGES>(g, block, ring); break;
+    case kGroupTn: deep_tile<false, false, ntp::EPI_F32, B, B, 2, WG, STAGES>(g, block, ring); break;
+    default: deep_tile<false, false, ntp::EPI_F32_ACCUM, B, B, 2, WG, STAGES>(g, block, ring); break;
   }
 }
 

@@ -1,8 +1,6 @@
 // Deep-pipelined GEMM instantiations per operand layout and epilogue: the 128 x 128 tile on 8 wavefronts with five K tiles in LDS, the
 // same with two (64 KiB: two workgroups on a compute unit, one's stores and first loads under the other's products), 128 x 256 with three, and
 // 64 x 64 on 4 wavefronts with three.
-#include <algorithm>
-
 #include "ntp_gemm_launch.h"
 
 #include "ntp_gemm_deep.h"
@@ -10,15 +8,11 @@
 namespace ntp_gemm {
 
 // The shared launches' kernels come first in the code object.  Small calls run four kernels in turn, and where those lie decides what they evict from the instruction
-// cache: 512 x 1024 x 586 forward and backward 34.2 us with these kernels last, 33.8 so (each call alone: the same).
-template __global__ void gemm_deep_group_kernel<64, 2, 3, false>(const GroupArgs);
-template __global__ void gemm_deep_group_kernel<128, 4, 5, false>(const GroupArgs);
-template __global__ void gemm_deep_group_kernel<128, 4, 5, true>(const GroupArgs);
+// cache.
+template __global__ void gemm_deep_group_kernel<64, 2, 3>(const GroupArgs);
+template __global__ void gemm_deep_group_kernel<128, 4, 5>(const GroupArgs);
 
 namespace {
-
-constexpr int kAlternateFrom = 20;  // K tiles from which the wavefronts of a SIMD alternate (both sides in ntp_gemm_deep.h)
-int k_tiles(const GemmArgs& g) { return (std::min(g.k_chunk, g.K) + 63) / 64; }
 
 template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, int STAGES>
 int launch_tile(GemmArgs g, hipStream_t s) {
@@ -27,9 +21,7 @@ int launch_tile(GemmArgs g, hipStream_t s) {
   const int64_t per_split = (int64_t(g.tiles_m) * g.tiles_n + 7) / 8 * 8;
   if (g.k_splits < 1 || g.k_chunk < 64 || g.k_chunk % 64 || int64_t(g.k_splits - 1) * g.k_chunk >= g.K || per_split * g.k_splits > 0x7fffffff)
     return NTP_ERR_INVALID_ARG;
-  const dim3 grid(uint32_t(per_split * g.k_splits)), block(64 * WGM * WGN);
-  if (can_alternate(BM_, STAGES) && k_tiles(g) >= kAlternateFrom) hipLaunchKernelGGL((gemm_deep_kernel<AKC, BKC, EPI, BM_, BN_, WGM, WGN, STAGES, can_alternate(BM_, STAGES)>), grid, block, 0, s, g);
-  else hipLaunchKernelGGL((gemm_deep_kernel<AKC, BKC, EPI, BM_, BN_, WGM, WGN, STAGES, false>), grid, block, 0, s, g);
+  hipLaunchKernelGGL((gemm_deep_kernel<AKC, BKC, EPI, BM_, BN_, WGM, WGN, STAGES>), dim3(uint32_t(per_split * g.k_splits)), dim3(64 * WGM * WGN), 0, s, g);
   return hipGetLastError() == hipSuccess ? NTP_OK : NTP_ERR_LAUNCH;
 }
 
@@ -74,22 +66,19 @@ int launch_deep_group(const GemmArgs* g, const int* layout, const int* epilogue,
   if (n < 1 || n > kMaxGroup) return NTP_ERR_INVALID_ARG;
   GroupArgs a{};
   int64_t blocks = 0;
-  int longest = 0;
   for (int i = 0; i < n; ++i) {
     a.g[i] = g[i];
     a.g[i].tiles_m = (g[i].M + b - 1) / b;
     a.g[i].tiles_n = (g[i].n_store + b - 1) / b;
     if (layout[i] == 2 ? epilogue[i] != ntp::EPI_F32 && epilogue[i] != ntp::EPI_F32_ACCUM : epilogue[i] != ntp::EPI_BF16) return NTP_ERR_UNSUPPORTED;
     a.kind[i] = layout[i] == 0 ? kGroupNt : layout[i] == 1 ? kGroupNn : epilogue[i] == ntp::EPI_F32 ? kGroupTn : kGroupTnAccum;
-    longest = std::max(longest, k_tiles(g[i]));
     a.first[i] = int32_t(blocks);
     blocks += (int64_t(a.g[i].tiles_m) * a.g[i].tiles_n + 7) / 8 * 8;
     if (blocks > 0x7fffffff) return NTP_ERR_UNSUPPORTED;
   }
   a.n = n;
-  if (form == kDeepSmall) hipLaunchKernelGGL((gemm_deep_group_kernel<64, 2, 3, false>), dim3(uint32_t(blocks)), dim3(256), 0, s, a);
-  else if (longest >= kAlternateFrom) hipLaunchKernelGGL((gemm_deep_group_kernel<128, 4, 5, true>), dim3(uint32_t(blocks)), dim3(512), 0, s, a);
-  else hipLaunchKernelGGL((gemm_deep_group_kernel<128, 4, 5, false>), dim3(uint32_t(blocks)), dim3(512), 0, s, a);
+  if (form == kDeepSmall) hipLaunchKernelGGL((gemm_deep_group_kernel<64, 2, 3>), dim3(uint32_t(blocks)), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((gemm_deep_group_kernel<128, 4, 5>), dim3(uint32_t(blocks)), dim3(512), 0, s, a);
   return hipGetLastError() == hipSuccess ? NTP_OK : NTP_ERR_LAUNCH;
 }
 
