@@ -7,11 +7,6 @@
 
 namespace ntp_gemm {
 
-// The shared launches' kernels come first in the code object.  Small calls run four kernels in turn, and where those lie decides what they evict from the instruction
-// cache.
-template __global__ void gemm_deep_group_kernel<64, 2, 3>(const GroupArgs);
-template __global__ void gemm_deep_group_kernel<128, 4, 5>(const GroupArgs);
-
 namespace {
 
 template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN, int STAGES>
