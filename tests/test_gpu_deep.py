@@ -46,6 +46,29 @@ def test_mlp_deep(names, M, H, n_r, mode):
         assert (raw[k][:, n_r:pad].float().cpu().numpy() == 0).all(), k
 
 
+# 16 chunks whose last one is shorter than the ring: one ragged K tile, two and three
+@pytest.mark.parametrize("M,H,n_r,layout", [(257, 9640, 520, "nt"), (257, 520, 9640, "nn"), (257, 10648, 520, "nt"), (257, 520, 10705, "nn")])
+def test_mlp_deep_short_last_chunk(M, H, n_r, layout):
+    import torch
+    import paper_2504_06095_amd as N
+    print(f"[gpu-case] deep GEMM MLP, short last chunk M={M} H={H} n_r={n_r}", file=sys.stderr, flush=True)
+    N.ntp_set_workspace(torch.full((8 << 20,), float("nan"), dtype=torch.float32, device="cuda"))
+    N.ntp_kernel_timing_enable(1)
+    N.ntp_kernel_timing_read()
+    try:
+        case = MlpCase(M, H, n_r, 1, 0)
+        got, _ = case.run_gpu()
+        picked = [r["name"] for r in N.ntp_kernel_timing_read()]
+    finally:
+        N.ntp_kernel_timing_enable(0)
+        N.ntp_set_workspace(None)
+    assert any(n.startswith(f"gemm_{layout}") and n.endswith("128x128w8dk16") for n in picked), picked
+    want = case.oracle()
+    for k in MLP_NAMES:
+        e = rel_err(got[k], want[k])
+        assert np.isfinite(got[k]).all() and e <= TOL, f"{k}: rel err {e:.3e}"
+
+
 @pytest.mark.parametrize("M,H,n_q,n_kv,d,tp,rank", [(385, 520, 6, 2, 64, 2, 1), (129, 1544, 8, 4, 64, 3, 1), (700, 264, 4, 4, 128, 2, 0)])
 def test_attn_proj_deep(names, M, H, n_q, n_kv, d, tp, rank):
     print(f"[gpu-case] deep GEMM attention projections M={M} H={H}", file=sys.stderr, flush=True)
@@ -137,7 +160,7 @@ def test_deep_matches_the_other_kernels_bit_for_bit(opts):
     import paper_2504_06095_amd as N
     from paper_2504_06095_amd import binding as K
     print("[gpu-case] deep GEMM against the ring kernel", file=sys.stderr, flush=True)
-    for M, H, n_r in ((512, 1024, 586), (640, 776, 1000), (258, 264, 257)):
+    for M, H, n_r in ((512, 1024, 586), (640, 776, 1000), (258, 264, 257), (640, 1288, 1320)):
         case = MlpCase(M, H, n_r, 1, 0)
         N.ntp_kernel_timing_enable(1)
         N.ntp_kernel_timing_read()

@@ -24,15 +24,24 @@ def _check(case, pad_to, tag):
 
 @pytest.mark.parametrize("k", [131, 200, 321])  # 3, 4 and 6 K tiles: as short as the persistent form takes, one more, and past the ring's length
 @pytest.mark.parametrize("tile", TILES)
-def test_k_tail_with_many_output_tiles_per_workgroup(opts, tile, k):
+def test_k_tail_with_many_output_tiles_per_workgroup(workspace, opts, tile, k):  # noqa: F811
+    import paper_2504_06095_amd as N
     opts(K.NTP_OPT_GEMM_SCHEDULE, 2)
     opts(K.NTP_OPT_GEMM_TILE, tile)
     opts(K.NTP_OPT_GEMM_WORKGROUPS, 8)
+    opts(K.NTP_OPT_GEMM_SPLIT, 1)
+
+    def check(case, pad_to, tag):
+        N.ntp_kernel_timing_read()
+        _check(case, pad_to, f"{tile}, {tag}")
+        names = [r["name"] for r in N.ntp_kernel_timing_read()]
+        assert len(names) == 6 and all(n.endswith(f"{tile}pp") for n in names), names
+
     for pad_to in (8, 64):  # K = n_r, whose rows end right behind it or at the next K tile
-        _check(MlpCase(1300, 1400, k, 1, 0, tag=f"ppt.n.{k}"), pad_to, f"{tile}, K = n_r = {k}, rows padded to {pad_to}")
+        check(MlpCase(1300, 1400, k, 1, 0, tag=f"ppt.n.{k}"), pad_to, f"K = n_r = {k}, rows padded to {pad_to}")
     h = (k + 7) // 8 * 8
-    _check(MlpCase(1300, h, 1403, 1, 0, tag=f"ppt.h.{k}"), 8, f"{tile}, K = H = {h}")
-    _check(MlpCase(k, 1400, 1403, 1, 0, tag=f"ppt.m.{k}"), 8, f"{tile}, K = tokens = {k}")
+    check(MlpCase(1300, h, 1403, 1, 0, tag=f"ppt.h.{k}"), 8, f"K = H = {h}")
+    check(MlpCase(k, 1400, 1403, 1, 0, tag=f"ppt.m.{k}"), 8, f"K = tokens = {k}")
 
 
 @pytest.mark.parametrize("k,splits", [(488, 8), (987, 8), (1272, 7)])  # chunks of 1, 2 and 3 K tiles, the last one ragged
