@@ -4,8 +4,8 @@
 // The two wavefronts of a SIMD (w and w + 4: wavefronts are dealt to the four SIMDs in turn) alternate between
 // two kinds of slot, with a workgroup barrier after every slot:
 //   memory slot   read all fragments of one K-step (32 k) of the current K tile from LDS into registers and
-//                 wait for them;
-//   compute slot  MI x NI matrix instructions on those fragments, this wavefront's DMA instructions evenly among them.
+//                 wait for them; where both operands are K-contiguous, DMA instructions of the long operand (below) behind the reads of the second one;
+//   compute slot  MI x NI matrix instructions on those fragments, this wavefront's other DMA instructions evenly among them.
 // Wavefronts 0-3 ("early") run M0 C0 M1 C1 per K tile, wavefronts 4-7 ("late") the same one slot behind, so
 // in every slot one wavefront of each SIMD computes while the other one's LDS latency hides behind it.
 //
@@ -16,13 +16,21 @@
 // per 128-byte line four K tiles ahead, by turns) cost a slot more than it brought and is gone.  Whole GEMMs: use_pingpong in ntp_gemm.hip.  A K chunk of the
 // non-persistent form, which ran on the ring kernel before: 8192 x 752 over K = 16384 in two chunks 189 -> 171 us, 4096 x 640 over 8192 in three 65 -> 58.
 //
+// Where the long operand's instructions go: with both operands K-contiguous the memory slots have room for them, and a compute slot is not held up by the vector memory
+// path.  Twenty-five such products with cold operands take 0.990 of the time with them in M1 against the compute slots, cached 0.993 (2048 x 7040 over 12288 279.9 -> 272.9 us,
+// 3024 x 3976 over 4488 109.4 -> 105.3, the other way 16384 x 1024 over 4096 102 -> 104.6); both operands' there 1.005 and 1.000, the short one's alone 1.011 and 1.005.  With one
+// operand K-strided M1 and the compute slots are even, with both M1 takes 1.003 and 1.006.
+// What the prefetch is missed for: rows that do not start on cache lines, in launches of one round of tiles with cold operands, up to 1.08 of the time that they took with it (2048 x
+// 8264 over 1544 73.1 -> 78.7 us; cached 70.2 -> 62.8); rows of whole lines take 0.93 to 1.00, launches of more rounds 0.89 to 0.98.  Put back, one load a wavefront in M0 that is
+// waited for a K tile later, it took 1.05 of the time cold and 1.10 cached over thirty shapes, and spilled registers on the widest tiles.
+//
 // LDS is a ring of five operand slots that runs on from one output tile of a persistent workgroup into the next.  Of the two operands one ("long", the
 // one of more rows) is asked for two K tiles ahead, the other ("short") one to two.  While K tile t is multiplied the slots hold
 //   long t, short t, long t+1, short t+1, long t+2;
 // the last reader of tile t is the late group's M1, the fourth slot of the tile, after which its two slots take short t+2 and long t+3.
 // Every wavefront moves an eighth of both operands:
-//   early group: short t+1 in C0 of tile t (second slot), long t+2 in C1 (fourth);
-//   late group:  long t+2 in C0 of tile t (third slot), short t+2 in C1 (first slot of tile t+1);
+//   early group: short t+1 in C0 of tile t (second slot), long t+2 in C1 (fourth), or M1 (third) where both operands are K-contiguous;
+//   late group:  long t+2 in C0 of tile t (third slot), or M1 (fourth), short t+2 in C1 (first slot of tile t+1);
 //   before the barrier that ends the fourth slot both wait for everything up to short t+1 (the instructions of long t+2 may stay in flight).
 // After that barrier tile t+1 is complete in LDS.  What a K tile asks for past the output tile's last one are the first K tiles of the workgroup's next
 // output tile, so that a tile switch is the epilogue alone; where there is none the loads lie past their view (zeros, no memory traffic), so that instruction
@@ -106,6 +114,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
   constexpr int RL = LB ? RB : RA, RS = LB ? RA : RB;
   // DMA instructions per K tile and wavefront for the long and the short operand
   constexpr int NL = RL * DK * 2 / 1024 / 8, NS = RS * DK * 2 / 1024 / 8;
+  constexpr bool LMEM = AKC && BKC;  // the long operand's instructions in the second memory slot
   static_assert((RL * DK * 2 / 1024) % 8 == 0 && (RS * DK * 2 / 1024) % 8 == 0, "operands split evenly over the wavefronts");
   __shared__ __attribute__((aligned(1024))) uint16_t ring[5 * SLOT];
 
@@ -241,19 +250,26 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(const GemmArgs g) {
     __builtin_amdgcn_s_waitcnt(lgkm0_imm());
     __builtin_amdgcn_s_barrier();
     // C0
-    if constexpr (LATE) compute_slot(Int<NL>{}, [&](int i) { dma_long(i, atl, s4); });
-    else compute_slot(Int<NS>{}, [&](int i) { dma_short(i, ats, s3); });
+    if constexpr (!LATE) compute_slot(Int<NS>{}, [&](int i) { dma_short(i, ats, s3); });
+    else if constexpr (LMEM) compute_slot(Int<0>{}, [](int) {});
+    else compute_slot(Int<NL>{}, [&](int i) { dma_long(i, atl, s4); });
     __builtin_amdgcn_s_barrier();
     // M1
     __builtin_amdgcn_sched_barrier(0);
     read_frags(Int<1>{}, LB ? s1 : s0, LB ? s0 : s1);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (LMEM) {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) dma_long(i, atl, s4);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     // late group: the tile's fourth slot
     if constexpr (LATE) __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(NL));
     else __builtin_amdgcn_s_waitcnt(lgkm0_imm());
     __builtin_amdgcn_s_barrier();
     // C1
     if constexpr (LATE) compute_slot(Int<NS>{}, [&](int i) { dma_short(i, ats, s0); });
+    else if constexpr (LMEM) compute_slot(Int<0>{}, [](int) {});
     else compute_slot(Int<NL>{}, [&](int i) { dma_long(i, atl, s4); });
     // early group: its C1 is the tile's fourth slot
     if constexpr (!LATE) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NL));
