@@ -1,7 +1,8 @@
 """The assembly of the GEMM kernels whose LDS reads are inline assembly (no GPU): the ping-pong kernel, persistent and with one workgroup per unit of work, and the
-deep-pipelined one, alone and in shared launches.  The compiler takes such a read's registers as written at once; that nothing touches them before the wait
+deep-pipelined one, alone and in shared launches; and the ring kernel's prefetch.  The compiler takes such a read's registers as written at once; that nothing touches them before the wait
 is kept by the source's order, and checked in what the compiler makes of it, for every instantiation."""
 import os
+import re
 from concurrent.futures import ThreadPoolExecutor
 
 import pytest
@@ -46,3 +47,20 @@ def test_registers_are_left_alone_while_reads_are_in_flight(assembly, source, ke
     stop = next(i for i, c in enumerate(code) if i > first and c[0].startswith("v_mfma"))
     line = [c for c in code[first:stop + 1] if not c[0].startswith(("s_branch", "s_cbranch"))] + [("s_endpgm", [], "s_endpgm")]
     assert _in_flight_faults(_without_waits(line), {})
+
+
+@pytest.mark.parametrize("source", ["ntp_gemm_nt", "ntp_gemm_nn", "ntp_gemm_tn"])
+def test_prefetched_words_register_is_theirs_alone(assembly, source):
+    """The ring kernel's prefetch to L2 loads words that nobody reads, in assembly: one register, which nothing else touches once a load may be in flight."""
+    prefetching = 0
+    for start in _symbols(assembly[source], "gemm_ring_kernel"):
+        code, _ = _code(assembly[source], start)
+        loads = [i for i, c in enumerate(code) if re.fullmatch(r"global_load_dword v\d+, v\d+, s\[\d+:\d+\]", c[2])]
+        if not loads:
+            continue
+        prefetching += 1
+        sinks = {code[i][1][0] for i in loads}
+        assert len(sinks) == 1, assembly[source][start]
+        touched = [c[2] for i, c in enumerate(code) if i not in loads and any(o & next(iter(sinks)) for o in c[1])]
+        assert len(touched) == 1 and re.fullmatch(r"v_mov_b32_e32 v\d+, 0", touched[0]), (assembly[source][start], touched[:5])
+    assert prefetching >= 8
