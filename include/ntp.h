@@ -101,8 +101,8 @@ int ntp_device_info(const ntp_handle_t* h, int32_t* device, int32_t* compute_uni
                                         256x224, 224x256, 256x192, 192x256, 256x128, 128x256, 128x128 (4 wavefronts),
                                         128x128 (8 wavefronts)                                                       */
 #define NTP_OPT_GEMM_SPLIT 1         /* 1: never cut the contraction axis; 2..8: that many chunks where they fit
-                                        (ring kernels)                                                               */
-#define NTP_OPT_GEMM_NO_RING_TAIL 2  /* 1: the K tail of row-parallel GEMMs goes through registers                 */
+                                        (ping-pong kernel)                                                           */
+#define NTP_OPT_GEMM_NO_RING_TAIL 2  /* 1: the K tail of uncut row-parallel GEMMs goes through registers           */
 #define NTP_OPT_ATTN_PARTS 3         /* 1..16: parts per attention-core walk where the workspace holds them        */
 #define NTP_OPT_RESHARD_BLOCK 4      /* bytes per workgroup of the row-wise gather kernel                           */
 #define NTP_OPT_RESHARD_FLAT_BLOCK 5 /* bytes per workgroup of the flat-destination kernel                          */

@@ -51,7 +51,7 @@ int launch_generic(GemmArgs g, int epi, hipStream_t s) {
 // HBM), every tile shape timed on each, with the ping-pong kernel on the 8-wavefront tiles: the tile that the table picks takes 1.012 (A, B K-contiguous), 1.003
 // and 1.009 of the best tile's time on the mean (with the table made for the ring schedule 1.014, 1.021 and 1.016).
 // The 4-wavefront 128 x 128 variant reaches its rate with two workgroups on a compute unit; alone on one
-// (at most 256 tiles) it runs at kLoneSmallTileRate, where the 8-wavefront variant of the same tile is faster.
+// (at most 256 tiles) it runs at kLoneSmallTileRate, where the 8-wavefront variant of the same tile is faster; with both operands K-strided it always is.
 //                                             256x256 256x224 224x256 256x192 192x256 256x128 128x256 128x128 128x128w8
 constexpr double kTileRate[3][kNumTileShapes] = {{1.050, 1.008, 0.945, 0.924, 0.975, 0.714, 0.764, 0.60, 0.53},   // A, B K-contiguous
                                                  {1.100, 0.977, 1.055, 1.023, 1.029, 0.705, 0.816, 0.60, 0.53},   // B K-strided
@@ -280,9 +280,9 @@ SplitChoice plan_gemm(const ntp_handle* h, int64_t ws_bytes, const GemmArgs& g, 
 }
 
 // Which kernel a persistent launch on an 8-wavefront tile gets: the ping-pong one (tile shapes 0-6, three K tiles or more), whose wavefronts read
-// fragments while the others of their SIMDs compute, unless NTP_OPT_GEMM_SCHEDULE = 1 asks for the ring kernel.  Measured on all tile shapes and layouts over ten
-// shapes of 26 to 350 GFLOP, ping-pong against ring: A, B K-contiguous 0.93-0.97 of the time, B K-strided 0.84-0.96, both K-strided 0.88-0.99 (2048 x
-// 12288 over K = 7040 269 -> 249, 288 -> 268 and 344 -> 310 us against the kernels that these layouts ran on before).
+// fragments while the others of their SIMDs compute, unless NTP_OPT_GEMM_SCHEDULE = 1 asks for the ring kernel.  Ping-pong against ring over 34 shapes of 17 to 730
+// GFLOP, each on its own best tile, with operands from HBM: column-parallel 0.96 of the time on the mean (0.82 to 1.03, above 1 where one round of tiles has rows that do not start on cache
+// lines), row-parallel 0.93 (0.81 to 0.99), weight gradients with the column-parallel product before them 0.97 (0.93 to 1.03); with cached operands 0.91, 0.91 and 0.95, nowhere slower.
 bool use_pingpong(const ntp_handle* h, int variant, int64_t K) {
   return variant >= 0 && variant <= 6 && K > 128 && h->opt[NTP_OPT_GEMM_SCHEDULE] != 1;
 }

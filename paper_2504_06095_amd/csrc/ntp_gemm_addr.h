@@ -1,5 +1,5 @@
-// Index arithmetic of the ring GEMM kernel's operand DMA, kept apart from the kernel so that a host
-// program can include it too and enumerate every address the kernel can form (the kernel's loads are
+// Index arithmetic of the GEMM kernels' operand DMA, kept apart from the kernels so that a host
+// program can include it too and enumerate every address that they can form (the kernels' loads are
 // range-checked by the hardware against the operand's extent; the host model checks the same
 // arithmetic against the same extent without a GPU).
 #ifndef NTP_GEMM_ADDR_H_

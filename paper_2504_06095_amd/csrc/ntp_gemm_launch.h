@@ -1,4 +1,4 @@
-// Launch side of the ring GEMM kernel: one translation unit per operand layout instantiates the
+// Launch side of the ring, ping-pong and deep-pipelined GEMM kernels: one translation unit per operand layout instantiates the
 // tile variants it needs (they compile in parallel); ntp_gemm.hip picks a variant and calls in.
 #ifndef NTP_GEMM_LAUNCH_H_
 #define NTP_GEMM_LAUNCH_H_
@@ -13,7 +13,7 @@
 
 namespace ntp_gemm {
 
-// Tile shapes of the ring kernel.  Wavefront grids are chosen so that a wavefront's tile is
+// Tile shapes of the ring and ping-pong kernels.  Wavefront grids are chosen so that a wavefront's tile is
 // 64..128 rows by 48..112 columns (LDS fragment reads per MFMA stay low).
 struct TileShape {
   int bm, bn, waves;
@@ -92,7 +92,7 @@ int launch_split_tile(const GemmArgs& g, int tile, hipStream_t s) {
   }
 }
 
-// Ping-pong schedule (8-wavefront tile shapes 0-6).
+// Ping-pong kernel, persistent form (8-wavefront tile shapes 0-6).
 template <bool AKC, bool BKC, int EPI>
 int launch_pp_tile(const GemmArgs& g, int tile, hipStream_t s) {
   switch (tile) {

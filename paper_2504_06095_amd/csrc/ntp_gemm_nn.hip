@@ -1,4 +1,4 @@
-// Ring GEMM instantiations, A K-contiguous and B K-strided: the row-parallel forward GEMMs
+// Ring GEMM instantiations and ping-pong ones with one workgroup per unit of work, A K-contiguous and B K-strided: the row-parallel forward GEMMs
 // (Eq. 2 and Eq. 4: Y_i B_i, C_i W_O,i) and the partial input gradients (dP_i A_i^T, dQKV_i W_qkv,i^T),
 // whose contraction runs over the ragged shard width.
 #include "ntp_gemm_launch.h"

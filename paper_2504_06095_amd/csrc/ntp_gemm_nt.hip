@@ -1,4 +1,4 @@
-// Ring GEMM instantiations, both operands K-contiguous: the column-parallel forward GEMMs
+// Ring GEMM instantiations and ping-pong ones with one workgroup per unit of work, both operands K-contiguous: the column-parallel forward GEMMs
 // (Eq. 3 and Eq. 6: X A_i, X W_qkv,i) and the activation gradients of the row-parallel ones
 // (dZ B_i^T, dZ W_O,i^T), with their bf16 / GeLU / GeLU' epilogues.
 #include "ntp_gemm_launch.h"

@@ -9,12 +9,12 @@
 // Wavefronts 0-3 ("early") run M0 C0 M1 C1 per K tile, wavefronts 4-7 ("late") the same one slot behind, so
 // in every slot one wavefront of each SIMD computes while the other one's LDS latency hides behind it.
 //
-// What bounds the loop is the longer of the two kinds of slot, then the board's power.  A compute slot is 448 cycles on a 256 x 224 tile.  With the DMA
+// What bounds the loop is the longer of the two kinds of slot, then the board's power.  A compute slot is 448 cycles on a 256 x 224 tile.  With all DMA
 // instructions in the memory slots these took 390 (M0) and 600-680 cycles (M1, which also held a prefetch to L2), 510 and 750-780 where both
-// operands are K-strided; without them they take 210-230 (340-400), and a compute slot with four DMA instructions in it about 500: the vector memory
-// path takes about 18 cycles per 1 KiB instruction and compute unit, and 16 of them in 448 cycles do not queue up.  The prefetch (a 4-byte load
-// per 128-byte line four K tiles ahead, by turns) cost a slot more than it brought and is gone.  Whole GEMMs: use_pingpong in ntp_gemm.hip.  A K chunk of the
-// non-persistent form, which ran on the ring kernel before: 8192 x 752 over K = 16384 in two chunks 189 -> 171 us, 4096 x 640 over 8192 in three 65 -> 58.
+// operands are K-strided; without them they take 210-250 (340-400), and a compute slot with four DMA instructions in it about 500: the vector memory
+// path takes about 18 cycles per 1 KiB instruction and compute unit, and 16 of them in 448 cycles do not queue up.  M1 with the long operand's takes 310-410.  The prefetch (a
+// 4-byte load per 128-byte line four K tiles ahead, by turns) cost a slot more than it brought to most products and is gone.  Whole GEMMs: use_pingpong in ntp_gemm.hip.  A K chunk,
+// which ran on the ring kernel before: 8192 x 752 over K = 16384 in two chunks 207 -> 188 us, 4096 x 640 over 8192 in three 67.3 -> 60.4 (operands from HBM).
 //
 // Where the long operand's instructions go: with both operands K-contiguous the memory slots have room for them, and a compute slot is not held up by the vector memory
 // path.  Twenty-five such products with cold operands take 0.990 of the time with them in M1 against the compute slots, cached 0.993 (2048 x 7040 over 12288 279.9 -> 272.9 us,

@@ -1,4 +1,4 @@
-// Ring GEMM instantiations with the ping-pong schedule, A K-contiguous and B K-strided (Y_i B_i, C_i W_O,i and the
+// Ping-pong GEMM instantiations, persistent form, A K-contiguous and B K-strided (Y_i B_i, C_i W_O,i and the
 // partial input gradients dP_i A_i^T, dQKV_i W_qkv,i^T).
 #include "ntp_gemm_launch.h"
 

@@ -1,4 +1,4 @@
-// Ring GEMM instantiations with the ping-pong schedule, both operands K-contiguous (X A_i, X W_qkv,i, dZ B_i^T,
+// Ping-pong GEMM instantiations, persistent form, both operands K-contiguous (X A_i, X W_qkv,i, dZ B_i^T,
 // dZ W_O,i^T and their bf16 / GeLU / GeLU' epilogues).
 #include "ntp_gemm_launch.h"
 

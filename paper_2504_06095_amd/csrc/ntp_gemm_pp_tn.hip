@@ -1,4 +1,4 @@
-// Ring GEMM instantiations with the ping-pong schedule, both operands K-strided: the weight gradients.
+// Ping-pong GEMM instantiations, persistent form, both operands K-strided: the weight gradients.
 #include "ntp_gemm_launch.h"
 
 namespace ntp_gemm {

@@ -1,4 +1,6 @@
-// Main bf16 MFMA GEMM kernel of the NTP shard layers.  Included by ntp_gemm.hip.
+// Ring GEMM kernel, bf16 MFMA.  It runs whole products on the 128 x 128 tiles where those are not the deep-pipelined kernel's, and on the 8-wavefront tiles what the
+// ping-pong kernel (ntp_gemm_pp.h, same tiles and slot layouts) does not take: K = 128, row-parallel K tails under NTP_OPT_GEMM_NO_RING_TAIL, and everything but cut products and
+// 256 x 256 weight gradients under NTP_OPT_GEMM_SCHEDULE = 1.
 //
 // Tile BM x BN x 64, WGM x WGN wavefronts, each computing (BM/WGM) x (BN/WGN) with
 // 16x16x32 bf16 MFMAs and fp32 accumulators.  Operands go global -> LDS by direct
@@ -159,7 +161,7 @@ template <int I>
 using Int = std::integral_constant<int, I>;
 
 // (Two wavefronts on a SIMD, also with four of them in a workgroup: left free, the compiler gives accumulating weight gradients on the 128 x 128 tile 272
-// registers, so that a compute unit holds one workgroup instead of two: 3511 x 6144 over 4096 324-346 -> 247-258 us.)
+// registers, so that a compute unit holds one workgroup instead of two: 3511 x 6144 over 4096 324-346 -> 247-258 us.  That layout gets this tile by NTP_OPT_GEMM_TILE only.)
 template <bool AKC, bool BKC, int EPI, int BM_, int BN_, int WGM, int WGN>
 __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_ring_kernel(const GemmArgs g) {
   constexpr int NW = WGM * WGN;

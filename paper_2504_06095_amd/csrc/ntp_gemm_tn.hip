@@ -1,4 +1,4 @@
-// Ring GEMM instantiations, both operands K-strided: the weight gradients (Y_i^T dZ, dP_i^T X,
+// Ring GEMM instantiations and ping-pong ones with one workgroup per unit of work, both operands K-strided: the weight gradients (Y_i^T dZ, dP_i^T X,
 // C_i^T dZ, dQKV_i^T X), contraction over tokens, fp32 store or accumulate.
 #include "ntp_gemm_launch.h"
 
